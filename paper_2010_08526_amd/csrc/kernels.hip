@@ -1717,7 +1717,7 @@ __device__ __forceinline__ int hv_traverse(const HvArgs<VT> &a, int64_t pbeg, in
 
 // Items: persistent workgroups take batches from a queue in slab-major
 // order: batch i covers slab t = i / nb of the chunk's columns
-// [64 (i % nb), 64 (i % nb) + 64), nb = ceil(Hc / 64), so that the
+// [ic (i % nb), ic (i % nb) + ic), ic up to 64, nb = ceil(Hc / ic), so that the
 // workgroups of the device work on the same few slabs of A at a time and
 // those slabs stay in L2.  The items of a batch (its nonzero slots) are
 // formed one after another by the whole workgroup.  A dense item accumulates
@@ -1757,6 +1757,15 @@ struct HvProductSrc {
 // slab in kItemCols consecutive heavy columns (one wave reads their slots).
 constexpr int kItemCols = 64;
 static_assert(kItemCols <= kWave, "one slot per lane");
+// A batch of kItemCols columns is too coarse when a chunk has few heavy
+// columns or few slabs: 274 heavy columns over 2 slabs (an R-MAT graph of
+// scale 13) are 10 batches, so 10 of 1024 workgroups formed every item.
+// Batches are halved until each workgroup can take kItemBatches of them:
+// that product's items go from 2611 to 88 us, those of a 60,000-row power-law
+// graph in 8 layers and 3 batches from 10.3 to 4.95 ms.  With at least 1 (16)
+// batches per workgroup the latter take 6.0 (7.2) ms: a batch costs a chain
+// of dependent loads whether or not its slots hold an item.
+constexpr int kItemBatches = 4;
 
 template <class VT, class Src>
 __global__ __launch_bounds__(kHvThreads) void k_hv_items(Src src, const int32_t *list,
@@ -1789,7 +1798,11 @@ __global__ __launch_bounds__(kHvThreads) void k_hv_items(Src src, const int32_t 
   const int P = src.P;
   const int64_t nheavy = hdr->bin_count[kNumBins - 1];
   hc = min(hc, max(nheavy - h0, (int64_t)0));  // the device count bounds a chunk sized on the host
-  const int64_t nb = (hc + kItemCols - 1) / kItemCols;
+  // columns per batch: halved from kItemCols until the queue holds
+  // kItemBatches batches per workgroup (see kItemBatches)
+  int ic = kItemCols;
+  while (ic > 1 && (hc + ic - 1) / ic * P < (int64_t)kItemBatches * gridDim.x) ic >>= 1;
+  const int64_t nb = (hc + ic - 1) / ic;
   const int64_t nbatch = nb * P;
   double *acc = (double *)s_tab;
   uint32_t *bits = (uint32_t *)(s_tab + kBitsOff);
@@ -1807,12 +1820,12 @@ __global__ __launch_bounds__(kHvThreads) void k_hv_items(Src src, const int32_t 
     const int64_t bi = s_batch;
     if (bi >= nbatch) break;
     const int t = (int)(bi / nb);
-    const int64_t hb = (bi % nb) * kItemCols;
+    const int64_t hb = (bi % nb) * ic;
     if (w == 0) {  // the batch's items: slot, column, input range and output column, one per lane
       const int64_t hl = hb + l;
       uint32_t e = 0u;
       int32_t jj = 0;
-      if (l < kItemCols && hl < hc && h0 + hl < nheavy) {
+      if (l < ic && hl < hc && h0 + hl < nheavy) {
         e = slots[hl * P + t];
         jj = list[h0 + hl];
       }
