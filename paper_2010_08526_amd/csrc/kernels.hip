@@ -37,6 +37,11 @@ struct SegScratch {
   double scale[kWave];  // B(k,j) of that segment
 };
 
+struct SymScratch {  // the same for a traversal of the pattern alone
+  int mark[kWave];
+  int64_t off[kWave];
+};
+
 struct PartDesc {  // one merge input, stored in the workspace
   const int64_t *cp;
   const int32_t *ri;
@@ -269,10 +274,10 @@ __device__ __forceinline__ void lp_a(const ProductArgs<VT> &a, LightPre<VT> &pre
   }
 }
 
-template <bool VALUES, class VT, bool SLAB = false, class Mul = SrPlusTimes, class Ins>
+template <bool VALUES, class VT, bool SLAB = false, class Mul = SrPlusTimes, class Sc, class Ins>
 __device__ __forceinline__ void traverse_product(const ProductArgs<VT> &a, int64_t col, int64_t c_rank,
                                                  int64_t c_stride, int64_t r_rank, int64_t r_stride,
-                                                 SegScratch &sc, int32_t *status, Ins &&ins,
+                                                 Sc &sc, int32_t *status, Ins &&ins,
                                                  SlabSel sl = SlabSel{nullptr, 0, 0, 0},
                                                  const LightPre<VT> *pre = nullptr) {
   // pre (non-SLAB): the column's B range and this wave's first chunk,
@@ -322,7 +327,7 @@ __device__ __forceinline__ void traverse_product(const ProductArgs<VT> &a, int64
       if (ls > 0) {  // the nonempty short segments in lane order
         const int o = mbcnt(nz);
         sc.off[o] = off - excl;
-        if (VALUES) sc.scale[o] = b;
+        if constexpr (VALUES) sc.scale[o] = b;
       }
       wave_sync();
       int oob = 0;
@@ -335,7 +340,13 @@ __device__ __forceinline__ void traverse_product(const ProductArgs<VT> &a, int64
             row = a.Ari[q];
             if (VALUES) raw = a.Av[q];
           },
-          [&](int o, VT raw) { return VALUES ? Mul::mul((double)raw, sc.scale[o]) : 0.0; }, ins);
+          [&](int o, VT raw) {
+            if constexpr (VALUES)
+              return Mul::mul((double)raw, sc.scale[o]);
+            else
+              return 0.0;
+          },
+          ins);
       if (__ballot(oob) && l == 0) flag_error(status, 5);
       rounds_before += (total + kWave - 1) / kWave;
       wave_sync();
@@ -364,9 +375,9 @@ __device__ __forceinline__ void traverse_product(const ProductArgs<VT> &a, int64
 // handful of long segments is typical of heavy columns) split the rounds of
 // every chunk instead, so that no wave idles.  (Splitting fewer chunks among
 // groups of waves loses more to uneven chunks than it saves in re-reads.)
-template <bool VALUES, class VT, bool SLAB = false, class Mul = SrPlusTimes, class Ins>
+template <bool VALUES, class VT, bool SLAB = false, class Mul = SrPlusTimes, class Sc, class Ins>
 __device__ __forceinline__ void traverse_product_block(const ProductArgs<VT> &a, int64_t col, int w, int nw,
-                                                       SegScratch &sc, int32_t *status, Ins &&ins,
+                                                       Sc &sc, int32_t *status, Ins &&ins,
                                                        SlabSel sl = SlabSel{nullptr, 0, 0, 0},
                                                        const LightPre<VT> *pre = nullptr) {
   const int64_t nchunks = ((pre ? pre->pend - pre->pbeg : a.Bcp[col + 1] - a.Bcp[col]) + kWave - 1) / kWave;
@@ -566,17 +577,26 @@ __global__ __launch_bounds__(256) void k_bin(const int64_t *Acp, const int64_t *
 // ============================================================================
 // Symbolic kernels.
 // ============================================================================
+// A column's distinct rows are counted in an LDS hash table of row keys or,
+// where one bit per row of C takes no more LDS than the table (BITS: m up to
+// 32 rows per slot), in a bitmap: an insert is then one OR without probes,
+// and only the words of rows that exist are cleared and counted, where the
+// largest table (128 KB) is cleared whole for each column by the one workgroup
+// that fits a CU.  Columns of 512-16384 terms, table against bitmap: 632 and
+// 66 -> 228 and 34 us at m = 65,536 (R-MAT scale 16), 2459 -> 711 us at
+// m = 262,144 (scale 18), 372 -> 178 us at m = 8192 (scale 13).
 // One wavefront per column, TBL-slot table private to the wave.
-template <int TBL>
+template <int TBL, bool BITS>
 __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t c0, const int32_t *list,
                                                   const int32_t *count_p, int64_t *nnz_out, int32_t *status) {
   __shared__ int32_t s_keys[4][TBL];
-  __shared__ SegScratch s_sc[4];
+  __shared__ SymScratch s_sc[4];
   const int w = threadIdx.x / kWave, l = lane();
   const int count = *count_p;
   int32_t *keys = s_keys[w];
-  SegScratch &sc = s_sc[w];
+  SymScratch &sc = s_sc[w];
   sc.mark[l] = 0;
+  const int nclear = BITS ? (int)((a.m + 31) / 32) : TBL;  // slots, or words of rows below m
   // the next column's B range and first chunk are loaded while one is counted
   const int64_t stride = (int64_t)gridDim.x * 4;  // 64-bit: no overflow near 2^31 columns
   int64_t idx = (int64_t)blockIdx.x * 4 + w;
@@ -599,13 +619,22 @@ __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t 
       lp_cols<false, float>(a, c0 + jn, pre);
       jn2 = idx + 2 * stride < count ? ld_global(list + idx + 2 * stride + z) : 0;
     }
-    for (int s = l; s < TBL; s += kWave) keys[s] = kEmpty;
+    for (int s = l; s < nclear; s += kWave) keys[s] = BITS ? 0 : kEmpty;
     wave_sync();
     int cnt = 0;
     traverse_product<false, float>(
         a, c0 + jj, 0, 1, 0, 1, sc, status,
-        [&](int32_t row, double) { cnt += ht_insert_key(keys, TBL, row) ? 1 : 0; }, SlabSel{nullptr, 0, 0, 0},
-        &cur);
+        [&](int32_t row, double) {
+          if (BITS)
+            atomicOr((uint32_t *)&keys[row >> 5], 1u << (row & 31));
+          else
+            cnt += ht_insert_key(keys, TBL, row) ? 1 : 0;
+        },
+        SlabSel{nullptr, 0, 0, 0}, &cur);
+    if (BITS) {
+      wave_sync();
+      for (int s = l; s < nclear; s += kWave) cnt += __popc((uint32_t)keys[s]);
+    }
     if (more) lp_b<false, float>(a, pre, 0, 1);
     cnt = wave_sum_i32(cnt);
     if (l == 0) nnz_out[jj] = cnt;
@@ -614,17 +643,21 @@ __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t 
   }
 }
 
-// One workgroup per column, TBL-slot table shared by its waves.
-template <int TBL, int THREADS>
+// One workgroup per column, table (TBL slots) or bitmap (one bit per row of
+// C, sized by the launch) shared by its waves.
+template <int TBL, int THREADS, bool BITS>
 __global__ __launch_bounds__(THREADS) void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list,
                                                        const int32_t *count_p, int64_t *nnz_out, int32_t *status) {
   constexpr int NW = THREADS / kWave;
-  __shared__ int32_t s_keys[TBL];
-  __shared__ SegScratch s_sc[NW];
+  extern __shared__ int32_t s_keys[];  // TBL slots, or (m + 31) / 32 words (all zero between columns)
+  __shared__ SymScratch s_sc[NW];
   __shared__ int s_cnt;
   const int w = threadIdx.x / kWave, l = lane();
   const int count = *count_p;
   s_sc[w].mark[l] = 0;
+  const int words = (int)((a.m + 31) / 32);
+  if (BITS)
+    for (int s = threadIdx.x; s < words; s += THREADS) s_keys[s] = 0;
   // the next column's B range and each wave's first chunk are loaded while
   // one is counted
   const int64_t z = opaque((int64_t)0);  // per-lane addresses: vector loads
@@ -647,14 +680,27 @@ __global__ __launch_bounds__(THREADS) void k_sym_block(ProductArgs<float> a, int
       lp_cols<false, float>(a, c0 + jn, pre);
       jn2 = item + 2 * (int64_t)gridDim.x < count ? ld_global(list + item + 2 * (int64_t)gridDim.x + z) : 0;
     }
-    for (int s = threadIdx.x; s < TBL; s += THREADS) s_keys[s] = kEmpty;
+    if (!BITS)
+      for (int s = threadIdx.x; s < TBL; s += THREADS) s_keys[s] = kEmpty;
     if (threadIdx.x == 0) s_cnt = 0;
     __syncthreads();
     int cnt = 0;
     traverse_product_block<false, float>(
         a, c0 + jj, w, NW, s_sc[w], status,
-        [&](int32_t row, double) { cnt += ht_insert_key(s_keys, TBL, row) ? 1 : 0; }, SlabSel{nullptr, 0, 0, 0},
-        &cur);
+        [&](int32_t row, double) {
+          if (BITS)
+            atomicOr((uint32_t *)&s_keys[row >> 5], 1u << (row & 31));
+          else
+            cnt += ht_insert_key(s_keys, TBL, row) ? 1 : 0;
+        },
+        SlabSel{nullptr, 0, 0, 0}, &cur);
+    if (BITS) {
+      __syncthreads();
+      for (int s = threadIdx.x; s < words; s += THREADS) {
+        cnt += __popc((uint32_t)s_keys[s]);
+        s_keys[s] = 0;
+      }
+    }
     if (more) lp_b<false, float>(a, pre, w, NW);
     cnt = wave_sum_i32(cnt);
     if (l == 0) atomicAdd(&s_cnt, cnt);
@@ -667,13 +713,15 @@ __global__ __launch_bounds__(THREADS) void k_sym_block(ProductArgs<float> a, int
 
 // Heavy columns: exact count with an LDS bitmap over windows of kBitmapRows
 // rows (one pass over the column's terms per window).
-constexpr int kBmWords = (int)(kBitmapRows / 32);
+// The launch sizes the bitmap for min(m, kBitmapRows) rows, so that two
+// workgroups fit a compute unit up to 524,288 rows (the walk over A's columns
+// bounds the kernel: 1.96 ms and 11.5 ms at scales 16 and 18 as with one).
 __global__ __launch_bounds__(1024) void k_sym_bitmap(ProductArgs<float> a, int64_t c0, const int32_t *list,
                                                      const int32_t *count_p, int *cursor, int64_t *nnz_out,
                                                      int32_t *status) {
   constexpr int NW = 1024 / kWave;
-  __shared__ uint32_t s_bm[kBmWords];
-  __shared__ SegScratch s_sc[NW];
+  extern __shared__ uint32_t s_bm[];
+  __shared__ SymScratch s_sc[NW];
   __shared__ unsigned long long s_cnt;
   __shared__ int s_item;
   const int w = threadIdx.x / kWave, l = lane();
@@ -2841,6 +2889,8 @@ __global__ void k_pack_last(int64_t *cp_out, int64_t ncols, int64_t nnz) {
   if (threadIdx.x == 0) cp_out[ncols] = nnz;
 }
 
+constexpr int64_t kLdsPerCu = 160 * 1024;
+
 // Counts of the bins: read back (one synchronization) or left on the device.
 static int bin_counts(WsHeader *hdr, hipStream_t st, bool sync, int *cnt, WsHeader *h) {
   if (sync) {
@@ -2878,18 +2928,54 @@ static int symbolic_pass(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   int32_t *status = &hdr->status;
   static const char *kSymNames[kNumBins] = {"sym_wave64", "sym_wave256", "sym_wave1024", "sym_block4096",
                                             "sym_block32768", "sym_bitmap"};
+  // one bit per row instead of a hash table where the bitmap is no larger
+  const int64_t words = (A->nrows + 31) / 32;
+  const auto bits = [&](int64_t tbl) { return words <= tbl; };
+  // workgroups per CU that the bitmap's LDS and the CU's 2048 threads allow
+  const auto fit = [&](int threads, int64_t lds) {
+    return (int)std::min<int64_t>(2048 / threads, kLdsPerCu / (lds + (threads / kWave) * (int64_t)sizeof(SymScratch) + 64));
+  };
+  const size_t wb = (size_t)words * 4;
+  const size_t bm = (size_t)std::min<int64_t>(words, kBitmapRows / 32) * 4;
   for (int b = 0; b < kNumBins; b++) {
     if (cnt[b] == 0) continue;
     ProfScope prof(kSymNames[b], st);
     const int32_t *list = bins + (int64_t)b * ncol;
     const int32_t *cp = &hdr->bin_count[b];
     switch (b) {
-      case 0: hipLaunchKernelGGL(k_sym_wave<64>, dim3(bin_grid(cnt[b], true, g_bpc[0][0])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status); break;
-      case 1: hipLaunchKernelGGL(k_sym_wave<256>, dim3(bin_grid(cnt[b], true, g_bpc[0][1])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status); break;
-      case 2: hipLaunchKernelGGL(k_sym_wave<1024>, dim3(bin_grid(cnt[b], true, g_bpc[0][2])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status); break;
-      case 3: hipLaunchKernelGGL((k_sym_block<4096, 256>), dim3(bin_grid(cnt[b], false, g_bpc[0][3])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status); break;
-      case 4: hipLaunchKernelGGL((k_sym_block<32768, 1024>), dim3(bin_grid(cnt[b], false, g_bpc[0][4])), dim3(1024), 0, st, a, c0, list, cp, nnz_row, status); break;
-      default: hipLaunchKernelGGL(k_sym_bitmap, dim3(bin_grid(cnt[b], false, 1)), dim3(1024), 0, st, a, c0, list, cp, &hdr->cursor[b], nnz_row, status); break;
+      case 0:
+        if (bits(64))
+          hipLaunchKernelGGL((k_sym_wave<64, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][0])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+        else
+          hipLaunchKernelGGL((k_sym_wave<64, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][0])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+        break;
+      case 1:
+        if (bits(256))
+          hipLaunchKernelGGL((k_sym_wave<256, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][1])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+        else
+          hipLaunchKernelGGL((k_sym_wave<256, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][1])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+        break;
+      case 2:
+        if (bits(1024))
+          hipLaunchKernelGGL((k_sym_wave<1024, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][2])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+        else
+          hipLaunchKernelGGL((k_sym_wave<1024, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][2])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+        break;
+      case 3:
+        if (bits(4096))
+          hipLaunchKernelGGL((k_sym_block<4096, 256, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][3], fit(256, (int64_t)wb)))), dim3(256), wb, st, a, c0, list, cp, nnz_row, status);
+        else
+          hipLaunchKernelGGL((k_sym_block<4096, 256, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][3])), dim3(256), 4096 * 4, st, a, c0, list, cp, nnz_row, status);
+        break;
+      case 4:
+        if (bits(32768))
+          hipLaunchKernelGGL((k_sym_block<32768, 512, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][4], fit(512, (int64_t)wb)))), dim3(512), wb, st, a, c0, list, cp, nnz_row, status);
+        else
+          hipLaunchKernelGGL((k_sym_block<32768, 1024, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][4])), dim3(1024), 32768 * 4, st, a, c0, list, cp, nnz_row, status);
+        break;
+      default:
+        hipLaunchKernelGGL(k_sym_bitmap, dim3(bin_grid(cnt[b], false, fit(1024, (int64_t)bm))), dim3(1024), bm, st, a, c0, list, cp, &hdr->cursor[b], nnz_row, status);
+        break;
     }
     LAUNCHCHK();
   }

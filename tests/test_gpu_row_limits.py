@@ -1,6 +1,7 @@
 """GPU parity at the row counts where a kernel changes its LDS structure:
-the item kernel cuts its work queue into smaller batches when a product has
-few heavy columns."""
+the symbolic pass counts a column's rows in a bitmap instead of a hash table
+up to 32 rows per slot of the bin's table, and the item kernel cuts its work
+queue into smaller batches when a product has few heavy columns."""
 from __future__ import annotations
 
 import numpy as np
@@ -28,6 +29,34 @@ def _csc(m, cols, dtype, rng):
     ri = np.concatenate(cols).astype(np.int32)
     return synth.CSC(m, len(cols), torch.from_numpy(cp), torch.from_numpy(ri),
                      torch.from_numpy(rng.standard_normal(ri.size)).to(dtype))
+
+
+def _operands(m, seed, dtype=torch.float32):
+    """A: columns of 1 to 200 rows that together touch the first and the last
+    row of C; B: columns whose term counts fall into every bin."""
+    rng = np.random.default_rng(seed)
+    acols = [rng.choice(m, min(m, n), replace=False) for n in rng.integers(1, 200, 400)]
+    acols += [np.unique([0, m - 1]), np.array([m - 1]), np.arange(max(0, m - 40), m), np.array([], np.int64)]
+    k = len(acols)
+    bcols = [np.array([], np.int64), np.array([k - 4]), np.array([k - 1]), np.array([k - 4, k - 3, k - 2, 0, 1])]
+    for n in (1, 2, 3, 6, 12, 25, 60, 130, 250, k):
+        bcols += [np.concatenate([rng.choice(k - 4, n - 1, replace=False), [k - 4]]) if n < k else np.arange(k)
+                  for _ in range(3)]
+    return _csc(m, acols, dtype, rng), _csc(k, bcols, dtype, rng)
+
+
+@pytest.mark.parametrize("m", [1, 31, 33, 2047, 2048, 2049, 8192, 8193, 32768, 32769, 131072, 131073, 524289,
+                               1048576, 1048577])
+@pytest.mark.parametrize("layers", [1, 3])
+def test_symbolic_counts_at_bitmap_limits(m, layers):
+    print(f"case: bitmap limit m={m} layers={layers}", flush=True)
+    A, B = _operands(m, 100 + m % 97)
+    plan = S.Engine(A.to("cuda"), B.to("cuda"), layers).plan()
+    assert np.array_equal(plan.nnz_host[-1], oracle.count(A, B))
+    assert np.array_equal(plan.flops.cpu().numpy(), oracle.flops(A, B))
+    if layers > 1:
+        for l, (lo, hi) in enumerate(S.layer_bounds(A.ncols, layers)):
+            assert np.array_equal(plan.nnz_host[l], oracle.count(A, B, klo=lo, khi=hi))
 
 
 @pytest.mark.parametrize("heavy", [1, 5, 63, 64, 65, 300])
