@@ -24,6 +24,7 @@
 #include "lds_hash.hpp"
 #include "hip_host.hpp"
 #include "profile.hpp"
+#include "rank_sort.hpp"
 #include "semiring.hpp"
 
 namespace spg {
@@ -458,7 +459,7 @@ __global__ void k_init_header(WsHeader *h, uint64_t keep_tag, int keep_status = 
     h->left_new = 0;
     for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
     for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
-    h->esc_count[0] = h->esc_count[1] = 0;
+    h->esc_count[0] = h->esc_count[1] = h->esc_count[2] = 0;
     h->split_cursor = 0;
     h->items = 0;
     h->item_cursor = 0;
@@ -512,9 +513,10 @@ __global__ __launch_bounds__(256) void k_bin(const int64_t *Acp, const int64_t *
                                              int64_t m, const int64_t *c_colptr, int64_t *flops_out,
                                              int64_t *nnz_out, int32_t *bins, WsHeader *hdr, int min_bin,
                                              BinCaps caps, const int64_t *esc_flops, double esc_cf) {
-  // lists kNumBins and kNumBins + 1: the row-sorted product's
-  // expand-sort-compress columns (numeric only, when esc_flops is given)
-  constexpr int NL = kNumBins + 2;
+  // lists kNumBins ...: the row-sorted product's expand-sort-compress columns
+  // (numeric only, when esc_flops is given), classes 0 and 2 in two arrays,
+  // class 1 from the end of class 0's
+  constexpr int NL = kNumBins + 3;
   __shared__ int s_cnt[NL];
   __shared__ int s_base[NL];
   __shared__ int s_bin[4 * kBinColsPerWave];
@@ -569,7 +571,11 @@ __global__ __launch_bounds__(256) void k_bin(const int64_t *Acp, const int64_t *
     const int bin = s_bin[slot];
     if (bin >= 0) {
       const int64_t jj = ((int64_t)blockIdx.x * 4 + slot / kBinColsPerWave) * kBinColsPerWave + slot % kBinColsPerWave;
-      bins[(int64_t)bin * ncol + s_base[bin] + s_pos[slot]] = (int32_t)jj;
+      const int64_t p = s_base[bin] + s_pos[slot];
+      const int64_t at = bin == kNumBins + 1   ? (int64_t)(kNumBins + 1) * ncol - 1 - p
+                         : bin == kNumBins + 2 ? (int64_t)(kNumBins + 1) * ncol + p
+                                               : (int64_t)bin * ncol + p;
+      bins[at] = (int32_t)jj;
     }
   }
 }
@@ -1004,7 +1010,7 @@ __global__ __launch_bounds__(THREADS) void k_num_block(Src src, const int32_t *l
 // ----------------------------------------------------------------------------
 // Row-sorted product, columns of low compression ratio: expand-sort-compress.
 // Every product term of the column is placed in LDS as (row, float64 term),
-// the terms are sorted by row with a bitonic network, and each run of equal
+// the terms are sorted by row (stable), and each run of equal
 // rows is combined in sorted order and written at its rank among the runs:
 // the column comes out in ascending row order with no hash table and no
 // second pass over the output.  Where nearly every term has a row of its own
@@ -1116,21 +1122,150 @@ __global__ __launch_bounds__(256) void k_esc_wave(ProductArgs<VT> a, int64_t c0,
   }
 }
 
-// One workgroup per column of up to kEscBlockTerms terms: B(:,j) in chunks
-// of 256 entries, each chunk's terms placed by all threads (the owner of a
-// term found by binary search over the chunk's exclusive prefix), then a
-// bitonic sort in LDS and the runs combined tile by tile.
+// The sorted terms of a column (key[0, n) ascending, val likewise), runs of
+// equal rows combined in order and written at their rank among the runs, by
+// one wave.  Returns the number of runs.
+template <int E, class VT, class SR>
+__device__ __forceinline__ int esc_emit_wave(const int32_t *key, const double *val, int n, int64_t base, int64_t cap,
+                                             int32_t *out_ri, VT *out_v) {
+  const int l = lane();
+  int done = 0;
+#pragma unroll 1
+  for (int e = 0; e < E; e++) {
+    const int t = l + e * kWave;
+    if (e * kWave >= n) break;  // uniform
+    const int32_t k = t < n ? key[t] : 0;
+    const bool head = t < n && (t == 0 || key[t - 1] != k);
+    const uint64_t hm = __ballot(head);
+    if (head) {
+      double acc = 0.0;  // all-zero slot: no term yet
+      for (int u = t; u < n && key[u] == k; u++) SR::acc_plain(acc, val[u]);
+      const int64_t r = done + mbcnt(hm);
+      if (r < cap) {
+        out_ri[base + r] = k;
+        out_v[base + r] = (VT)SR::out(acc);
+      }
+    }
+    done += __popcll(hm);
+  }
+  return done;
+}
+
+// One wavefront per column of kEscWaveTerms + 1 to kEscWave512Terms terms:
+// B(:,j) in chunks of 64 entries, each chunk's terms placed in LDS in rounds
+// of 64 (owners from a marker and a max-scan), then ranked by (row, term
+// number) by distribution (rank_sort.hpp), put in order and combined.  No
+// barrier: the waves of a CU hide each other's chain of dependent loads (B
+// entry, A's column pointers, A's entries).  100,000 columns of 200 terms
+// (A A^T, two entries per inner column): 0.82 ms; a workgroup of 256 threads
+// per column and a bitonic network took 4.72.
 template <class VT, class SR>
-__global__ __launch_bounds__(256) void k_esc_block(ProductArgs<VT> a, int64_t c0, const int32_t *list,
-                                                   const int32_t *count_p, const int64_t *c_colptr, int32_t *out_ri,
-                                                   VT *out_v, int32_t *status) {
-  constexpr int T = 256, NW = T / kWave, N = (int)kEscBlockTerms;
-  __shared__ int32_t s_row[N];
-  __shared__ double s_val[N];
-  __shared__ int s_ex[T];
-  __shared__ int64_t s_ab[T];
-  __shared__ double s_bv[T];
+__global__ __launch_bounds__(256) void k_esc_wave512(ProductArgs<VT> a, int64_t c0, const int32_t *list,
+                                                     const int32_t *count_p, const int64_t *c_colptr,
+                                                     int32_t *out_ri, VT *out_v, int32_t *status) {
+  constexpr int N = (int)kEscWave512Terms, E = N / kWave;
+  __shared__ RankLds<N, double> s_r[4];
+  __shared__ int s_mark[4][kWave];
+  const int w = threadIdx.x / kWave, l = lane();
+  const int count = *count_p;
+  auto &L = s_r[w];
+  s_mark[w][l] = 0;
+  wave_sync();
+  for (int64_t idx = (int64_t)blockIdx.x * 4 + w; idx < count; idx += (int64_t)gridDim.x * 4) {
+    const int64_t jj = list[-idx];  // listed from the end of the array
+    const int64_t bb = a.Bcp[c0 + jj], be = a.Bcp[c0 + jj + 1];
+    const int64_t base = c_colptr[jj], cap = c_colptr[jj + 1] - base;
+    int n = 0;  // terms placed (uniform)
+    bool bad = false;
+    for (int64_t p0 = bb; p0 < be; p0 += kWave) {
+      const int64_t p = p0 + l;
+      int len = 0;
+      int64_t ab = 0;
+      double bv = 0.0;
+      if (p < be) {
+        const int32_t k = a.Bri[p];
+        bv = (double)a.Bv[p];
+        if (k >= a.klo && k < a.khi) {
+          ab = a.Acp[k];
+          len = (int)min<int64_t>(a.Acp[k + 1] - ab, N + 1);
+        }
+      }
+      const int incl = wave_incl_add(len), excl = incl - len;
+      const int tot = readlane(incl, kWave - 1);
+      if (n + tot > N) {  // more terms than the flops the column was listed with
+        bad = true;
+        break;
+      }
+      int carry = 0;
+      for (int f = 0; f < tot; f += kWave) {
+        // owner of term f + l: the last lane whose segment starts at or below it
+        if (len > 0 && excl >= f && excl < f + kWave) s_mark[w][excl - f] = l + 1;
+        wave_sync();
+        const int mk = s_mark[w][l];
+        s_mark[w][l] = 0;
+        const int own = max(wave_incl_max(mk), carry);
+        carry = readlane(own, kWave - 1);
+        const int o = max(own - 1, 0);
+        const int64_t oab = __shfl(ab, o, kWave);
+        const int oex = __shfl(excl, o, kWave);
+        const double obv = __shfl(bv, o, kWave);
+        if (f + l < tot) {
+          const int64_t q = oab + (f + l - oex);
+          L.u.s.key[n + f + l] = a.Ari[q];
+          L.u.s.val[n + f + l] = SR::mul((double)a.Av[q], obv);
+        }
+        wave_sync();
+      }
+      n += tot;
+    }
+    if (bad) {
+      if (l == 0) flag_error(status, 4);
+      continue;
+    }
+    wave_sync();
+    int32_t row[E];
+    double val[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      const int t = l + e * kWave;
+      row[e] = t < n ? L.u.s.key[t] : 0;
+      val[e] = t < n ? L.u.s.val[t] : 0.0;
+    }
+    wave_sync();  // the ranking reuses the arrays
+    int rank[E];
+    rank_rows<kWave, E, true>(row, n, l, L, (uint32_t *)nullptr, rank);
+#pragma unroll
+    for (int e = 0; e < E; e++)
+      if (l + e * kWave < n) {
+        L.u.s.key[rank[e]] = row[e];
+        L.u.s.val[rank[e]] = val[e];
+      }
+    wave_sync();
+    const int runs = esc_emit_wave<E, VT, SR>(L.u.s.key, L.u.s.val, n, base, cap, out_ri, out_v);
+    if (l == 0 && runs != cap) flag_error(status, 4);
+    wave_sync();  // the next column overwrites the LDS
+  }
+}
+
+// One workgroup per column of more terms, up to kEscBlockTerms: B(:,j) in
+// chunks of kEscThreads entries, each chunk's terms placed by all threads (the
+// owner of a term found by binary search over the chunk's exclusive prefix),
+// then ranked, put in order and combined tile by tile.  Columns of 513-4096
+// terms of the square of a scale 16 R-MAT graph: 0.63 ms (bitonic: 2.75).
+constexpr int kEscThreads = 512;
+template <class VT, class SR>
+__global__ __launch_bounds__(kEscThreads) void k_esc_block(ProductArgs<VT> a, int64_t c0, const int32_t *list,
+                                                           const int32_t *count_p, const int64_t *c_colptr,
+                                                           int32_t *out_ri, VT *out_v, int32_t *status) {
+  constexpr int T = kEscThreads, NW = T / kWave, N = (int)kEscBlockTerms, E = N / T;
+  __shared__ RankLds<N, double> L;
+  __shared__ uint32_t s_red[4 * NW];
   __shared__ int s_w[NW];
+  // the chunk's prefix, column starts and B values share the counters' LDS
+  int *s_ex = L.cnt;
+  int64_t *s_ab = reinterpret_cast<int64_t *>(L.cnt + T);
+  double *s_bv = reinterpret_cast<double *>(L.cnt + 3 * T);
+  static_assert(5 * T <= N, "the chunk's arrays fit the counters' room");
   const int tid = threadIdx.x;
   const int count = *count_p;
   for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
@@ -1146,10 +1281,10 @@ __global__ __launch_bounds__(256) void k_esc_block(ProductArgs<VT> a, int64_t c0
       double bv = 0.0;
       if (p < be) {
         const int32_t k = a.Bri[p];
+        bv = (double)a.Bv[p];
         if (k >= a.klo && k < a.khi) {
           ab = a.Acp[k];
           len = (int)min<int64_t>(a.Acp[k + 1] - ab, N + 1);
-          bv = (double)a.Bv[p];
         }
       }
       int tot;
@@ -1171,8 +1306,8 @@ __global__ __launch_bounds__(256) void k_esc_block(ProductArgs<VT> a, int64_t c0
           else hi = mid - 1;
         }
         const int64_t qa = s_ab[lo] + (q - s_ex[lo]);
-        s_row[n + q] = a.Ari[qa];
-        s_val[n + q] = SR::mul((double)a.Av[qa], s_bv[lo]);
+        L.u.s.key[n + q] = a.Ari[qa];
+        L.u.s.val[n + q] = SR::mul((double)a.Av[qa], s_bv[lo]);
       }
       n += tot;
       __syncthreads();  // s_ex, s_ab, s_bv, s_w are reused by the next chunk
@@ -1182,41 +1317,34 @@ __global__ __launch_bounds__(256) void k_esc_block(ProductArgs<VT> a, int64_t c0
       __syncthreads();
       continue;
     }
-    int M = 128;
-    while (M < n) M <<= 1;
-    for (int t = n + tid; t < M; t += T) {
-      s_row[t] = INT32_MAX;  // padding sorts last
-      s_val[t] = 0.0;
+    int32_t row[E];
+    double val[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      const int t = tid + e * T;
+      row[e] = t < n ? L.u.s.key[t] : 0;
+      val[e] = t < n ? L.u.s.val[t] : 0.0;
     }
-    __syncthreads();
-    for (int k = 2; k <= M; k <<= 1) {
-      for (int s = k >> 1; s > 0; s >>= 1) {
-        for (int t = tid; t < M / 2; t += T) {
-          const int lo = ((t & ~(s - 1)) << 1) | (t & (s - 1));  // lower element of pair t at distance s
-          const int hi = lo + s;
-          const bool up = (lo & k) == 0;
-          const int32_t kl = s_row[lo], kh = s_row[hi];
-          if ((kl > kh) == up) {
-            const double vl = s_val[lo];
-            s_row[lo] = kh;
-            s_row[hi] = kl;
-            s_val[lo] = s_val[hi];
-            s_val[hi] = vl;
-          }
-        }
-        __syncthreads();
+    __syncthreads();  // the ranking reuses the arrays
+    int rank[E];
+    rank_rows<T, E, true>(row, n, tid, L, s_red, rank);
+#pragma unroll
+    for (int e = 0; e < E; e++)
+      if (tid + e * T < n) {
+        L.u.s.key[rank[e]] = row[e];
+        L.u.s.val[rank[e]] = val[e];
       }
-    }
+    __syncthreads();
     int done = 0;  // runs written so far (uniform)
     for (int t0 = 0; t0 < n; t0 += T) {
       const int t = t0 + tid;
-      const int32_t key = t < n ? s_row[t] : INT32_MAX;
-      const bool head = t < n && (t == 0 || s_row[t - 1] != key);
+      const int32_t key = t < n ? L.u.s.key[t] : INT32_MAX;
+      const bool head = t < n && (t == 0 || L.u.s.key[t - 1] != key);
       int tot;
       const int r = done + block_excl<NW>(head ? 1 : 0, s_w, tot);
       if (head) {
         double acc = 0.0;  // all-zero slot: no term yet
-        for (int u = t; u < n && s_row[u] == key; u++) SR::acc_plain(acc, s_val[u]);
+        for (int u = t; u < n && L.u.s.key[u] == key; u++) SR::acc_plain(acc, L.u.s.val[u]);
         if (r < cap) {
           out_ri[base + r] = key;
           out_v[base + r] = (VT)SR::out(acc);
@@ -1226,7 +1354,7 @@ __global__ __launch_bounds__(256) void k_esc_block(ProductArgs<VT> a, int64_t c0
       __syncthreads();  // s_w is reused by the next tile
     }
     if (tid == 0 && done != cap) flag_error(status, 4);
-    __syncthreads();  // the next column overwrites s_row, s_val
+    __syncthreads();  // the next column overwrites the LDS
   }
 }
 
@@ -1852,6 +1980,7 @@ __global__ __launch_bounds__(kHvThreads) void k_hv_items(Src src, const int32_t 
   while (ic > 1 && (hc + ic - 1) / ic * P < (int64_t)kItemBatches * gridDim.x) ic >>= 1;
   const int64_t nb = (hc + ic - 1) / ic;
   const int64_t nbatch = nb * P;
+  if (blockIdx.x >= nbatch) return;  // the other workgroups empty the queue
   double *acc = (double *)s_tab;
   uint32_t *bits = (uint32_t *)(s_tab + kBitsOff);
   int32_t *keys = (int32_t *)s_tab;  // hash items: key = row + 1, 0 = free
@@ -3085,17 +3214,21 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   src.c0 = c0;
   if (esc) {
     int32_t *status = &hdr->status;
-    for (int e = 0; e < 2; e++) {
+    static const char *kEscNames[3] = {"esc_wave", "esc_wave512", "esc_block"};
+    for (int e = 0; e < 3; e++) {
       const int ce = sync ? h.esc_count[e] : -1;
       if (ce == 0) continue;
-      const int32_t *list = bins + (int64_t)(kNumBins + e) * ncol;
+      const int32_t *list = bins + (int64_t)(kNumBins + (e == 0 ? 0 : 1)) * ncol - (e == 1 ? 1 : 0);
       const int32_t *cp = &hdr->esc_count[e];
-      ProfScope prof(e == 0 ? "esc_wave" : "esc_block", st);
+      ProfScope prof(kEscNames[e], st);
       if (e == 0)
         hipLaunchKernelGGL((k_esc_wave<VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st, src.a, c0, list, cp,
                            c_colptr, esc->ri, (VT *)esc->v, status);
+      else if (e == 1)
+        hipLaunchKernelGGL((k_esc_wave512<VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st, src.a, c0, list, cp,
+                           c_colptr, esc->ri, (VT *)esc->v, status);
       else
-        hipLaunchKernelGGL((k_esc_block<VT, SR>), dim3(bin_grid(ce, false, 3)), dim3(256), 0, st, src.a, c0, list,
+        hipLaunchKernelGGL((k_esc_block<VT, SR>), dim3(bin_grid(ce, false, 4)), dim3(kEscThreads), 0, st, src.a, c0, list,
                            cp, c_colptr, esc->ri, (VT *)esc->v, status);
       LAUNCHCHK();
     }

@@ -10,13 +10,14 @@
 // same).  Rows must be unique within a column, as in every output of the
 // library.  Columns are binned by length:
 //   up to 64 entries  : one wave, a bitonic network across the lanes;
-//   up to 4096        : one workgroup, a bitonic network in LDS;
-//   longer            : one workgroup of 1024 threads, row windows of
-//                       2^19 rows: the window's rows are marked in an LDS
-//                       bitmap, a prefix count over the bitmap words gives
-//                       every row its rank, and each entry is written
-//                       straight to its sorted position (no data movement
-//                       between passes; a window with no entry is skipped).
+//   up to 512         : one wave, ranked in LDS by distribution;
+//   up to 4096        : one workgroup, likewise;
+//   longer            : one workgroup, row windows of up to 2^19 rows: the
+//                       window's rows are marked in an LDS bitmap, a prefix
+//                       count over the bitmap words gives every row its
+//                       rank, and each entry is written straight to its
+//                       sorted position (no data movement between passes; a
+//                       window with no entry is skipped).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -24,21 +25,22 @@
 #include "hip_host.hpp"
 #include "internal.hpp"
 #include "profile.hpp"
+#include "rank_sort.hpp"
 
 namespace spg {
 namespace {
 
 constexpr int kSortWaveLen = 64;
+constexpr int kSortWave512Len = 512;
 constexpr int kSortBlockLen = 4096;
-constexpr int kSortBlockThreads = 256;
-constexpr int kSortHeavyThreads = 1024;
-constexpr int kSortWinShift = 19;
-constexpr int64_t kSortWinRows = int64_t(1) << kSortWinShift;
-constexpr int kSortWinWords = (int)(kSortWinRows / 32);
+constexpr int kSortBlockThreads = 512;
+constexpr int kSortWinWords = (1 << 19) / 32;  // bitmap words of the largest row window
 constexpr int kSortDupCode = 11;  // status code: a row twice in one column, or a row outside [0, m)
 
-// Column lists per length class: lists[c * ncols + i], counts in the
-// header's first three bin counters.
+// Column lists per length class, counts in the header's bin counters: up to
+// 64 entries from the front of the first array (bin_count[0]), up to 512 from
+// its end (bin_count[3]), up to 4096 in the second (bin_count[1]), longer ones
+// in the third (bin_count[2]).
 // Columns formed in row order by expand-sort-compress (skip_flops given) are
 // left out.
 __global__ __launch_bounds__(256) void k_sort_bin(const int64_t *cp, int64_t n, int32_t *lists, WsHeader *hdr,
@@ -47,16 +49,18 @@ __global__ __launch_bounds__(256) void k_sort_bin(const int64_t *cp, int64_t n, 
   int cls = -1;
   if (j < n) {
     const int64_t len = cp[j + 1] - cp[j];
-    cls = len <= 0 ? -1 : (len <= kSortWaveLen ? 0 : (len <= kSortBlockLen ? 1 : 2));
+    cls = len <= 0 ? -1
+                   : (len <= kSortWaveLen ? 0 : (len <= kSortWave512Len ? 3 : (len <= kSortBlockLen ? 1 : 2)));
     if (skip_flops && esc_class(skip_flops[j], len, skip_cf) >= 0) cls = -1;
   }
-  for (int c = 0; c < 3; c++) {
+  for (int c = 0; c < 4; c++) {
     const uint64_t mask = __ballot(cls == c);
     if (!mask) continue;
     int base = 0;
     if (lane() == 0) base = atomicAdd(&hdr->bin_count[c], __popcll(mask));
     base = readlane(base, 0);
-    if (cls == c) lists[(int64_t)c * n + base + mbcnt(mask)] = (int32_t)j;
+    const int64_t p = base + mbcnt(mask);
+    if (cls == c) lists[c == 3 ? n - 1 - p : (int64_t)c * n + p] = (int32_t)j;
   }
 }
 
@@ -106,135 +110,226 @@ __global__ __launch_bounds__(256) void k_sort_wave(const int64_t *cp, const int3
   }
 }
 
+// 65 to 512 entries: one wave per column.  The column's loads are issued
+// together, the sorted order is formed in LDS (rank_sort.hpp) and written out
+// in order, so both sides of the copy are coalesced.  2.1e6 entries in 18,900
+// columns of 65-512: 19 us (a workgroup's bitonic network in LDS took 135).
+template <class VT>
+__global__ __launch_bounds__(256) void k_sort_wave512(const int64_t *cp, const int32_t *ri, const VT *v, int64_t m,
+                                                      const int32_t *list, const int32_t *count_p, int32_t *ro,
+                                                      VT *vo, int32_t *status) {
+  constexpr int E = kSortWave512Len / kWave;
+  __shared__ RankLds<kSortWave512Len, VT> s_r[4];
+  const int count = *count_p;
+  const int w = threadIdx.x / kWave, l = lane();
+  auto &L = s_r[w];
+  for (int64_t i = (int64_t)blockIdx.x * 4 + w; i < count; i += (int64_t)gridDim.x * 4) {
+    const int64_t j = list[-i];  // listed from the end of the array
+    const int64_t b = cp[j];
+    const int len = (int)(cp[j + 1] - b);
+    int32_t row[E];
+    VT val[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      row[e] = 0;
+      val[e] = VT(0);
+      if (l + e * kWave < len) {
+        row[e] = ri[b + l + e * kWave];
+        val[e] = v[b + l + e * kWave];
+      }
+    }
+    int rank[E];
+    rank_rows<kWave, E, false>(row, len, l, L, (uint32_t *)nullptr, rank);
+#pragma unroll
+    for (int e = 0; e < E; e++)
+      if (l + e * kWave < len) {
+        L.u.s.key[rank[e]] = row[e];
+        L.u.s.val[rank[e]] = val[e];
+      }
+    wave_sync();
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      const int t = l + e * kWave;
+      if (t < len) {
+        const int32_t k = L.u.s.key[t];
+        ro[b + t] = k;
+        vo[b + t] = L.u.s.val[t];
+        bad |= k < 0 || (int64_t)k >= m;
+        // a repeated row: two entries took one place, which shows next to them
+        // or leaves a place that no entry took
+        bad |= L.u.s.key[rank[e]] != row[e] || (t + 1 < len && L.u.s.key[t + 1] <= k);
+      }
+    }
+    if (__ballot(bad) && l == 0) flag_error(status, kSortDupCode);
+    wave_sync();  // the next column overwrites the LDS
+  }
+}
+
+// 513 to 4096 entries: one workgroup per column, likewise.  9e6 entries
+// (float64) in columns of 513-4096: 39 us against 424 by the bitonic network.
 template <class VT>
 __global__ __launch_bounds__(kSortBlockThreads) void k_sort_block(const int64_t *cp, const int32_t *ri, const VT *v,
                                                                   int64_t m, const int32_t *list,
                                                                   const int32_t *count_p, int32_t *ro, VT *vo,
                                                                   int32_t *status) {
-  __shared__ int32_t s_k[kSortBlockLen];
-  __shared__ VT s_v[kSortBlockLen];
+  constexpr int E = kSortBlockLen / kSortBlockThreads;
+  __shared__ RankLds<kSortBlockLen, VT> L;
+  __shared__ uint32_t s_red[4 * kSortBlockThreads / kWave];
   const int count = *count_p;
+  const int t = threadIdx.x;
   for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
     const int64_t j = list[i];
     const int64_t b = cp[j];
     const int len = (int)(cp[j + 1] - b);
-    int N = 128;
-    while (N < len) N <<= 1;
-    for (int t = threadIdx.x; t < N; t += kSortBlockThreads) {
-      s_k[t] = t < len ? ri[b + t] : INT32_MAX;
-      s_v[t] = t < len ? v[b + t] : VT(0);
-    }
-    __syncthreads();
-    for (int k = 2; k <= N; k <<= 1) {
-      for (int s = k >> 1; s > 0; s >>= 1) {
-        for (int t = threadIdx.x; t < N / 2; t += kSortBlockThreads) {
-          const int a = ((t & ~(s - 1)) << 1) | (t & (s - 1));  // lower element of pair t at distance s
-          const int c = a + s;
-          const bool up = (a & k) == 0;
-          const int32_t ka = s_k[a], kc = s_k[c];
-          if ((ka > kc) == up) {
-            const VT va = s_v[a];
-            s_k[a] = kc;
-            s_k[c] = ka;
-            s_v[a] = s_v[c];
-            s_v[c] = va;
-          }
-        }
-        __syncthreads();
+    int32_t row[E];
+    VT val[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      const int q = t + e * kSortBlockThreads;
+      row[e] = 0;
+      val[e] = VT(0);
+      if (q < len) {
+        row[e] = ri[b + q];
+        val[e] = v[b + q];
       }
     }
+    int rank[E];
+    rank_rows<kSortBlockThreads, E, false>(row, len, t, L, s_red, rank);
+#pragma unroll
+    for (int e = 0; e < E; e++)
+      if (t + e * kSortBlockThreads < len) {
+        L.u.s.key[rank[e]] = row[e];
+        L.u.s.val[rank[e]] = val[e];
+      }
+    __syncthreads();
     bool bad = false;
-    for (int t = threadIdx.x; t < len; t += kSortBlockThreads) {
-      const int32_t k = s_k[t];
-      ro[b + t] = k;
-      vo[b + t] = s_v[t];
-      bad |= (t + 1 < len && s_k[t + 1] == k) || k < 0 || (int64_t)k >= m;  // a repeated row sits next to its twin
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      const int q = t + e * kSortBlockThreads;
+      if (q < len) {
+        const int32_t k = L.u.s.key[q];
+        ro[b + q] = k;
+        vo[b + q] = L.u.s.val[q];
+        bad |= k < 0 || (int64_t)k >= m || L.u.s.key[rank[e]] != row[e] || (q + 1 < len && L.u.s.key[q + 1] <= k);
+      }
     }
     if (__ballot(bad) && lane() == 0) flag_error(status, kSortDupCode);
-    __syncthreads();  // the next column overwrites s_k, s_v
+    __syncthreads();  // the next column overwrites the LDS
   }
 }
 
-template <class VT>
-__global__ __launch_bounds__(kSortHeavyThreads) void k_sort_heavy(const int64_t *cp, const int32_t *ri, const VT *v,
-                                                                  int64_t m, const int32_t *list,
-                                                                  const int32_t *count_p, int32_t *ro, VT *vo,
-                                                                  int32_t *status) {
-  constexpr int NW = kSortHeavyThreads / kWave;
-  constexpr int kWordsPerThread = kSortWinWords / kSortHeavyThreads;
-  static_assert(kSortWinWords % kSortHeavyThreads == 0, "bitmap words split evenly over threads");
-  __shared__ uint32_t s_bits[kSortWinWords];
-  __shared__ int32_t s_pref[kSortWinWords];  // entries of the window in words before this one
+// Longer columns: windows of rows (the launch sizes the window: every row up
+// to 2^19, so one window where m allows).  s_dyn holds the window's bitmap
+// and, per word, the entries of the window in words before it.  Columns come
+// from a work queue.  A window no larger than m leaves room for two to four
+// workgroups per CU, and one that covers m saves the pass for the row range:
+// 3.1e8 float32 entries at m = 65,536 take 1.58 ms (3.25 with one workgroup
+// and a 2^19-row window each; the copy itself 1.04 at 4.77 TB/s).
+template <int THREADS, class VT>
+__global__ __launch_bounds__(THREADS) void k_sort_heavy(const int64_t *cp, const int32_t *ri, const VT *v, int64_t m,
+                                                        const int32_t *list, const int32_t *count_p, int *cursor,
+                                                        int words, int32_t *ro, VT *vo, int32_t *status) {
+  constexpr int NW = THREADS / kWave;
+  constexpr int U = 8;
+  extern __shared__ uint32_t s_dyn[];
+  uint32_t *s_bits = s_dyn;
+  int32_t *s_pref = (int32_t *)(s_dyn + words);
   __shared__ int s_wtot[NW];
-  __shared__ int s_lo, s_hi;
+  __shared__ uint32_t s_lo[NW], s_hi[NW];
+  __shared__ int s_item;
   const int w = threadIdx.x / kWave, l = lane();
   const int count = *count_p;
-  for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
+  if (blockIdx.x >= count) return;  // the other workgroups empty the queue
+  const int64_t win = (int64_t)words * 32;
+  const int per = words / NW;  // a multiple of 64
+  for (;;) {
+    if (threadIdx.x == 0) s_item = atomicAdd(cursor, 1);
+    __syncthreads();
+    const int64_t i = s_item;
+    if (i >= count) break;
     const int64_t j = list[i];
     const int64_t b = cp[j], e = cp[j + 1];
-    // the column's row range: windows that hold no entry are skipped
-    int lo = INT32_MAX, hi = -1;
-    for (int64_t p = b + threadIdx.x; p < e; p += kSortHeavyThreads) {
-      const int32_t r = ri[p];
-      lo = min(lo, r);
-      hi = max(hi, r);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = min(lo, __shfl_xor(lo, o, kWave));
-      hi = max(hi, __shfl_xor(hi, o, kWave));
-    }
-    if (threadIdx.x == 0) {
-      s_lo = INT32_MAX;
-      s_hi = -1;
-    }
-    __syncthreads();
-    if (l == 0) {
-      atomicMin(&s_lo, lo);
-      atomicMax(&s_hi, hi);
-    }
-    __syncthreads();
-    const int64_t rlo = max((int64_t)s_lo, (int64_t)0), rhi = min((int64_t)s_hi, m - 1);
-    int64_t done = 0;
-    for (int64_t w0 = (rlo >> kSortWinShift) << kSortWinShift; w0 <= rhi; w0 += kSortWinRows) {
-      for (int q = threadIdx.x; q < kSortWinWords; q += kSortHeavyThreads) s_bits[q] = 0u;
-      __syncthreads();
-      for (int64_t p = b + threadIdx.x; p < e; p += kSortHeavyThreads) {
-        const int64_t r = (int64_t)ri[p] - w0;
-        if (r >= 0 && r < kSortWinRows) atomicOr(&s_bits[r >> 5], 1u << (r & 31));
+    int64_t rlo = 0, rhi = m - 1;
+    if (m > win) {  // the column's row range: windows that hold no entry are skipped
+      uint32_t hi = 0, nlo = 0;
+      for (int64_t p = b + threadIdx.x; p < e; p += THREADS) {
+        const int32_t r = ri[p];
+        hi = max(hi, (uint32_t)max(r, 0));
+        nlo = max(nlo, ~(uint32_t)max(r, 0));
+      }
+      hi = wave_umax(hi);
+      nlo = wave_umax(nlo);
+      if (l == 0) {
+        s_hi[w] = hi;
+        s_lo[w] = nlo;
       }
       __syncthreads();
-      // exclusive prefix of the word counts: kWordsPerThread consecutive
-      // words per thread, a scan over the threads
-      const int q0 = threadIdx.x * kWordsPerThread;
-      int c = 0;
-#pragma unroll 8
-      for (int q = 0; q < kWordsPerThread; q++) c += __popc(s_bits[q0 + q]);
-      const int incl = wave_incl_add(c);
-      if (l == kWave - 1) s_wtot[w] = incl;
+#pragma unroll
+      for (int z = 0; z < NW; z++) {
+        hi = max(hi, s_hi[z]);
+        nlo = max(nlo, s_lo[z]);
+      }
+      rlo = (int64_t)~nlo;
+      rhi = min((int64_t)hi, m - 1);
+    }
+    int64_t done = 0;
+    for (int64_t w0 = rlo / win * win; w0 <= rhi; w0 += win) {
+      const int64_t lim = min(win, m - w0);
+      for (int q = threadIdx.x; q < words; q += THREADS) s_bits[q] = 0u;
+      __syncthreads();
+      for (int64_t p0 = b + threadIdx.x; p0 < e; p0 += U * THREADS) {
+        int32_t row[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int64_t p = p0 + u * THREADS;
+          row[u] = p < e ? ri[p] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int64_t r = (int64_t)opaque(row[u]) - w0;
+          if (row[u] >= 0 && r >= 0 && r < lim) atomicOr(&s_bits[r >> 5], 1u << (r & 31));
+        }
+      }
+      __syncthreads();
+      // exclusive prefix of the word counts: wave w takes its share of the
+      // words, 64 at a time; then the waves' totals are added
+      int run = 0;
+      for (int q = w * per; q < (w + 1) * per; q += kWave) {
+        const int c = __popc(s_bits[q + l]);
+        const int incl = wave_incl_add(c);
+        s_pref[q + l] = run + incl - c;
+        run += readlane(incl, kWave - 1);
+      }
+      if (l == 0) s_wtot[w] = run;
       __syncthreads();
       int before = 0, tot = 0;
 #pragma unroll
       for (int z = 0; z < NW; z++) {
-        const int t = s_wtot[z];
-        if (z < w) before += t;
-        tot += t;
+        if (z < w) before += s_wtot[z];
+        tot += s_wtot[z];
       }
-      int run = before + incl - c;
-#pragma unroll 8
-      for (int q = 0; q < kWordsPerThread; q++) {
-        s_pref[q0 + q] = run;
-        run += __popc(s_bits[q0 + q]);
-      }
+      for (int q = w * per; q < (w + 1) * per; q += kWave) s_pref[q + l] += before;
       __syncthreads();
-      for (int64_t p = b + threadIdx.x; p < e; p += kSortHeavyThreads) {
-        const int32_t row = ri[p];
-        const int64_t r = (int64_t)row - w0;
-        if (r >= 0 && r < kSortWinRows) {
-          const int q = (int)(r >> 5);
-          const int64_t dst = b + done + s_pref[q] + __popc(s_bits[q] & ((1u << (r & 31)) - 1u));
-          if (dst < e) {
-            ro[dst] = row;
-            vo[dst] = v[p];
+      for (int64_t p0 = b + threadIdx.x; p0 < e; p0 += U * THREADS) {
+        int32_t row[U];
+        VT val[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int64_t p = p0 + u * THREADS;
+          row[u] = p < e ? ri[p] : -1;
+          val[u] = p < e ? v[p] : VT(0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int64_t r = (int64_t)opaque(row[u]) - w0;
+          if (row[u] >= 0 && r >= 0 && r < lim) {
+            const int q = (int)(r >> 5);
+            const int64_t dst = b + done + s_pref[q] + __popc(s_bits[q] & ((1u << (r & 31)) - 1u));
+            if (dst < e) {
+              ro[dst] = row[u];
+              vo[dst] = opaque(val[u]);
+            }
           }
         }
       }
@@ -258,11 +353,23 @@ int sort_typed(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHea
   hipLaunchKernelGGL(k_sort_wave<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows, lists,
                      (const int32_t *)&hdr->bin_count[0], ro, (VT *)vo, &hdr->status);
   LAUNCHCHK();
+  hipLaunchKernelGGL(k_sort_wave512<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows,
+                     lists + n - 1, (const int32_t *)&hdr->bin_count[3], ro, (VT *)vo, &hdr->status);
+  LAUNCHCHK();
   hipLaunchKernelGGL(k_sort_block<VT>, dim3(4 * cus), dim3(kSortBlockThreads), 0, st, C->colptr, C->rowidx, v,
                      C->nrows, lists + n, (const int32_t *)&hdr->bin_count[1], ro, (VT *)vo, &hdr->status);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_sort_heavy<VT>, dim3(cus), dim3(kSortHeavyThreads), 0, st, C->colptr, C->rowidx, v, C->nrows,
-                     lists + 2 * n, (const int32_t *)&hdr->bin_count[2], ro, (VT *)vo, &hdr->status);
+  // a window as large as m asks for, so that several workgroups fit a CU
+  int words = 1024;
+  while (words < kSortWinWords && (int64_t)words * 32 < C->nrows) words *= 2;
+  const size_t lds = (size_t)words * 8;
+  const int32_t *hl = lists + 2 * n, *hc = (const int32_t *)&hdr->bin_count[2];
+  if (words <= 4096)
+    hipLaunchKernelGGL((k_sort_heavy<512, VT>), dim3(4 * cus), dim3(512), lds, st, C->colptr, C->rowidx, v, C->nrows,
+                       hl, hc, &hdr->cursor[2], words, ro, (VT *)vo, &hdr->status);
+  else
+    hipLaunchKernelGGL((k_sort_heavy<1024, VT>), dim3((words <= 8192 ? 2 : 1) * cus), dim3(1024), lds, st, C->colptr,
+                       C->rowidx, v, C->nrows, hl, hc, &hdr->cursor[2], words, ro, (VT *)vo, &hdr->status);
   LAUNCHCHK();
   return SPGEMM_OK;
 }
