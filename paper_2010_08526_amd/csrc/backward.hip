@@ -101,16 +101,19 @@ struct MxtyArgs {
 };
 
 // Binning by nnz(Y(:,j)) with the numeric bins' capacities; columns of M
-// with no entry need no work.
+// with no entry need no work.  Columns that fill at most half of what bins 2
+// and 3 hold take tables of half the slots (two more lists): LDS, and with it
+// the waves in flight, is what bounds these kernels.
 constexpr int kMxColsPerWave = 16;
 __global__ __launch_bounds__(256) void k_mxty_bin(const int64_t *Ycp, const int64_t *Mcp, int64_t ncol, int min_bin,
                                                   BinCaps caps, int32_t *bins, WsHeader *hdr) {
-  __shared__ int s_cnt[kNumBins];
-  __shared__ int s_base[kNumBins];
+  constexpr int NL = kNumBins + 2;
+  __shared__ int s_cnt[NL];
+  __shared__ int s_base[NL];
   __shared__ int s_bin[256];
   __shared__ int s_pos[256];
   const int t = threadIdx.x;
-  if (t < kNumBins) s_cnt[t] = 0;
+  if (t < NL) s_cnt[t] = 0;
   __syncthreads();
   const int64_t j = (int64_t)blockIdx.x * 256 + t;
   int bin = -1;
@@ -121,13 +124,19 @@ __global__ __launch_bounds__(256) void k_mxty_bin(const int64_t *Ycp, const int6
     for (int b = kNumBins - 2; b >= 0; b--)
       if (u <= caps.cap[b]) bin = b;
     bin = max(bin, min_bin);
+    // half tables: listed from the end of their bin's array
+    if ((bin == 2 || bin == 3) && 2 * u <= kNumTableCap[bin]) bin += kNumBins - 2;
   }
   s_bin[t] = bin;
   s_pos[t] = bin >= 0 ? atomicAdd(&s_cnt[bin], 1) : 0;
   __syncthreads();
-  if (t < kNumBins) s_base[t] = s_cnt[t] ? atomicAdd(&hdr->bin_count[t], s_cnt[t]) : 0;
+  if (t < NL)
+    s_base[t] = s_cnt[t] ? atomicAdd(t < kNumBins ? &hdr->bin_count[t] : &hdr->half_count[t - kNumBins], s_cnt[t]) : 0;
   __syncthreads();
-  if (bin >= 0) bins[(int64_t)bin * ncol + s_base[bin] + s_pos[t]] = (int32_t)j;
+  if (bin >= 0) {
+    const int64_t p = s_base[bin] + s_pos[t];
+    bins[bin < kNumBins ? (int64_t)bin * ncol + p : (int64_t)(bin - kNumBins + 3) * ncol - 1 - p] = (int32_t)j;
+  }
 }
 
 constexpr int kLongDot = 64;
@@ -143,6 +152,12 @@ struct FbScratch {
 };
 constexpr int kFbPipe = 4;  // rounds whose gathers are in flight together
 
+// Entries a wave takes at once when nw waves share a column of n entries: 64,
+// or fewer where that would leave waves without any.
+__device__ __forceinline__ int chunk_width(int64_t n, int nw) {
+  return (int)max((int64_t)1, min((int64_t)kWave, (n + nw - 1) / nw));
+}
+
 // Dot products for the entries [pb, pe) of M(:,j) taken in chunks of 64
 // (chunk c by the wave with c % c_stride == c_rank).  Short X columns are
 // flattened into rounds of 64 products, one per lane (owners as in the
@@ -153,8 +168,10 @@ template <class VT, class Look>
 __device__ __forceinline__ void mxty_dots(const MxtyArgs<VT> &a, int64_t pb, int64_t pe, int c_rank, int c_stride,
                                           int32_t *status, FbScratch &sc, Look &&look) {
   const int l = lane();
-  for (int64_t base = pb + (int64_t)c_rank * kWave; base < pe; base += (int64_t)c_stride * kWave) {
+  const int cw = chunk_width(pe - pb, c_stride);
+  for (int64_t base = pb + (int64_t)c_rank * cw, end = pe; base < end; base += (int64_t)c_stride * cw) {
     const int64_t p = base + l;
+    pe = min(end, base + cw);  // this chunk's entries
     int64_t x0 = 0, x1 = 0;
     if (p < pe) {
       const int32_t k = a.Mri[p];
@@ -264,27 +281,27 @@ __device__ __forceinline__ void mxty_dots(const MxtyArgs<VT> &a, int64_t pb, int
 
 // One wavefront per column, TBL-slot table of Y(:,j) private to the wave.
 template <int TBL, class VT>
-__global__ __launch_bounds__(256) void k_mxty_wave(MxtyArgs<VT> a, const int32_t *list, const int32_t *count_p,
+__global__ __launch_bounds__(256) void k_mxty_wave(MxtyArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
                                                    int32_t *status) {
   __shared__ int32_t s_keys[4][TBL];
-  __shared__ double s_vals[4][TBL];
+  __shared__ VT s_vals[4][TBL];
   __shared__ FbScratch s_fb[4];
   const int w = threadIdx.x / kWave, l = lane();
   const int count = *count_p;
   int32_t *keys = s_keys[w];
-  double *vals = s_vals[w];
+  VT *vals = s_vals[w];
   s_fb[w].mark[l] = 0;
-  for (int idx = blockIdx.x * 4 + w; idx < count; idx += gridDim.x * 4) {
+  for (int64_t idx = (int64_t)blockIdx.x * 4 + w; idx < count; idx += (int64_t)gridDim.x * 4) {
     for (int s = l; s < TBL; s += kWave) {
       keys[s] = kEmpty;
-      vals[s] = 0.0;
+      vals[s] = VT(0);
     }
     wave_sync();
-    const int32_t j = list[idx];
+    const int32_t j = list[dir * idx];
     for (int64_t p = a.Ycp[j] + l; p < a.Ycp[j + 1]; p += kWave) {
       const int32_t r = a.Yri[p];
       if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(keys, vals, TBL, r, (double)a.Yv[p]);
+        ht_accumulate(keys, vals, TBL, r, a.Yv[p]);
       else
         flag_error(status, 3);
     }
@@ -296,26 +313,26 @@ __global__ __launch_bounds__(256) void k_mxty_wave(MxtyArgs<VT> a, const int32_t
 
 // One workgroup per column, shared table.
 template <int TBL, int THREADS, class VT>
-__global__ __launch_bounds__(THREADS) void k_mxty_block(MxtyArgs<VT> a, const int32_t *list, const int32_t *count_p,
+__global__ __launch_bounds__(THREADS) void k_mxty_block(MxtyArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
                                                         int32_t *status) {
   constexpr int NW = THREADS / kWave;
   __shared__ int32_t s_keys[TBL];
-  __shared__ double s_vals[TBL];
+  __shared__ VT s_vals[TBL];
   __shared__ FbScratch s_fb[NW];
   const int w = threadIdx.x / kWave;
   const int count = *count_p;
   s_fb[w].mark[lane()] = 0;
-  for (int item = blockIdx.x; item < count; item += gridDim.x) {
+  for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
     for (int s = threadIdx.x; s < TBL; s += THREADS) {
       s_keys[s] = kEmpty;
-      s_vals[s] = 0.0;
+      s_vals[s] = VT(0);
     }
     __syncthreads();
-    const int32_t j = list[item];
+    const int32_t j = list[dir * item];
     for (int64_t p = a.Ycp[j] + threadIdx.x; p < a.Ycp[j + 1]; p += THREADS) {
       const int32_t r = a.Yri[p];
       if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(s_keys, s_vals, TBL, r, (double)a.Yv[p]);
+        ht_accumulate(s_keys, s_vals, TBL, r, a.Yv[p]);
       else
         flag_error(status, 3);
     }
@@ -389,17 +406,22 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
   MxtyArgs<VT> a{X->colptr, X->rowidx, (const VT *)X->values, Y->colptr, Y->rowidx, (const VT *)Y->values,
                  M->colptr, M->rowidx, (VT *)out, Y->nrows, X->ncols, X->nnz};
   int32_t *status = &hdr->status;
-  for (int b = 0; b < kNumBins - 1; b++) {
-    if (cnt[b] == 0) continue;
+  for (int b = 0; b < kNumBins + 1; b++) {
+    const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
+    const int c = half < 0 ? cnt[b] : (sync ? h.half_count[half] : -1);
+    if (c == 0) continue;
     ProfScope prof("masked_xty", st);
-    const int32_t *list = bins + (int64_t)b * n;
-    const int32_t *cp = &hdr->bin_count[b];
+    const int32_t *list = half < 0 ? bins + (int64_t)b * n : bins + (int64_t)(half + 3) * n - 1;
+    const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
+    const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_mxty_wave<64, VT>), dim3(mx_grid(cnt[b], true, 8)), dim3(256), 0, st, a, list, cp, status); break;
-      case 1: hipLaunchKernelGGL((k_mxty_wave<256, VT>), dim3(mx_grid(cnt[b], true, 8)), dim3(256), 0, st, a, list, cp, status); break;
-      case 2: hipLaunchKernelGGL((k_mxty_wave<1024, VT>), dim3(mx_grid(cnt[b], true, 4)), dim3(256), 0, st, a, list, cp, status); break;
-      case 3: hipLaunchKernelGGL((k_mxty_block<4096, 256, VT>), dim3(mx_grid(cnt[b], false, 4)), dim3(256), 0, st, a, list, cp, status); break;
-      default: hipLaunchKernelGGL((k_mxty_block<10240, 1024, VT>), dim3(mx_grid(cnt[b], false, 1)), dim3(1024), 0, st, a, list, cp, status); break;
+      case 0: hipLaunchKernelGGL((k_mxty_wave<64, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 1: hipLaunchKernelGGL((k_mxty_wave<256, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 2: hipLaunchKernelGGL((k_mxty_wave<1024, VT>), dim3(mx_grid(c, true, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 3: hipLaunchKernelGGL((k_mxty_block<4096, 256, VT>), dim3(mx_grid(c, false, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 4: hipLaunchKernelGGL((k_mxty_block<10240, 1024, VT>), dim3(mx_grid(c, false, 1)), dim3(1024), 0, st, a, list, dir, cp, status); break;
+      case 5: hipLaunchKernelGGL((k_mxty_wave<512, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      default: hipLaunchKernelGGL((k_mxty_block<2048, 256, VT>), dim3(mx_grid(c, false, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
     }
     LAUNCHCHK();
   }
@@ -473,9 +495,11 @@ template <class VT, class Look>
 __device__ __forceinline__ void fbwd_column(const FbArgs<VT> &a, int64_t j, int c_rank, int c_stride, int32_t *status,
                                             FbScratch &sc, Look &&look) {
   const int l = lane();
-  const int64_t pb = a.Bcp[j], pe = a.Bcp[j + 1];
-  for (int64_t base = pb + (int64_t)c_rank * kWave; base < pe; base += (int64_t)c_stride * kWave) {
+  const int64_t pb = a.Bcp[j], end = a.Bcp[j + 1];
+  const int cw = chunk_width(end - pb, c_stride);
+  for (int64_t base = pb + (int64_t)c_rank * cw; base < end; base += (int64_t)c_stride * cw) {
     const int64_t p = base + l;
+    const int64_t pe = min(end, base + cw);  // this chunk's entries
     int64_t x0 = 0, x1 = 0;
     double bkj = 0.0;
     if (p < pe) {
@@ -578,27 +602,27 @@ __device__ __forceinline__ void fbwd_column(const FbArgs<VT> &a, int64_t j, int 
 }
 
 template <int TBL, class VT>
-__global__ __launch_bounds__(256) void k_fbwd_wave(FbArgs<VT> a, const int32_t *list, const int32_t *count_p,
+__global__ __launch_bounds__(256) void k_fbwd_wave(FbArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
                                                    int32_t *status) {
   __shared__ int32_t s_keys[4][TBL];
-  __shared__ double s_vals[4][TBL];
+  __shared__ VT s_vals[4][TBL];
   __shared__ FbScratch s_fb[4];
   const int w = threadIdx.x / kWave, l = lane();
   const int count = *count_p;
   int32_t *keys = s_keys[w];
-  double *vals = s_vals[w];
+  VT *vals = s_vals[w];
   s_fb[w].mark[l] = 0;
-  for (int idx = blockIdx.x * 4 + w; idx < count; idx += gridDim.x * 4) {
+  for (int64_t idx = (int64_t)blockIdx.x * 4 + w; idx < count; idx += (int64_t)gridDim.x * 4) {
     for (int s = l; s < TBL; s += kWave) {
       keys[s] = kEmpty;
-      vals[s] = 0.0;
+      vals[s] = VT(0);
     }
     wave_sync();
-    const int32_t j = list[idx];
+    const int32_t j = list[dir * idx];
     for (int64_t p = a.Ccp[j] + l; p < a.Ccp[j + 1]; p += kWave) {
       const int32_t r = a.Cri[p];
       if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(keys, vals, TBL, r, (double)a.dC[p]);
+        ht_accumulate(keys, vals, TBL, r, a.dC[p]);
       else
         flag_error(status, 3);
     }
@@ -609,26 +633,26 @@ __global__ __launch_bounds__(256) void k_fbwd_wave(FbArgs<VT> a, const int32_t *
 }
 
 template <int TBL, int THREADS, class VT>
-__global__ __launch_bounds__(THREADS) void k_fbwd_block(FbArgs<VT> a, const int32_t *list, const int32_t *count_p,
+__global__ __launch_bounds__(THREADS) void k_fbwd_block(FbArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
                                                         int32_t *status) {
   constexpr int NW = THREADS / kWave;
   __shared__ int32_t s_keys[TBL];
-  __shared__ double s_vals[TBL];
+  __shared__ VT s_vals[TBL];
   __shared__ FbScratch s_fb[NW];
   const int w = threadIdx.x / kWave;
   const int count = *count_p;
   s_fb[w].mark[lane()] = 0;
-  for (int item = blockIdx.x; item < count; item += gridDim.x) {
+  for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
     for (int s = threadIdx.x; s < TBL; s += THREADS) {
       s_keys[s] = kEmpty;
-      s_vals[s] = 0.0;
+      s_vals[s] = VT(0);
     }
     __syncthreads();
-    const int32_t j = list[item];
+    const int32_t j = list[dir * item];
     for (int64_t p = a.Ccp[j] + threadIdx.x; p < a.Ccp[j + 1]; p += THREADS) {
       const int32_t r = a.Cri[p];
       if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(s_keys, s_vals, TBL, r, (double)a.dC[p]);
+        ht_accumulate(s_keys, s_vals, TBL, r, a.dC[p]);
       else
         flag_error(status, 3);
     }
@@ -666,16 +690,22 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   FbArgs<VT> a{A->colptr, A->rowidx, (const VT *)A->values, B->colptr, B->rowidx, (const VT *)B->values,
                C->colptr, C->rowidx, (const VT *)dC, (VT *)dB, acc, C->nrows, A->ncols, A->nnz};
   int32_t *status = &hdr->status;
-  for (int b = 0; b < kNumBins - 1; b++) {
-    ProfScope prof("fused_backward", st);
-    const int32_t *list = bins + (int64_t)b * n;
-    const int32_t *cp = &hdr->bin_count[b];
+  for (int b = 0; b < kNumBins + 1; b++) {
+    const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
+    static const char *kNames[kNumBins + 1] = {"fbwd_wave64", "fbwd_wave256", "fbwd_wave1024", "fbwd_block4096",
+                                               "fbwd_block10240", "fbwd_wave512", "fbwd_block2048"};
+    ProfScope prof(kNames[b], st);
+    const int32_t *list = half < 0 ? bins + (int64_t)b * n : bins + (int64_t)(half + 3) * n - 1;
+    const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
+    const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_fbwd_wave<64, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, cp, status); break;
-      case 1: hipLaunchKernelGGL((k_fbwd_wave<256, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, cp, status); break;
-      case 2: hipLaunchKernelGGL((k_fbwd_wave<1024, VT>), dim3(mx_grid(-1, true, 4)), dim3(256), 0, st, a, list, cp, status); break;
-      case 3: hipLaunchKernelGGL((k_fbwd_block<4096, 256, VT>), dim3(mx_grid(-1, false, 4)), dim3(256), 0, st, a, list, cp, status); break;
-      default: hipLaunchKernelGGL((k_fbwd_block<10240, 1024, VT>), dim3(mx_grid(-1, false, 1)), dim3(1024), 0, st, a, list, cp, status); break;
+      case 0: hipLaunchKernelGGL((k_fbwd_wave<64, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 1: hipLaunchKernelGGL((k_fbwd_wave<256, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 2: hipLaunchKernelGGL((k_fbwd_wave<1024, VT>), dim3(mx_grid(-1, true, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 3: hipLaunchKernelGGL((k_fbwd_block<4096, 256, VT>), dim3(mx_grid(-1, false, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 4: hipLaunchKernelGGL((k_fbwd_block<10240, 1024, VT>), dim3(mx_grid(-1, false, 1)), dim3(1024), 0, st, a, list, dir, cp, status); break;
+      case 5: hipLaunchKernelGGL((k_fbwd_wave<512, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      default: hipLaunchKernelGGL((k_fbwd_block<2048, 256, VT>), dim3(mx_grid(-1, false, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
     }
     LAUNCHCHK();
   }

@@ -104,6 +104,7 @@ struct WsHeader {
   int32_t split_cursor; // numeric: work-queue position over the columns of A (slabbed copy)
   uint64_t left_tag;    // fingerprint (| 1) of the source of the slabbed copy of A in the workspace; 0 = none
   uint64_t left_new;    // fingerprint of the current call's left operand (summed by k_left_sum)
+  int32_t half_count[2];  // columns of bins 2 and 3 that take half-size tables
   int32_t esc_count[3];  // row-sorted product: columns listed for the expand-sort-compress kernels
 };
 constexpr size_t kHeaderBytes = 4096;

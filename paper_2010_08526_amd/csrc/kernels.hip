@@ -460,6 +460,7 @@ __global__ void k_init_header(WsHeader *h, uint64_t keep_tag, int keep_status = 
     for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
     for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
     h->esc_count[0] = h->esc_count[1] = h->esc_count[2] = 0;
+    h->half_count[0] = h->half_count[1] = 0;
     h->split_cursor = 0;
     h->items = 0;
     h->item_cursor = 0;

@@ -20,7 +20,8 @@ __device__ __forceinline__ bool ht_insert_key(int32_t *keys, uint32_t T, int32_t
 }
 
 // Adds `v` to the slot of `key`, creating it if needed.
-__device__ __forceinline__ void ht_accumulate(int32_t *keys, double *vals, uint32_t T, int32_t key, double v) {
+template <class VT>
+__device__ __forceinline__ void ht_accumulate(int32_t *keys, VT *vals, uint32_t T, int32_t key, VT v) {
   uint32_t h = hash_slot(key, T);
   for (uint32_t probe = 0; probe < T; probe++) {
     const int32_t old = atomicCAS(&keys[h], kEmpty, key);
@@ -86,11 +87,12 @@ __device__ __forceinline__ void ht_accumulate_z(int32_t *keys, double *vals, uin
 }
 
 // Value stored under `key`, or 0 if absent (tables are read-only here).
-__device__ __forceinline__ double ht_lookup(const int32_t *keys, const double *vals, uint32_t T, int32_t key) {
+template <class VT>
+__device__ __forceinline__ double ht_lookup(const int32_t *keys, const VT *vals, uint32_t T, int32_t key) {
   uint32_t h = hash_slot(key, T);
   for (uint32_t probe = 0; probe < T; probe++) {
     const int32_t k = keys[h];
-    if (k == key) return vals[h];
+    if (k == key) return (double)vals[h];
     if (k == kEmpty) return 0.0;
     h = (h + 1 == T) ? 0 : h + 1;
   }
