@@ -86,8 +86,11 @@ __global__ void k_permute(const T *src, const int64_t *perm, int64_t n, T *dst, 
 // ============================================================================
 // Masked X^T Y
 // ============================================================================
+// Operands of a masked product out = (X^T Y) on the pattern of M, and of the
+// fused backward (X = A, Y = dC, M = B), which also adds M(k,j) Y(i,j) to
+// acc at X(i,k).
 template <class VT>
-struct MxtyArgs {
+struct DotArgs {
   const int64_t *Xcp;
   const int32_t *Xri;
   const VT *Xv;
@@ -96,7 +99,9 @@ struct MxtyArgs {
   const VT *Yv;
   const int64_t *Mcp;
   const int32_t *Mri;
+  const VT *Mv;  // fused backward only
   VT *out;
+  double *acc;  // fused backward only: one float64 per entry of X
   int64_t m, kdim, nnzX;
 };
 
@@ -140,17 +145,19 @@ __global__ __launch_bounds__(256) void k_mxty_bin(const int64_t *Ycp, const int6
 }
 
 constexpr int kLongDot = 64;
+constexpr int kDotPipe = 4;  // rounds whose gathers are in flight together
+constexpr int kDotIns = 4;   // entries of Y(:,j) a thread has in flight when the table is filled
 
-// Scratch of one wave for the masked dot products and the fused backward:
-// the segments of a chunk of 64 entries (a column of X or A each), flattened
-// into rounds of 64 products.
-struct FbScratch {
-  int mark[kWave];
-  int64_t off[kWave];   // first A entry of the lane's segment minus its exclusive prefix
-  double scale[kWave];  // B(k,j) of the lane's segment (fused backward)
-  double db[kWave];     // the segment's dot product, summed by LDS atomics
+// Scratch of one wave: the nonempty short segments (columns of X) of a chunk
+// of up to 64 entries of M(:,j), flattened into rounds of 64 products.
+struct DotScratch {
+  uint64_t rmask[kWave];  // one bit per product of a round that starts a segment
+  struct {
+    int64_t off;   // first X entry of the segment minus its exclusive prefix
+    double scale;  // M(k,j) (fused backward)
+  } seg[kWave];
+  double db[kWave];  // the segment's dot product, summed by LDS atomics
 };
-constexpr int kFbPipe = 4;  // rounds whose gathers are in flight together
 
 // Entries a wave takes at once when nw waves share a column of n entries: 64,
 // or fewer where that would leave waves without any.
@@ -158,95 +165,189 @@ __device__ __forceinline__ int chunk_width(int64_t n, int nw) {
   return (int)max((int64_t)1, min((int64_t)kWave, (n + nw - 1) / nw));
 }
 
-// Dot products for the entries [pb, pe) of M(:,j) taken in chunks of 64
-// (chunk c by the wave with c % c_stride == c_rank).  Short X columns are
-// flattened into rounds of 64 products, one per lane (owners as in the
-// forward traversal), and each entry's sum is gathered by LDS atomics; long
-// ones are summed by the whole wave with a wave reduction.  look(row)
-// returns Y(row, j).
-template <class VT, class Look>
-__device__ __forceinline__ void mxty_dots(const MxtyArgs<VT> &a, int64_t pb, int64_t pe, int c_rank, int c_stride,
-                                          int32_t *status, FbScratch &sc, Look &&look) {
+template <int CTRL>
+__device__ __forceinline__ double dpp_quad(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)dpp0<CTRL>((int)(uint32_t)b), hi = (uint32_t)dpp0<CTRL>((int)(uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sums t over lanes of a pair, then a quad, that share an owner (own < 0: no
+// product); returns whether this lane holds a sum to be added.  A segment's
+// products sit in consecutive lanes, and LDS atomics of many lanes on one
+// address are served one after another.  Called by the whole wave.
+__device__ __forceinline__ bool quad_sum(int own, double &t) {
   const int l = lane();
-  const int cw = chunk_width(pe - pb, c_stride);
-  for (int64_t base = pb + (int64_t)c_rank * cw, end = pe; base < end; base += (int64_t)c_stride * cw) {
+  const int o1 = dpp0<0xB1>(own);  // quad_perm [1,0,3,2]
+  const bool pair = o1 == own;
+  const double t1 = dpp_quad<0xB1>(t);
+  if (pair) t += t1;
+  const int c = pair ? own : -2 - l;  // pairs that are not uniform match nothing
+  const int c2 = dpp0<0x4E>(c);  // quad_perm [2,3,0,1]; every lane active
+  const double t2 = dpp_quad<0x4E>(t);
+  const bool quad = pair && c2 == c;
+  if (quad) t += t2;
+  return own >= 0 && (quad ? (l & 3) == 0 : (!pair || (l & 1) == 0));
+}
+
+// A column and a wave's first chunk of its M entries, loaded ahead in
+// dependent steps placed where the current column has other work: the
+// pointers, the entries, X's column pointers.
+template <class VT>
+struct DotPre {
+  int64_t y0, y1, m0, m1;
+  int32_t k;
+  VT mv;
+  int64_t x0, x1;
+};
+
+template <class VT>
+__device__ __forceinline__ void dot_pre_ptr(const DotArgs<VT> &a, int64_t j, DotPre<VT> &pre) {
+  const int64_t z = opaque((int64_t)0);  // per-lane addresses: vector loads do not hold up LDS waits
+  pre.y0 = ld_global(a.Ycp + j + z);
+  pre.y1 = ld_global(a.Ycp + j + 1 + z);
+  pre.m0 = ld_global(a.Mcp + j + z);
+  pre.m1 = ld_global(a.Mcp + j + 1 + z);
+}
+
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+         ((int64_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32)) << 32);
+}
+
+template <bool FUSED, class VT>
+__device__ __forceinline__ void dot_pre_m(const DotArgs<VT> &a, int w, int nw, DotPre<VT> &pre) {
+  pre.y0 = uniform64(pre.y0);
+  pre.y1 = uniform64(pre.y1);
+  pre.m0 = uniform64(pre.m0);
+  pre.m1 = uniform64(pre.m1);
+  const int cw = chunk_width(pre.m1 - pre.m0, nw);
+  const int64_t p = pre.m0 + (int64_t)w * cw + lane();
+  pre.k = -1;
+  pre.mv = VT(0);
+  if (lane() < cw && p < pre.m1) {
+    pre.k = a.Mri[p];
+    if (FUSED) pre.mv = a.Mv[p];
+  }
+}
+
+template <class VT>
+__device__ __forceinline__ void dot_pre_x(const DotArgs<VT> &a, DotPre<VT> &pre) {
+  pre.x0 = pre.x1 = 0;
+  if ((uint32_t)pre.k < (uint32_t)a.kdim) {
+    pre.x0 = a.Xcp[pre.k];
+    pre.x1 = a.Xcp[pre.k + 1];
+  }
+}
+
+// Entries [pb, end) of M(:,j) in chunks of chunk_width (chunk c by the wave
+// with c % c_stride == c_rank): each entry's dot product of X(:,k) with
+// Y(:,j), look(row) giving Y(row, j).  Columns of X shorter than kLongDot are
+// flattened into rounds of 64 products, one per lane, so a column with few
+// entries of M still fills the wave; one 64-bit word per round marks where
+// segments start, so a product's owner is (segments starting before the
+// round) + (starts in the round at or below it) - 1.  Sums are gathered by
+// LDS atomics; FUSED products also add to acc (float64 global atomics).  Long
+// columns are walked by the whole wave with a wave reduction.
+// pre: the first chunk loaded ahead (or nullptr).
+template <bool FUSED, class VT, class Look>
+__device__ __forceinline__ void dot_entries(const DotArgs<VT> &a, int64_t pb, int64_t end, int c_rank, int c_stride,
+                                            int32_t *status, DotScratch &sc, const DotPre<VT> *pre, Look &&look) {
+  const int l = lane();
+  const int cw = chunk_width(end - pb, c_stride);
+  for (int64_t base = pb + (int64_t)c_rank * cw; base < end; base += (int64_t)c_stride * cw) {
     const int64_t p = base + l;
-    pe = min(end, base + cw);  // this chunk's entries
+    const int64_t pe = min(end, base + cw);  // this chunk's entries
+    const bool ahead = pre && base == pb + (int64_t)c_rank * cw;  // uniform
     int64_t x0 = 0, x1 = 0;
+    double mkj = 0.0;
     if (p < pe) {
-      const int32_t k = a.Mri[p];
+      const int32_t k = ahead ? pre->k : a.Mri[p];
       if ((uint32_t)k >= (uint32_t)a.kdim) {
         flag_error(status, 1);
       } else {
-        x0 = a.Xcp[k];
-        x1 = a.Xcp[k + 1];
+        x0 = ahead ? pre->x0 : a.Xcp[k];
+        x1 = ahead ? pre->x1 : a.Xcp[k + 1];
+        if (FUSED) mkj = (double)(ahead ? pre->mv : a.Mv[p]);
         if (x0 < 0 || x1 < x0 || x1 > a.nnzX) {
           flag_error(status, 5);
           x0 = x1 = 0;
         }
       }
     }
-    const int len = (int)(x1 - x0);
-    const bool lg = len >= kLongDot;
-    const int ls = (p < pe && !lg) ? len : 0;
+    const bool lg = x1 - x0 >= kLongDot;
+    const int ls = lg ? 0 : (int)(x1 - x0);
     const int incl = wave_incl_add(ls);
     const int excl = incl - ls;
     const int total = readlane(incl, kWave - 1);
-    sc.off[l] = x0 - excl;
+    const uint64_t nz = __ballot(ls > 0);
+    const int ord = mbcnt(nz);
+    if (ls > 0) {  // the nonempty short segments in lane order
+      sc.seg[ord].off = x0 - excl;
+      if (FUSED) sc.seg[ord].scale = mkj;
+    }
     sc.db[l] = 0.0;
+    sc.rmask[l] = 0ull;  // at most 64 segments of 63 products: 63 rounds
     wave_sync();
-    for (int r = 0; r * kWave < total; r += kFbPipe) {
-      int own_[kFbPipe];
+    if (ls > 0) atomicOr((unsigned long long *)&sc.rmask[excl >> 6], 1ull << (excl & 63));
+    wave_sync();
+    const int nround = (total + kWave - 1) / kWave;
+    for (int r = 0; r < nround; r += kDotPipe) {
+      int own_[kDotPipe];
+      int64_t q_[kDotPipe];
+      double sc_[kDotPipe];
 #pragma unroll
-      for (int u = 0; u < kFbPipe; u++) {
-        const int fb = (r + u) * kWave;
+      for (int u = 0; u < kDotPipe; u++) {
         own_[u] = -1;
-        if (fb < total) {
-          const int last = min(fb + kWave - 1, total - 1);
-          const uint64_t started = __ballot(ls > 0 && excl <= fb);
-          const int carry = started ? 64 - __clzll((long long)started) : 0;
-          int own = carry;
-          if (__ballot(ls > 0 && excl <= last) != started) {
-            if (ls > 0 && excl > fb && excl < fb + kWave) sc.mark[excl - fb] = l + 1;
-            wave_sync();
-            const int mk = sc.mark[l];
-            sc.mark[l] = 0;
-            own = max(wave_incl_max(mk), carry);
-            wave_sync();
-          }
-          if (fb + l < total) own_[u] = own - 1;
+        if (r + u < nround) {
+          const int fb = (r + u) * kWave;
+          const uint64_t mm = sc.rmask[r + u];
+          const int carry = __popcll(__ballot(ls > 0 && excl < fb));
+          if (fb + l < total) own_[u] = carry + mbcnt(mm) + (int)((mm >> l) & 1ull) - 1;
         }
       }
-      int32_t row_[kFbPipe];
-      VT xv_[kFbPipe];
 #pragma unroll
-      for (int u = 0; u < kFbPipe; u++) {
+      for (int u = 0; u < kDotPipe; u++) {
+        const int o = max(own_[u], 0);
+        q_[u] = sc.seg[o].off + (r + u) * kWave + l;
+        if (FUSED) sc_[u] = sc.seg[o].scale;
+      }
+      int32_t row_[kDotPipe];
+      VT xv_[kDotPipe];
+#pragma unroll
+      for (int u = 0; u < kDotPipe; u++) {
         row_[u] = -1;
         xv_[u] = VT(0);
         if (own_[u] >= 0) {
-          const int64_t q = sc.off[own_[u]] + (r + u) * kWave + l;
-          row_[u] = a.Xri[q];
-          xv_[u] = a.Xv[q];
+          row_[u] = a.Xri[q_[u]];
+          xv_[u] = a.Xv[q_[u]];
         }
       }
 #pragma unroll
-      for (int u = 0; u < kFbPipe; u++) {
+      for (int u = 0; u < kDotPipe; u++) {
+        if (r + u >= nround) break;  // uniform
+        double t = 0.0;
         if (own_[u] >= 0) {
           const int32_t rt = opaque(row_[u]);
-          if ((uint32_t)rt < (uint32_t)a.m)
-            atomicAdd(&sc.db[own_[u]], (double)opaque(xv_[u]) * look(rt));
-          else
+          if ((uint32_t)rt < (uint32_t)a.m) {
+            const double g = look(rt);
+            if (FUSED) atomicAdd(&a.acc[q_[u]], sc_[u] * g);
+            t = (double)opaque(xv_[u]) * g;
+          } else {
             flag_error(status, 3);
+          }
         }
+        if (quad_sum(own_[u], t)) atomicAdd(&sc.db[own_[u]], t);
       }
     }
     wave_sync();
-    if (p < pe && !lg) a.out[p] = (VT)sc.db[l];
-    uint64_t lm = __ballot(p < pe && lg);
+    if (p < pe && !lg) a.out[p] = ls > 0 ? (VT)sc.db[ord] : VT(0);
+    uint64_t lm = __ballot(lg);
     while (lm) {
       const int L = __builtin_ctzll(lm);
       lm &= lm - 1;
       const int64_t lx0 = readlane64(x0, L), lx1 = readlane64(x1, L);
+      const double lb = FUSED ? readlane_f64(mkj, L) : 0.0;
       double s = 0.0;
       for (int64_t q0 = lx0 + l; q0 < lx1; q0 += 4 * kWave) {
         int32_t r[4];
@@ -265,10 +366,13 @@ __device__ __forceinline__ void mxty_dots(const MxtyArgs<VT> &a, int64_t pb, int
         for (int t = 0; t < 4; t++) {
           if (q0 + t * kWave < lx1) {
             const int32_t rt = opaque(r[t]);
-            if ((uint32_t)rt < (uint32_t)a.m)
-              s += (double)opaque(xv[t]) * look(rt);
-            else
+            if ((uint32_t)rt < (uint32_t)a.m) {
+              const double g = look(rt);
+              s += (double)opaque(xv[t]) * g;
+              if (FUSED) atomicAdd(&a.acc[q0 + t * kWave], lb * g);
+            } else {
               flag_error(status, 3);
+            }
           }
         }
       }
@@ -279,65 +383,130 @@ __device__ __forceinline__ void mxty_dots(const MxtyArgs<VT> &a, int64_t pb, int
   }
 }
 
+// Fills the table with Y(:,j) (entries [y0, y1)), kDotIns loads in flight
+// per thread.
+template <int TBL, int THREADS, class VT>
+__device__ __forceinline__ void dot_fill(const DotArgs<VT> &a, int64_t y0, int64_t y1, int t, int32_t *keys, VT *vals,
+                                         int32_t *status) {
+  for (int64_t p0 = y0 + t; p0 < y1; p0 += kDotIns * THREADS) {
+    int32_t row[kDotIns];
+    VT v[kDotIns];
+#pragma unroll
+    for (int u = 0; u < kDotIns; u++) {
+      const int64_t p = p0 + u * THREADS;
+      row[u] = 0;
+      v[u] = VT(0);
+      if (p < y1) {
+        row[u] = a.Yri[p];
+        v[u] = a.Yv[p];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kDotIns; u++) {
+      if (p0 + u * THREADS < y1) {
+        const int32_t r = opaque(row[u]);
+        if ((uint32_t)r < (uint32_t)a.m)
+          ht_put(keys, vals, TBL, r, opaque(v[u]));
+        else
+          flag_error(status, 3);
+      }
+    }
+  }
+}
+
+template <int TBL, int THREADS>
+__device__ __forceinline__ void dot_clear(int t, int32_t *keys) {
+  static_assert(TBL % 4 == 0, "tables cleared 16 bytes at a time");
+  for (int s = t; s < TBL / 4; s += THREADS)
+    reinterpret_cast<int4 *>(keys)[s] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
+}
+
+// Both kernels are bound by LDS atomics (57% of the LDS cycles at first) and
+// by the latency of the dependent loads.  Fused backward of 256 products,
+// 1.0e9 terms: 18.8 ms with a marker and max-scan per round and one LDS atomic
+// per product; 17.0 with loads ahead and start words; 13.0 with the products
+// of a quad summed first and values put without a read.
+// The kernels below: the next column's pointers, first chunk of M and X's
+// column pointers are loaded while a column is processed, and a table's
+// entries are loaded kDotIns at a time, so that a column does not wait for
+// each of its dependent loads in turn.  list[dir * i]: half tables are listed
+// from the end of their array.
 // One wavefront per column, TBL-slot table of Y(:,j) private to the wave.
-template <int TBL, class VT>
-__global__ __launch_bounds__(256) void k_mxty_wave(MxtyArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
-                                                   int32_t *status) {
-  __shared__ int32_t s_keys[4][TBL];
-  __shared__ VT s_vals[4][TBL];
-  __shared__ FbScratch s_fb[4];
+template <int TBL, bool FUSED, class VT>
+__global__ __launch_bounds__(256) void k_dot_wave(DotArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
+                                                  int32_t *status) {
+  __shared__ __align__(16) int32_t s_keys[4][TBL];
+  __shared__ __align__(16) VT s_vals[4][TBL];
+  __shared__ DotScratch s_sc[4];
   const int w = threadIdx.x / kWave, l = lane();
   const int count = *count_p;
   int32_t *keys = s_keys[w];
   VT *vals = s_vals[w];
-  s_fb[w].mark[l] = 0;
-  for (int64_t idx = (int64_t)blockIdx.x * 4 + w; idx < count; idx += (int64_t)gridDim.x * 4) {
-    for (int s = l; s < TBL; s += kWave) {
-      keys[s] = kEmpty;
-      vals[s] = VT(0);
+  const int64_t stride = (int64_t)gridDim.x * 4;
+  int64_t idx = (int64_t)blockIdx.x * 4 + w;
+  const int64_t z = opaque((int64_t)0);
+  DotPre<VT> pre;
+  int32_t jn2 = 0;
+  if (idx < count) {
+    dot_pre_ptr(a, (int64_t)list[dir * idx], pre);
+    dot_pre_m<FUSED>(a, 0, 1, pre);
+    dot_pre_x(a, pre);
+    if (idx + stride < count) jn2 = ld_global(list + dir * (idx + stride) + z);
+  }
+  for (; idx < count; idx += stride) {
+    const DotPre<VT> cur = pre;
+    const bool more = idx + stride < count;  // uniform
+    if (more) {
+      dot_pre_ptr(a, (int64_t)__builtin_amdgcn_readfirstlane(jn2), pre);
+      if (idx + 2 * stride < count) jn2 = ld_global(list + dir * (idx + 2 * stride) + z);
     }
+    dot_clear<TBL, kWave>(l, keys);
     wave_sync();
-    const int32_t j = list[dir * idx];
-    for (int64_t p = a.Ycp[j] + l; p < a.Ycp[j + 1]; p += kWave) {
-      const int32_t r = a.Yri[p];
-      if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(keys, vals, TBL, r, a.Yv[p]);
-      else
-        flag_error(status, 3);
-    }
+    dot_fill<TBL, kWave>(a, cur.y0, cur.y1, l, keys, vals, status);
+    if (more) dot_pre_m<FUSED>(a, 0, 1, pre);
     wave_sync();
-    mxty_dots(a, a.Mcp[j], a.Mcp[j + 1], 0, 1, status, s_fb[w], [&](int32_t r) { return ht_lookup(keys, vals, TBL, r); });
+    dot_entries<FUSED>(a, cur.m0, cur.m1, 0, 1, status, s_sc[w], &cur,
+                       [&](int32_t r) { return ht_lookup(keys, vals, TBL, r); });
+    if (more) dot_pre_x(a, pre);
     wave_sync();
   }
 }
 
 // One workgroup per column, shared table.
-template <int TBL, int THREADS, class VT>
-__global__ __launch_bounds__(THREADS) void k_mxty_block(MxtyArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
-                                                        int32_t *status) {
+template <int TBL, int THREADS, bool FUSED, class VT>
+__global__ __launch_bounds__(THREADS) void k_dot_block(DotArgs<VT> a, const int32_t *list, int dir,
+                                                       const int32_t *count_p, int32_t *status) {
   constexpr int NW = THREADS / kWave;
-  __shared__ int32_t s_keys[TBL];
-  __shared__ VT s_vals[TBL];
-  __shared__ FbScratch s_fb[NW];
+  __shared__ __align__(16) int32_t s_keys[TBL];
+  __shared__ __align__(16) VT s_vals[TBL];
+  __shared__ DotScratch s_sc[NW];
   const int w = threadIdx.x / kWave;
   const int count = *count_p;
-  s_fb[w].mark[lane()] = 0;
-  for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
-    for (int s = threadIdx.x; s < TBL; s += THREADS) {
-      s_keys[s] = kEmpty;
-      s_vals[s] = VT(0);
+  int64_t item = blockIdx.x;
+  const int64_t z = opaque((int64_t)0);
+  DotPre<VT> pre;
+  int32_t jn2 = 0;
+  if (item < count) {
+    dot_pre_ptr(a, (int64_t)list[dir * item], pre);
+    dot_pre_m<FUSED>(a, w, NW, pre);
+    dot_pre_x(a, pre);
+    if (item + gridDim.x < count) jn2 = ld_global(list + dir * (item + gridDim.x) + z);
+  }
+  for (; item < count; item += gridDim.x) {
+    const DotPre<VT> cur = pre;
+    const bool more = item + gridDim.x < count;  // uniform
+    if (more) {
+      dot_pre_ptr(a, (int64_t)__builtin_amdgcn_readfirstlane(jn2), pre);
+      if (item + 2 * (int64_t)gridDim.x < count) jn2 = ld_global(list + dir * (item + 2 * (int64_t)gridDim.x) + z);
     }
+    dot_clear<TBL, THREADS>(threadIdx.x, s_keys);
     __syncthreads();
-    const int32_t j = list[dir * item];
-    for (int64_t p = a.Ycp[j] + threadIdx.x; p < a.Ycp[j + 1]; p += THREADS) {
-      const int32_t r = a.Yri[p];
-      if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(s_keys, s_vals, TBL, r, a.Yv[p]);
-      else
-        flag_error(status, 3);
-    }
+    dot_fill<TBL, THREADS>(a, cur.y0, cur.y1, threadIdx.x, s_keys, s_vals, status);
+    if (more) dot_pre_m<FUSED>(a, w, NW, pre);
     __syncthreads();
-    mxty_dots(a, a.Mcp[j], a.Mcp[j + 1], w, NW, status, s_fb[w], [&](int32_t r) { return ht_lookup(s_keys, s_vals, TBL, r); });
+    dot_entries<FUSED>(a, cur.m0, cur.m1, w, NW, status, s_sc[w], &cur,
+                       [&](int32_t r) { return ht_lookup(s_keys, s_vals, TBL, r); });
+    if (more) dot_pre_x(a, pre);
     __syncthreads();
   }
 }
@@ -345,7 +514,7 @@ __global__ __launch_bounds__(THREADS) void k_mxty_block(MxtyArgs<VT> a, const in
 // Heavy columns: Y(:,j) scattered into a dense float64 column of the
 // workspace (zero outside Y's rows), dots read it, then it is cleared.
 template <class VT>
-__global__ __launch_bounds__(256) void k_mxty_heavy_fill(MxtyArgs<VT> a, const int32_t *list, int first, int ns,
+__global__ __launch_bounds__(256) void k_mxty_heavy_fill(DotArgs<VT> a, const int32_t *list, int first, int ns,
                                                          double *dense, int clear) {
   const int slot = blockIdx.y;
   if (slot >= ns) return;
@@ -359,16 +528,16 @@ __global__ __launch_bounds__(256) void k_mxty_heavy_fill(MxtyArgs<VT> a, const i
 }
 
 template <class VT>
-__global__ __launch_bounds__(256) void k_mxty_heavy_dot(MxtyArgs<VT> a, const int32_t *list, int first, int ns,
+__global__ __launch_bounds__(256) void k_mxty_heavy_dot(DotArgs<VT> a, const int32_t *list, int first, int ns,
                                                         const double *dense, int parts, int32_t *status) {
-  __shared__ FbScratch s_fb[4];
+  __shared__ DotScratch s_sc[4];
   const int slot = blockIdx.x / parts, part = blockIdx.x % parts;
   if (slot >= ns) return;
   const int32_t j = list[first + slot];
   const double *d = dense + (int64_t)slot * a.m;
   const int w = threadIdx.x / kWave;
-  s_fb[w].mark[lane()] = 0;
-  mxty_dots(a, a.Mcp[j], a.Mcp[j + 1], part * 4 + w, parts * 4, status, s_fb[w], [&](int32_t r) { return d[r]; });
+  dot_entries<false>(a, a.Mcp[j], a.Mcp[j + 1], part * 4 + w, parts * 4, status, s_sc[w],
+                     (const DotPre<VT> *)nullptr, [&](int32_t r) { return d[r]; });
 }
 
 static unsigned mx_grid(int cnt, bool wave_kernel, int blocks_per_cu) {
@@ -403,8 +572,8 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
     for (int b = 0; b < kNumBins; b++) cnt[b] = -1;
     memset(&h, 0, sizeof(h));
   }
-  MxtyArgs<VT> a{X->colptr, X->rowidx, (const VT *)X->values, Y->colptr, Y->rowidx, (const VT *)Y->values,
-                 M->colptr, M->rowidx, (VT *)out, Y->nrows, X->ncols, X->nnz};
+  DotArgs<VT> a{X->colptr, X->rowidx, (const VT *)X->values, Y->colptr, Y->rowidx, (const VT *)Y->values,
+                 M->colptr, M->rowidx, (const VT *)nullptr, (VT *)out, (double *)nullptr, Y->nrows, X->ncols, X->nnz};
   int32_t *status = &hdr->status;
   for (int b = 0; b < kNumBins + 1; b++) {
     const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
@@ -415,13 +584,13 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
     const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
     const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_mxty_wave<64, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 1: hipLaunchKernelGGL((k_mxty_wave<256, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 2: hipLaunchKernelGGL((k_mxty_wave<1024, VT>), dim3(mx_grid(c, true, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 3: hipLaunchKernelGGL((k_mxty_block<4096, 256, VT>), dim3(mx_grid(c, false, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 4: hipLaunchKernelGGL((k_mxty_block<10240, 1024, VT>), dim3(mx_grid(c, false, 1)), dim3(1024), 0, st, a, list, dir, cp, status); break;
-      case 5: hipLaunchKernelGGL((k_mxty_wave<512, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      default: hipLaunchKernelGGL((k_mxty_block<2048, 256, VT>), dim3(mx_grid(c, false, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 0: hipLaunchKernelGGL((k_dot_wave<64, false, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 1: hipLaunchKernelGGL((k_dot_wave<256, false, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 2: hipLaunchKernelGGL((k_dot_wave<1024, false, VT>), dim3(mx_grid(c, true, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 3: hipLaunchKernelGGL((k_dot_block<4096, 256, false, VT>), dim3(mx_grid(c, false, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 4: hipLaunchKernelGGL((k_dot_block<10240, 1024, false, VT>), dim3(mx_grid(c, false, 1)), dim3(1024), 0, st, a, list, dir, cp, status); break;
+      case 5: hipLaunchKernelGGL((k_dot_wave<512, false, VT>), dim3(mx_grid(c, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      default: hipLaunchKernelGGL((k_dot_block<2048, 256, false, VT>), dim3(mx_grid(c, false, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
     }
     LAUNCHCHK();
   }
@@ -466,202 +635,6 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
 // in one traversal of the product's terms, with no transpose.  dA is
 // accumulated in a float64 workspace array and rounded once.
 // ============================================================================
-template <class VT>
-struct FbArgs {
-  const int64_t *Acp;
-  const int32_t *Ari;
-  const VT *Av;
-  const int64_t *Bcp;
-  const int32_t *Bri;
-  const VT *Bv;
-  const int64_t *Ccp;
-  const int32_t *Cri;
-  const VT *dC;
-  VT *dB;
-  double *dA;
-  int64_t m, kdim, nnzA;
-};
-
-
-// Entries (k,j) of B(:,j), 64 per chunk (chunk c by the wave with
-// c % c_stride == c_rank).  Segments A(:,k) shorter than kLongDot are
-// flattened into rounds of 64 products, one per lane (owner of each product
-// from a ballot, or an LDS marker and a max-scan when a segment starts inside
-// the round), so a column with few entries of B still fills the wave; each
-// product adds to dA(i,k) (float64 global atomics) and to its segment's
-// dB(k,j) (float64 LDS atomics).  Long segments are walked by the whole wave
-// with a wave reduction.  look(row) returns dC(row, j).
-template <class VT, class Look>
-__device__ __forceinline__ void fbwd_column(const FbArgs<VT> &a, int64_t j, int c_rank, int c_stride, int32_t *status,
-                                            FbScratch &sc, Look &&look) {
-  const int l = lane();
-  const int64_t pb = a.Bcp[j], end = a.Bcp[j + 1];
-  const int cw = chunk_width(end - pb, c_stride);
-  for (int64_t base = pb + (int64_t)c_rank * cw; base < end; base += (int64_t)c_stride * cw) {
-    const int64_t p = base + l;
-    const int64_t pe = min(end, base + cw);  // this chunk's entries
-    int64_t x0 = 0, x1 = 0;
-    double bkj = 0.0;
-    if (p < pe) {
-      const int32_t k = a.Bri[p];
-      if ((uint32_t)k >= (uint32_t)a.kdim) {
-        flag_error(status, 1);
-      } else {
-        x0 = a.Acp[k];
-        x1 = a.Acp[k + 1];
-        bkj = (double)a.Bv[p];
-        if (x0 < 0 || x1 < x0 || x1 > a.nnzA) {
-          flag_error(status, 5);
-          x0 = x1 = 0;
-        }
-      }
-    }
-    const int len = (int)(x1 - x0);
-    const bool lg = len >= kLongDot;
-    const int ls = (p < pe && !lg) ? len : 0;
-    const int incl = wave_incl_add(ls);
-    const int excl = incl - ls;
-    const int total = readlane(incl, kWave - 1);
-    sc.off[l] = x0 - excl;
-    sc.scale[l] = bkj;
-    sc.db[l] = 0.0;
-    wave_sync();
-    for (int r = 0; r * kWave < total; r += kFbPipe) {
-      int own_[kFbPipe];
-#pragma unroll
-      for (int u = 0; u < kFbPipe; u++) {
-        const int fb = (r + u) * kWave;
-        own_[u] = -1;
-        if (fb < total) {
-          const int last = min(fb + kWave - 1, total - 1);
-          const uint64_t started = __ballot(ls > 0 && excl <= fb);
-          const int carry = started ? 64 - __clzll((long long)started) : 0;
-          int own = carry;
-          if (__ballot(ls > 0 && excl <= last) != started) {
-            if (ls > 0 && excl > fb && excl < fb + kWave) sc.mark[excl - fb] = l + 1;
-            wave_sync();
-            const int mk = sc.mark[l];
-            sc.mark[l] = 0;
-            own = max(wave_incl_max(mk), carry);
-            wave_sync();
-          }
-          if (fb + l < total) own_[u] = own - 1;
-        }
-      }
-      int64_t q_[kFbPipe];
-      int32_t row_[kFbPipe];
-      VT av_[kFbPipe];
-#pragma unroll
-      for (int u = 0; u < kFbPipe; u++) {
-        q_[u] = sc.off[max(own_[u], 0)] + (r + u) * kWave + l;
-        row_[u] = -1;
-        av_[u] = VT(0);
-        if (own_[u] >= 0) {
-          row_[u] = a.Ari[q_[u]];
-          av_[u] = a.Av[q_[u]];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kFbPipe; u++) {
-        if (own_[u] >= 0) {
-          const int32_t rt = opaque(row_[u]);
-          if ((uint32_t)rt < (uint32_t)a.m) {
-            const double g = look(rt);
-            atomicAdd(&a.dA[q_[u]], sc.scale[own_[u]] * g);
-            atomicAdd(&sc.db[own_[u]], (double)opaque(av_[u]) * g);
-          } else {
-            flag_error(status, 3);
-          }
-        }
-      }
-    }
-    wave_sync();
-    if (p < pe && !lg) a.dB[p] = (VT)sc.db[l];
-    uint64_t lm = __ballot(p < pe && lg);
-    while (lm) {
-      const int L = __builtin_ctzll(lm);
-      lm &= lm - 1;
-      const int64_t lx0 = readlane64(x0, L), lx1 = readlane64(x1, L);
-      const double lb = readlane_f64(bkj, L);
-      double s = 0.0;
-      for (int64_t q = lx0 + l; q < lx1; q += kWave) {
-        const int32_t r = a.Ari[q];
-        if ((uint32_t)r < (uint32_t)a.m) {
-          const double g = look(r);
-          s += (double)a.Av[q] * g;
-          atomicAdd(&a.dA[q], lb * g);
-        } else {
-          flag_error(status, 3);
-        }
-      }
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
-      if (l == 0) a.dB[base + L] = (VT)s;
-    }
-    wave_sync();  // sc is rewritten by the next chunk
-  }
-}
-
-template <int TBL, class VT>
-__global__ __launch_bounds__(256) void k_fbwd_wave(FbArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
-                                                   int32_t *status) {
-  __shared__ int32_t s_keys[4][TBL];
-  __shared__ VT s_vals[4][TBL];
-  __shared__ FbScratch s_fb[4];
-  const int w = threadIdx.x / kWave, l = lane();
-  const int count = *count_p;
-  int32_t *keys = s_keys[w];
-  VT *vals = s_vals[w];
-  s_fb[w].mark[l] = 0;
-  for (int64_t idx = (int64_t)blockIdx.x * 4 + w; idx < count; idx += (int64_t)gridDim.x * 4) {
-    for (int s = l; s < TBL; s += kWave) {
-      keys[s] = kEmpty;
-      vals[s] = VT(0);
-    }
-    wave_sync();
-    const int32_t j = list[dir * idx];
-    for (int64_t p = a.Ccp[j] + l; p < a.Ccp[j + 1]; p += kWave) {
-      const int32_t r = a.Cri[p];
-      if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(keys, vals, TBL, r, a.dC[p]);
-      else
-        flag_error(status, 3);
-    }
-    wave_sync();
-    fbwd_column(a, j, 0, 1, status, s_fb[w], [&](int32_t r) { return ht_lookup(keys, vals, TBL, r); });
-    wave_sync();
-  }
-}
-
-template <int TBL, int THREADS, class VT>
-__global__ __launch_bounds__(THREADS) void k_fbwd_block(FbArgs<VT> a, const int32_t *list, int dir, const int32_t *count_p,
-                                                        int32_t *status) {
-  constexpr int NW = THREADS / kWave;
-  __shared__ int32_t s_keys[TBL];
-  __shared__ VT s_vals[TBL];
-  __shared__ FbScratch s_fb[NW];
-  const int w = threadIdx.x / kWave;
-  const int count = *count_p;
-  s_fb[w].mark[lane()] = 0;
-  for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
-    for (int s = threadIdx.x; s < TBL; s += THREADS) {
-      s_keys[s] = kEmpty;
-      s_vals[s] = VT(0);
-    }
-    __syncthreads();
-    const int32_t j = list[dir * item];
-    for (int64_t p = a.Ccp[j] + threadIdx.x; p < a.Ccp[j + 1]; p += THREADS) {
-      const int32_t r = a.Cri[p];
-      if ((uint32_t)r < (uint32_t)a.m)
-        ht_accumulate(s_keys, s_vals, TBL, r, a.dC[p]);
-      else
-        flag_error(status, 3);
-    }
-    __syncthreads();
-    fbwd_column(a, j, w, NW, status, s_fb[w], [&](int32_t r) { return ht_lookup(s_keys, s_vals, TBL, r); });
-    __syncthreads();
-  }
-}
-
 __global__ void k_zero_f64(double *p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0.0;
 }
@@ -687,8 +660,8 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n, g_min_bin_value(),
                      bin_caps(1), bins, hdr);
   LAUNCHCHK();
-  FbArgs<VT> a{A->colptr, A->rowidx, (const VT *)A->values, B->colptr, B->rowidx, (const VT *)B->values,
-               C->colptr, C->rowidx, (const VT *)dC, (VT *)dB, acc, C->nrows, A->ncols, A->nnz};
+  DotArgs<VT> a{A->colptr, A->rowidx, (const VT *)A->values, C->colptr, C->rowidx, (const VT *)dC,
+                B->colptr, B->rowidx, (const VT *)B->values, (VT *)dB, acc, C->nrows, A->ncols, A->nnz};
   int32_t *status = &hdr->status;
   for (int b = 0; b < kNumBins + 1; b++) {
     const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
@@ -699,13 +672,13 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
     const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
     const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_fbwd_wave<64, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 1: hipLaunchKernelGGL((k_fbwd_wave<256, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 2: hipLaunchKernelGGL((k_fbwd_wave<1024, VT>), dim3(mx_grid(-1, true, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 3: hipLaunchKernelGGL((k_fbwd_block<4096, 256, VT>), dim3(mx_grid(-1, false, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      case 4: hipLaunchKernelGGL((k_fbwd_block<10240, 1024, VT>), dim3(mx_grid(-1, false, 1)), dim3(1024), 0, st, a, list, dir, cp, status); break;
-      case 5: hipLaunchKernelGGL((k_fbwd_wave<512, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
-      default: hipLaunchKernelGGL((k_fbwd_block<2048, 256, VT>), dim3(mx_grid(-1, false, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 0: hipLaunchKernelGGL((k_dot_wave<64, true, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 1: hipLaunchKernelGGL((k_dot_wave<256, true, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 2: hipLaunchKernelGGL((k_dot_wave<1024, true, VT>), dim3(mx_grid(-1, true, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 3: hipLaunchKernelGGL((k_dot_block<4096, 256, true, VT>), dim3(mx_grid(-1, false, 4)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      case 4: hipLaunchKernelGGL((k_dot_block<10240, 1024, true, VT>), dim3(mx_grid(-1, false, 1)), dim3(1024), 0, st, a, list, dir, cp, status); break;
+      case 5: hipLaunchKernelGGL((k_dot_wave<512, true, VT>), dim3(mx_grid(-1, true, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
+      default: hipLaunchKernelGGL((k_dot_block<2048, 256, true, VT>), dim3(mx_grid(-1, false, 8)), dim3(256), 0, st, a, list, dir, cp, status); break;
     }
     LAUNCHCHK();
   }

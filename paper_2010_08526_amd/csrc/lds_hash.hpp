@@ -19,22 +19,23 @@ __device__ __forceinline__ bool ht_insert_key(int32_t *keys, uint32_t T, int32_t
   return false;  // unreachable with tables at most half full
 }
 
-// Adds `v` to the slot of `key`, creating it if needed.
+// Stores `v` under `key` (each key is put once; no read of the slot's value,
+// so values need no clearing).
 template <class VT>
-__device__ __forceinline__ void ht_accumulate(int32_t *keys, VT *vals, uint32_t T, int32_t key, VT v) {
+__device__ __forceinline__ void ht_put(int32_t *keys, VT *vals, uint32_t T, int32_t key, VT v) {
   uint32_t h = hash_slot(key, T);
   for (uint32_t probe = 0; probe < T; probe++) {
     const int32_t old = atomicCAS(&keys[h], kEmpty, key);
     if (old == kEmpty || old == key) {
-      atomicAdd(&vals[h], v);
+      vals[h] = v;
       return;
     }
     h = (h + 1 == T) ? 0 : h + 1;
   }
 }
 
-// As ht_accumulate, combining values with the addition of semiring SR
-// (SR::acc on the slot; slots start all zero).
+// Adds `v` to the slot of `key`, creating it if needed, with the addition of
+// semiring SR (SR::acc on the slot; slots start all zero).
 template <class SR>
 __device__ __forceinline__ void ht_accumulate_sr(int32_t *keys, double *vals, uint32_t T, int32_t key, double v) {
   uint32_t h = hash_slot(key, T);

@@ -1,0 +1,70 @@
+"""GPU parity of the masked products at the edges of their classes: table
+sizes of Y(:,j) (full and half tables), entries of M(:,j) shared among one to
+sixteen waves, and columns of X from empty to longer than a wave's walk."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+S = None
+YLEN = [0, 1, 32, 33, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 5120, 5121]
+MLEN = [0, 1, 3, 4, 5, 63, 64, 65, 257, 1100]
+XLEN = [0, 1, 2, 3, 5, 31, 62, 63, 64, 65, 130, 300]
+
+
+def setup_module(module):
+    global S
+    import paper_2010_08526_amd as lib
+    S = lib
+    assert torch.cuda.is_available()
+
+
+def _csc(m, cols, rng, dtype):
+    cp = np.concatenate([[0], np.cumsum([c.size for c in cols])]).astype(np.int64)
+    ri = np.concatenate(cols).astype(np.int32)
+    return synth.CSC(m, len(cols), torch.from_numpy(cp), torch.from_numpy(ri),
+                     torch.from_numpy(rng.integers(1, 9, ri.size)).to(dtype))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("mix", ["mixed", "short", "long"])
+def test_masked_product_limits(dtype, mix):
+    """Values are small integers, so every dot product is exact."""
+    print(f"case: masked product limits {mix} {dtype}", flush=True)
+    rng = np.random.default_rng(len(mix))
+    m = 6000
+    xl = {"mixed": XLEN, "short": [0, 1, 2, 3], "long": [63, 64, 130, 300]}[mix]
+    X = _csc(m, [rng.choice(m, xl[i % len(xl)], replace=False) for i in range(1200)], rng, dtype)
+    Y = _csc(m, [rng.choice(m, n, replace=False) for n in YLEN for _ in MLEN], rng, dtype)
+    M = _csc(X.ncols, [rng.choice(X.ncols, n, replace=False) for _ in YLEN for n in MLEN], rng, dtype)
+    got = S.masked_xty(X.to("cuda"), Y.to("cuda"), M.to("cuda"))
+    assert np.array_equal(got.double().cpu().numpy(), oracle.masked_xty(X, Y, M))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_gradient_limits(dtype):
+    """Both gradients of products whose columns hold 1 to 5120 rows, the
+    entries of B ranging from one per column to several per wave; exact."""
+    print(f"case: gradient limits {dtype}", flush=True)
+    rng = np.random.default_rng(5)
+    m = 6000
+    lens = [1, 2, 16, 63, 64, 65, 128]
+    A = _csc(m, [np.arange(s, s + n) for n in lens for s in rng.integers(0, m - 200, 60)], rng, dtype)
+    cols = [rng.choice(A.ncols, n, replace=False) for n in (1, 2, 3, 5, 8, 13, 21, 34, 64, 65, 130) for _ in range(4)]
+    B = _csc(A.ncols, cols, rng, dtype)
+    Ad, Bd = A.to("cuda"), B.to("cuda")
+    C = S.spgemm(Ad, Bd)
+    assert int((C.colptr[1:] - C.colptr[:-1]).max()) > 2048
+    dC = torch.from_numpy(rng.integers(1, 5, C.nnz)).to(dtype).cuda()
+    bw = S.Backward(Ad, Bd, C)
+    dA, dB = bw(dC)
+    bw.check()
+    G = oracle.Mat(C.nrows, C.ncols, C.colptr.cpu().numpy(), C.rowidx.cpu().numpy(), dC.double().cpu().numpy())
+    assert np.array_equal(dA.double().cpu().numpy(), oracle.grad_a(A, B, G))
+    assert np.array_equal(dB.double().cpu().numpy(), oracle.grad_b(A, B, G))
