@@ -224,7 +224,7 @@ def fwd_bwd(args, torch, np, S, synth):
     # targets are taken at the first forward's storage slots (one wavefront per
     # column keeps the slot order of these columns fixed from run to run)
     T = synth.target_values(C.rowidx, col, C.ncols, synth.WORKLOADS["er262k"].seed, torch.float32)
-    bw = S.Backward(A, B, C)  # pattern transposes made once per structure
+    bw = S.Backward(A, B, C)  # formed once per structure
 
     def fwd():
         p = eng.plan()
@@ -238,8 +238,8 @@ def fwd_bwd(args, torch, np, S, synth):
         bw(dC)
 
     # the differentiated form as autograd runs it: SpGEMMFn's forward (a new
-    # engine: symbolic pass, plan, numeric) and its backward, which forms the
-    # transposes of A's, B's and C's patterns on every call
+    # engine: symbolic pass, plan, numeric) and its backward (a new workspace on
+    # every call)
     a_vals = A.values.clone().requires_grad_(True)
     b_vals = B.values.clone().requires_grad_(True)
     Ap = S.CSC(A.nrows, A.ncols, A.colptr, A.rowidx, None)

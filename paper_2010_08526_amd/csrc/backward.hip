@@ -650,15 +650,19 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
                       void *dB, const WsLayout &L, char *ws, hipStream_t st) {
   WsHeader *hdr = (WsHeader *)ws;
   int32_t *bins = (int32_t *)(ws + L.bins);
-  double *acc = (double *)(ws + L.heavy_vals);
+  // float64 gradients are summed where they are wanted, float32 ones in the workspace
+  constexpr bool kInPlace = sizeof(VT) == sizeof(double);
+  double *acc = kInPlace ? (double *)dA : (double *)(ws + L.heavy_vals);
   const int64_t n = C->ncols;
   int rc = launch_init_header(hdr, (uint64_t)0, st);
   if (rc) return rc;
   const unsigned gz = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid_of(A->nnz, 256), 8 * device_cus()));
   hipLaunchKernelGGL(k_zero_f64, dim3(gz), dim3(256), 0, st, acc, A->nnz);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n, g_min_bin_value(),
-                     bin_caps(1), bins, hdr);
+  BinCaps caps = bin_caps(1);
+  caps.cap[kNumBins - 2] = kNumTableCap[kNumBins - 2];  // whatever fits the largest table is formed
+  hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n,
+                     std::min(g_min_bin_value(), kNumBins - 2), caps, bins, hdr);
   LAUNCHCHK();
   DotArgs<VT> a{A->colptr, A->rowidx, (const VT *)A->values, C->colptr, C->rowidx, (const VT *)dC,
                 B->colptr, B->rowidx, (const VT *)B->values, (VT *)dB, acc, C->nrows, A->ncols, A->nnz};
@@ -684,8 +688,10 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   }
   hipLaunchKernelGGL(k_mx_flag_if_nonzero, dim3(1), dim3(64), 0, st, &hdr->bin_count[kNumBins - 1], status, 7);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_round<VT>, dim3(gz), dim3(256), 0, st, acc, A->nnz, (VT *)dA);
-  LAUNCHCHK();
+  if (!kInPlace) {
+    hipLaunchKernelGGL(k_round<VT>, dim3(gz), dim3(256), 0, st, acc, A->nnz, (VT *)dA);
+    LAUNCHCHK();
+  }
   return SPGEMM_OK;
 }
 

@@ -68,3 +68,43 @@ def test_gradient_limits(dtype):
     G = oracle.Mat(C.nrows, C.ncols, C.colptr.cpu().numpy(), C.rowidx.cpu().numpy(), dC.double().cpu().numpy())
     assert np.array_equal(dA.double().cpu().numpy(), oracle.grad_a(A, B, G))
     assert np.array_equal(dB.double().cpu().numpy(), oracle.grad_b(A, B, G))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_backward_forms_agree(dtype, monkeypatch):
+    """Gradients in one traversal and by transposed patterns: the same exact
+    values (small integers) for the values B had at construction or at the last
+    refresh; transposed patterns of the first form made on request; a dC of
+    another type is refused by both."""
+    print(f"case: backward forms {dtype}", flush=True)
+    rng = np.random.default_rng(8)
+    A = _csc(500, [rng.choice(500, n, replace=False) for n in rng.integers(0, 90, 300)], rng, dtype).to("cuda")
+    B = _csc(300, [rng.choice(300, n, replace=False) for n in rng.integers(0, 70, 200)], rng, dtype).to("cuda")
+    C = S.spgemm(A, B)
+    dC = torch.from_numpy(rng.integers(1, 5, C.nnz)).to(dtype).cuda()
+    fused = S.Backward(A, B, C)
+    monkeypatch.setattr(S, "FUSED_COL_MAX", 0)
+    trans = S.Backward(A, B, C)
+    assert fused.ws_f is not None and trans.ws_f is None
+
+    def same():
+        for x, y in zip(fused(dC), trans(dC)):
+            assert x.dtype == dtype and torch.equal(x, y)
+        fused.check()
+        trans.check()
+
+    same()
+    B.values.mul_(3)  # not seen before a refresh
+    same()
+    B2 = S.CSC(B.nrows, B.ncols, B.colptr, B.rowidx, B.values + 1)
+    fused.refresh_values(B2)
+    trans.refresh_values(B2)
+    same()
+    BT = fused.BT
+    assert torch.equal(BT.colptr, trans.BT.colptr)
+    fused.refresh_values(B)
+    assert torch.equal(fused.BT.values, B.values[fused.permB])
+    other = torch.float64 if dtype == torch.float32 else torch.float32
+    for bw in (fused, trans):
+        with pytest.raises(S.SpgemmError):
+            bw(dC.to(other))
