@@ -495,8 +495,6 @@ __global__ void k_store_parts(PartDesc *dst, PartsChunk src, int n) {
 //   SYM: bound = min(flops, m); writes flops_out (optional); columns with no
 //        product term get nnz 0 here and no bin.
 //   NUM: bound = exact count from c_colptr; empty columns get no bin.
-// One wavefront per column, 16 columns per wave, one block-level append per
-// bin and block.
 // ============================================================================
 __device__ __forceinline__ int bin_of(int64_t bound, const BinCaps &caps) {
 #pragma unroll
@@ -507,59 +505,19 @@ __device__ __forceinline__ int bin_of(int64_t bound, const BinCaps &caps) {
 }
 
 constexpr int kBinColsPerWave = 16;
+constexpr int kBinUnroll = 8;  // entries of B a lane has in flight
 
-template <bool SYM>
-__global__ __launch_bounds__(256) void k_bin(const int64_t *Acp, const int64_t *Bcp, const int32_t *Bri,
-                                             int64_t c0, int64_t ncol, int64_t klo, int64_t khi, int64_t kdim,
-                                             int64_t m, const int64_t *c_colptr, int64_t *flops_out,
-                                             int64_t *nnz_out, int32_t *bins, WsHeader *hdr, int min_bin,
-                                             BinCaps caps, const int64_t *esc_flops, double esc_cf) {
-  // lists kNumBins ...: the row-sorted product's expand-sort-compress columns
-  // (numeric only, when esc_flops is given), classes 0 and 2 in two arrays,
-  // class 1 from the end of class 0's
+// Appends column jj of each thread with bin >= 0 to the bins' lists: one LDS
+// counter per list, one global atomic per list and block.  Lists kNumBins ...:
+// the row-sorted product's expand-sort-compress columns, classes 0 and 2 in
+// two arrays, class 1 from the end of class 0's.
+__device__ __forceinline__ void bin_append(int bin, int64_t jj, int64_t ncol, int32_t *bins, WsHeader *hdr) {
   constexpr int NL = kNumBins + 3;
   __shared__ int s_cnt[NL];
   __shared__ int s_base[NL];
-  __shared__ int s_bin[4 * kBinColsPerWave];
-  __shared__ int s_pos[4 * kBinColsPerWave];
-  const int w = threadIdx.x / kWave, l = lane();
   if (threadIdx.x < NL) s_cnt[threadIdx.x] = 0;
   __syncthreads();
-  for (int t = 0; t < kBinColsPerWave; t++) {
-    const int slot = w * kBinColsPerWave + t;
-    const int64_t jj = ((int64_t)blockIdx.x * 4 + w) * kBinColsPerWave + t;
-    int bin = -1;
-    if (jj < ncol) {
-      int64_t bound;
-      if (SYM) {
-        const int64_t col = c0 + jj;
-        int64_t f = 0;
-        for (int64_t p = Bcp[col] + l; p < Bcp[col + 1]; p += kWave) {
-          const int32_t k = Bri[p];
-          if (k < 0 || (int64_t)k >= kdim) {
-            flag_error(&hdr->status, 1);
-          } else if (k >= klo && k < khi) {
-            f += Acp[k + 1] - Acp[k];
-          }
-        }
-        f = wave_sum_i64(f);
-        if (l == 0 && flops_out) flops_out[jj] = f;
-        bound = f < m ? f : m;
-        if (bound == 0 && l == 0) nnz_out[jj] = 0;
-      } else {
-        bound = c_colptr[jj + 1] - c_colptr[jj];
-      }
-      if (bound > 0) bin = max(bin_of(bound, caps), min_bin);
-      if (!SYM && esc_flops && bound > 0) {
-        const int e = esc_class(esc_flops[jj], bound, esc_cf);
-        if (e >= 0) bin = kNumBins + e;
-      }
-    }
-    if (l == 0) {
-      s_bin[slot] = bin;
-      s_pos[slot] = bin >= 0 ? atomicAdd(&s_cnt[bin], 1) : 0;
-    }
-  }
+  const int pos = bin >= 0 ? atomicAdd(&s_cnt[bin], 1) : 0;
   __syncthreads();
   if (threadIdx.x < NL) {
     const int b = threadIdx.x;
@@ -567,18 +525,100 @@ __global__ __launch_bounds__(256) void k_bin(const int64_t *Acp, const int64_t *
     s_base[b] = c ? atomicAdd(b < kNumBins ? &hdr->bin_count[b] : &hdr->esc_count[b - kNumBins], c) : 0;
   }
   __syncthreads();
-  if (threadIdx.x < 4 * kBinColsPerWave) {
-    const int slot = threadIdx.x;
-    const int bin = s_bin[slot];
-    if (bin >= 0) {
-      const int64_t jj = ((int64_t)blockIdx.x * 4 + slot / kBinColsPerWave) * kBinColsPerWave + slot % kBinColsPerWave;
-      const int64_t p = s_base[bin] + s_pos[slot];
-      const int64_t at = bin == kNumBins + 1   ? (int64_t)(kNumBins + 1) * ncol - 1 - p
-                         : bin == kNumBins + 2 ? (int64_t)(kNumBins + 1) * ncol + p
-                                               : (int64_t)bin * ncol + p;
-      bins[at] = (int32_t)jj;
+  if (bin >= 0) {
+    const int64_t p = s_base[bin] + pos;
+    const int64_t at = bin == kNumBins + 1   ? (int64_t)(kNumBins + 1) * ncol - 1 - p
+                       : bin == kNumBins + 2 ? (int64_t)(kNumBins + 1) * ncol + p
+                                             : (int64_t)bin * ncol + p;
+    bins[at] = (int32_t)jj;
+  }
+}
+
+// Symbolic: one wave per 16 columns.  Their entries are consecutive in B, so
+// the wave walks them 64 at a time, kBinUnroll loads in flight per lane,
+// whatever the columns' lengths; a lane keeps the sum of the column it is in
+// and adds it to the column's LDS counter when it leaves it.  Latency bounds
+// the kernel (a column walked on its own waits for two dependent loads per 64
+// entries): 422 -> 211 us at 1.8e6 entries with columns of up to 9639 (the
+// longest ends the launch), 828 -> 677 us at 5.6e7 entries in columns of 4-32.
+__global__ __launch_bounds__(256) void k_bin_flops(const int64_t *Acp, const int64_t *Bcp, const int32_t *Bri,
+                                                   int64_t c0, int64_t ncol, int64_t klo, int64_t khi, int64_t kdim,
+                                                   int64_t m, int64_t *flops_out, int64_t *nnz_out, int32_t *bins,
+                                                   WsHeader *hdr, int min_bin, BinCaps caps) {
+  constexpr int C = kBinColsPerWave;
+  __shared__ int64_t s_bp[4][C + 1];
+  __shared__ unsigned long long s_f[4][C];
+  const int w = threadIdx.x / kWave, l = lane();
+  const int64_t j0 = ((int64_t)blockIdx.x * 4 + w) * C;
+  if (l <= C) s_bp[w][l] = Bcp[c0 + min(j0 + l, ncol)];
+  if (l < C) s_f[w][l] = 0ull;
+  wave_sync();
+  const int64_t p1 = s_bp[w][C];
+  int64_t next = s_bp[w][1];  // end of the lane's column
+  int o = 0;
+  int64_t acc = 0;
+  bool bad = false;
+  for (int64_t q0 = s_bp[w][0] + l; q0 < p1; q0 += kBinUnroll * kWave) {
+    int32_t k_[kBinUnroll];
+#pragma unroll
+    for (int u = 0; u < kBinUnroll; u++) {
+      const int64_t p = q0 + u * kWave;
+      k_[u] = p < p1 ? Bri[p] : 0;
+    }
+    int64_t d_[kBinUnroll];
+#pragma unroll
+    for (int u = 0; u < kBinUnroll; u++) {
+      const int32_t k = opaque(k_[u]);
+      const bool in = q0 + u * kWave < p1;
+      const bool out = k < 0 || (int64_t)k >= kdim;
+      bad |= in && out;
+      d_[u] = 0;
+      if (in && !out && k >= klo && k < khi) d_[u] = Acp[k + 1] - Acp[k];
+    }
+#pragma unroll
+    for (int u = 0; u < kBinUnroll; u++) {
+      const int64_t p = q0 + u * kWave;
+      if (p >= p1) break;
+      if (p >= next) {
+        if (acc) atomicAdd(&s_f[w][o], (unsigned long long)acc);
+        acc = 0;
+        while (o < C - 1 && p >= s_bp[w][o + 1]) o++;
+        next = s_bp[w][o + 1];
+      }
+      acc += d_[u];
     }
   }
+  if (acc) atomicAdd(&s_f[w][o], (unsigned long long)acc);
+  if (__ballot(bad) && l == 0) flag_error(&hdr->status, 1);
+  __syncthreads();
+  // thread t < 4 C: column t of the block
+  int bin = -1;
+  const int64_t jj = (int64_t)blockIdx.x * 4 * C + threadIdx.x;
+  if (threadIdx.x < 4 * C && jj < ncol) {
+    const int64_t f = (int64_t)s_f[threadIdx.x / C][threadIdx.x % C];
+    if (flops_out) flops_out[jj] = f;
+    const int64_t bound = f < m ? f : m;
+    if (bound == 0) nnz_out[jj] = 0;
+    if (bound > 0) bin = max(bin_of(bound, caps), min_bin);
+  }
+  bin_append(bin, jj, ncol, bins, hdr);
+}
+
+// Numeric and merge: one thread per column, its length from the column
+// pointers.
+__global__ __launch_bounds__(256) void k_bin_len(const int64_t *c_colptr, int64_t ncol, int32_t *bins, WsHeader *hdr,
+                                                 int min_bin, BinCaps caps, const int64_t *esc_flops, double esc_cf) {
+  const int64_t jj = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  int bin = -1;
+  if (jj < ncol) {
+    const int64_t len = c_colptr[jj + 1] - c_colptr[jj];
+    if (len > 0) bin = max(bin_of(len, caps), min_bin);
+    if (esc_flops && len > 0) {
+      const int e = esc_class(esc_flops[jj], len, esc_cf);
+      if (e >= 0) bin = kNumBins + e;
+    }
+  }
+  bin_append(bin, jj, ncol, bins, hdr);
 }
 
 // ============================================================================
@@ -1393,10 +1433,17 @@ __global__ __launch_bounds__(256) void k_left_sum(const int64_t *Acp, const int3
   uint64_t s = 0;
   for (int64_t k = klo + tid; k <= khi; k += nth) s += fmix64(seed ^ fmix64((uint64_t)k) ^ (uint64_t)Acp[k]);
   const int64_t e0 = Acp[klo], e1 = Acp[khi];
+#pragma unroll 4
   for (int64_t p = e0 + tid; p < e1; p += nth)
     s += fmix64(seed + fmix64((uint64_t)p) + (((uint64_t)(uint32_t)Ari[p] << 32) ^ value_bits(Av[p])));
   for (int o = 32; o > 0; o >>= 1) s += (uint64_t)__shfl_xor((long long)s, o, kWave);
-  if (lane() == 0) atomicAdd((unsigned long long *)&h->left_new, (unsigned long long)s);
+  // one global atomic per workgroup: atomics on one address pass at about 13 ns
+  // each (one per wave of 1024 workgroups took 52 us whatever A's size)
+  __shared__ uint64_t s_w[4];
+  if (lane() == 0) s_w[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicAdd((unsigned long long *)&h->left_new, (unsigned long long)(s_w[0] + s_w[1] + s_w[2] + s_w[3]));
 }
 
 __device__ __forceinline__ bool left_is_current(const WsHeader *h) { return h->left_tag == (h->left_new | 1ull); }
@@ -1428,7 +1475,10 @@ struct __align__(16) SlabEnt<double> {
   double v;
 };
 
-constexpr int kSplitCols = 16;  // columns of A a wave takes from the work queue at once
+constexpr int kSplitCols = 16;   // columns of A a wave takes from the work queue at once
+// Entries a lane has in flight: the longest columns, walked by one wave each,
+// end the launch (463 -> 243 us at 1.8e6 entries, columns of up to 9639).
+constexpr int kSplitUnroll = 8;
 
 template <class VT>
 __global__ __launch_bounds__(256) void k_slab_split(const int64_t *Acp, const int32_t *Ari, const VT *Av,
@@ -1453,11 +1503,19 @@ __global__ __launch_bounds__(256) void k_slab_split(const int64_t *Acp, const in
       wave_sync();
       const int64_t a0 = Acp[k], a1 = Acp[k + 1];
       bool bad = false;
-      for (int64_t p = a0 + l; p < a1; p += kWave) {
-        const int32_t row = Ari[p];
-        bad |= row < 0 || row >= m;
-        const uint32_t sl = min((uint32_t)row >> kSlabShift, (uint32_t)(P - 1));
-        atomicAdd(&h[sl], 1);
+      for (int64_t p0 = a0 + l; p0 < a1; p0 += kSplitUnroll * kWave) {
+        int32_t row_[kSplitUnroll];
+#pragma unroll
+        for (int u = 0; u < kSplitUnroll; u++) row_[u] = p0 + u * kWave < a1 ? Ari[p0 + u * kWave] : 0;
+#pragma unroll
+        for (int u = 0; u < kSplitUnroll; u++) {
+          if (p0 + u * kWave < a1) {
+            const int32_t row = opaque(row_[u]);
+            bad |= row < 0 || row >= m;
+            const uint32_t sl = min((uint32_t)row >> kSlabShift, (uint32_t)(P - 1));
+            atomicAdd(&h[sl], 1);
+          }
+        }
       }
       if (__ballot(bad) && l == 0) flag_error(status, 3);
       wave_sync();
@@ -1475,14 +1533,27 @@ __global__ __launch_bounds__(256) void k_slab_split(const int64_t *Acp, const in
       }
       if (l == 0) o[P] = carry;
       wave_sync();
-      for (int64_t p = a0 + l; p < a1; p += kWave) {
-        const int32_t row = Ari[p];
-        const uint32_t sl = min((uint32_t)row >> kSlabShift, (uint32_t)(P - 1));
-        const int pos = atomicAdd(&h[sl], 1);
-        SlabEnt<VT> e;
-        e.row = row;
-        e.v = Av[p];
-        s_ent[a0 + pos] = e;
+      for (int64_t p0 = a0 + l; p0 < a1; p0 += kSplitUnroll * kWave) {
+        int32_t row_[kSplitUnroll];
+        VT v_[kSplitUnroll];
+#pragma unroll
+        for (int u = 0; u < kSplitUnroll; u++) {
+          const bool in = p0 + u * kWave < a1;
+          row_[u] = in ? Ari[p0 + u * kWave] : 0;
+          v_[u] = in ? Av[p0 + u * kWave] : VT(0);
+        }
+#pragma unroll
+        for (int u = 0; u < kSplitUnroll; u++) {
+          if (p0 + u * kWave < a1) {
+            const int32_t row = opaque(row_[u]);
+            const uint32_t sl = min((uint32_t)row >> kSlabShift, (uint32_t)(P - 1));
+            const int pos = atomicAdd(&h[sl], 1);
+            SlabEnt<VT> e;
+            e.row = row;
+            e.v = opaque(v_[u]);
+            s_ent[a0 + pos] = e;
+          }
+        }
       }
       wave_sync();  // the next column clears h
     }
@@ -2703,7 +2774,8 @@ __global__ __launch_bounds__(256) void k_heavy_write(const int32_t *list, int fi
 // ============================================================================
 // Exclusive scan of int64 counts into column pointers.
 // ============================================================================
-constexpr int kScanPer = 32, kScanThreads = 256, kScanBlock = kScanPer * kScanThreads;
+constexpr int kScanPer = 8, kScanThreads = 1024, kScanBlock = kScanPer * kScanThreads;
+constexpr int64_t kScanDirect = 4096;  // blocks up to which each block adds up the sums before it
 
 __device__ __forceinline__ int64_t wave_incl_add_i64(int64_t v) {
   const int l = lane();
@@ -2714,7 +2786,7 @@ __device__ __forceinline__ int64_t wave_incl_add_i64(int64_t v) {
   return v;
 }
 
-// Exclusive block scan (256 threads); returns this thread's exclusive prefix
+// Exclusive block scan; returns this thread's exclusive prefix
 // and writes the block total to *total.
 __device__ __forceinline__ int64_t block_excl_i64(int64_t v, int64_t *s_w, int64_t *total) {
   const int w = threadIdx.x / kWave, l = lane();
@@ -2757,6 +2829,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_bsums(int64_t *bsum, int6
   }
 }
 
+// DIRECT: bsum holds the blocks' own sums (none is read by block 0), else
+// their exclusive scan.
+template <bool DIRECT>
 __global__ __launch_bounds__(kScanThreads) void k_scan_final(const int64_t *x, int64_t n, const int64_t *bsum,
                                                              int64_t *out) {
   __shared__ int64_t s_w[kScanThreads / kWave];
@@ -2765,12 +2840,20 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(const int64_t *x, i
   int64_t v[kScanPer];
   int64_t s = 0;
 #pragma unroll
-  for (int i = 0; i < kScanPer; i++) {
-    v[i] = (t0 + i < n) ? x[t0 + i] : 0;
-    s += v[i];
+  for (int i = 0; i < kScanPer; i++) v[i] = (t0 + i < n) ? x[t0 + i] : 0;
+  int64_t before = 0;
+  if (DIRECT) {
+    for (int64_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) before += bsum[i];
+    int64_t tot;
+    block_excl_i64(before, s_w, &tot);
+    before = tot;
+  } else {
+    before = bsum[blockIdx.x];
   }
+#pragma unroll
+  for (int i = 0; i < kScanPer; i++) s += v[i];
   int64_t tot;
-  int64_t run = bsum[blockIdx.x] + block_excl_i64(s, s_w, &tot);
+  int64_t run = before + block_excl_i64(s, s_w, &tot);
   if (blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
 #pragma unroll
   for (int i = 0; i < kScanPer; i++) {
@@ -2851,11 +2934,19 @@ int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *out, int64_t *
   }
   const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
   ProfScope prof("scan", s);
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum);
-  LAUNCHCHK();
-  hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(kScanThreads), 0, s, bsum, nb);
-  LAUNCHCHK();
-  hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out);
+  // launches count here: one block needs no sums, and up to kScanDirect blocks
+  // each adds the sums before it itself (at most 4 per thread)
+  if (nb > 1) {
+    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum);
+    LAUNCHCHK();
+  }
+  if (nb > kScanDirect) {
+    hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(kScanThreads), 0, s, bsum, nb);
+    LAUNCHCHK();
+    hipLaunchKernelGGL(k_scan_final<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out);
+  } else {
+    hipLaunchKernelGGL(k_scan_final<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out);
+  }
   LAUNCHCHK();
   return SPGEMM_OK;
 }
@@ -3045,9 +3136,9 @@ static int symbolic_pass(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   const int64_t per_block = 4 * kBinColsPerWave;
   {
     ProfScope prof_bin("bin_symbolic", st);
-    hipLaunchKernelGGL(k_bin<true>, dim3(grid_of(ncol, per_block)), dim3(256), 0, st, A->colptr, B->colptr,
-                       B->rowidx, c0, ncol, klo, khi, (int64_t)A->ncols, A->nrows, (const int64_t *)nullptr,
-                       flops_out, nnz_row, bins, hdr, g_min_bin, g_caps[0], (const int64_t *)nullptr, 0.0);
+    hipLaunchKernelGGL(k_bin_flops, dim3(grid_of(ncol, per_block)), dim3(256), 0, st, A->colptr, B->colptr,
+                       B->rowidx, c0, ncol, klo, khi, (int64_t)A->ncols, A->nrows, flops_out, nnz_row, bins, hdr,
+                       g_min_bin, g_caps[0]);
     LAUNCHCHK();
   }
   int cnt[kNumBins];
@@ -3201,10 +3292,8 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, hdr, zero_region_tag(kTagProduct, L),
                      keep_status ? 1 : 0, 1);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_bin<false>, dim3(grid_of(ncol, 4 * kBinColsPerWave)), dim3(256), 0, st, A->colptr, B->colptr,
-                     B->rowidx, c0, ncol, klo, khi, (int64_t)A->ncols, A->nrows, c_colptr, (int64_t *)nullptr,
-                     (int64_t *)nullptr, bins, hdr, g_min_bin, g_caps[1], esc ? esc->flops : (const int64_t *)nullptr,
-                     esc ? esc->cf : 0.0);
+  hipLaunchKernelGGL(k_bin_len, dim3(grid_of(ncol, 256)), dim3(256), 0, st, c_colptr, ncol, bins, hdr, g_min_bin,
+                     g_caps[1], esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0);
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;
@@ -3249,7 +3338,7 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
                          (uint64_t)A->nnz, (uint64_t)A->nrows, (uint64_t)klo, (uint64_t)khi, (uint64_t)L.P,
                          (uint64_t)sizeof(VT), (uint64_t)L.slab_off, (uint64_t)L.slab_pack})
         seed = fmix64(seed ^ x);
-      hipLaunchKernelGGL(k_left_sum<VT>, dim3((unsigned)(4 * device_cus())), dim3(256), 0, st, A->colptr, A->rowidx,
+      hipLaunchKernelGGL(k_left_sum<VT>, dim3((unsigned)(2 * device_cus())), dim3(256), 0, st, A->colptr, A->rowidx,
                          (const VT *)A->values, klo, khi, seed, hdr, hc);
       LAUNCHCHK();
       const unsigned pgrid = (unsigned)(8 * device_cus());
@@ -3332,10 +3421,8 @@ static int merge_typed(const spgemm_csc *parts, int32_t n_parts, const int64_t *
     hipLaunchKernelGGL(k_store_parts, dim3(1), dim3(64), 0, st, pd + c, hc, nc);
     LAUNCHCHK();
   }
-  hipLaunchKernelGGL(k_bin<false>, dim3(grid_of(L.ncol, 4 * kBinColsPerWave)), dim3(256), 0, st,
-                     (const int64_t *)nullptr, (const int64_t *)nullptr, (const int32_t *)nullptr, (int64_t)0, L.ncol,
-                     (int64_t)0, (int64_t)0, (int64_t)0, L.m, c_colptr, (int64_t *)nullptr, (int64_t *)nullptr, bins,
-                     hdr, g_min_bin, g_caps[1], (const int64_t *)nullptr, 0.0);
+  hipLaunchKernelGGL(k_bin_len, dim3(grid_of(L.ncol, 256)), dim3(256), 0, st, c_colptr, L.ncol, bins, hdr, g_min_bin,
+                     g_caps[1], (const int64_t *)nullptr, 0.0);
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;

@@ -74,3 +74,29 @@ def test_item_batches_at_few_heavy_columns(heavy, m):
     assert int((oracle.count(A, B) > 5120).sum()) == heavy + 1
     C, _ = S.Engine(A.to("cuda"), B.to("cuda")).run()
     assert_matches(C, oracle.spgemm(A, B), torch.float64, f"heavy={heavy} m={m}")
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 300])
+def test_column_flops_and_counts(n):
+    """Columns of B from empty to far longer than a wave's step, in groups
+    that start and end with empty ones."""
+    print(f"case: column flops n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    k = 6000
+    A = _csc(900, [rng.choice(900, c, replace=False) for c in rng.integers(0, 4, k)], torch.float64, rng)
+    lens = rng.choice([0, 0, 1, 2, 63, 64, 65, 511, 512, 513, 5000], n)
+    lens[-1] = 0
+    lens[n // 2] = 1500
+    B = _csc(k, [rng.choice(k, c, replace=False) for c in lens], torch.float64, rng)
+    plan = S.Engine(A.to("cuda"), B.to("cuda")).plan()
+    assert np.array_equal(plan.flops.cpu().numpy(), oracle.flops(A, B))
+    assert np.array_equal(plan.nnz_host[0], oracle.count(A, B))
+
+
+@pytest.mark.parametrize("n", [0, 1, 7, 8191, 8192, 8193, 100003, 8192 * 4096, 8192 * 4096 + 1])
+def test_column_pointers(n):
+    print(f"case: column pointers n={n}", flush=True)
+    x = torch.randint(0, 1 << 33, (n + 1,), device="cuda", generator=torch.Generator("cuda").manual_seed(n))[1:]
+    out = torch.full((n + 1,), -1, dtype=torch.int64, device="cuda")
+    S.colptr(x, out, S.alloc_workspace(S.workspace_size(S.OP_COLPTR, None, None, 0, n)))
+    assert int(out[0]) == 0 and torch.equal(out[1:], torch.cumsum(x, 0))
