@@ -182,6 +182,13 @@ int spgemm_numeric(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t
                    int32_t n_layers, const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx,
                    void *c_values, int32_t semiring, void *ws, size_t ws_bytes, void *stream);
 
+/* spgemm_numeric for a caller that knows that no column of the call holds
+ * more than max_len entries (from the symbolic counts it read back): kernels
+ * for longer columns are not launched.  A longer column sets status 4. */
+int spgemm_numeric_upto(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1, int32_t layer,
+                        int32_t n_layers, const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx,
+                        void *c_values, int32_t semiring, int64_t max_len, void *ws, size_t ws_bytes, void *stream);
+
 /* Sort-free hash merge (Sec. IV-D, sort-free hash merging; Merge in Alg. 1
  * and Alg. 2): C(:,j) = sum over parts of parts[p](:,j), entries with equal
  * row combined (added, for plus-times).  parts is a HOST array of n_parts descriptors (device arrays
@@ -375,6 +382,12 @@ int spgemm_numeric_sorted(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, 
                           void *tmp_values, double esc_cf_max, int32_t semiring, void *ws, size_t ws_bytes,
                           void *stream);
 
+/* The same under a bound on the columns' entries, as spgemm_numeric_upto. */
+int spgemm_numeric_sorted_upto(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1,
+                               const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx, void *c_values,
+                               int32_t *tmp_rowidx, void *tmp_values, double esc_cf_max, int32_t semiring,
+                               int64_t max_len, void *ws, size_t ws_bytes, void *stream);
+
 /* Bin thresholds (process-wide; used by calls launched afterwards): which = 0
  * for the symbolic pass, 1 for numeric, merge and masked products.
  * caps_host[5] are the largest bounds on distinct rows that go to bins 0..4
@@ -417,6 +430,11 @@ int spgemm_ws_status(void *ws, void *stream);
  * malformed internal work item, 10 a row twice in a pruned column that had
  * more than k candidates. */
 int spgemm_ws_status_code(void *ws, void *stream, int32_t *code_host);
+
+/* spgemm_ws_status_code for n workspaces with one synchronization per 8:
+ * codes_host[i] gets the code of ws[i] (0: none); SPGEMM_E_DEVICE if any is
+ * nonzero. */
+int spgemm_ws_status_many(void *const *ws, int32_t n, void *stream, int32_t *codes_host);
 
 /* What a workspace keeps between calls: consecutive spgemm_numeric calls on
  * one workspace with the same left operand and layer share the copy of A

@@ -103,7 +103,8 @@ def _check(rc: int, where: str):
 
 
 def _ptr(t) -> int | None:
-    return None if t is None else int(t.data_ptr())
+    """Address of a tensor (or an address as it is)."""
+    return t if t is None or isinstance(t, int) else t.data_ptr()
 
 
 def _stream(stream) -> int | None:
@@ -130,6 +131,8 @@ class CSC:
 
 def desc(M, dtype: int | None = None) -> spgemm_csc:
     """C descriptor of any object with nrows/ncols/colptr/rowidx/values."""
+    if isinstance(M, spgemm_csc):
+        return M
     v = M.values
     if dtype is None:
         dtype = _DTYPE.get(v.dtype, -1) if v is not None else F32
@@ -164,6 +167,7 @@ def plan_batches(nnz_host, ncols: int, n_layers: int, value_bytes: int, input_by
     """Returns (bounds: list[int], batch_nnz: np.ndarray[b, rows])."""
     nnz_host = np.ascontiguousarray(np.asarray(nnz_host, dtype=np.int64))
     rows = n_layers + 1 if n_layers > 1 else 1
+    max_batches = max(1, min(max_batches, ncols))  # a batch holds at least one column
     bounds = np.zeros(max_batches + 1, np.int64)
     tot = np.zeros(max_batches * rows, np.int64)
     nb = _i32(0)
@@ -188,15 +192,22 @@ def semiring_id(semiring) -> int:
     return int(semiring)
 
 
+NO_BOUND = (1 << 63) - 1  # max_len of a caller that knows no bound on the columns' entries
+
+
 def numeric(A, B, c0: int, c1: int, layer: int, n_layers: int, flops, c_colptr, c_rowidx, c_values,
-            ws: torch.Tensor, stream=None, semiring=PLUS_TIMES):
-    _check(_lib.spgemm_numeric(ctypes.byref(desc(A)), ctypes.byref(desc(B)), c0, c1, layer, n_layers, _ptr(flops),
-                               _ptr(c_colptr), _ptr(c_rowidx), _ptr(c_values), semiring_id(semiring), _ptr(ws),
-                               ws.numel(), _stream(stream)), "spgemm_numeric")
+            ws: torch.Tensor, stream=None, semiring=PLUS_TIMES, max_len: int = NO_BOUND):
+    _check(_lib.spgemm_numeric_upto(ctypes.byref(desc(A)), ctypes.byref(desc(B)), c0, c1, layer, n_layers,
+                                    _ptr(flops), _ptr(c_colptr), _ptr(c_rowidx), _ptr(c_values),
+                                    semiring_id(semiring), max_len, _ptr(ws), ws.numel(), _stream(stream)),
+           "spgemm_numeric")
 
 
+_lib.spgemm_numeric_upto.argtypes = [_P, _P, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i32, _i64, _vp, _sz, _vp]
 _lib.spgemm_numeric_sorted.argtypes = [_P, _P, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, ctypes.c_double, _i32, _vp,
                                        _sz, _vp]
+_lib.spgemm_numeric_sorted_upto.argtypes = [_P, _P, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, ctypes.c_double, _i32,
+                                            _i64, _vp, _sz, _vp]
 
 # Compression ratio up to which a column of at most 4096 product terms is
 # formed in row order by expand-sort-compress rather than hashed and sorted.
@@ -204,13 +215,14 @@ ESC_CF_DEFAULT = 2.0
 
 
 def numeric_sorted(A, B, c0: int, c1: int, flops, c_colptr, c_rowidx, c_values, tmp_rowidx, tmp_values,
-                   ws: torch.Tensor, stream=None, semiring=PLUS_TIMES, esc_cf: float = ESC_CF_DEFAULT):
+                   ws: torch.Tensor, stream=None, semiring=PLUS_TIMES, esc_cf: float = ESC_CF_DEFAULT,
+                   max_len: int = NO_BOUND):
     """Columns [c0, c1) of A*B in row order: low-compression columns by
     expand-sort-compress, the others hashed into tmp_* and sorted."""
-    _check(_lib.spgemm_numeric_sorted(ctypes.byref(desc(A)), ctypes.byref(desc(B)), c0, c1, _ptr(flops),
-                                      _ptr(c_colptr), _ptr(c_rowidx), _ptr(c_values), _ptr(tmp_rowidx),
-                                      _ptr(tmp_values), float(esc_cf), semiring_id(semiring), _ptr(ws), ws.numel(),
-                                      _stream(stream)), "spgemm_numeric_sorted")
+    _check(_lib.spgemm_numeric_sorted_upto(ctypes.byref(desc(A)), ctypes.byref(desc(B)), c0, c1, _ptr(flops),
+                                           _ptr(c_colptr), _ptr(c_rowidx), _ptr(c_values), _ptr(tmp_rowidx),
+                                           _ptr(tmp_values), float(esc_cf), semiring_id(semiring), max_len, _ptr(ws),
+                                           ws.numel(), _stream(stream)), "spgemm_numeric_sorted")
 
 
 def merge(parts, c_colptr, c_rowidx, c_values, ws: torch.Tensor, stream=None, semiring=PLUS_TIMES):
@@ -261,6 +273,19 @@ def check_ws(ws: torch.Tensor, where: str = "device check", stream=None):
     _check(rc, f"{where} (device code {code})" if code else where)
 
 
+_lib.spgemm_ws_status_many.argtypes = [_vp, _i32, _vp, _vp]
+
+
+def check_many(workspaces, where: str = "device check", stream=None):
+    """check_ws for several workspaces with one synchronization; the first
+    recorded code is raised."""
+    n = len(workspaces)
+    codes = (_i32 * n)()
+    rc = int(_lib.spgemm_ws_status_many((_vp * n)(*[_ptr(w) for w in workspaces]), n, _stream(stream), codes))
+    code = next((c for c in codes if c), 0)
+    _check(rc, f"{where} (device code {code})" if code else where)
+
+
 # -------------------------------------------------------------- batch loop
 def layer_bounds(kdim: int, n_layers: int) -> list[tuple[int, int]]:
     """The inner-dimension ranges the library uses for n_layers layers."""
@@ -285,6 +310,13 @@ class Plan:
     @property
     def nbatches(self) -> int:
         return len(self.bounds) - 1
+
+    @property
+    def longest(self) -> int:
+        """Entries of C's longest column."""
+        if "_longest" not in self.__dict__:
+            self._longest = int(self.nnz_host[-1].max(initial=0))
+        return self._longest
 
     @property
     def total_flops(self) -> int:
@@ -334,7 +366,8 @@ class Engine:
             free, _ = torch.cuda.mem_get_info()
             budget_bytes = int(free * 0.9) + self.input_bytes + self.reserve_bytes
         self.budget_bytes = int(budget_bytes)
-        self._bufs = None
+        self._bufs = None  # output buffers of run_batch
+        self._stage = None  # staging of a whole product (run without a consumer)
 
     # -- passes --------------------------------------------------------------
     def plan(self, stream=None) -> Plan:
@@ -350,8 +383,7 @@ class Engine:
         bounds, tot = plan_batches(counts.reshape(-1), n, self.L, self.vbytes, self.input_bytes, self.budget_bytes,
                                    self.reserve_bytes, self.max_batches)
         if self.sorted_output:
-            tot = np.stack([nnz_host[:, a:b].sum(1) for a, b in zip(bounds[:-1], bounds[1:])]) if len(bounds) > 1 \
-                else tot
+            tot[:, -1] //= 2
         return Plan(self.flops, self.nnz, nnz_host, bounds, tot, self.L, self.budget_bytes, self.input_bytes,
                     self.reserve_bytes)
 
@@ -382,6 +414,7 @@ class Engine:
     def release_buffers(self):
         """Drops the output buffers (they are allocated again, at the size the next plan needs)."""
         self._bufs = None
+        self._stage = None
 
     def run_batch(self, plan: Plan, i: int, stream=None, marks=None) -> CSC:
         """Forms batch i; the returned CSC views buffers reused by the next call.
@@ -398,67 +431,127 @@ class Engine:
         c0, c1 = plan.bounds[i], plan.bounds[i + 1]
         w = c1 - c0
         bufs = self._buffers(plan)
-        ccp, cri, cv = bufs["ccp"][:w + 1], bufs["cri"], bufs["cv"]
-        if L == 1:
-            e0 = mark()
-            colptr(self.nnz[0, c0:c1], ccp, self.ws_scan, stream)
-            nnzc = int(plan.batch_nnz[i, 0])
-            if self.sorted_output:  # formed in row order (hashed columns staged in cri / cv)
-                numeric_sorted(A, B, c0, c1, self.flops[c0:c1], ccp, bufs["sri"], bufs["sv"], cri, cv, self.ws_num,
-                               stream, self.semiring, self.esc_cf)
-                if marks is not None:
-                    marks.append(("numeric_sorted", e0, mark()))
-                return CSC(A.nrows, w, ccp, bufs["sri"][:nnzc], bufs["sv"][:nnzc])
-            numeric(A, B, c0, c1, 0, 1, self.flops[c0:c1], ccp, cri, cv, self.ws_num, stream, self.semiring)
-            if marks is not None:
-                marks.append(("numeric", e0, mark()))
-        else:
-            parts = []
+        ccp = bufs["ccp"][:w + 1]
+        nnzc = int(plan.batch_nnz[i, -1])
+        parts = []
+        e0 = mark()
+        if L > 1:
             off = 0
-            e0 = mark()
             for l in range(L):
                 dcp = bufs["dcp"][l, :w + 1]
                 colptr(self.nnz[l, c0:c1], dcp, self.ws_scan, stream)
                 cnt = int(plan.batch_nnz[i, l])
-                dri = bufs["dri"][off:off + cnt]
-                dv = bufs["dv"][off:off + cnt]
-                numeric(A, B, c0, c1, l, L, self.flops[c0:c1], dcp, dri, dv, self.ws_num, stream, self.semiring)
-                parts.append(CSC(A.nrows, w, dcp, dri, dv))
+                parts.append(CSC(A.nrows, w, dcp, bufs["dri"][off:off + cnt], bufs["dv"][off:off + cnt]))
                 off += cnt
-            e1 = mark()
-            colptr(self.nnz[L, c0:c1], ccp, self.ws_scan, stream)
-            merge(parts, ccp, cri, cv, self.ws_mrg, stream, self.semiring)
+        colptr(self.nnz[L if L > 1 else 0, c0:c1], ccp, self.ws_scan, stream)
+        hashed = (bufs["cri"], bufs["cv"])
+        out = (bufs["sri"], bufs["sv"]) if self.sorted_output else hashed
+        self._form(plan, i, ccp, nnzc, parts, hashed, out, stream, mark, e0, marks)
+        return CSC(A.nrows, w, ccp, out[0][:nnzc], out[1][:nnzc])
+
+    def _form(self, plan: Plan, i: int, ccp, nnzc: int, parts, hashed, out, stream=None, mark=lambda: None, e0=None,
+              marks=None):
+        """Batch i at the positions of the column pointers ccp: into ``out``
+        (rows, values), with ``hashed`` holding the unsorted columns of a
+        row-sorted product and ``parts`` the partial products of a layered one
+        (tensors, or addresses that the pointers count from)."""
+        A, B, L = self.A, self.B, self.L
+        c0, c1 = plan.bounds[i], plan.bounds[i + 1]
+        top = plan.longest
+        if L == 1:
+            if self.sorted_output:  # formed in row order (hashed columns staged)
+                numeric_sorted(A, B, c0, c1, self.flops[c0:c1], ccp, *out, *hashed, self.ws_num, stream,
+                               self.semiring, self.esc_cf, top)
+            else:
+                numeric(A, B, c0, c1, 0, 1, self.flops[c0:c1], ccp, *out, self.ws_num, stream, self.semiring, top)
             if marks is not None:
-                marks.append(("numeric", e0, e1))
-                marks.append(("merge", e1, mark()))
-            nnzc = int(plan.batch_nnz[i, L])
+                marks.append(("numeric_sorted" if self.sorted_output else "numeric", e0, mark()))
+            return
+        for l, D in enumerate(parts):
+            numeric(A, B, c0, c1, l, L, self.flops[c0:c1], D.colptr, D.rowidx, D.values, self.ws_num, stream,
+                    self.semiring, top)
+        e1 = mark()
+        merge(parts, ccp, *hashed, self.ws_mrg, stream, self.semiring)
+        e2 = mark()
         if self.sorted_output:
-            e0 = mark()
-            Cs = sort_columns(CSC(A.nrows, w, ccp, cri[:nnzc], cv[:nnzc]), bufs["sri"], bufs["sv"], self.ws_sort, stream)
-            if marks is not None:
-                marks.append(("sort", e0, mark()))
-            return Cs
-        return CSC(A.nrows, w, ccp, cri[:nnzc], cv[:nnzc])
+            Cu = spgemm_csc(int(A.nrows), c1 - c0, nnzc, _ptr(ccp), _ptr(hashed[0]), _ptr(hashed[1]),
+                            _DTYPE[self.vdtype])
+            _check(_lib.spgemm_sort_columns(ctypes.byref(Cu), _ptr(out[0]), _ptr(out[1]), _ptr(self.ws_sort),
+                                            self.ws_sort.numel(), _stream(stream)), "spgemm_sort_columns")
+        if marks is not None:
+            marks.append(("numeric", e0, e1))
+            marks.append(("merge", e1, e2))
+            if self.sorted_output:
+                marks.append(("sort", e2, mark()))
+
+    def _whole(self, plan: Plan, stream=None) -> CSC:
+        """Every batch formed at its place in one output: nothing is copied, and
+        one scan gives the column pointers of all batches (of all layers).
+        1.3e9 bytes of rows and as many of values took 2.4 ms to copy twice."""
+        A, L, n = self.A, self.L, self.B.ncols
+        dev = self.device
+        sizes = plan.batch_nnz[:, -1]
+        total = int(sizes.sum())
+        cp = torch.empty(n + 1, dtype=torch.int64, device=dev)
+        ri = torch.empty(max(1, total), dtype=torch.int32, device=dev)
+        v = torch.empty(max(1, total), dtype=self.vdtype, device=dev)
+        colptr(self.nnz[L if L > 1 else 0], cp, self.ws_scan, stream)
+        vb = self.vbytes
+        part_max = plan.batch_nnz[:, :L].sum(1).max() if L > 1 else 0
+        key = (int(sizes.max()) if self.sorted_output else 0, int(part_max))
+        st = self._stage
+        if st is None or st["key"][0] < key[0] or st["key"][1] < key[1]:
+            self._stage = None
+            st = {"key": key,
+                  "ri": torch.empty(max(1, key[0]), dtype=torch.int32, device=dev),
+                  "v": torch.empty(max(1, key[0]), dtype=self.vdtype, device=dev),
+                  "dri": torch.empty(max(1, key[1]), dtype=torch.int32, device=dev),
+                  "dv": torch.empty(max(1, key[1]), dtype=self.vdtype, device=dev)}
+            if L > 1:
+                st["dcp"] = torch.empty(L * n + 1, dtype=torch.int64, device=dev)
+                st["ws"] = alloc_workspace(workspace_size(OP_COLPTR, None, None, 0, L * n), dev)
+            self._stage = st
+        if L > 1:  # the layers' counts one after another: layer l's pointers start at l * n
+            dcp = st["dcp"]
+            colptr(self.nnz[:L].reshape(-1), dcp, st["ws"], stream)
+            before = np.concatenate([[0], np.cumsum(plan.batch_nnz[:, :L].sum(0))])  # entries of earlier layers
+        off = 0
+        done = np.zeros(max(1, L), np.int64)
+        for i in range(plan.nbatches):
+            c0, c1 = plan.bounds[i], plan.bounds[i + 1]
+            parts = []
+            if L > 1:
+                at = 0
+                for l in range(L):
+                    s = int(before[l] + done[l])  # the pointers' count at this batch's first column
+                    cnt = int(plan.batch_nnz[i, l])
+                    parts.append(spgemm_csc(int(A.nrows), c1 - c0, cnt, _ptr(dcp) + 8 * (l * n + c0),
+                                            _ptr(st["dri"]) + 4 * (at - s), _ptr(st["dv"]) + vb * (at - s),
+                                            _DTYPE[self.vdtype]))
+                    at += cnt
+                done += plan.batch_nnz[i, :L]
+            out = (_ptr(ri), _ptr(v))
+            hashed = (_ptr(st["ri"]) - 4 * off, _ptr(st["v"]) - vb * off) if self.sorted_output else out
+            self._form(plan, i, cp[c0:c1 + 1], int(sizes[i]), parts, hashed, out, stream)
+            off += int(sizes[i])
+        return CSC(A.nrows, n, cp, ri[:total], v[:total])
 
     def check(self, stream=None):
-        for w in (self.ws_sym, self.ws_num, self.ws_mrg, self.ws_sort):
-            if w is not None:
-                check_ws(w, "device-side check", stream)
+        check_many([w for w in (self.ws_sym, self.ws_num, self.ws_mrg, self.ws_sort) if w is not None],
+                   "device-side check", stream)
 
     def run(self, consume=None, stream=None):
         """All batches; consume(c0, c1, C_batch) per batch, or the whole C."""
+        stream = _stream(stream)  # looked up once
         plan = self.plan(stream)
-        out = [] if consume is None else None
+        if consume is None:
+            C = self._whole(plan, stream)
+            self.check(stream)
+            return C, plan
         for i in range(plan.nbatches):
-            Cb = self.run_batch(plan, i, stream)
-            if consume is None:
-                out.append(CSC(Cb.nrows, Cb.ncols, Cb.colptr.clone(), Cb.rowidx.clone(), Cb.values.clone()))
-            else:
-                consume(plan.bounds[i], plan.bounds[i + 1], Cb)
+            consume(plan.bounds[i], plan.bounds[i + 1], self.run_batch(plan, i, stream))
         self.check(stream)
-        if consume is not None:
-            return plan
-        return _concat(out, self.A.nrows), plan
+        return plan
 
 
 def _concat(batches, nrows):
@@ -701,7 +794,8 @@ class SpGEMMFn(torch.autograd.Function):
         Av = CSC(A.nrows, A.ncols, A.colptr, A.rowidx, a_vals)
         Bv = CSC(B.nrows, B.ncols, B.colptr, B.rowidx, b_vals)
         C, plan = Engine(Av, Bv, layers, budget_bytes).run()
-        ctx.longest = int(plan.nnz_host[-1].max()) if C.ncols > 0 else 0
+        ctx.longest = plan.longest
+        ctx.set_materialize_grads(False)  # the pattern outputs need no gradients of zeros
         ctx.save_for_backward(a_vals, b_vals)
         ctx.A, ctx.B, ctx.C = A, B, CSC(C.nrows, C.ncols, C.colptr, C.rowidx, None)
         ctx.mark_non_differentiable(C.colptr, C.rowidx)
@@ -709,6 +803,8 @@ class SpGEMMFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, d_vals, _d_cp, _d_ri):
+        if d_vals is None:
+            return None, None, None, None, None, None
         a_vals, b_vals = ctx.saved_tensors
         A = CSC(ctx.A.nrows, ctx.A.ncols, ctx.A.colptr, ctx.A.rowidx, a_vals)
         B = CSC(ctx.B.nrows, ctx.B.ncols, ctx.B.colptr, ctx.B.rowidx, b_vals)

@@ -275,28 +275,50 @@ int spgemm_plan_batches(const int64_t *nnz_host, int64_t ncols, int32_t n_layers
   const uint64_t r = 4 + (uint64_t)value_bytes;
   const size_t n = (size_t)ncols;
 
-  // Memory of every output column and its prefix sums.
-  std::vector<uint64_t> pre(n + 1, 0);
-  uint64_t maxcol = 0;
+  // Memory of output column j, or a negative count's error.
+  const auto column = [&](size_t j, uint64_t *mem) {
+    if (n_layers == 1) {
+      const int64_t u = nnz_host[j];
+      *mem = r * (uint64_t)u + 8;
+      return u >= 0;
+    }
+    uint64_t parts = 0;
+    for (int l = 0; l < n_layers; l++) {
+      const int64_t u = nnz_host[(size_t)l * n + j];
+      if (u < 0) return false;
+      parts += (uint64_t)u;
+    }
+    const int64_t u = nnz_host[(size_t)n_layers * n + j];
+    *mem = r * parts + 8 * (uint64_t)n_layers + r * (uint64_t)u + 8;
+    return u >= 0;
+  };
+  // One pass over the counts settles the common case, a product that fits as
+  // a whole (the GPU waits meanwhile).
+  uint64_t sum = 0, maxcol = 0;
   for (size_t j = 0; j < n; j++) {
     uint64_t mem;
-    if (n_layers == 1) {
-      int64_t u = nnz_host[j];
-      if (u < 0) return SPGEMM_E_INVAL;
-      mem = r * (uint64_t)u + 8;
-    } else {
-      uint64_t parts = 0;
-      for (int l = 0; l < n_layers; l++) {
-        int64_t u = nnz_host[(size_t)l * n + j];
-        if (u < 0) return SPGEMM_E_INVAL;
-        parts += (uint64_t)u;
-      }
-      int64_t u = nnz_host[(size_t)n_layers * n + j];
-      if (u < 0) return SPGEMM_E_INVAL;
-      mem = r * parts + 8 * (uint64_t)n_layers + r * (uint64_t)u + 8;
-    }
+    if (!column(j, &mem)) return SPGEMM_E_INVAL;
     if (mem > avail) return SPGEMM_E_BUDGET;
     maxcol = std::max(maxcol, mem);
+    sum += mem;
+  }
+  if (sum <= avail) {
+    bounds_host[0] = 0;
+    bounds_host[1] = ncols;
+    *nbatches_host = 1;
+    for (int rr = 0; rr < rows && batch_nnz_host; rr++) {
+      int64_t t = 0;
+      for (size_t j = 0; j < n; j++) t += nnz_host[(size_t)rr * n + j];
+      batch_nnz_host[rr] = t;
+    }
+    return SPGEMM_OK;
+  }
+  // Prefix sums of the columns' memory.
+  std::vector<uint64_t> pre(n + 1);
+  pre[0] = 0;
+  for (size_t j = 0; j < n; j++) {
+    uint64_t mem;
+    (void)column(j, &mem);
     pre[j + 1] = pre[j] + mem;
   }
   const uint64_t total = pre[n];

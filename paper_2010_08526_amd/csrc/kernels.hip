@@ -607,11 +607,13 @@ __global__ __launch_bounds__(256) void k_bin_flops(const int64_t *Acp, const int
 // Numeric and merge: one thread per column, its length from the column
 // pointers.
 __global__ __launch_bounds__(256) void k_bin_len(const int64_t *c_colptr, int64_t ncol, int32_t *bins, WsHeader *hdr,
-                                                 int min_bin, BinCaps caps, const int64_t *esc_flops, double esc_cf) {
+                                                 int min_bin, BinCaps caps, const int64_t *esc_flops, double esc_cf,
+                                                 int64_t max_len) {
   const int64_t jj = (int64_t)blockIdx.x * 256 + threadIdx.x;
   int bin = -1;
   if (jj < ncol) {
     const int64_t len = c_colptr[jj + 1] - c_colptr[jj];
+    if (len > max_len) flag_error(&hdr->status, 4);  // above what the caller promised: its bin may not run
     if (len > 0) bin = max(bin_of(len, caps), min_bin);
     if (esc_flops && len > 0) {
       const int e = esc_class(esc_flops[jj], len, esc_cf);
@@ -2870,8 +2872,9 @@ int hip_fail(hipError_t e) {
   return SPGEMM_E_HIP;
 }
 
+constexpr int kStatusMany = 8;  // headers read back with one synchronization
 struct HostPinned {
-  WsHeader *hdr = nullptr;
+  WsHeader *hdr = nullptr;  // kStatusMany of them
 };
 static thread_local HostPinned g_pin;
 
@@ -2885,12 +2888,17 @@ static BinCaps g_caps[2] = {BinCaps{{kSymCap[0], kSymCap[1], kSymCap[2], kSymCap
 constexpr int kBpcDefault[2][kNumBins - 1] = {{8, 8, 8, 8, 1}, {8, 8, 4, 4, 1}};
 static int g_bpc[2][kNumBins - 1] = {{8, 8, 8, 8, 1}, {8, 8, 4, 4, 1}};
 
-int read_header(WsHeader *dev, hipStream_t st, WsHeader *out) {
-  if (!g_pin.hdr) HIPCHK(hipHostMalloc((void **)&g_pin.hdr, sizeof(WsHeader), hipHostMallocDefault));
-  HIPCHK(hipMemcpyAsync(g_pin.hdr, dev, sizeof(WsHeader), hipMemcpyDeviceToHost, st));
+int read_headers(void *const *dev, int n, hipStream_t st, WsHeader *out) {
+  if (!g_pin.hdr) HIPCHK(hipHostMalloc((void **)&g_pin.hdr, sizeof(WsHeader) * kStatusMany, hipHostMallocDefault));
+  for (int i = 0; i < n; i++) HIPCHK(hipMemcpyAsync(g_pin.hdr + i, dev[i], sizeof(WsHeader), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  *out = *g_pin.hdr;
+  for (int i = 0; i < n; i++) out[i] = g_pin.hdr[i];
   return SPGEMM_OK;
+}
+
+int read_header(WsHeader *dev, hipStream_t st, WsHeader *out) {
+  void *d = dev;
+  return read_headers(&d, 1, st, out);
 }
 
 int device_cus() {
@@ -3286,19 +3294,24 @@ template <class VT, class SR>
 static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t ncol, int64_t klo,
                          int64_t khi, const int64_t *c_colptr, int32_t *c_rowidx, void *c_values, const WsLayout &L,
                          char *ws, hipStream_t st, bool sync, bool keep_status = false,
-                         const EscOut *esc = nullptr) {
+                         const EscOut *esc = nullptr, int64_t max_len = INT64_MAX) {
   WsHeader *hdr = (WsHeader *)ws;
   int32_t *bins = (int32_t *)(ws + L.bins);
+  max_len = std::min(max_len, A->nrows);
   hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, hdr, zero_region_tag(kTagProduct, L),
                      keep_status ? 1 : 0, 1);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_bin_len, dim3(grid_of(ncol, 256)), dim3(256), 0, st, c_colptr, ncol, bins, hdr, g_min_bin,
-                     g_caps[1], esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0);
+                     g_caps[1], esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0, max_len);
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;
   int rc = bin_counts(hdr, st, sync, cnt, &h);
   if (rc) return rc;
+  // bins that no column can reach are not launched (an empty launch costs
+  // about 4.6 us of the stream's time)
+  for (int b = g_min_bin + 1; b < kNumBins; b++)
+    if (cnt[b] < 0 && max_len <= g_caps[1].cap[b - 1]) cnt[b] = 0;
   ProductSrc<VT, SR> src;
   src.a = product_args<VT>(A, B, klo, khi);
   src.c0 = c0;
@@ -3306,7 +3319,9 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
     int32_t *status = &hdr->status;
     static const char *kEscNames[3] = {"esc_wave", "esc_wave512", "esc_block"};
     for (int e = 0; e < 3; e++) {
-      const int ce = sync ? h.esc_count[e] : -1;
+      // (a column taken has at most cf times its length in terms)
+      static constexpr int64_t kBelow[3] = {0, kEscWaveTerms, kEscWave512Terms};
+      const int ce = sync ? h.esc_count[e] : ((double)max_len * esc->cf <= (double)kBelow[e] ? 0 : -1);
       if (ce == 0) continue;
       const int32_t *list = bins + (int64_t)(kNumBins + (e == 0 ? 0 : 1)) * ncol - (e == 1 ? 1 : 0);
       const int32_t *cp = &hdr->esc_count[e];
@@ -3422,7 +3437,7 @@ static int merge_typed(const spgemm_csc *parts, int32_t n_parts, const int64_t *
     LAUNCHCHK();
   }
   hipLaunchKernelGGL(k_bin_len, dim3(grid_of(L.ncol, 256)), dim3(256), 0, st, c_colptr, L.ncol, bins, hdr, g_min_bin,
-                     g_caps[1], (const int64_t *)nullptr, 0.0);
+                     g_caps[1], (const int64_t *)nullptr, 0.0, INT64_MAX);
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;
@@ -3568,7 +3583,7 @@ namespace spg {
 static int numeric_dispatch(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t ncol, int64_t klo,
                             int64_t khi, const int64_t *c_colptr, int32_t *c_rowidx, void *c_values, int32_t semiring,
                             const WsLayout &L, char *ws, hipStream_t s, bool keep_status,
-                            const EscOut *esc = nullptr) {
+                            const EscOut *esc = nullptr, int64_t max_len = INT64_MAX) {
   const bool f32 = A->dtype == SPGEMM_F32;
   // The bin counts are read back only when heavy columns may need the
   // global accumulators (their launches are sized on the host); otherwise
@@ -3578,19 +3593,19 @@ static int numeric_dispatch(const spgemm_csc *A, const spgemm_csc *B, int64_t c0
   switch (semiring) {
     case SPGEMM_SR_MIN_PLUS:
       return f32 ? numeric_typed<float, SrMinPlus>(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, L, ws, s,
-                                                   sync, keep_status, esc)
+                                                   sync, keep_status, esc, max_len)
                  : numeric_typed<double, SrMinPlus>(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, L, ws, s,
-                                                    sync, keep_status, esc);
+                                                    sync, keep_status, esc, max_len);
     case SPGEMM_SR_OR_AND:
       return f32 ? numeric_typed<float, SrOrAnd>(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, L, ws, s,
-                                                 sync, keep_status, esc)
+                                                 sync, keep_status, esc, max_len)
                  : numeric_typed<double, SrOrAnd>(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, L, ws, s,
-                                                  sync, keep_status, esc);
+                                                  sync, keep_status, esc, max_len);
     default:
       return f32 ? numeric_typed<float, SrPlusTimes>(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, L, ws,
-                                                     s, sync, keep_status, esc)
+                                                     s, sync, keep_status, esc, max_len)
                  : numeric_typed<double, SrPlusTimes>(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, L, ws,
-                                                      s, sync, keep_status, esc);
+                                                      s, sync, keep_status, esc, max_len);
   }
 }
 }  // namespace spg
@@ -3639,6 +3654,13 @@ int spgemm_symbolic(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_
 int spgemm_numeric(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1, int32_t layer,
                    int32_t n_layers, const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx,
                    void *c_values, int32_t semiring, void *ws, size_t ws_bytes, void *stream) {
+  return spgemm_numeric_upto(A, B, c0, c1, layer, n_layers, flops, c_colptr, c_rowidx, c_values, semiring, INT64_MAX,
+                             ws, ws_bytes, stream);
+}
+
+int spgemm_numeric_upto(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1, int32_t layer,
+                        int32_t n_layers, const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx,
+                        void *c_values, int32_t semiring, int64_t max_len, void *ws, size_t ws_bytes, void *stream) {
   if (semiring < SPGEMM_SR_PLUS_TIMES || semiring > SPGEMM_SR_OR_AND) return SPGEMM_E_INVAL;
   (void)flops;
   int st = check_csc(A, true);
@@ -3672,15 +3694,24 @@ int spgemm_numeric(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t
                                 : build_layer<double>(B, c0, ncol, klo, khi, kdim, true, L, (char *)ws, s, &Bl);
     if (st) return st;
     return numeric_dispatch(A, &Bl, 0, ncol, klo, khi, c_colptr, c_rowidx, c_values, semiring, L, (char *)ws, s,
-                            true);
+                            true, nullptr, max_len);
   }
-  return numeric_dispatch(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, semiring, L, (char *)ws, s, false);
+  return numeric_dispatch(A, B, c0, ncol, klo, khi, c_colptr, c_rowidx, c_values, semiring, L, (char *)ws, s, false,
+                          nullptr, max_len);
 }
 
 int spgemm_numeric_sorted(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1, const int64_t *flops,
                           const int64_t *c_colptr, int32_t *c_rowidx, void *c_values, int32_t *tmp_rowidx,
                           void *tmp_values, double esc_cf_max, int32_t semiring, void *ws, size_t ws_bytes,
                           void *stream) {
+  return spgemm_numeric_sorted_upto(A, B, c0, c1, flops, c_colptr, c_rowidx, c_values, tmp_rowidx, tmp_values,
+                                    esc_cf_max, semiring, INT64_MAX, ws, ws_bytes, stream);
+}
+
+int spgemm_numeric_sorted_upto(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1,
+                               const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx, void *c_values,
+                               int32_t *tmp_rowidx, void *tmp_values, double esc_cf_max, int32_t semiring,
+                               int64_t max_len, void *ws, size_t ws_bytes, void *stream) {
   if (semiring < SPGEMM_SR_PLUS_TIMES || semiring > SPGEMM_SR_OR_AND) return SPGEMM_E_INVAL;
   if (!(esc_cf_max >= 0.0)) return SPGEMM_E_INVAL;  // NaN included
   int st = check_csc(A, true);
@@ -3707,7 +3738,7 @@ int spgemm_numeric_sorted(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, 
   if (use_esc && !flops) return SPGEMM_E_INVAL;
   const EscOut esc{flops, esc_cf_max, c_rowidx, c_values};
   st = numeric_dispatch(A, B, c0, ncol, 0, A->ncols, c_colptr, tmp_rowidx, tmp_values, semiring, L, (char *)ws, s,
-                        false, use_esc ? &esc : nullptr);
+                        false, use_esc ? &esc : nullptr, max_len);
   if (st) return st;
   // the hashed columns, from the staging arrays into row order (the bin
   // lists are free again: the sort pass lists its columns there)
@@ -3719,7 +3750,7 @@ int spgemm_numeric_sorted(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, 
   T.rowidx = tmp_rowidx;
   T.values = tmp_values;
   return sort_column_lists(&T, c_rowidx, c_values, (int32_t *)((char *)ws + L.bins), (WsHeader *)ws,
-                           use_esc ? flops : nullptr, esc_cf_max, s);
+                           use_esc ? flops : nullptr, esc_cf_max, s, max_len);
 }
 
 int spgemm_merge(const spgemm_csc *parts, int32_t n_parts, const int64_t *c_colptr, int32_t *c_rowidx,
@@ -3927,5 +3958,29 @@ int spgemm_ws_status_code(void *ws, void *stream, int32_t *code_host) {
 }
 
 int spgemm_ws_status(void *ws, void *stream) { return spgemm_ws_status_code(ws, stream, nullptr); }
+
+int spgemm_ws_status_many(void *const *ws, int32_t n, void *stream, int32_t *codes_host) {
+  if (n < 0 || (n > 0 && (!ws || !codes_host))) return SPGEMM_E_INVAL;
+  for (int i = 0; i < n; i++) {
+    codes_host[i] = 0;
+    if (!ws[i]) return SPGEMM_E_WORKSPACE;
+  }
+  hipStream_t s = (hipStream_t)stream;
+  int out = SPGEMM_OK;
+  for (int i0 = 0; i0 < n; i0 += kStatusMany) {
+    const int c = std::min(kStatusMany, n - i0);
+    WsHeader h[kStatusMany];
+    int rc = read_headers(ws + i0, c, s, h);
+    if (rc) return rc;
+    for (int i = 0; i < c; i++) {
+      if (h[i].status == 0) continue;
+      codes_host[i0 + i] = h[i].status;
+      hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, s, (WsHeader *)ws[i0 + i], kKeepAnyTag, 0);
+      LAUNCHCHK();
+      out = SPGEMM_E_DEVICE;
+    }
+  }
+  return out;
+}
 
 }  // extern "C"

@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "device.hpp"
 #include "hip_host.hpp"
 #include "internal.hpp"
@@ -44,11 +46,12 @@ constexpr int kSortDupCode = 11;  // status code: a row twice in one column, or 
 // Columns formed in row order by expand-sort-compress (skip_flops given) are
 // left out.
 __global__ __launch_bounds__(256) void k_sort_bin(const int64_t *cp, int64_t n, int32_t *lists, WsHeader *hdr,
-                                                  const int64_t *skip_flops, double skip_cf) {
+                                                  const int64_t *skip_flops, double skip_cf, int64_t max_len) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   int cls = -1;
   if (j < n) {
     const int64_t len = cp[j + 1] - cp[j];
+    if (len > max_len) flag_error(&hdr->status, kSortDupCode);  // its class may not be launched
     cls = len <= 0 ? -1
                    : (len <= kSortWaveLen ? 0 : (len <= kSortWave512Len ? 3 : (len <= kSortBlockLen ? 1 : 2)));
     if (skip_flops && esc_class(skip_flops[j], len, skip_cf) >= 0) cls = -1;
@@ -342,23 +345,29 @@ __global__ __launch_bounds__(THREADS) void k_sort_heavy(const int64_t *cp, const
 
 template <class VT>
 int sort_typed(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHeader *hdr,
-               const int64_t *skip_flops, double skip_cf, hipStream_t st) {
+               const int64_t *skip_flops, double skip_cf, hipStream_t st, int64_t max_len) {
   const int64_t n = C->ncols;
+  max_len = std::min(max_len, C->nrows);  // longer columns hold a row twice: listed, and flagged below
   ProfScope prof("sort_columns", st);
   hipLaunchKernelGGL(k_sort_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, n, lists, hdr, skip_flops,
-                     skip_cf);
+                     skip_cf, max_len);
   LAUNCHCHK();
   const VT *v = (const VT *)C->values;
   const int cus = device_cus();
   hipLaunchKernelGGL(k_sort_wave<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows, lists,
                      (const int32_t *)&hdr->bin_count[0], ro, (VT *)vo, &hdr->status);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_sort_wave512<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows,
-                     lists + n - 1, (const int32_t *)&hdr->bin_count[3], ro, (VT *)vo, &hdr->status);
-  LAUNCHCHK();
-  hipLaunchKernelGGL(k_sort_block<VT>, dim3(4 * cus), dim3(kSortBlockThreads), 0, st, C->colptr, C->rowidx, v,
-                     C->nrows, lists + n, (const int32_t *)&hdr->bin_count[1], ro, (VT *)vo, &hdr->status);
-  LAUNCHCHK();
+  if (max_len > kSortWaveLen) {
+    hipLaunchKernelGGL(k_sort_wave512<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows,
+                       lists + n - 1, (const int32_t *)&hdr->bin_count[3], ro, (VT *)vo, &hdr->status);
+    LAUNCHCHK();
+  }
+  if (max_len > kSortWave512Len) {
+    hipLaunchKernelGGL(k_sort_block<VT>, dim3(4 * cus), dim3(kSortBlockThreads), 0, st, C->colptr, C->rowidx, v,
+                       C->nrows, lists + n, (const int32_t *)&hdr->bin_count[1], ro, (VT *)vo, &hdr->status);
+    LAUNCHCHK();
+  }
+  if (max_len <= kSortBlockLen) return SPGEMM_OK;
   // a window as large as m asks for, so that several workgroups fit a CU
   int words = 1024;
   while (words < kSortWinWords && (int64_t)words * 32 < C->nrows) words *= 2;
@@ -377,9 +386,9 @@ int sort_typed(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHea
 }  // namespace
 
 int sort_column_lists(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHeader *hdr,
-                      const int64_t *skip_flops, double skip_cf, hipStream_t st) {
-  if (C->dtype == SPGEMM_F32) return sort_typed<float>(C, ro, vo, lists, hdr, skip_flops, skip_cf, st);
-  return sort_typed<double>(C, ro, vo, lists, hdr, skip_flops, skip_cf, st);
+                      const int64_t *skip_flops, double skip_cf, hipStream_t st, int64_t max_len) {
+  if (C->dtype == SPGEMM_F32) return sort_typed<float>(C, ro, vo, lists, hdr, skip_flops, skip_cf, st, max_len);
+  return sort_typed<double>(C, ro, vo, lists, hdr, skip_flops, skip_cf, st, max_len);
 }
 
 }  // namespace spg
@@ -406,7 +415,7 @@ int spgemm_sort_columns(const spgemm_csc *C, int32_t *rowidx_out, void *values_o
   st = launch_init_header((WsHeader *)ws, (uint64_t)0, s);
   if (st) return st;
   return sort_column_lists(C, rowidx_out, values_out, (int32_t *)((char *)ws + L.bins), (WsHeader *)ws, nullptr, 0.0,
-                           s);
+                           s, INT64_MAX);
 }
 
 }  // extern "C"
