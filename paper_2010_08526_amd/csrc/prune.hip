@@ -9,6 +9,10 @@
 // their input order, so the hash-table order of the numeric pass carries
 // over unchanged.
 //
+// For k up to 1024 on columns of at least k entries on average, k_prune_top
+// reads every column once (see there).  Otherwise, and for columns with too
+// many equal values for it:
+//
 // One workgroup per column.  Every entry gets a composite key that orders
 // it as the selection does: the value mapped onto an unsigned integer in
 // numeric order (-0 folded onto +0), then the row mapped so that a smaller
@@ -23,12 +27,17 @@
 // entries in order with one exchange of per-wave counts per 2048 entries
 // that keep any (one flag per wave for those that keep none).
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
 
 #include "device.hpp"
 #include "hip_host.hpp"
 #include "internal.hpp"
 #include "profile.hpp"
+#include "rank_sort.hpp"
 
 namespace spg {
 namespace {
@@ -39,6 +48,11 @@ constexpr int kPrMaxGrid = 65536;
 constexpr int kSelUnroll = 8;    // select: coalesced loads per thread per step
 constexpr int kFillUnroll = 8;   // compaction: coalesced slots per thread per step
 constexpr int kPrDupRows = 10;  // status code: a row twice in one column
+
+// Values of cutv for the columns that k_prune_top has seen; neither is the key
+// of a candidate (float keys are below 2^32, a double's would be a NaN).
+constexpr uint64_t kTopDone = ~0ull;      // settled
+constexpr uint64_t kTopLeft = ~0ull - 1;  // left to the kernels that follow
 
 __device__ __forceinline__ uint64_t order_key(float v) {
   uint32_t b = __float_as_uint(v);
@@ -132,7 +146,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_select(const int64_t *__re
                                                              const VT *__restrict__ vals, int64_t ncols, double thr,
                                                              int64_t nnz, int64_t k, int64_t *__restrict__ cnt,
                                                              uint64_t *__restrict__ cutv, uint32_t *__restrict__ cutr,
-                                                             int32_t *status) {
+                                                             int left_only, int32_t *status) {
   constexpr int VD = (int)sizeof(VT), ND = VD + 4;
   constexpr int kShift = 8 * VD - kWideBits;  // value key bits below the wide digit
   __shared__ int s_hist[256];
@@ -145,6 +159,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_select(const int64_t *__re
   int *s_whist = reinterpret_cast<int *>(s_wide);
   const int t = threadIdx.x;
   for (int64_t j = blockIdx.x; j < ncols; j += gridDim.x) {
+    if (left_only && cutv[j] != kTopLeft) continue;  // settled by k_prune_top
     int64_t b = colptr[j], e = colptr[j + 1];
     if (b < 0 || e < b || e > nnz) {  // pointers outside the arrays: the column counts as empty
       if (t == 0) flag_error(status, 5);
@@ -422,7 +437,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_fill(
     const int64_t *__restrict__ colptr, const int32_t *__restrict__ rowidx, const VT *__restrict__ vals,
     int64_t ncols, int64_t nnz, double thr, const uint64_t *__restrict__ cutv, const uint32_t *__restrict__ cutr,
     const int64_t *__restrict__ out_colptr, int32_t *__restrict__ out_rowidx, VT *__restrict__ out_vals,
-    int32_t *status) {
+    int left_only, int32_t *status) {
   __shared__ int s_cnt[kFillUnroll][kPrWaves];
   __shared__ int s_any[2][kPrWaves];
   const int t = threadIdx.x, w = t / kWave;
@@ -432,6 +447,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_fill(
     if (b < 0 || e < b || e > nnz) b = e = 0;  // flagged by the select kernel
     const int64_t o = out_colptr[j], lim = out_colptr[j + 1];
     const uint64_t cv = cutv[j];
+    if (left_only && cv == kTopDone) continue;  // written by k_prune_take
     const uint32_t cr = cutr[j];
     int64_t run = 0;
     // kFillUnroll coalesced slots per thread per step (entry c0 + q * 256 + t
@@ -502,6 +518,350 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_fill(
   }
 }
 
+// ----------------------------------------------------------------------------
+// One reading of a column, for 1 <= k <= kTopMaxK: entries at or above a bound
+// are appended to a list in LDS (value key and position); whenever the list
+// holds more than kTopLimit of them, the bound rises to its k-th largest value
+// and the list shrinks to the entries at or above it.  The k largest entries
+// are always in the list, an entry below the bound costs one comparison, and
+// after N entries about one in N / k passes.  The kept positions, in input
+// order, go to stage[j * k ...]; cutv / cutr are set to kTopDone.  A column
+// with more equal values at its bound than the list can hold is left to the
+// kernels above (kTopLeft).
+//
+// Values are read once, the next step's while one is worked on, where the
+// digit histogram read them twice and worked on each, and the fill kernel a
+// third time.  2.0e8 float32 entries in 20,011 columns, k = 100: 367 us (2.2
+// TB/s; the bounds' digit passes, two or three per column, take most of the
+// rest) and 100 us for the entries kept, against 973 and 394 us; 2.96e9 entries
+// of a scale 18 R-MAT square in four batches: 6.6 + 0.9 against 15.2 + 8.4 ms.
+// ----------------------------------------------------------------------------
+constexpr int kTopMaxK = 1024;
+constexpr int kTopStep = kSelUnroll * kPrThreads;
+
+template <typename VT>
+struct TopKey;
+template <>
+struct TopKey<float> {
+  using T = uint32_t;
+};
+template <>
+struct TopKey<double> {
+  using T = uint64_t;
+};
+
+__device__ __forceinline__ float key_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k);
+}
+__device__ __forceinline__ double key_value(uint64_t k) {
+  return __longlong_as_double((long long)((k >> 63) ? k & 0x7fffffffffffffffull : ~k));
+}
+
+// The need-th largest of the keys key[e] with bit e of `have` set, over the
+// workgroup (1 <= need <= their number), by 8-bit digits, most significant
+// first.  Digits stop once no more than `stop` keys are at or above the chosen
+// bucket: returned is its lower edge (the key itself after the last digit).
+// above / equal: the keys above the bucket, and in it.  s_hist: 2 x 256 + 4
+// words; a digit uses one half while the other is cleared.  Contains barriers.
+template <int E, typename KT>
+__device__ __forceinline__ KT block_kth(const KT (&key)[E], uint32_t have, int need, int stop, int *s_hist, int &above,
+                                        int &equal) {
+  constexpr int ND = (int)sizeof(KT);
+  int *s_sel = s_hist + 512;
+  const int t = threadIdx.x;
+  KT prefix = 0;
+  above = 0;
+  equal = 0;
+  s_hist[t] = 0;  // (256 threads)
+  __syncthreads();
+#pragma unroll 1
+  for (int d = ND - 1; d >= 0; d--) {
+    int *h_cur = s_hist + 256 * (d & 1 ? 0 : 1), *h_next = s_hist + 256 * (d & 1 ? 1 : 0);
+    const KT mask = d == ND - 1 ? KT(0) : (KT)(~KT(0) << (8 * (d + 1)));
+#pragma unroll
+    for (int e = 0; e < E; e++)
+      hist_add(h_cur, ((have >> e) & 1u) && (key[e] & mask) == prefix, (int)((key[e] >> (8 * d)) & 255u));
+    __syncthreads();
+    h_next[t] = 0;
+    if (t < kWave) {
+      int h[4], sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        h[q] = h_cur[255 - 4 * t - q];
+        sum += h[q];
+      }
+      const int incl = wave_incl_add(sum);
+      int acc = incl - sum;
+      const int want = need - above;
+      if (acc < want && want <= incl) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          if (acc + h[q] >= want) {
+            s_sel[0] = 255 - 4 * t - q;
+            s_sel[1] = acc;
+            s_sel[2] = h[q];
+            break;
+          }
+          acc += h[q];
+        }
+      }
+    }
+    __syncthreads();
+    prefix |= (KT)s_sel[0] << (8 * d);
+    above += s_sel[1];
+    equal = s_sel[2];
+    if (above + equal <= stop) break;  // uniform
+  }
+  __syncthreads();  // s_hist and s_sel may be written again
+  return prefix;
+}
+
+// One step's values from entry c0 on; past e a value that no bound lets pass.
+template <typename VT>
+__device__ __forceinline__ void top_load(const VT *__restrict__ vals, int64_t c0, int64_t e, int t,
+                                         VT (&v)[kSelUnroll]) {
+  if (c0 + kTopStep <= e) {
+#pragma unroll
+    for (int q = 0; q < kSelUnroll; q++) v[q] = vals[c0 + q * kPrThreads + t];
+  } else {
+#pragma unroll
+    for (int q = 0; q < kSelUnroll; q++) {
+      const int64_t p = c0 + q * kPrThreads + t;
+      v[q] = p < e ? vals[p] : VT(NAN);
+    }
+  }
+}
+
+template <int CAP, typename VT>
+__global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restrict__ colptr,
+                                                          const int32_t *__restrict__ rowidx,
+                                                          const VT *__restrict__ vals, int64_t ncols, VT thr,
+                                                          int64_t nnz, int k, int64_t *__restrict__ cnt,
+                                                          uint64_t *__restrict__ cutv, int32_t *__restrict__ stage,
+                                                          int32_t *status) {
+  using KT = typename TopKey<VT>::T;
+  constexpr int E = CAP / kPrThreads;      // list entries per thread
+  constexpr int kLimit = CAP - kTopStep;   // a step fits on top of this many
+  constexpr int KE = kTopMaxK / kPrThreads;
+  static_assert(CAP % kPrThreads == 0 && kLimit >= 512, "a whole step fits the list");
+  union Lds {
+    struct {
+      KT key[CAP];
+      int32_t pos[CAP];
+    } list;
+    RankLds<kTopMaxK, int32_t> rank;
+  };
+  __shared__ Lds s;
+  __shared__ int s_hist[2 * 256 + 4];
+  __shared__ uint32_t s_red[4 * kPrWaves];
+  __shared__ int s_add[3];  // entries appended by the steps t, t + 1, t + 2 (mod 3)
+  __shared__ int s_n;
+  const int t = threadIdx.x, l = lane();
+  for (int64_t j = blockIdx.x; j < ncols; j += gridDim.x) {
+    int64_t b = colptr[j], e = colptr[j + 1];
+    if (b < 0 || e < b || e > nnz) {  // pointers outside the arrays: the column counts as empty
+      if (t == 0) flag_error(status, 5);
+      b = e = 0;
+    }
+    if (t < 3) s_add[t] = 0;
+    __syncthreads();  // also: the previous column's LDS is free
+    VT lo = thr;
+    int n = 0;        // list length (uniform)
+    bool left = false;
+    int step = 0;
+    VT nv[kSelUnroll];
+    top_load(vals, b, e, t, nv);
+    for (int64_t c0 = b; c0 < e; c0 += kTopStep, step = step == 2 ? 0 : step + 1) {
+      // the next step's values are loaded before this one's are worked on
+      VT v[kSelUnroll];
+#pragma unroll
+      for (int q = 0; q < kSelUnroll; q++) v[q] = nv[q];
+      if (c0 + kTopStep < e) top_load(vals, c0 + kTopStep, e, t, nv);
+      // the counter of the next step was last read before the previous barrier
+      if (t == 0) s_add[step == 2 ? 0 : step + 1] = 0;
+      uint64_t any = 0;
+#pragma unroll
+      for (int q = 0; q < kSelUnroll; q++) any |= __ballot(v[q] >= lo);
+      if (any) {  // uniform
+#pragma unroll
+        for (int q = 0; q < kSelUnroll; q++) {
+          const bool in = v[q] >= lo;
+          const uint64_t m = __ballot(in);
+          if (m == 0) continue;
+          int at = 0;
+          if (l == 0) at = atomicAdd(&s_add[step], __popcll(m));
+          at = n + readlane(at, 0) + mbcnt(m);
+          if (in) {  // at < n + kTopStep <= CAP
+            s.list.key[at] = (KT)order_key(v[q]);
+            s.list.pos[at] = (int32_t)(c0 - b) + q * kPrThreads + t;
+          }
+        }
+      }
+      __syncthreads();
+      n += s_add[step];
+      if (n > kLimit) {  // uniform: raise the bound (n > kLimit >= k)
+        KT key[E];
+        int32_t pos[E];
+        uint32_t have = 0;
+#pragma unroll
+        for (int i = 0; i < E; i++) {
+          const int x = t + i * kPrThreads;
+          key[i] = 0;
+          pos[i] = 0;
+          if (x < n) {
+            key[i] = s.list.key[x];
+            pos[i] = s.list.pos[x];
+            have |= 1u << i;
+          }
+        }
+        int above, equal;
+        // (the lower edge of the k-th largest key's bucket will do, unless
+        // the bucket is crowded; no value is below -infinity)
+        KT kth = block_kth<E>(key, have, k, (k + kLimit) / 2, s_hist, above, equal);
+        const KT least = (KT)order_key(VT(-INFINITY));
+        kth = kth < least ? least : kth;
+        if (t == 0) s_n = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < E; i++) {
+          const bool in = ((have >> i) & 1u) && key[i] >= kth;
+          const uint64_t m = __ballot(in);
+          if (m == 0) continue;
+          int at = 0;
+          if (l == 0) at = atomicAdd(&s_n, __popcll(m));
+          at = readlane(at, 0) + mbcnt(m);
+          if (in) {
+            s.list.key[at] = key[i];
+            s.list.pos[at] = pos[i];
+          }
+        }
+        n = above + equal;
+        lo = key_value(kth);
+        left = n > kLimit;
+        __syncthreads();
+        if (left) break;  // uniform
+      }
+    }
+    int kept = n;
+    if (!left && n > 0) {
+      // the list holds every candidate, or at least the k largest
+      KT key[E];
+      int32_t pos[E];
+      uint32_t have = 0;
+#pragma unroll
+      for (int i = 0; i < E; i++) {
+        const int x = t + i * kPrThreads;
+        key[i] = 0;
+        pos[i] = 0;
+        if (x < n) {
+          key[i] = s.list.key[x];
+          pos[i] = s.list.pos[x];
+          have |= 1u << i;
+        }
+      }
+      if (n > k) {
+        int above, equal;
+        const KT kth = block_kth<E>(key, have, k, k, s_hist, above, equal);
+        uint32_t keep = 0, tie = 0;
+#pragma unroll
+        for (int i = 0; i < E; i++) {
+          if (!((have >> i) & 1u)) continue;
+          if (key[i] >= kth) {
+            // exactly k at or above the edge, or kth is the k-th largest key
+            if (above + equal == k || key[i] > kth) keep |= 1u << i;
+            else tie |= 1u << i;
+          }
+        }
+        if (above + equal > k) {  // uniform: among equal values the smaller rows
+          uint32_t rk[E];
+#pragma unroll
+          for (int i = 0; i < E; i++) rk[i] = (tie >> i) & 1u ? row_key(rowidx[b + pos[i]]) : 0u;
+          int ra, re;
+          const uint32_t rth = block_kth<E>(rk, tie, k - above, k - above, s_hist, ra, re);
+#pragma unroll
+          for (int i = 0; i < E; i++)
+            if (((tie >> i) & 1u) && rk[i] < rth) tie &= ~(1u << i);
+          if (above + ra + re != k) {  // a row twice: the column is cut to k entries below
+            if (t == 0) flag_error(status, kPrDupRows);
+          }
+        }
+        have = keep | tie;
+        kept = k;
+      }
+      // the kept positions, one list again, in input order
+      if (t == 0) s_n = 0;
+      __syncthreads();  // also: the list is in registers
+#pragma unroll
+      for (int i = 0; i < E; i++) {
+        const bool in = (have >> i) & 1u;
+        const uint64_t m = __ballot(in);
+        if (m == 0) continue;
+        int at = 0;
+        if (l == 0) at = atomicAdd(&s_n, __popcll(m));
+        at = readlane(at, 0) + mbcnt(m);
+        if (in) s.list.pos[at] = pos[i];
+      }
+      __syncthreads();
+      int32_t row[KE];
+      int rank[KE];
+#pragma unroll
+      for (int i = 0; i < KE; i++) row[i] = t + i * kPrThreads < kept ? s.list.pos[t + i * kPrThreads] : 0;
+      __syncthreads();
+      rank_rows<kPrThreads, KE, false>(row, kept, t, s.rank, s_red, rank);
+      int32_t *dst = stage + j * (int64_t)k;
+#pragma unroll
+      for (int i = 0; i < KE; i++)
+        if (t + i * kPrThreads < kept) dst[rank[i]] = row[i];
+    }
+    if (t == 0) {
+      cnt[j] = left ? 0 : kept;
+      cutv[j] = left ? kTopLeft : kTopDone;
+    }
+    __syncthreads();  // s_add is reset for the next column
+  }
+}
+
+// The staged positions of the columns that k_prune_top settled, moved to the
+// columns' places in the output (one wave per column) ...
+__global__ __launch_bounds__(kPrThreads) void k_prune_place(const int64_t *__restrict__ out_colptr, int64_t ncols,
+                                                            int64_t k, const uint64_t *__restrict__ cutv,
+                                                            const int32_t *__restrict__ stage,
+                                                            int32_t *__restrict__ out_rowidx) {
+  for (int64_t j = (int64_t)blockIdx.x * kPrWaves + threadIdx.x / kWave; j < ncols; j += (int64_t)gridDim.x * kPrWaves) {
+    if (cutv[j] != kTopDone) continue;
+    const int64_t o = out_colptr[j], n = out_colptr[j + 1] - o;
+    for (int64_t i = lane(); i < n; i += kWave) out_rowidx[o + i] = stage[j * k + i];
+  }
+}
+
+// ... and replaced by the entries they name (the stage, which shares its
+// memory with out_vals, is no longer needed).
+template <typename VT>
+__global__ __launch_bounds__(kPrThreads) void k_prune_take(const int64_t *__restrict__ colptr,
+                                                           const int32_t *__restrict__ rowidx,
+                                                           const VT *__restrict__ vals, int64_t ncols,
+                                                           const uint64_t *__restrict__ cutv,
+                                                           const int64_t *__restrict__ out_colptr,
+                                                           int32_t *__restrict__ out_rowidx,
+                                                           VT *__restrict__ out_vals) {
+  for (int64_t j = (int64_t)blockIdx.x * kPrWaves + threadIdx.x / kWave; j < ncols; j += (int64_t)gridDim.x * kPrWaves) {
+    if (cutv[j] != kTopDone) continue;
+    const int64_t b = colptr[j], o = out_colptr[j], n = out_colptr[j + 1] - o;
+    for (int64_t i = lane(); i < n; i += kWave) {
+      const int64_t p = b + out_rowidx[o + i];
+      out_rowidx[o + i] = rowidx[p];
+      out_vals[o + i] = vals[p];
+    }
+  }
+}
+
+// The smallest value of type VT that a candidate can have.
+inline double threshold_of(double thr, double) { return thr; }
+inline float threshold_of(double thr, float) {
+  const float f = (float)thr;
+  return (double)f < thr ? std::nextafterf(f, INFINITY) : f;
+}
+
 template <typename VT>
 int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr, int32_t *out_rowidx,
                 void *out_values, const WsLayout &L, char *ws, hipStream_t st) {
@@ -513,18 +873,46 @@ int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr,
   uint64_t *cutv = (uint64_t *)(ws + L.pr_cutv);
   uint32_t *cutr = (uint32_t *)(ws + L.pr_cutr);
   const unsigned grid = (unsigned)(n < kPrMaxGrid ? n : kPrMaxGrid);
+  // The one-reading kernel stages k positions per column in out_values, which
+  // holds that many where k * n is within the output's bound, that is, where
+  // columns hold k entries or more on average; otherwise most columns keep
+  // everything and the two kernels below read them as often.
+  const bool top = n > 0 && k >= 1 && k <= kTopMaxK && k <= C->nnz / n;
+  int32_t *stage = (int32_t *)out_values;
+  if (top) {
+    ProfScope prof("prune_top", st);
+    const VT t = threshold_of(thr, VT(0));
+    if (k <= 512)
+      hipLaunchKernelGGL((k_prune_top<2560, VT>), dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
+                         (const VT *)C->values, n, t, C->nnz, (int)k, cnt, cutv, stage, &hdr->status);
+    else
+      hipLaunchKernelGGL((k_prune_top<3072, VT>), dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
+                         (const VT *)C->values, n, t, C->nnz, (int)k, cnt, cutv, stage, &hdr->status);
+    LAUNCHCHK();
+  }
   if (n > 0) {
     ProfScope prof("prune_select", st);
-    hipLaunchKernelGGL(k_prune_select<VT>, dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
-                       (const VT *)C->values, n, thr, C->nnz, k, cnt, cutv, cutr, &hdr->status);
+    hipLaunchKernelGGL(k_prune_select<VT>, dim3(top ? std::min(grid, 4096u) : grid), dim3(kPrThreads), 0, st, C->colptr,
+                       C->rowidx, (const VT *)C->values, n, thr, C->nnz, k, cnt, cutv, cutr, top ? 1 : 0, &hdr->status);
     LAUNCHCHK();
   }
   rc = launch_colptr_scan(cnt, n, out_colptr, (int64_t *)(ws + L.scan), st);
   if (rc || n == 0) return rc;
+  if (top) {
+    ProfScope prof("prune_take", st);
+    const unsigned gw = std::min(grid_of(n, kPrWaves), 8u * (unsigned)device_cus());
+    hipLaunchKernelGGL(k_prune_place, dim3(gw), dim3(kPrThreads), 0, st, (const int64_t *)out_colptr, n, k,
+                       (const uint64_t *)cutv, (const int32_t *)stage, out_rowidx);
+    LAUNCHCHK();
+    hipLaunchKernelGGL(k_prune_take<VT>, dim3(gw), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
+                       (const VT *)C->values, n, (const uint64_t *)cutv, (const int64_t *)out_colptr, out_rowidx,
+                       (VT *)out_values);
+    LAUNCHCHK();
+  }
   ProfScope prof("prune_fill", st);
-  hipLaunchKernelGGL(k_prune_fill<VT>, dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
-                     (const VT *)C->values, n, C->nnz, thr, (const uint64_t *)cutv, (const uint32_t *)cutr,
-                     (const int64_t *)out_colptr, out_rowidx, (VT *)out_values, &hdr->status);
+  hipLaunchKernelGGL(k_prune_fill<VT>, dim3(top ? std::min(grid, 4096u) : grid), dim3(kPrThreads), 0, st, C->colptr,
+                     C->rowidx, (const VT *)C->values, n, C->nnz, thr, (const uint64_t *)cutv, (const uint32_t *)cutr,
+                     (const int64_t *)out_colptr, out_rowidx, (VT *)out_values, top ? 1 : 0, &hdr->status);
   LAUNCHCHK();
   return SPGEMM_OK;
 }

@@ -1,0 +1,126 @@
+"""GPU parity of the pruning that reads each column once: limits of k and of
+the list, ties by the thousand (left to the digit kernels), special values,
+and columns shorter than k among longer ones.  Bit-exact against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.gpu_util import host_sorted
+
+pytestmark = pytest.mark.gpu
+
+S = None
+
+
+def setup_module(module):
+    global S
+    import paper_2010_08526_amd as lib
+    S = lib
+    assert torch.cuda.is_available()
+
+
+def _values(kind, n, rng):
+    if kind == "normal":
+        return rng.standard_normal(n)
+    if kind == "rising":  # every step raises the bound
+        return np.arange(n) / 7.0 - 5.0
+    if kind == "falling":
+        return 5.0 - np.arange(n) / 7.0
+    if kind == "levels":
+        return rng.integers(-3, 4, n) / 4.0
+    if kind == "few_large":
+        v = rng.random(n)
+        v[-max(1, n // 50):] += 2.0
+        return v
+    if kind == "equal":
+        return np.full(n, 0.5)
+    v = rng.standard_normal(n)  # special
+    s = rng.random(n)
+    v[s < 0.1] = np.nan
+    v[(s >= 0.1) & (s < 0.15)] = np.inf
+    v[(s >= 0.15) & (s < 0.2)] = -np.inf
+    v[(s >= 0.2) & (s < 0.3)] = -0.0
+    v[(s >= 0.3) & (s < 0.4)] = 0.0
+    return v
+
+
+@pytest.mark.parametrize("kind", ["normal", "rising", "falling", "levels", "few_large", "equal", "special"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_prune_once(kind, dtype):
+    print(f"case: prune once {kind} {dtype}", flush=True)
+    rng = np.random.default_rng(len(kind))
+    lens = [0, 1, 2, 255, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049, 2560, 2561, 4097, 9000, 30011]
+    m = 40000
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, n, replace=False) for n in lens]).astype(np.int32)
+    v = torch.from_numpy(np.concatenate([_values(kind, n, rng) for n in lens])).to(dtype)
+    M = synth.CSC(m, len(lens), torch.from_numpy(cp), torch.from_numpy(ri), v)
+    D = M.to("cuda")
+    assert 1025 <= M.nnz // len(lens)  # (so every k below takes the kernel, up to its limit)
+    for k in (1, 2, 100, 512, 513, 1024, 1025):
+        for thr in (-np.inf, 0.0, 0.1, 1e300, np.nan):
+            G = S.prune_topk(D, thr, k)
+            P = oracle.prune_topk(M, thr, k)
+            cp_, ri_, v_ = host_sorted(G)
+            what = f"{kind} k={k} thr={thr}"
+            assert np.array_equal(G.colptr.cpu().numpy(), P.colptr), what
+            assert np.array_equal(G.rowidx.cpu().numpy(), P.rowidx), what  # input order
+            assert np.array_equal(G.values.double().cpu().numpy(), P.values.astype(np.float64)), what
+
+
+def test_prune_once_reports_a_repeated_row():
+    """Two equal entries of one row at the cut."""
+    print("case: prune once repeated row", flush=True)
+    n = 3000
+    r = torch.randperm(5000)[:n].to(torch.int32)
+    v = torch.rand(n)
+    order = torch.argsort(v, descending=True)
+    v[order[9]] = v[order[10]]
+    r[order[9]] = r[order[10]]
+    C = S.CSC(5000, 1, torch.tensor([0, n], device="cuda"), r.cuda(), v.cuda())
+    with pytest.raises(S.SpgemmError):
+        S.prune_topk(C, 0.0, 10)
+
+
+def test_prune_once_in_a_graph():
+    print("case: prune once graph", flush=True)
+    rng = np.random.default_rng(3)
+    lens = rng.integers(0, 6000, 300)
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(7000, n, replace=False) for n in lens]).astype(np.int32)
+    M = synth.CSC(7000, 300, torch.from_numpy(cp), torch.from_numpy(ri), torch.from_numpy(rng.random(ri.size)).float())
+    D = M.to("cuda")
+    k, cap = 50, 50 * 300
+    out = (torch.empty(301, dtype=torch.int64, device="cuda"), torch.empty(cap, dtype=torch.int32, device="cuda"),
+           torch.empty(cap, device="cuda"))
+    ws = S.alloc_workspace(S.workspace_size(S.OP_PRUNE, D))
+    import ctypes
+
+    def call():
+        S._check(S._lib.spgemm_prune_topk(ctypes.byref(S.desc(D)), 0.2, k, *[S._ptr(x) for x in out], cap, S._ptr(ws),
+                                          ws.numel(), S._stream(None)), "prune")
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        call()
+    torch.cuda.current_stream().wait_stream(s)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(4):
+        D.values.copy_(torch.rand_like(D.values))  # eager work between replays
+        for x in out:
+            x.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        S.check_ws(ws)
+        P = oracle.prune_topk(synth.CSC(7000, 300, M.colptr, M.rowidx, D.values.cpu()), 0.2, k)
+        n = int(out[0][-1])
+        assert np.array_equal(out[0].cpu().numpy(), P.colptr)
+        assert np.array_equal(out[1][:n].cpu().numpy(), P.rowidx)
+        assert np.array_equal(out[2][:n].double().cpu().numpy(), P.values.astype(np.float64))
