@@ -510,9 +510,11 @@ constexpr int kBinUnroll = 8;  // entries of B a lane has in flight
 // Appends column jj of each thread with bin >= 0 to the bins' lists: one LDS
 // counter per list, one global atomic per list and block.  Lists kNumBins ...:
 // the row-sorted product's expand-sort-compress columns, classes 0 and 2 in
-// two arrays, class 1 from the end of class 0's.
+// two arrays, class 1 from the end of class 0's; then the half tables of bins
+// 2 and 3, from the end of their bins' arrays.
+constexpr int kHalfList = kNumBins + 3;
 __device__ __forceinline__ void bin_append(int bin, int64_t jj, int64_t ncol, int32_t *bins, WsHeader *hdr) {
-  constexpr int NL = kNumBins + 3;
+  constexpr int NL = kHalfList + 2;
   __shared__ int s_cnt[NL];
   __shared__ int s_base[NL];
   if (threadIdx.x < NL) s_cnt[threadIdx.x] = 0;
@@ -522,12 +524,14 @@ __device__ __forceinline__ void bin_append(int bin, int64_t jj, int64_t ncol, in
   if (threadIdx.x < NL) {
     const int b = threadIdx.x;
     const int c = s_cnt[b];
-    s_base[b] = c ? atomicAdd(b < kNumBins ? &hdr->bin_count[b] : &hdr->esc_count[b - kNumBins], c) : 0;
+    int32_t *n = b < kNumBins ? &hdr->bin_count[b] : (b < kHalfList ? &hdr->esc_count[b - kNumBins] : &hdr->half_count[b - kHalfList]);
+    s_base[b] = c ? atomicAdd(n, c) : 0;
   }
   __syncthreads();
   if (bin >= 0) {
     const int64_t p = s_base[bin] + pos;
-    const int64_t at = bin == kNumBins + 1   ? (int64_t)(kNumBins + 1) * ncol - 1 - p
+    const int64_t at = bin >= kHalfList      ? (int64_t)(bin - kHalfList + 3) * ncol - 1 - p
+                       : bin == kNumBins + 1 ? (int64_t)(kNumBins + 1) * ncol - 1 - p
                        : bin == kNumBins + 2 ? (int64_t)(kNumBins + 1) * ncol + p
                                              : (int64_t)bin * ncol + p;
     bins[at] = (int32_t)jj;
@@ -615,6 +619,9 @@ __global__ __launch_bounds__(256) void k_bin_len(const int64_t *c_colptr, int64_
     const int64_t len = c_colptr[jj + 1] - c_colptr[jj];
     if (len > max_len) flag_error(&hdr->status, 4);  // above what the caller promised: its bin may not run
     if (len > 0) bin = max(bin_of(len, caps), min_bin);
+    // columns that fill at most half of what bins 2 and 3 hold take tables of
+    // half the slots (see k_num_wave)
+    if ((bin == 2 || bin == 3) && 2 * len <= kNumTableCap[bin]) bin += kHalfList - 2;
     if (esc_flops && len > 0) {
       const int e = esc_class(esc_flops[jj], len, esc_cf);
       if (e >= 0) bin = kNumBins + e;
@@ -913,8 +920,14 @@ __device__ __forceinline__ int64_t compact_run(int32_t *keys, double *vals, int 
   return o;
 }
 
+// The waves in flight bound the light kernels (a column is a chain of
+// dependent loads; LDS is busy a fifth of the time), and LDS bounds the waves:
+// tables of 1024 slots allow 12 per CU, of 512 slots 20; of 4096 slots shared
+// by 4 waves 8, of 2048 slots 20.  Hence the half tables of bins 2 and 3:
+// 4.95e8 terms in columns of 129-512 rows 6.0 -> 4.8 ms, 4.4e8 terms in columns
+// of 513-1024 rows 5.9 -> 3.9 ms.
 template <int TBL, class VT, class Src>
-__global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, const int32_t *count_p,
+__global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, int dir, const int32_t *count_p,
                                                   const int64_t *c_colptr, int32_t *out_ri, VT *out_v,
                                                   int32_t *status) {
   static_assert(TBL % 4 == 0, "tables cleared 16 bytes at a time");
@@ -939,14 +952,14 @@ __global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, 
   int32_t jn = 0;
   int64_t cb = 0, ce = 0;
   if (idx < count) {
-    jn = __builtin_amdgcn_readfirstlane(ld_global(list + idx + z));
+    jn = __builtin_amdgcn_readfirstlane(ld_global(list + dir * idx + z));
     src.pre_cols(jn, pre);
     cb = ld_global(c_colptr + jn + z);
     ce = ld_global(c_colptr + jn + 1 + z);
     src.pre_b(pre, 0, 1);
     src.pre_a(pre);
   }
-  int32_t jn2 = idx + stride < count ? ld_global(list + idx + stride + z) : 0;
+  int32_t jn2 = idx + stride < count ? ld_global(list + dir * (idx + stride) + z) : 0;
   for (; idx < count; idx += stride) {
     const int32_t jj = jn;
     const int64_t base = first_lane64(cb), cap = first_lane64(ce) - base;
@@ -957,7 +970,7 @@ __global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, 
       src.pre_cols(jn, pre);
       cb = ld_global(c_colptr + jn + z);
       ce = ld_global(c_colptr + jn + 1 + z);
-      jn2 = idx + 2 * stride < count ? ld_global(list + idx + 2 * stride + z) : 0;
+      jn2 = idx + 2 * stride < count ? ld_global(list + dir * (idx + 2 * stride) + z) : 0;
     }
     wave_sync();
     src.visit_pre(jj, cur, s_sc[w], status,
@@ -975,7 +988,7 @@ __global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, 
 }
 
 template <int TBL, int THREADS, class VT, class Src>
-__global__ __launch_bounds__(THREADS) void k_num_block(Src src, const int32_t *list, const int32_t *count_p,
+__global__ __launch_bounds__(THREADS) void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p,
                                                        const int64_t *c_colptr, int32_t *out_ri, VT *out_v,
                                                        int32_t *status) {
   constexpr int NW = THREADS / kWave;
@@ -1002,14 +1015,14 @@ __global__ __launch_bounds__(THREADS) void k_num_block(Src src, const int32_t *l
   int32_t jn = 0;
   int64_t cb = 0, ce = 0;
   if (item < count) {
-    jn = __builtin_amdgcn_readfirstlane(ld_global(list + item + z));
+    jn = __builtin_amdgcn_readfirstlane(ld_global(list + dir * item + z));
     src.pre_cols(jn, pre);
     cb = ld_global(c_colptr + jn + z);
     ce = ld_global(c_colptr + jn + 1 + z);
     src.pre_b(pre, w, NW);
     src.pre_a(pre);
   }
-  int32_t jn2 = item + (int64_t)gridDim.x < count ? ld_global(list + item + (int64_t)gridDim.x + z) : 0;
+  int32_t jn2 = item + (int64_t)gridDim.x < count ? ld_global(list + dir * (item + (int64_t)gridDim.x) + z) : 0;
   for (; item < count; item += gridDim.x) {
     const int32_t jj = jn;
     const int64_t base = first_lane64(cb), cap = first_lane64(ce) - base;
@@ -1020,7 +1033,7 @@ __global__ __launch_bounds__(THREADS) void k_num_block(Src src, const int32_t *l
       src.pre_cols(jn, pre);
       cb = ld_global(c_colptr + jn + z);
       ce = ld_global(c_colptr + jn + 1 + z);
-      jn2 = item + 2 * (int64_t)gridDim.x < count ? ld_global(list + item + 2 * (int64_t)gridDim.x + z) : 0;
+      jn2 = item + 2 * (int64_t)gridDim.x < count ? ld_global(list + dir * (item + 2 * (int64_t)gridDim.x) + z) : 0;
     }
     __syncthreads();
     src.visit_pre_block(jj, cur, w, NW, s_sc[w], status, [&](int32_t row, double v) {
@@ -1457,8 +1470,19 @@ __global__ void k_left_forget(WsHeader *h) {
   if (threadIdx.x == 0) h->left_tag = 0;
 }
 
-__global__ void k_left_set(WsHeader *h, const int32_t *heavy_count) {
-  if (threadIdx.x == 0 && *heavy_count != 0) h->left_tag = h->status == 0 ? (h->left_new | 1ull) : 0ull;
+// Also clears the output cursors of the heavy columns (cur, n16 times 16
+// bytes) and the first chunk's counters (k_hv_reset).
+__global__ void k_left_set(WsHeader *h, const int32_t *heavy_count, uint4 *cur, int64_t n16) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (*heavy_count != 0) h->left_tag = h->status == 0 ? (h->left_new | 1ull) : 0ull;
+    h->items = 0;
+    h->item_cursor = 0;
+    h->nwide = 0;
+    h->wide_cursor = 0;
+    h->mb_cursor = 0;
+  }
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
+    cur[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // One entry of the slabbed copy of the left operand: row and value side by
@@ -3217,29 +3241,34 @@ static int symbolic_pass(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
 // then heavy columns must take the slab path (heavy_global = false), and a
 // heavy column that would need the global path is reported as an error.
 template <class VT, class Src>
-static int accumulate_pass(const Src &src, const int *cnt, const WsHeader &h, const WsLayout &L, char *ws,
+static int accumulate_pass(const Src &src, const int *cnt, const int *half_cnt, const WsHeader &h, const WsLayout &L, char *ws,
                            const int64_t *c_colptr, int32_t *out_ri, VT *out_v, hipStream_t st,
                            bool heavy_global = true) {
   WsHeader *hdr = (WsHeader *)ws;
   int32_t *bins = (int32_t *)(ws + L.bins);
   int32_t *status = &hdr->status;
   const int64_t ncol = L.ncol;
-  static const char *kNumNames[kNumBins - 1] = {"num_wave64", "num_wave256", "num_wave1024", "num_block4096",
-                                                "num_block10240"};
-  static const char *kMrgNames[kNumBins - 1] = {"mrg_wave64", "mrg_wave256", "mrg_wave1024", "mrg_block4096",
-                                                "mrg_block10240"};
+  static const char *kNumNames[kNumBins + 1] = {"num_wave64", "num_wave256", "num_wave1024", "num_block4096",
+                                                "num_block10240", "num_wave512", "num_block2048"};
+  static const char *kMrgNames[kNumBins + 1] = {"mrg_wave64", "mrg_wave256", "mrg_wave1024", "mrg_block4096",
+                                                "mrg_block10240", "mrg_wave512", "mrg_block2048"};
   const char *const *names = Src::kMerge ? kMrgNames : kNumNames;
-  for (int b = 0; b < kNumBins - 1; b++) {
-    if (cnt[b] == 0) continue;
+  for (int b = 0; b < kNumBins + 1; b++) {
+    const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
+    const int c = half < 0 ? cnt[b] : half_cnt[half];
+    if (c == 0) continue;
     ProfScope prof(names[b], st);
-    const int32_t *list = bins + (int64_t)b * ncol;
-    const int32_t *cp = &hdr->bin_count[b];
+    const int32_t *list = half < 0 ? bins + (int64_t)b * ncol : bins + (int64_t)(half + 3) * ncol - 1;
+    const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
+    const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_num_wave<64, VT, Src>), dim3(bin_grid(cnt[b], true, g_bpc[1][0])), dim3(256), 0, st, src, list, cp, c_colptr, out_ri, out_v, status); break;
-      case 1: hipLaunchKernelGGL((k_num_wave<256, VT, Src>), dim3(bin_grid(cnt[b], true, g_bpc[1][1])), dim3(256), 0, st, src, list, cp, c_colptr, out_ri, out_v, status); break;
-      case 2: hipLaunchKernelGGL((k_num_wave<1024, VT, Src>), dim3(bin_grid(cnt[b], true, g_bpc[1][2])), dim3(256), 0, st, src, list, cp, c_colptr, out_ri, out_v, status); break;
-      case 3: hipLaunchKernelGGL((k_num_block<4096, 256, VT, Src>), dim3(bin_grid(cnt[b], false, g_bpc[1][3])), dim3(256), 0, st, src, list, cp, c_colptr, out_ri, out_v, status); break;
-      default: hipLaunchKernelGGL((k_num_block<10240, 1024, VT, Src>), dim3(bin_grid(cnt[b], false, g_bpc[1][4])), dim3(1024), 0, st, src, list, cp, c_colptr, out_ri, out_v, status); break;
+      case 0: hipLaunchKernelGGL((k_num_wave<64, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][0])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 1: hipLaunchKernelGGL((k_num_wave<256, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][1])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 2: hipLaunchKernelGGL((k_num_wave<1024, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][2])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 3: hipLaunchKernelGGL((k_num_block<4096, 256, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][3])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 4: hipLaunchKernelGGL((k_num_block<10240, 1024, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][4])), dim3(1024), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 5: hipLaunchKernelGGL((k_num_wave<512, VT, Src>), dim3(bin_grid(c, true, 2 * g_bpc[1][2])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      default: hipLaunchKernelGGL((k_num_block<2048, 256, VT, Src>), dim3(bin_grid(c, false, 2 * g_bpc[1][3])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
     }
     LAUNCHCHK();
   }
@@ -3312,6 +3341,9 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   // about 4.6 us of the stream's time)
   for (int b = g_min_bin + 1; b < kNumBins; b++)
     if (cnt[b] < 0 && max_len <= g_caps[1].cap[b - 1]) cnt[b] = 0;
+  const int half_cnt[2] = {sync ? h.half_count[0] : cnt[2], sync ? h.half_count[1] : cnt[3]};
+  for (int b = 2; b <= 3; b++)
+    if (cnt[b] < 0 && 2 * max_len <= kNumTableCap[b]) cnt[b] = 0;  // its half tables hold every column
   ProductSrc<VT, SR> src;
   src.a = product_args<VT>(A, B, klo, khi);
   src.c0 = c0;
@@ -3339,7 +3371,7 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
     }
   }
   const bool slabs = L.P > 0;
-  rc = accumulate_pass<VT>(src, cnt, h, L, ws, c_colptr, c_rowidx, (VT *)c_values, st, !slabs);
+  rc = accumulate_pass<VT>(src, cnt, half_cnt, h, L, ws, c_colptr, c_rowidx, (VT *)c_values, st, !slabs);
   if (rc) return rc;
   const int heavy = cnt[kNumBins - 1];
   if (slabs && heavy != 0) {
@@ -3365,9 +3397,11 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
                          (const int32_t *)soff, A->colptr, klo, khi - klo, (int)L.P, (uint64_t *)(ws + L.slab_pack), hc,
                          (const WsHeader *)hdr);
       LAUNCHCHK();
-      hipLaunchKernelGGL(k_left_set, dim3(1), dim3(64), 0, st, hdr, hc);
-      LAUNCHCHK();
     }
+    int32_t *hv_cur = (int32_t *)(ws + L.hv_cur);
+    hipLaunchKernelGGL(k_left_set, dim3(std::min(grid_of(ncol, 1024), 1024u)), dim3(256), 0, st, hdr, hc,
+                       (uint4 *)hv_cur, (ncol * 4 + 15) / 16);
+    LAUNCHCHK();
     HvArgs<VT> ha;
     ha.Acp = A->colptr;
     ha.ent = s_ent;
@@ -3381,19 +3415,17 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
     ha.kdim = (int32_t)A->ncols;
     ha.P = (int32_t)L.P;
     const int32_t *list = bins + (int64_t)(kNumBins - 1) * ncol;
-    int32_t *hv_cur = (int32_t *)(ws + L.hv_cur);
     uint32_t *slots = (uint32_t *)(ws + L.hv_items);
     int32_t *wlist = (int32_t *)(ws + L.hv_wide);
     const int64_t icap = hv_item_cap(ncol, L.P);
     const int64_t H = std::max<int64_t>(1, icap / L.P);
     const int64_t hmax = heavy > 0 ? heavy : ncol;  // heavy < 0: the count is only on the device
-    hipLaunchKernelGGL(k_fill_zero, dim3(grid_of((ncol * 4 + 15) / 16, 256)), dim3(256), 0, st, (uint4 *)hv_cur,
-                       (ncol * 4 + 15) / 16);
-    LAUNCHCHK();
     for (int64_t h0 = 0; h0 < hmax; h0 += H) {
       const int64_t h1 = std::min(hmax, h0 + H);
-      hipLaunchKernelGGL(k_hv_reset, dim3(1), dim3(64), 0, st, hdr);
-      LAUNCHCHK();
+      if (h0 > 0) {
+        hipLaunchKernelGGL(k_hv_reset, dim3(1), dim3(64), 0, st, hdr);
+        LAUNCHCHK();
+      }
       {
         ProfScope prof("heavy_plan", st);
         const unsigned pg = (unsigned)std::min<int64_t>(h1 - h0, 16 * (int64_t)device_cus());
@@ -3449,7 +3481,7 @@ static int merge_typed(const spgemm_csc *parts, int32_t n_parts, const int64_t *
   src.m = L.m;
   const int heavy = cnt[kNumBins - 1];
   const bool buckets = L.P > 0 && heavy > 0;
-  rc = accumulate_pass<VT>(src, cnt, h, L, ws, c_colptr, c_rowidx, (VT *)c_values, st, !buckets);
+  rc = accumulate_pass<VT>(src, cnt, h.half_count, h, L, ws, c_colptr, c_rowidx, (VT *)c_values, st, !buckets);
   if (rc || !buckets) return rc;
   // heavy columns through the slab buckets
   const int32_t *list = bins + (int64_t)(kNumBins - 1) * L.ncol;

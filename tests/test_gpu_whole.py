@@ -62,7 +62,7 @@ def test_whole_empty(shape, layers):
         assert C.colptr.tolist() == [0] * (n + 1) and C.nnz == 0 and C.values.dtype == torch.float32
 
 
-@pytest.mark.parametrize("limit", [32, 128, 512, 2048, 5120])
+@pytest.mark.parametrize("limit", [32, 128, 256, 257, 512, 1024, 1025, 2048, 5120])
 @pytest.mark.parametrize("sorted_output", [False, True])
 def test_bound_on_column_entries(limit, sorted_output):
     """Columns up to the bound are formed; one entry more is reported."""
