@@ -13,8 +13,9 @@
 // (row -> value) and forms one dot product per requested entry (k,j) of M
 // against X(:,k); the work equals the forward flops plus nnz(Y).
 //
-// The transposes are sort-free: a row histogram, a scan, and a scatter
-// with atomic cursors (entry order inside each output column is arbitrary).
+// The transposes are sort-free: a row histogram that also ranks the entries of
+// a row, a scan, and a scatter (entry order inside each output column is
+// arbitrary).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -34,37 +35,102 @@ __global__ void k_tr_zero(unsigned long long *p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
-__global__ void k_tr_count(const int32_t *ri, int64_t nnz, int64_t m, unsigned long long *cnt, int32_t *status) {
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t r = ri[p];
-    if ((uint32_t)r < (uint32_t)m)
-      atomicAdd(&cnt[r], 1ull);
-    else
-      flag_error(status, 3);
+// Row counts, and each entry's place among its row's entries (as counted).
+__global__ __launch_bounds__(256) void k_tr_count(const int32_t *ri, int64_t nnz, int64_t m, unsigned long long *cnt,
+                                                  int32_t *rank, int32_t *status) {
+  constexpr int U = 4;  // entries a thread has in flight
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t p0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p0 < nnz; p0 += U * step) {
+    int32_t r_[U];
+    unsigned long long c_[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) r_[u] = p0 + u * step < nnz ? ri[p0 + u * step] : 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      c_[u] = 0;
+      if (p0 + u * step < nnz) {
+        const int32_t r = opaque(r_[u]);
+        if ((uint32_t)r < (uint32_t)m)
+          c_[u] = atomicAdd(&cnt[r], 1ull);
+        else
+          flag_error(status, 3);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (p0 + u * step < nnz) rank[p0 + u * step] = (int32_t)c_[u];
   }
 }
 
-__global__ void k_tr_cursor(const int64_t *t_colptr, int64_t m, unsigned long long *cursor) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-    cursor[i] = (unsigned long long)t_colptr[i];
-}
-
-// One wavefront per source column (grid-stride).
+// Entries in tiles of kTrTile consecutive ones, whatever the columns' lengths:
+// the tile's columns mark where they start in LDS, a prefix maximum gives
+// every entry its column, and an entry goes to its row's column pointer plus
+// its rank.  Random atomics (23e9 a second) and random writes bound a
+// transpose, so each entry pays for one of each: 1.0e7 entries, two per
+// column: 1.87 ms with a wave per column and a second atomic, 0.81 now.
+constexpr int kTrPer = 16;
+constexpr int kTrTile = 256 * kTrPer;
 template <class VT>
 __global__ __launch_bounds__(256) void k_tr_scatter(const int64_t *cp, const int32_t *ri, const VT *v, int64_t ncols,
-                                                    int64_t m, unsigned long long *cursor, int32_t *t_ri, VT *t_v,
-                                                    int64_t *perm) {
-  const int l = lane();
-  const int64_t nwaves = (int64_t)gridDim.x * 4;
-  for (int64_t j = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave; j < ncols; j += nwaves) {
-    for (int64_t p = cp[j] + l; p < cp[j + 1]; p += kWave) {
-      const int32_t r = ri[p];
-      if ((uint32_t)r >= (uint32_t)m) continue;  // counted as an error by k_tr_count
-      const unsigned long long pos = atomicAdd(&cursor[r], 1ull);
-      t_ri[pos] = (int32_t)j;
-      if (t_v) t_v[pos] = v[p];
-      if (perm) perm[pos] = p;
+                                                    int64_t m, int64_t nnz, const int64_t *t_colptr,
+                                                    const int32_t *rank, int32_t *t_ri, VT *t_v, int64_t *perm) {
+  __shared__ int s_own[kTrTile];
+  __shared__ int s_w[4];
+  const int t = threadIdx.x, l = lane(), w = t / kWave;
+  const int64_t first = max(cp[0], (int64_t)0), end = min(cp[ncols], nnz);
+  for (int64_t p0 = first + (int64_t)blockIdx.x * kTrTile; p0 < end; p0 += (int64_t)gridDim.x * kTrTile) {
+    const int64_t p1 = min(end, p0 + kTrTile);
+    // the last column that starts at or before p0 (64 probes a step)
+    int64_t lo = 0, hi = ncols;  // cp[lo] <= p0 < cp[hi]
+    while (hi - lo > 1) {
+      const int64_t d = (hi - lo + kWave - 1) / kWave;
+      const int64_t j = min(lo + (int64_t)l * d, hi);
+      const uint64_t le = __ballot(j < hi && cp[j] <= p0);  // lane 0 always
+      const int c = 63 - __clzll((long long)le);
+      const int64_t nlo = lo + (int64_t)c * d;
+      hi = min(hi, nlo + d);
+      lo = nlo;
     }
+#pragma unroll
+    for (int i = 0; i < kTrPer; i++) s_own[t + i * 256] = 0;
+    __syncthreads();
+    for (int64_t j0 = lo + 1;; j0 += 256) {
+      const int64_t j = j0 + t;
+      const int64_t c = j < ncols ? cp[j] : p1;
+      if (c > p0 && c < p1) atomicMax(&s_own[c - p0], (int)(j - lo));
+      if (!__syncthreads_or(t == 255 && c < p1)) break;
+    }
+    // prefix maximum, kTrPer consecutive entries per thread
+    int x[kTrPer], top = 0;
+#pragma unroll
+    for (int i = 0; i < kTrPer; i++) {
+      top = max(top, s_own[t * kTrPer + i]);
+      x[i] = top;
+    }
+    const int incl = wave_incl_max(top);
+    if (l == kWave - 1) s_w[w] = incl;
+    __syncthreads();
+    int before = wave_prev(incl);
+#pragma unroll
+    for (int z = 0; z < 4; z++)
+      if (z < w) before = max(before, s_w[z]);
+#pragma unroll
+    for (int i = 0; i < kTrPer; i++) s_own[t * kTrPer + i] = max(x[i], before);
+    __syncthreads();
+#pragma unroll 4
+    for (int i = 0; i < kTrPer; i++) {
+      const int64_t p = p0 + t + i * 256;
+      if (p < p1) {
+        const int32_t r = ri[p];
+        if ((uint32_t)r < (uint32_t)m) {  // (counted as an error otherwise)
+          const int64_t pos = t_colptr[r] + rank[p];
+          t_ri[pos] = (int32_t)(lo + s_own[t + i * 256]);
+          if (t_v) t_v[pos] = v[p];
+          if (perm) perm[pos] = p;
+        }
+      }
+    }
+    __syncthreads();  // the next tile clears s_own
   }
 }
 
@@ -704,22 +770,21 @@ static int transpose_typed(const spgemm_csc *X, int64_t *t_colptr, int32_t *t_ro
   ProfScope prof("transpose", st);
   const int64_t m = X->nrows;
   unsigned long long *cnt = (unsigned long long *)(ws + L.bins);
+  int32_t *rank = (int32_t *)(ws + L.slab_ri);
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid_of(std::max(m, X->nnz), 256), 8 * device_cus()));
   hipLaunchKernelGGL(k_tr_zero, dim3(g), dim3(256), 0, st, cnt, m);
   LAUNCHCHK();
   if (X->nnz > 0) {
-    hipLaunchKernelGGL(k_tr_count, dim3(g), dim3(256), 0, st, X->rowidx, X->nnz, m, cnt, &hdr->status);
+    hipLaunchKernelGGL(k_tr_count, dim3(g), dim3(256), 0, st, X->rowidx, X->nnz, m, cnt, rank, &hdr->status);
     LAUNCHCHK();
   }
   rc = launch_colptr_scan((const int64_t *)cnt, m, t_colptr, (int64_t *)(ws + L.scan), st);
   if (rc) return rc;
   if (X->nnz > 0) {
-    hipLaunchKernelGGL(k_tr_cursor, dim3(g), dim3(256), 0, st, t_colptr, m, cnt);
-    LAUNCHCHK();
-    const unsigned gs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid_of(X->ncols, 4), 16 * device_cus()));
+    const unsigned gs = (unsigned)std::min<int64_t>((X->nnz + kTrTile - 1) / kTrTile, 8 * device_cus());
     hipLaunchKernelGGL(k_tr_scatter<VT>, dim3(gs), dim3(256), 0, st, X->colptr, X->rowidx,
-                       t_values ? (const VT *)X->values : (const VT *)nullptr, X->ncols, m, cnt, t_rowidx, (VT *)t_values,
-                       perm);
+                       t_values ? (const VT *)X->values : (const VT *)nullptr, X->ncols, m, X->nnz,
+                       (const int64_t *)t_colptr, (const int32_t *)rank, t_rowidx, (VT *)t_values, perm);
     LAUNCHCHK();
   }
   return SPGEMM_OK;

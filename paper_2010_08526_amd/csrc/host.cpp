@@ -160,10 +160,13 @@ int ws_layout(int op, const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int6
       if (!A) return SPGEMM_E_INVAL;
       if (A->nrows < 0 || A->nrows > INT32_MAX) return SPGEMM_E_OVERFLOW;
       L->m = A->nrows;
-      L->bins = off;  // int64 row counts, then cursors
+      if (A->nnz < 0) return SPGEMM_E_INVAL;
+      L->bins = off;  // int64 row counts
       off = align_up(off + sizeof(int64_t) * (size_t)A->nrows);
       L->scan = off;
       off = align_up(off + sizeof(int64_t) * (size_t)(A->nrows / 8192 + 2));
+      L->slab_ri = off;  // int32 place of each entry among its row's
+      off = align_up(off + sizeof(int32_t) * (size_t)A->nnz);
       break;
     }
     case SPGEMM_OP_MASKED_XTY: {

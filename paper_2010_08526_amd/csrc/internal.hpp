@@ -130,7 +130,7 @@ struct WsLayout {
   size_t parts = 0;       // merge: part descriptors
   size_t slab_off = 0;    // numeric: int32 [kcols][P+1] slab offsets of the left operand
   size_t slab_ent = 0;    // numeric: [nnzA] slabbed entries of A (row and value side by side)
-  size_t slab_ri = 0;     // merge: int32 [mb_cap] bucketed rows
+  size_t slab_ri = 0;     // merge: int32 [mb_cap] bucketed rows; transpose: int32 [nnz] ranks
   size_t slab_v = 0;      // merge: 8-byte [mb_cap] bucketed values
   size_t slab_pack = 0;   // numeric: uint64 [P][kcols] slab segments, slab-major (start << kSegLenBits | len)
   size_t hv_cur = 0;      // numeric: int32 [ncol] output cursor per heavy column

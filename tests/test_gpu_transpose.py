@@ -1,0 +1,64 @@
+"""GPU parity of the transpose: columns against the tiles of 4096 entries it
+works on (empty runs longer than a tile's threads, columns longer than a tile,
+starts at tile edges), every output it can be asked for."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+S = None
+
+
+def setup_module(module):
+    global S
+    import paper_2010_08526_amd as lib
+    S = lib
+    assert torch.cuda.is_available()
+
+
+LENS = {
+    "one": [1], "empty": [0, 0, 0], "pairs": [2] * 9001, "edge": [4096, 4096, 1], "edge1": [4095, 2, 4095],
+    "long": [3, 20000, 0, 1], "gaps": [1] + [0] * 70000 + [5] + [0] * 300 + [4090] + [0] * 9000 + [7],
+    "ragged": None,
+}
+
+
+@pytest.mark.parametrize("case", sorted(LENS))
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_transpose_tiles(case, dtype):
+    print(f"case: transpose {case} {dtype}", flush=True)
+    rng = np.random.default_rng(len(case))
+    m = 30000
+    lens = np.array(LENS[case] if LENS[case] is not None else rng.integers(0, 300, 2000))
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, n, replace=False) for n in lens]).astype(np.int32)
+    v = torch.from_numpy(rng.standard_normal(ri.size)).to(dtype)
+    X = S.CSC(m, lens.size, torch.from_numpy(cp).cuda(), torch.from_numpy(ri).cuda(), v.cuda())
+    col = np.repeat(np.arange(lens.size), lens)
+    want = np.lexsort((col, ri))  # by row, then column
+    for values, perm in ((True, True), (True, False), (False, True), (False, False)):
+        ws = S.alloc_workspace(S.workspace_size(S.OP_TRANSPOSE, X))
+        T, pm = S.transpose(X, ws, values=values, perm=perm)
+        S.check_ws(ws)
+        tcp = T.colptr.cpu().numpy()
+        assert np.array_equal(tcp, np.concatenate([[0], np.cumsum(np.bincount(ri, minlength=m))]))
+        tri = T.rowidx.cpu().numpy()
+        order = np.lexsort((tri, np.repeat(np.arange(m), np.diff(tcp))))
+        assert np.array_equal(tri[order], col[want])
+        if values:
+            assert np.array_equal(T.values.cpu().numpy()[order], v.numpy()[want])
+        if perm:
+            assert np.array_equal(pm.cpu().numpy()[order], want)
+
+
+def test_transpose_reports_a_bad_row():
+    print("case: transpose bad row", flush=True)
+    X = S.CSC(5, 2, torch.tensor([0, 2, 3], device="cuda"), torch.tensor([1, 7, 2], dtype=torch.int32, device="cuda"),
+              torch.ones(3, device="cuda"))
+    ws = S.alloc_workspace(S.workspace_size(S.OP_TRANSPOSE, X))
+    S.transpose(X, ws)
+    with pytest.raises(S.SpgemmError):
+        S.check_ws(ws)
