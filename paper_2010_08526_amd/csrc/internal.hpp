@@ -45,13 +45,14 @@ constexpr int kMaxParts = 4096;  // merge: parts per call
 // sorted by row, equal rows combined in order), one wavefront per column up
 // to kEscWave512Terms terms (the terms of up to kEscWaveTerms in one register
 // per lane), one workgroup above; every other column is hashed and sorted
-// afterwards.  Returns the kernel class (0, 1, 2) or -1 (hashed).
+// afterwards.  Returns the kernel class (0 ... 3) or -1 (hashed).
 constexpr int64_t kEscWaveTerms = 64;
+constexpr int64_t kEscWave256Terms = 256;
 constexpr int64_t kEscWave512Terms = 512;
 constexpr int64_t kEscBlockTerms = 4096;
 constexpr int esc_class(int64_t flops, int64_t nnz, double cf_max) {
   return (nnz <= 0 || flops > kEscBlockTerms || (double)flops > cf_max * (double)nnz) ? -1
-         : (flops <= kEscWaveTerms ? 0 : (flops <= kEscWave512Terms ? 1 : 2));
+         : (flops <= kEscWaveTerms ? 0 : (flops <= kEscWave256Terms ? 1 : (flops <= kEscWave512Terms ? 2 : 3)));
 }
 constexpr size_t kPartDescBytes = 24;  // device-side copy of one part's pointers
 constexpr int64_t kBitmapRows = 1 << 20;  // heavy symbolic: rows per LDS bitmap window (128 KiB)
@@ -105,7 +106,7 @@ struct WsHeader {
   uint64_t left_tag;    // fingerprint (| 1) of the source of the slabbed copy of A in the workspace; 0 = none
   uint64_t left_new;    // fingerprint of the current call's left operand (summed by k_left_sum)
   int32_t half_count[2];  // columns of bins 2 and 3 that take half-size tables
-  int32_t esc_count[3];  // row-sorted product: columns listed for the expand-sort-compress kernels
+  int32_t esc_count[4];  // row-sorted product: columns listed for the expand-sort-compress kernels
 };
 constexpr size_t kHeaderBytes = 4096;
 

@@ -459,7 +459,7 @@ __global__ void k_init_header(WsHeader *h, uint64_t keep_tag, int keep_status = 
     h->left_new = 0;
     for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
     for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
-    h->esc_count[0] = h->esc_count[1] = h->esc_count[2] = 0;
+    h->esc_count[0] = h->esc_count[1] = h->esc_count[2] = h->esc_count[3] = 0;
     h->half_count[0] = h->half_count[1] = 0;
     h->split_cursor = 0;
     h->items = 0;
@@ -509,10 +509,10 @@ constexpr int kBinUnroll = 8;  // entries of B a lane has in flight
 
 // Appends column jj of each thread with bin >= 0 to the bins' lists: one LDS
 // counter per list, one global atomic per list and block.  Lists kNumBins ...:
-// the row-sorted product's expand-sort-compress columns, classes 0 and 2 in
-// two arrays, class 1 from the end of class 0's; then the half tables of bins
-// 2 and 3, from the end of their bins' arrays.
-constexpr int kHalfList = kNumBins + 3;
+// the row-sorted product's expand-sort-compress columns, classes 0 and 3 in
+// two arrays, classes 1 and 2 from their ends; then the half tables of bins 2
+// and 3, from the end of their bins' arrays.
+constexpr int kHalfList = kNumBins + 4;
 __device__ __forceinline__ void bin_append(int bin, int64_t jj, int64_t ncol, int32_t *bins, WsHeader *hdr) {
   constexpr int NL = kHalfList + 2;
   __shared__ int s_cnt[NL];
@@ -532,7 +532,8 @@ __device__ __forceinline__ void bin_append(int bin, int64_t jj, int64_t ncol, in
     const int64_t p = s_base[bin] + pos;
     const int64_t at = bin >= kHalfList      ? (int64_t)(bin - kHalfList + 3) * ncol - 1 - p
                        : bin == kNumBins + 1 ? (int64_t)(kNumBins + 1) * ncol - 1 - p
-                       : bin == kNumBins + 2 ? (int64_t)(kNumBins + 1) * ncol + p
+                       : bin == kNumBins + 2 ? (int64_t)(kNumBins + 2) * ncol - 1 - p
+                       : bin == kNumBins + 3 ? (int64_t)(kNumBins + 1) * ncol + p
                                              : (int64_t)bin * ncol + p;
     bins[at] = (int32_t)jj;
   }
@@ -1207,19 +1208,19 @@ __device__ __forceinline__ int esc_emit_wave(const int32_t *key, const double *v
   return done;
 }
 
-// One wavefront per column of kEscWaveTerms + 1 to kEscWave512Terms terms:
-// B(:,j) in chunks of 64 entries, each chunk's terms placed in LDS in rounds
+// One wavefront per column of kEscWaveTerms + 1 to N terms (N = 256, and 512
+// for longer columns: LDS bounds the waves in flight, 32 and 16 per CU): B(:,j) in chunks of 64 entries, each chunk's terms placed in LDS in rounds
 // of 64 (owners from a marker and a max-scan), then ranked by (row, term
 // number) by distribution (rank_sort.hpp), put in order and combined.  No
 // barrier: the waves of a CU hide each other's chain of dependent loads (B
 // entry, A's column pointers, A's entries).  100,000 columns of 200 terms
 // (A A^T, two entries per inner column): 0.82 ms; a workgroup of 256 threads
 // per column and a bitonic network took 4.72.
-template <class VT, class SR>
-__global__ __launch_bounds__(256) void k_esc_wave512(ProductArgs<VT> a, int64_t c0, const int32_t *list,
-                                                     const int32_t *count_p, const int64_t *c_colptr,
-                                                     int32_t *out_ri, VT *out_v, int32_t *status) {
-  constexpr int N = (int)kEscWave512Terms, E = N / kWave;
+template <int N, class VT, class SR>
+__global__ __launch_bounds__(256) void k_esc_wave_n(ProductArgs<VT> a, int64_t c0, const int32_t *list,
+                                                    const int32_t *count_p, const int64_t *c_colptr,
+                                                    int32_t *out_ri, VT *out_v, int32_t *status) {
+  constexpr int E = N / kWave;
   __shared__ RankLds<N, double> s_r[4];
   __shared__ int s_mark[4][kWave];
   const int w = threadIdx.x / kWave, l = lane();
@@ -3349,21 +3350,24 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   src.c0 = c0;
   if (esc) {
     int32_t *status = &hdr->status;
-    static const char *kEscNames[3] = {"esc_wave", "esc_wave512", "esc_block"};
-    for (int e = 0; e < 3; e++) {
+    static const char *kEscNames[4] = {"esc_wave", "esc_wave256", "esc_wave512", "esc_block"};
+    for (int e = 0; e < 4; e++) {
       // (a column taken has at most cf times its length in terms)
-      static constexpr int64_t kBelow[3] = {0, kEscWaveTerms, kEscWave512Terms};
+      static constexpr int64_t kBelow[4] = {0, kEscWaveTerms, kEscWave256Terms, kEscWave512Terms};
       const int ce = sync ? h.esc_count[e] : ((double)max_len * esc->cf <= (double)kBelow[e] ? 0 : -1);
       if (ce == 0) continue;
-      const int32_t *list = bins + (int64_t)(kNumBins + (e == 0 ? 0 : 1)) * ncol - (e == 1 ? 1 : 0);
+      const int32_t *list = bins + (int64_t)(kNumBins + (e == 0 ? 0 : (e == 2 ? 2 : 1))) * ncol - (e == 1 || e == 2 ? 1 : 0);
       const int32_t *cp = &hdr->esc_count[e];
       ProfScope prof(kEscNames[e], st);
       if (e == 0)
         hipLaunchKernelGGL((k_esc_wave<VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st, src.a, c0, list, cp,
                            c_colptr, esc->ri, (VT *)esc->v, status);
       else if (e == 1)
-        hipLaunchKernelGGL((k_esc_wave512<VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st, src.a, c0, list, cp,
-                           c_colptr, esc->ri, (VT *)esc->v, status);
+        hipLaunchKernelGGL((k_esc_wave_n<(int)kEscWave256Terms, VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st,
+                           src.a, c0, list, cp, c_colptr, esc->ri, (VT *)esc->v, status);
+      else if (e == 2)
+        hipLaunchKernelGGL((k_esc_wave_n<(int)kEscWave512Terms, VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st,
+                           src.a, c0, list, cp, c_colptr, esc->ri, (VT *)esc->v, status);
       else
         hipLaunchKernelGGL((k_esc_block<VT, SR>), dim3(bin_grid(ce, false, 4)), dim3(kEscThreads), 0, st, src.a, c0, list,
                            cp, c_colptr, esc->ri, (VT *)esc->v, status);

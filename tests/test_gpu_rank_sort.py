@@ -13,7 +13,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 S = None
-LENS = [0, 1, 2, 63, 64, 65, 127, 128, 129, 511, 512, 513, 1023, 1025, 4095, 4096, 4097, 6000]
+LENS = [0, 1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1025, 4095, 4096, 4097, 6000]
 
 
 def setup_module(module):
