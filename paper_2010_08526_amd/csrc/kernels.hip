@@ -80,7 +80,7 @@ struct ProductArgs {
 // segment o and must not use their results), then every insert
 // (ins(row, value(o, raw))), so that a wavefront keeps kPipe independent
 // global loads in flight.
-constexpr int kPipe = 8;
+constexpr int kPipe = 4;
 
 template <class RawT, class Load, class Value, class Ins>
 __device__ __forceinline__ void flatten_rounds(int len, int excl, int total, int *mark, int64_t r_base,
@@ -641,7 +641,9 @@ __global__ __launch_bounds__(256) void k_bin_len(const int64_t *c_colptr, int64_
 // largest table (128 KB) is cleared whole for each column by the one workgroup
 // that fits a CU.  Columns of 512-16384 terms, table against bitmap: 632 and
 // 66 -> 228 and 34 us at m = 65,536 (R-MAT scale 16), 2459 -> 711 us at
-// m = 262,144 (scale 18), 372 -> 178 us at m = 8192 (scale 13).
+// m = 262,144 (scale 18), 372 -> 178 us at m = 8192 (scale 13).  The walk keeps
+// as many waves in flight as 64 registers allow (4 gathers each): 190, 583 and
+// 154 us, and 2.8 -> 2.3 ms on 6.3e5 columns of 513-1024 terms in tables.
 // One wavefront per column, TBL-slot table private to the wave.
 template <int TBL, bool BITS>
 __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t c0, const int32_t *list,
@@ -703,7 +705,7 @@ __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t 
 // One workgroup per column, table (TBL slots) or bitmap (one bit per row of
 // C, sized by the launch) shared by its waves.
 template <int TBL, int THREADS, bool BITS>
-__global__ __launch_bounds__(THREADS) void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list,
                                                        const int32_t *count_p, int64_t *nnz_out, int32_t *status) {
   constexpr int NW = THREADS / kWave;
   extern __shared__ int32_t s_keys[];  // TBL slots, or (m + 31) / 32 words (all zero between columns)
@@ -771,9 +773,10 @@ __global__ __launch_bounds__(THREADS) void k_sym_block(ProductArgs<float> a, int
 // Heavy columns: exact count with an LDS bitmap over windows of kBitmapRows
 // rows (one pass over the column's terms per window).
 // The launch sizes the bitmap for min(m, kBitmapRows) rows, so that two
-// workgroups fit a compute unit up to 524,288 rows (the walk over A's columns
-// bounds the kernel: 1.96 ms and 11.5 ms at scales 16 and 18 as with one).
-__global__ __launch_bounds__(1024) void k_sym_bitmap(ProductArgs<float> a, int64_t c0, const int32_t *list,
+// workgroups fit a compute unit up to 524,288 rows, if they also fit its
+// registers: 1.96 and 11.6 ms at scales 16 and 18 with one, 1.46 and 8.9 with
+// two (the walk over A's columns bounds the kernel).
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_sym_bitmap(ProductArgs<float> a, int64_t c0, const int32_t *list,
                                                      const int32_t *count_p, int *cursor, int64_t *nnz_out,
                                                      int32_t *status) {
   constexpr int NW = 1024 / kWave;
@@ -989,7 +992,7 @@ __global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, 
 }
 
 template <int TBL, int THREADS, class VT, class Src>
-__global__ __launch_bounds__(THREADS) void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TBL <= 2048 ? 5 : 4))) void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p,
                                                        const int64_t *c_colptr, int32_t *out_ri, VT *out_v,
                                                        int32_t *status) {
   constexpr int NW = THREADS / kWave;
