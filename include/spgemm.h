@@ -182,6 +182,15 @@ int spgemm_numeric(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t
                    int32_t n_layers, const int64_t *flops, const int64_t *c_colptr, int32_t *c_rowidx,
                    void *c_values, int32_t semiring, void *ws, size_t ws_bytes, void *stream);
 
+/* Sums of the rows of the symbolic counts (device, int64 [rows][n]) and the
+ * largest count of the last row, to host memory: enough to see that a product
+ * fits as a whole without reading the counts back.  Synchronizes the stream.
+ * Workspace: any with its header block (SPGEMM_OP_COLPTR's will do); its status
+ * is kept.  SPGEMM_E_INVAL for more than SPGEMM_COUNT_SUMS_MAX_ROWS rows. */
+#define SPGEMM_COUNT_SUMS_MAX_ROWS 64
+int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
+                      void *ws, size_t ws_bytes, void *stream);
+
 /* spgemm_numeric for a caller that knows that no column of the call holds
  * more than max_len entries (from the symbolic counts it read back): kernels
  * for longer columns are not launched.  A longer column sets status 4. */

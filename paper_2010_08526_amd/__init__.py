@@ -203,6 +203,8 @@ def numeric(A, B, c0: int, c1: int, layer: int, n_layers: int, flops, c_colptr, 
            "spgemm_numeric")
 
 
+COUNT_SUMS_MAX_ROWS = 64
+_lib.spgemm_count_sums.argtypes = [_vp, _i64, _i32, _vp, ctypes.POINTER(_i64), _vp, _sz, _vp]
 _lib.spgemm_numeric_upto.argtypes = [_P, _P, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i32, _i64, _vp, _sz, _vp]
 _lib.spgemm_numeric_sorted.argtypes = [_P, _P, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, ctypes.c_double, _i32, _vp,
                                        _sz, _vp]
@@ -299,24 +301,25 @@ class Plan:
 
     flops: torch.Tensor  # int64 [n] per output column (device)
     nnz: torch.Tensor  # int64 [rows, n] (device)
-    nnz_host: np.ndarray  # int64 [rows, n]
+    counts: object  # nnz as it was: numpy, or a tensor that is read back on first use
     bounds: list
     batch_nnz: np.ndarray  # [b, rows]
     n_layers: int
     budget_bytes: int
     input_bytes: int
     reserve_bytes: int
+    longest: int  # entries of C's longest column
+
+    @property
+    def nnz_host(self) -> np.ndarray:
+        """int64 [rows, n] on the host."""
+        if isinstance(self.counts, torch.Tensor):
+            self.counts = self.counts.cpu().numpy()
+        return self.counts
 
     @property
     def nbatches(self) -> int:
         return len(self.bounds) - 1
-
-    @property
-    def longest(self) -> int:
-        """Entries of C's longest column."""
-        if "_longest" not in self.__dict__:
-            self._longest = int(self.nnz_host[-1].max(initial=0))
-        return self._longest
 
     @property
     def total_flops(self) -> int:
@@ -375,6 +378,9 @@ class Engine:
         # a product starts from scratch: its batches share one slabbed copy of A
         ws_invalidate(self.ws_num, stream)
         symbolic(A, B, 0, n, self.L, self.flops, self.nnz, self.ws_sym, stream)
+        whole = self._plan_whole(stream)
+        if whole is not None:
+            return whole
         nnz_host = self.nnz.cpu().numpy()
         counts = nnz_host
         if self.sorted_output:  # the merged batch is held twice: as formed and sorted
@@ -385,7 +391,29 @@ class Engine:
         if self.sorted_output:
             tot[:, -1] //= 2
         return Plan(self.flops, self.nnz, nnz_host, bounds, tot, self.L, self.budget_bytes, self.input_bytes,
-                    self.reserve_bytes)
+                    self.reserve_bytes, int(nnz_host[-1].max(initial=0)))
+
+    def _plan_whole(self, stream=None) -> Plan | None:
+        """The plan of a product that fits as a whole, from sums formed on the
+        device: reading the counts of 262,144 columns back and planning them on
+        the host kept the GPU waiting for 1.0 ms.  None: the planner decides
+        (and below 32,768 counts its way is the shorter)."""
+        n, L = self.B.ncols, self.L
+        rows = L + 1 if L > 1 else 1
+        if n * rows < 32768 or rows > COUNT_SUMS_MAX_ROWS:
+            return None
+        sums = np.zeros(rows, np.int64)
+        longest = _i64(0)
+        _check(_lib.spgemm_count_sums(_ptr(self.nnz), n, rows, sums.ctypes.data, ctypes.byref(longest),
+                                      _ptr(self.ws_scan), self.ws_scan.numel(), _stream(stream)), "spgemm_count_sums")
+        avail = self.budget_bytes - self.input_bytes - self.reserve_bytes
+        held = int(sums[-1]) * (2 if self.sorted_output else 1) + (int(sums[:-1].sum()) if L > 1 else 0)
+        if (4 + self.vbytes) * held + 8 * (L + 1 if L > 1 else 1) * n > avail or self.max_batches < 1:
+            return None
+        with _on_stream(stream):
+            counts = self.nnz.clone()  # self.nnz is written again by the next product
+        return Plan(self.flops, self.nnz, counts, [0, n], sums.reshape(1, rows), L, self.budget_bytes,
+                    self.input_bytes, self.reserve_bytes, int(longest.value))
 
     def _buffers(self, plan: Plan):
         widths = [b - a for a, b in zip(plan.bounds[:-1], plan.bounds[1:])]

@@ -2892,6 +2892,35 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(const int64_t *x, i
   }
 }
 
+// Sums of the rows of counts[rows][n] (res[0, rows)) and the largest count of
+// the last row (res[rows]); res all zero on entry.
+__global__ __launch_bounds__(256) void k_count_sums(const int64_t *counts, int64_t n, int rows, uint64_t *res) {
+  __shared__ int64_t s_sum[4], s_max[4];
+  const int row = blockIdx.y;
+  const int64_t *c = counts + (int64_t)row * n;
+  int64_t sum = 0, top = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int64_t v = c[i];
+    sum += v;
+    top = max(top, v);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    sum += __shfl_xor(sum, o, kWave);
+    top = max(top, (int64_t)__shfl_xor(top, o, kWave));
+  }
+  if (lane() == 0) {
+    s_sum[threadIdx.x / kWave] = sum;
+    s_max[threadIdx.x / kWave] = top;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    atomicAdd((unsigned long long *)&res[row], (unsigned long long)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]));
+    if (row == rows - 1)
+      atomicMax((unsigned long long *)&res[rows],
+                (unsigned long long)max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3])));
+  }
+}
+
 // ============================================================================
 // Host side.
 // ============================================================================
@@ -2916,8 +2945,14 @@ static BinCaps g_caps[2] = {BinCaps{{kSymCap[0], kSymCap[1], kSymCap[2], kSymCap
 constexpr int kBpcDefault[2][kNumBins - 1] = {{8, 8, 8, 8, 1}, {8, 8, 4, 4, 1}};
 static int g_bpc[2][kNumBins - 1] = {{8, 8, 8, 8, 1}, {8, 8, 4, 4, 1}};
 
-int read_headers(void *const *dev, int n, hipStream_t st, WsHeader *out) {
+static int pin_buffer() {
   if (!g_pin.hdr) HIPCHK(hipHostMalloc((void **)&g_pin.hdr, sizeof(WsHeader) * kStatusMany, hipHostMallocDefault));
+  return SPGEMM_OK;
+}
+
+int read_headers(void *const *dev, int n, hipStream_t st, WsHeader *out) {
+  int rc = pin_buffer();
+  if (rc) return rc;
   for (int i = 0; i < n; i++) HIPCHK(hipMemcpyAsync(g_pin.hdr + i, dev[i], sizeof(WsHeader), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   for (int i = 0; i < n; i++) out[i] = g_pin.hdr[i];
@@ -3841,6 +3876,32 @@ int spgemm_colptr(const int64_t *counts, int64_t n, int64_t *colptr_out, void *w
   st = launch_init_header((WsHeader *)w, 0, s);
   if (st) return st;
   return launch_colptr_scan(counts, n, colptr_out, (int64_t *)(w + L.scan), s);
+}
+
+int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
+                      void *ws, size_t ws_bytes, void *stream) {
+  if (n < 0 || rows < 1 || rows > SPGEMM_COUNT_SUMS_MAX_ROWS || (n > 0 && !counts) || !sums_host || !longest_host)
+    return SPGEMM_E_INVAL;
+  int st = check_ws(ws, ws_bytes, kHeaderBytes);
+  if (st) return st;
+  hipStream_t s = (hipStream_t)stream;
+  // the second half of the header block is free
+  uint64_t *res = (uint64_t *)((char *)ws + 2048);
+  static_assert(2048 + 8 * (SPGEMM_COUNT_SUMS_MAX_ROWS + 1) <= kHeaderBytes, "results fit the header block");
+  static_assert(8 * (SPGEMM_COUNT_SUMS_MAX_ROWS + 1) <= sizeof(WsHeader) * kStatusMany, "and the pinned buffer");
+  hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(256), 0, s, (int64_t *)res, (int64_t)rows + 1);
+  LAUNCHCHK();
+  const unsigned gx = std::max(1u, std::min(grid_of(n, 2048), (unsigned)device_cus()));
+  hipLaunchKernelGGL(k_count_sums, dim3(gx, (unsigned)rows), dim3(256), 0, s, counts, n, (int)rows, res);
+  LAUNCHCHK();
+  st = pin_buffer();
+  if (st) return st;
+  const size_t bytes = 8 * ((size_t)rows + 1);
+  HIPCHK(hipMemcpyAsync(g_pin.hdr, res, bytes, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  memcpy(sums_host, g_pin.hdr, 8 * (size_t)rows);
+  memcpy(longest_host, (const char *)g_pin.hdr + 8 * (size_t)rows, 8);
+  return SPGEMM_OK;
 }
 
 int spgemm_batched_forward(const spgemm_csc *A, const spgemm_csc *B, int64_t nnz_cap, int64_t *flops_out,

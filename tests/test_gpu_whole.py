@@ -94,3 +94,34 @@ def test_bound_on_column_entries(limit, sorted_output):
             with pytest.raises(S.SpgemmError, match="device code 4"):
                 S.check_many([eng.ws_sym, ws])
             S.check_many([ws])  # reported once
+
+
+@pytest.mark.parametrize("layers", [1, 3])
+@pytest.mark.parametrize("sorted_output", [False, True])
+def test_plan_from_device_sums(layers, sorted_output):
+    """A product of enough columns to be planned from sums on the device: the
+    same plan as the planner's, at the smallest budget that holds it whole and
+    one byte below; counts read back later are those of their own product."""
+    print(f"case: device sums layers={layers} sorted={sorted_output}", flush=True)
+    A = synth.erdos_renyi(40000, 40000, 3, 5, torch.float32)
+    B = synth.erdos_renyi(40000, 40000, 5, 6, torch.float32)
+    eng = S.Engine(A.to("cuda"), B.to("cuda"), layers, sorted_output=sorted_output)
+    plan = eng.plan()
+    assert isinstance(plan.counts, torch.Tensor)  # not read back yet
+    first = eng.plan()
+    eng.B.rowidx[:1000] = eng.B.rowidx[0]  # another product in the same engine
+    eng.plan()
+    want = oracle.count(A, B)
+    assert np.array_equal(plan.nnz_host[-1], want) and np.array_equal(first.nnz_host, plan.nnz_host)
+    assert plan.longest == want.max() and plan.bounds == [0, 40000]
+    assert np.array_equal(plan.batch_nnz, plan.nnz_host.sum(1)[None])
+    eng = S.Engine(A.to("cuda"), B.to("cuda"), layers, sorted_output=sorted_output)
+    u = plan.nnz_host.sum(1)
+    held = int(u[-1]) * (2 if sorted_output else 1) + (int(u[:-1].sum()) if layers > 1 else 0)
+    need = 8 * held + 8 * (layers + 1 if layers > 1 else 1) * 40000
+    for extra, nb in ((0, 1), (-1, 2)):
+        eng.budget_bytes = eng.input_bytes + eng.reserve_bytes + need + extra
+        assert eng.plan().nbatches == nb
+    eng.budget_bytes = eng.input_bytes + eng.reserve_bytes
+    with pytest.raises(S.SpgemmError):
+        eng.plan()
