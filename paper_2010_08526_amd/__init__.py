@@ -204,6 +204,7 @@ def numeric(A, B, c0: int, c1: int, layer: int, n_layers: int, flops, c_colptr, 
 
 
 COUNT_SUMS_MAX_ROWS = 64
+SLAB_MIN_ROWS = 5120  # more rows than this: heavy columns are formed from a slabbed copy of A
 _lib.spgemm_count_sums.argtypes = [_vp, _i64, _i32, _vp, ctypes.POINTER(_i64), _vp, _sz, _vp]
 _lib.spgemm_numeric_upto.argtypes = [_P, _P, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i32, _i64, _vp, _sz, _vp]
 _lib.spgemm_numeric_sorted.argtypes = [_P, _P, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, ctypes.c_double, _i32, _vp,
@@ -355,7 +356,8 @@ class Engine:
         mparts = CSC(A.nrows, n, A.colptr, A.rowidx, A.values)
         self.ws_mrg = alloc_workspace(workspace_size(OP_MERGE, mparts, None, 0, 0, max(1, self.L)), device) \
             if self.L > 1 else None
-        self.ws_scan = alloc_workspace(workspace_size(OP_COLPTR, None, None, 0, n + 1), device)
+        # (the scan's status is not asked for: its header needs no clearing)
+        self.ws_scan = torch.empty(workspace_size(OP_COLPTR, None, None, 0, n + 1), dtype=torch.uint8, device=device)
         self.ws_sort = alloc_workspace(workspace_size(OP_SORT, CSC(A.nrows, n, B.colptr, B.rowidx, B.values)), device) \
             if self.sorted_output and self.L > 1 else None
         rows = self.L + 1 if self.L > 1 else 1
@@ -376,7 +378,9 @@ class Engine:
     def plan(self, stream=None) -> Plan:
         A, B, n = self.A, self.B, self.B.ncols
         # a product starts from scratch: its batches share one slabbed copy of A
-        ws_invalidate(self.ws_num, stream)
+        # (with few rows there is none)
+        if A.nrows > SLAB_MIN_ROWS:
+            ws_invalidate(self.ws_num, stream)
         symbolic(A, B, 0, n, self.L, self.flops, self.nnz, self.ws_sym, stream)
         whole = self._plan_whole(stream)
         if whole is not None:

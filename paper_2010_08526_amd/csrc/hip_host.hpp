@@ -14,11 +14,9 @@ int device_cus();
 // header's clean_tag survives only if it equals it), 0, or kKeepAnyTag
 int launch_init_header(WsHeader *h, uint64_t keep_tag, hipStream_t st);
 int launch_set_tag(WsHeader *h, uint64_t tag, hipStream_t st);
-// zeroes the bin counters and work-queue cursors only (status, tags kept)
-int launch_reset_counters(WsHeader *h, hipStream_t st);
 // Row sort of C's columns into (ro, vo) with column lists in `lists`
-// (3 * C->ncols int32) and counters in hdr's bin_count[0..2] (zero on
-// entry).  Columns that esc_class(skip_flops[j], nnz_j, skip_cf) places in
+// (3 * C->ncols int32) and counters in hdr's sort_count and sort_cursor (zero
+// on entry).  Columns that esc_class(skip_flops[j], nnz_j, skip_cf) places in
 // an expand-sort-compress kernel are skipped (skip_flops NULL: none).
 // Kernels for columns longer than max_len are not launched.
 int sort_column_lists(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHeader *hdr,
@@ -26,7 +24,9 @@ int sort_column_lists(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists
 int g_min_bin_value();  // the spgemm_debug_min_bin setting
 BinCaps bin_caps(int which);  // 0: symbolic, 1: numeric / merge / masked product
 // colptr_out[0] = 0, colptr_out[i+1] = counts[0] + ... + counts[i]; bsum holds n / 8192 + 2 int64
-int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *colptr_out, int64_t *bsum, hipStream_t st);
+// (hdr, if given, is initialised as by launch_init_header(hdr, 0, st))
+int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *colptr_out, int64_t *bsum, hipStream_t st,
+                       WsHeader *hdr = nullptr);
 
 inline unsigned grid_of(int64_t n, int64_t per) { return (unsigned)((n + per - 1) / per); }
 

@@ -105,6 +105,8 @@ struct WsHeader {
   int32_t split_cursor; // numeric: work-queue position over the columns of A (slabbed copy)
   uint64_t left_tag;    // fingerprint (| 1) of the source of the slabbed copy of A in the workspace; 0 = none
   uint64_t left_new;    // fingerprint of the current call's left operand (summed by k_left_sum)
+  int32_t sort_count[4];  // row sort: columns of each length class
+  int32_t sort_cursor;    // row sort: work-queue position over the longest class
   int32_t half_count[2];  // columns of bins 2 and 3 that take half-size tables
   int32_t esc_count[4];  // row-sorted product: columns listed for the expand-sort-compress kernels
 };

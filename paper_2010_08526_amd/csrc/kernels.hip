@@ -452,22 +452,26 @@ __device__ __forceinline__ void traverse_merge(const PartDesc *P, int nparts, in
 // ============================================================================
 // Small kernels: header init, fills.
 // ============================================================================
+__device__ __forceinline__ void init_header(WsHeader *h, uint64_t keep_tag, int keep_status, int keep_left) {
+  if (!keep_status) h->status = 0;
+  if (!keep_left) h->left_tag = 0;  // every other operation may overwrite the slabbed copy
+  h->left_new = 0;
+  for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
+  for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
+  for (int b = 0; b < 4; b++) h->esc_count[b] = 0;
+  for (int b = 0; b < 4; b++) h->sort_count[b] = 0;
+  h->sort_cursor = 0;
+  h->half_count[0] = h->half_count[1] = 0;
+  h->split_cursor = 0;
+  h->items = 0;
+  h->item_cursor = 0;
+  h->nwide = 0;
+  h->wide_cursor = 0;
+  if (keep_tag != kKeepAnyTag && h->clean_tag != keep_tag) h->clean_tag = 0;
+}
+
 __global__ void k_init_header(WsHeader *h, uint64_t keep_tag, int keep_status = 0, int keep_left = 0) {
-  if (threadIdx.x == 0) {
-    if (!keep_status) h->status = 0;
-    if (!keep_left) h->left_tag = 0;  // every other operation may overwrite the slabbed copy
-    h->left_new = 0;
-    for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
-    for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
-    h->esc_count[0] = h->esc_count[1] = h->esc_count[2] = h->esc_count[3] = 0;
-    h->half_count[0] = h->half_count[1] = 0;
-    h->split_cursor = 0;
-    h->items = 0;
-    h->item_cursor = 0;
-    h->nwide = 0;
-    h->wide_cursor = 0;
-    if (keep_tag != kKeepAnyTag && h->clean_tag != keep_tag) h->clean_tag = 0;
-  }
+  if (threadIdx.x == 0) init_header(h, keep_tag, keep_status, keep_left);
 }
 
 __global__ void k_set_tag(WsHeader *h, uint64_t tag) {
@@ -992,7 +996,7 @@ __global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, 
 }
 
 template <int TBL, int THREADS, class VT, class Src>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TBL <= 2048 ? 5 : 4))) void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TBL <= 2048 ? 5 : (THREADS == 1024 ? 4 : 2)))) void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p,
                                                        const int64_t *c_colptr, int32_t *out_ri, VT *out_v,
                                                        int32_t *status) {
   constexpr int NW = THREADS / kWave;
@@ -2863,8 +2867,11 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_bsums(int64_t *bsum, int6
 // their exclusive scan.
 template <bool DIRECT>
 __global__ __launch_bounds__(kScanThreads) void k_scan_final(const int64_t *x, int64_t n, const int64_t *bsum,
-                                                             int64_t *out) {
+                                                             int64_t *out, WsHeader *hdr) {
   __shared__ int64_t s_w[kScanThreads / kWave];
+  // a caller whose workspace is used by the scan alone has its header
+  // initialised here (hdr), not by a launch of its own
+  if (hdr && blockIdx.x == 0 && threadIdx.x == 0) init_header(hdr, 0, 0, 0);
   const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
   const int64_t t0 = b0 + (int64_t)threadIdx.x * kScanPer;  // contiguous items per thread
   int64_t v[kScanPer];
@@ -2985,20 +2992,18 @@ int launch_set_tag(WsHeader *h, uint64_t tag, hipStream_t st) {
   return SPGEMM_OK;
 }
 
-int launch_reset_counters(WsHeader *h, hipStream_t st) {
-  hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, h, kKeepAnyTag, 1, 1);
-  LAUNCHCHK();
-  return SPGEMM_OK;
-}
-
 int launch_init_header(WsHeader *h, uint64_t keep_tag, hipStream_t st) {
   hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, h, keep_tag, 0);
   LAUNCHCHK();
   return SPGEMM_OK;
 }
 
-int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *out, int64_t *bsum, hipStream_t s) {
+int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *out, int64_t *bsum, hipStream_t s, WsHeader *hdr) {
   if (n == 0) {
+    if (hdr) {
+      const int rc = launch_init_header(hdr, 0, s);
+      if (rc) return rc;
+    }
     hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(64), 0, s, out, (int64_t)1);
     LAUNCHCHK();
     return SPGEMM_OK;
@@ -3014,9 +3019,9 @@ int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *out, int64_t *
   if (nb > kScanDirect) {
     hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(kScanThreads), 0, s, bsum, nb);
     LAUNCHCHK();
-    hipLaunchKernelGGL(k_scan_final<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out);
+    hipLaunchKernelGGL(k_scan_final<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out, hdr);
   } else {
-    hipLaunchKernelGGL(k_scan_final<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out);
+    hipLaunchKernelGGL(k_scan_final<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, n, bsum, out, hdr);
   }
   LAUNCHCHK();
   return SPGEMM_OK;
@@ -3132,10 +3137,11 @@ static ProductArgs<VT> product_args(const spgemm_csc *A, const spgemm_csc *B, in
 // One symbolic pass over inner range [klo, khi) writing one row of counts.
 // Grid of a persistent bin kernel: the exact need when the bin's count is
 // known on the host (cnt >= 0), else a fixed grid that fills the device.
-static unsigned bin_grid(int cnt, bool wave_kernel, int blocks_per_cu) {
+// `most`: columns the call has.
+static unsigned bin_grid(int cnt, bool wave_kernel, int blocks_per_cu, int64_t most) {
   const unsigned full = (unsigned)(blocks_per_cu * device_cus());
-  if (cnt < 0) return full;
-  const unsigned need = wave_kernel ? grid_of(cnt, 4) : (unsigned)cnt;
+  const int64_t c = cnt < 0 ? most : cnt;
+  const unsigned need = wave_kernel ? grid_of(c, 4) : (unsigned)c;
   return std::max(1u, std::min(need, full));
 }
 
@@ -3183,6 +3189,11 @@ __global__ void k_pack_last(int64_t *cp_out, int64_t ncols, int64_t nnz) {
 
 constexpr int64_t kLdsPerCu = 160 * 1024;
 
+// Columns up to which the symbolic pass launches its few kernels without
+// reading the bins' counts back first: 4096 columns took 165 us with the
+// read-back (whole product), 148 without.
+constexpr int64_t kBlindCols = 8192;
+
 // Counts of the bins: read back (one synchronization) or left on the device.
 static int bin_counts(WsHeader *hdr, hipStream_t st, bool sync, int *cnt, WsHeader *h) {
   if (sync) {
@@ -3220,6 +3231,9 @@ static int symbolic_pass(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   int32_t *status = &hdr->status;
   static const char *kSymNames[kNumBins] = {"sym_wave64", "sym_wave256", "sym_wave1024", "sym_block4096",
                                             "sym_block32768", "sym_bitmap"};
+  // bins that no column can reach (a bound is at most m)
+  for (int b = g_min_bin + 1; b < kNumBins; b++)
+    if (cnt[b] < 0 && A->nrows <= g_caps[0].cap[b - 1]) cnt[b] = 0;
   // one bit per row instead of a hash table where the bitmap is no larger
   const int64_t words = (A->nrows + 31) / 32;
   const auto bits = [&](int64_t tbl) { return words <= tbl; };
@@ -3237,36 +3251,36 @@ static int symbolic_pass(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
     switch (b) {
       case 0:
         if (bits(64))
-          hipLaunchKernelGGL((k_sym_wave<64, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][0])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<64, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][0], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_wave<64, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][0])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<64, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][0], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
         break;
       case 1:
         if (bits(256))
-          hipLaunchKernelGGL((k_sym_wave<256, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][1])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<256, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][1], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_wave<256, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][1])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<256, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][1], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
         break;
       case 2:
         if (bits(1024))
-          hipLaunchKernelGGL((k_sym_wave<1024, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][2])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<1024, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][2], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_wave<1024, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][2])), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<1024, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][2], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
         break;
       case 3:
         if (bits(4096))
-          hipLaunchKernelGGL((k_sym_block<4096, 256, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][3], fit(256, (int64_t)wb)))), dim3(256), wb, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<4096, 256, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][3], fit(256, (int64_t)wb)), ncol)), dim3(256), wb, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_block<4096, 256, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][3])), dim3(256), 4096 * 4, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<4096, 256, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][3], ncol)), dim3(256), 4096 * 4, st, a, c0, list, cp, nnz_row, status);
         break;
       case 4:
         if (bits(32768))
-          hipLaunchKernelGGL((k_sym_block<32768, 512, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][4], fit(512, (int64_t)wb)))), dim3(512), wb, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<32768, 512, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][4], fit(512, (int64_t)wb)), ncol)), dim3(512), wb, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_block<32768, 1024, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][4])), dim3(1024), 32768 * 4, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<32768, 1024, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][4], ncol)), dim3(1024), 32768 * 4, st, a, c0, list, cp, nnz_row, status);
         break;
       default:
-        hipLaunchKernelGGL(k_sym_bitmap, dim3(bin_grid(cnt[b], false, fit(1024, (int64_t)bm))), dim3(1024), bm, st, a, c0, list, cp, &hdr->cursor[b], nnz_row, status);
+        hipLaunchKernelGGL(k_sym_bitmap, dim3(bin_grid(cnt[b], false, fit(1024, (int64_t)bm), ncol)), dim3(1024), bm, st, a, c0, list, cp, &hdr->cursor[b], nnz_row, status);
         break;
     }
     LAUNCHCHK();
@@ -3301,13 +3315,13 @@ static int accumulate_pass(const Src &src, const int *cnt, const int *half_cnt, 
     const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
     const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_num_wave<64, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][0])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 1: hipLaunchKernelGGL((k_num_wave<256, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][1])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 2: hipLaunchKernelGGL((k_num_wave<1024, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][2])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 3: hipLaunchKernelGGL((k_num_block<4096, 256, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][3])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 4: hipLaunchKernelGGL((k_num_block<10240, 1024, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][4])), dim3(1024), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 5: hipLaunchKernelGGL((k_num_wave<512, VT, Src>), dim3(bin_grid(c, true, 2 * g_bpc[1][2])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      default: hipLaunchKernelGGL((k_num_block<2048, 256, VT, Src>), dim3(bin_grid(c, false, 2 * g_bpc[1][3])), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 0: hipLaunchKernelGGL((k_num_wave<64, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][0], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 1: hipLaunchKernelGGL((k_num_wave<256, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][1], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 2: hipLaunchKernelGGL((k_num_wave<1024, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][2], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 3: hipLaunchKernelGGL((k_num_block<4096, 256, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][3], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 4: hipLaunchKernelGGL((k_num_block<10240, 1024, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][4], ncol)), dim3(1024), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 5: hipLaunchKernelGGL((k_num_wave<512, VT, Src>), dim3(bin_grid(c, true, 2 * g_bpc[1][2], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      default: hipLaunchKernelGGL((k_num_block<2048, 256, VT, Src>), dim3(bin_grid(c, false, 2 * g_bpc[1][3], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
     }
     LAUNCHCHK();
   }
@@ -3398,16 +3412,16 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
       const int32_t *cp = &hdr->esc_count[e];
       ProfScope prof(kEscNames[e], st);
       if (e == 0)
-        hipLaunchKernelGGL((k_esc_wave<VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st, src.a, c0, list, cp,
+        hipLaunchKernelGGL((k_esc_wave<VT, SR>), dim3(bin_grid(ce, true, 8, ncol)), dim3(256), 0, st, src.a, c0, list, cp,
                            c_colptr, esc->ri, (VT *)esc->v, status);
       else if (e == 1)
-        hipLaunchKernelGGL((k_esc_wave_n<(int)kEscWave256Terms, VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_esc_wave_n<(int)kEscWave256Terms, VT, SR>), dim3(bin_grid(ce, true, 8, ncol)), dim3(256), 0, st,
                            src.a, c0, list, cp, c_colptr, esc->ri, (VT *)esc->v, status);
       else if (e == 2)
-        hipLaunchKernelGGL((k_esc_wave_n<(int)kEscWave512Terms, VT, SR>), dim3(bin_grid(ce, true, 8)), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_esc_wave_n<(int)kEscWave512Terms, VT, SR>), dim3(bin_grid(ce, true, 8, ncol)), dim3(256), 0, st,
                            src.a, c0, list, cp, c_colptr, esc->ri, (VT *)esc->v, status);
       else
-        hipLaunchKernelGGL((k_esc_block<VT, SR>), dim3(bin_grid(ce, false, 4)), dim3(kEscThreads), 0, st, src.a, c0, list,
+        hipLaunchKernelGGL((k_esc_block<VT, SR>), dim3(bin_grid(ce, false, 4, ncol)), dim3(kEscThreads), 0, st, src.a, c0, list,
                            cp, c_colptr, esc->ri, (VT *)esc->v, status);
       LAUNCHCHK();
     }
@@ -3710,7 +3724,8 @@ int spgemm_symbolic(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_
     return SPGEMM_OK;
   }
   const int64_t kdim = A->ncols;
-  if (n_layers == 1) return symbolic_pass(A, B, c0, ncol, 0, kdim, flops_out, nnz_out, L, w, s, true);
+  if (n_layers == 1)
+    return symbolic_pass(A, B, c0, ncol, 0, kdim, flops_out, nnz_out, L, w, s, ncol > kBlindCols);
   const int64_t width = (kdim + n_layers - 1) / n_layers;
   for (int32_t l = 0; l < n_layers; l++) {
     const int64_t klo = std::min<int64_t>(kdim, (int64_t)l * width), khi = std::min<int64_t>(kdim, klo + width);
@@ -3815,9 +3830,8 @@ int spgemm_numeric_sorted_upto(const spgemm_csc *A, const spgemm_csc *B, int64_t
                         false, use_esc ? &esc : nullptr, max_len);
   if (st) return st;
   // the hashed columns, from the staging arrays into row order (the bin
-  // lists are free again: the sort pass lists its columns there)
-  st = launch_reset_counters((WsHeader *)ws, s);
-  if (st) return st;
+  // lists are free again: the sort pass lists its columns there; its counters
+  // are its own, still zero)
   spgemm_csc T = *A;
   T.ncols = ncol;
   T.colptr = c_colptr;
@@ -3873,9 +3887,7 @@ int spgemm_colptr(const int64_t *counts, int64_t n, int64_t *colptr_out, void *w
   if (st) return st;
   hipStream_t s = (hipStream_t)stream;
   char *w = (char *)ws;
-  st = launch_init_header((WsHeader *)w, 0, s);
-  if (st) return st;
-  return launch_colptr_scan(counts, n, colptr_out, (int64_t *)(w + L.scan), s);
+  return launch_colptr_scan(counts, n, colptr_out, (int64_t *)(w + L.scan), s, (WsHeader *)w);
 }
 
 int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,

@@ -39,10 +39,10 @@ constexpr int kSortBlockThreads = 512;
 constexpr int kSortWinWords = (1 << 19) / 32;  // bitmap words of the largest row window
 constexpr int kSortDupCode = 11;  // status code: a row twice in one column, or a row outside [0, m)
 
-// Column lists per length class, counts in the header's bin counters: up to
-// 64 entries from the front of the first array (bin_count[0]), up to 512 from
-// its end (bin_count[3]), up to 4096 in the second (bin_count[1]), longer ones
-// in the third (bin_count[2]).
+// Column lists per length class, counts in the header: up to 64 entries from
+// the front of the first array (sort_count[0]), up to 512 from its end
+// (sort_count[3]), up to 4096 in the second (sort_count[1]), longer ones in the
+// third (sort_count[2]).
 // Columns formed in row order by expand-sort-compress (skip_flops given) are
 // left out.
 __global__ __launch_bounds__(256) void k_sort_bin(const int64_t *cp, int64_t n, int32_t *lists, WsHeader *hdr,
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void k_sort_bin(const int64_t *cp, int64_t n, 
     const uint64_t mask = __ballot(cls == c);
     if (!mask) continue;
     int base = 0;
-    if (lane() == 0) base = atomicAdd(&hdr->bin_count[c], __popcll(mask));
+    if (lane() == 0) base = atomicAdd(&hdr->sort_count[c], __popcll(mask));
     base = readlane(base, 0);
     const int64_t p = base + mbcnt(mask);
     if (cls == c) lists[c == 3 ? n - 1 - p : (int64_t)c * n + p] = (int32_t)j;
@@ -355,16 +355,16 @@ int sort_typed(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHea
   const VT *v = (const VT *)C->values;
   const int cus = device_cus();
   hipLaunchKernelGGL(k_sort_wave<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows, lists,
-                     (const int32_t *)&hdr->bin_count[0], ro, (VT *)vo, &hdr->status);
+                     (const int32_t *)&hdr->sort_count[0], ro, (VT *)vo, &hdr->status);
   LAUNCHCHK();
   if (max_len > kSortWaveLen) {
     hipLaunchKernelGGL(k_sort_wave512<VT>, dim3(8 * cus), dim3(256), 0, st, C->colptr, C->rowidx, v, C->nrows,
-                       lists + n - 1, (const int32_t *)&hdr->bin_count[3], ro, (VT *)vo, &hdr->status);
+                       lists + n - 1, (const int32_t *)&hdr->sort_count[3], ro, (VT *)vo, &hdr->status);
     LAUNCHCHK();
   }
   if (max_len > kSortWave512Len) {
     hipLaunchKernelGGL(k_sort_block<VT>, dim3(4 * cus), dim3(kSortBlockThreads), 0, st, C->colptr, C->rowidx, v,
-                       C->nrows, lists + n, (const int32_t *)&hdr->bin_count[1], ro, (VT *)vo, &hdr->status);
+                       C->nrows, lists + n, (const int32_t *)&hdr->sort_count[1], ro, (VT *)vo, &hdr->status);
     LAUNCHCHK();
   }
   if (max_len <= kSortBlockLen) return SPGEMM_OK;
@@ -372,13 +372,13 @@ int sort_typed(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHea
   int words = 1024;
   while (words < kSortWinWords && (int64_t)words * 32 < C->nrows) words *= 2;
   const size_t lds = (size_t)words * 8;
-  const int32_t *hl = lists + 2 * n, *hc = (const int32_t *)&hdr->bin_count[2];
+  const int32_t *hl = lists + 2 * n, *hc = (const int32_t *)&hdr->sort_count[2];
   if (words <= 4096)
     hipLaunchKernelGGL((k_sort_heavy<512, VT>), dim3(4 * cus), dim3(512), lds, st, C->colptr, C->rowidx, v, C->nrows,
-                       hl, hc, &hdr->cursor[2], words, ro, (VT *)vo, &hdr->status);
+                       hl, hc, &hdr->sort_cursor, words, ro, (VT *)vo, &hdr->status);
   else
     hipLaunchKernelGGL((k_sort_heavy<1024, VT>), dim3((words <= 8192 ? 2 : 1) * cus), dim3(1024), lds, st, C->colptr,
-                       C->rowidx, v, C->nrows, hl, hc, &hdr->cursor[2], words, ro, (VT *)vo, &hdr->status);
+                       C->rowidx, v, C->nrows, hl, hc, &hdr->sort_cursor, words, ro, (VT *)vo, &hdr->status);
   LAUNCHCHK();
   return SPGEMM_OK;
 }
