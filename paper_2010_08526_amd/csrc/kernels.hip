@@ -3379,12 +3379,19 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
                          const EscOut *esc = nullptr, int64_t max_len = INT64_MAX) {
   WsHeader *hdr = (WsHeader *)ws;
   int32_t *bins = (int32_t *)(ws + L.bins);
+  // Where the caller's bound says that heavy columns are there, so that the
+  // slabbed copy of A is made anyway, the columns of the largest table go with
+  // them: that table leaves one workgroup to a CU (columns of 2049-5120 rows of
+  // a scale 13 R-MAT square: 0.25 ms in tables, 0.08 as items).
+  BinCaps caps = g_caps[1];
+  if (L.P > 0 && max_len != INT64_MAX && std::min(max_len, A->nrows) > kNumTableCap[kNumBins - 2])
+    caps.cap[kNumBins - 2] = caps.cap[kNumBins - 3];
   max_len = std::min(max_len, A->nrows);
   hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, hdr, zero_region_tag(kTagProduct, L),
                      keep_status ? 1 : 0, 1);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_bin_len, dim3(grid_of(ncol, 256)), dim3(256), 0, st, c_colptr, ncol, bins, hdr, g_min_bin,
-                     g_caps[1], esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0, max_len);
+                     caps, esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0, max_len);
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;
@@ -3393,7 +3400,7 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   // bins that no column can reach are not launched (an empty launch costs
   // about 4.6 us of the stream's time)
   for (int b = g_min_bin + 1; b < kNumBins; b++)
-    if (cnt[b] < 0 && max_len <= g_caps[1].cap[b - 1]) cnt[b] = 0;
+    if (cnt[b] < 0 && (max_len <= caps.cap[b - 1] || (b < kNumBins - 1 && caps.cap[b] == caps.cap[b - 1]))) cnt[b] = 0;
   const int half_cnt[2] = {sync ? h.half_count[0] : cnt[2], sync ? h.half_count[1] : cnt[3]};
   for (int b = 2; b <= 3; b++)
     if (cnt[b] < 0 && 2 * max_len <= kNumTableCap[b]) cnt[b] = 0;  // its half tables hold every column
