@@ -531,10 +531,10 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_fill(
 //
 // Values are read once, the next step's while one is worked on, where the
 // digit histogram read them twice and worked on each, and the fill kernel a
-// third time.  2.0e8 float32 entries in 20,011 columns, k = 100: 367 us (2.2
-// TB/s; the bounds' digit passes, two or three per column, take most of the
+// third time.  2.0e8 float32 entries in 20,011 columns, k = 100: 349 us (2.3
+// TB/s; digit passes for the bounds, two or three per column, take most of the
 // rest) and 100 us for the entries kept, against 973 and 394 us; 2.96e9 entries
-// of a scale 18 R-MAT square in four batches: 6.6 + 0.9 against 15.2 + 8.4 ms.
+// of a scale 18 R-MAT square in four batches: 6.3 + 0.9 against 15.2 + 8.4 ms.
 // ----------------------------------------------------------------------------
 constexpr int kTopMaxK = 1024;
 constexpr int kTopStep = kSelUnroll * kPrThreads;
@@ -677,6 +677,28 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
 #pragma unroll
       for (int q = 0; q < kSelUnroll; q++) v[q] = nv[q];
       if (c0 + kTopStep < e) top_load(vals, c0 + kTopStep, e, t, nv);
+      if (c0 == b && k <= kPrThreads && e - b > kTopStep) {
+        // A first bound from the first step: the k-th largest of the threads'
+        // largest values has k entries at or above it.  (The list then holds
+        // little more than k entries after the step, not all of its 2048.)
+        KT mk[1] = {0};
+        bool has = false;
+#pragma unroll
+        for (int q = 0; q < kSelUnroll; q++) {
+          if (v[q] >= lo) {
+            const KT key = (KT)order_key(v[q]);
+            mk[0] = has && mk[0] > key ? mk[0] : key;
+            has = true;
+          }
+        }
+        if (__syncthreads_count(has ? 1 : 0) >= k) {  // uniform
+          int above, equal;
+          const KT kth = block_kth<1>(mk, has ? 1u : 0u, k, (k + kPrThreads) / 2, s_hist, above, equal);
+          const KT least = (KT)order_key(VT(-INFINITY));
+          const VT edge = key_value(kth < least ? least : kth);
+          lo = edge > lo ? edge : lo;
+        }
+      }
       // the counter of the next step was last read before the previous barrier
       if (t == 0) s_add[step == 2 ? 0 : step + 1] = 0;
       uint64_t any = 0;
@@ -880,7 +902,7 @@ int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr,
   const bool top = n > 0 && k >= 1 && k <= kTopMaxK && k <= C->nnz / n;
   int32_t *stage = (int32_t *)out_values;
   if (top) {
-    ProfScope prof("prune_top", st);
+    ProfScope prof("prune_select", st);
     const VT t = threshold_of(thr, VT(0));
     if (k <= 512)
       hipLaunchKernelGGL((k_prune_top<2560, VT>), dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
@@ -899,7 +921,7 @@ int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr,
   rc = launch_colptr_scan(cnt, n, out_colptr, (int64_t *)(ws + L.scan), st);
   if (rc || n == 0) return rc;
   if (top) {
-    ProfScope prof("prune_take", st);
+    ProfScope prof("prune_fill", st);
     const unsigned gw = std::min(grid_of(n, kPrWaves), 8u * (unsigned)device_cus());
     hipLaunchKernelGGL(k_prune_place, dim3(gw), dim3(kPrThreads), 0, st, (const int64_t *)out_colptr, n, k,
                        (const uint64_t *)cutv, (const int32_t *)stage, out_rowidx);
