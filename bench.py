@@ -280,10 +280,9 @@ def fwd_bwd(args, torch, np, S, synth):
            "fwd_bwd_autograd_ms": round(t_fa * 1e3, 3), "fwd_bwd_autograd_GFLOPs": round(6 * flops / t_fa / 1e9, 2),
            "fwd_bwd_over_fwd_time": round(t_fb / t_f, 3),
            "fwd_bwd_autograd_over_fwd_time": round(t_fa / t_f, 3),
-           "note": "fwd_bwd = forward + transpose-based backward (dA via B^T, dC^T) with the pattern transposes of "
-                   "A, B and C made once per structure (outside the step); fwd_bwd_autograd = SpGEMMFn forward + "
-                   "loss + backward through torch.autograd, every transpose (A, B, C patterns) and permutation "
-                   "formed inside the step; fused = graph-capturable forward + one-pass backward (float64 atomics "
+           "note": "fwd_bwd = forward + gradients by a Backward formed once per structure (outside the step); "
+                   "fwd_bwd_autograd = SpGEMMFn forward + loss + backward through torch.autograd, everything formed "
+                   "inside the step; fused = graph-capturable forward + one-pass backward (float64 atomics "
                    "for dA, no transposes); GFLOP/s counts 3x forward flops"}
     log(f"fwd_bwd: fwd {t_f * 1e3:.2f} ms, fwd+bwd {t_fb * 1e3:.2f} ms, autograd {t_fa * 1e3:.2f} ms, "
         f"fused {t_ff * 1e3:.2f} ms")

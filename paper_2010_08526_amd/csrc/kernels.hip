@@ -709,7 +709,7 @@ __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t 
 // One workgroup per column, table (TBL slots) or bitmap (one bit per row of
 // C, sized by the launch) shared by its waves.
 template <int TBL, int THREADS, bool BITS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(!BITS && THREADS == 1024 ? 4 : 8))) void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list,
                                                        const int32_t *count_p, int64_t *nnz_out, int32_t *status) {
   constexpr int NW = THREADS / kWave;
   extern __shared__ int32_t s_keys[];  // TBL slots, or (m + 31) / 32 words (all zero between columns)
@@ -3193,6 +3193,7 @@ constexpr int64_t kLdsPerCu = 160 * 1024;
 // reading the bins' counts back first: 4096 columns took 165 us with the
 // read-back (whole product), 148 without.
 constexpr int64_t kBlindCols = 8192;
+constexpr int64_t kItemSlabs = 64;  // see numeric_typed
 
 // Counts of the bins: read back (one synchronization) or left on the device.
 static int bin_counts(WsHeader *hdr, hipStream_t st, bool sync, int *cnt, WsHeader *h) {
@@ -3382,9 +3383,12 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   // Where the caller's bound says that heavy columns are there, so that the
   // slabbed copy of A is made anyway, the columns of the largest table go with
   // them: that table leaves one workgroup to a CU (columns of 2049-5120 rows of
-  // a scale 13 R-MAT square: 0.25 ms in tables, 0.08 as items).
+  // a scale 13 R-MAT square: 0.25 ms in tables, 0.08 as items).  Up to 64 slabs:
+  // their items are looked for slab by slab, and over the 489 slabs of a
+  // 2,000,000-row graph in 16 layers the numeric pass took 1.30 s that way, 1.06
+  // with the tables; at 64 slabs (scale 18) both are within 1%.
   BinCaps caps = g_caps[1];
-  if (L.P > 0 && max_len != INT64_MAX && std::min(max_len, A->nrows) > kNumTableCap[kNumBins - 2])
+  if (L.P > 0 && L.P <= kItemSlabs && max_len != INT64_MAX && std::min(max_len, A->nrows) > kNumTableCap[kNumBins - 2])
     caps.cap[kNumBins - 2] = caps.cap[kNumBins - 3];
   max_len = std::min(max_len, A->nrows);
   hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, hdr, zero_region_tag(kTagProduct, L),
