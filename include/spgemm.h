@@ -311,8 +311,8 @@ int spgemm_batched_masked_xty(const spgemm_csc *X, const spgemm_csc *Y, const sp
  * stored (k,j) of B yields
  *   dB(k,j)  = sum over i in A(:,k) of A(i,k) * dC(i,j)       -> dB_out[nnz(B)]
  *   dA(i,k) += B(k,j) * dC(i,j) for every i in A(:,k)          -> dA_out[nnz(A)]
- * dA is accumulated with float64 atomics in the workspace and rounded once
- * (summation order is not fixed, so dA may differ in the last bits between
+ * dA is accumulated with float64 atomics (float32: in the workspace, rounded
+ * once; float64: in dA_out, which is overwritten; summation order is not fixed, so dA may differ in the last bits between
  * calls).  C gives only the pattern (values not read).  Columns of C above
  * the largest LDS table are reported through the workspace status; the
  * transpose-based path (spgemm_transpose + spgemm_masked_xty) handles them.
