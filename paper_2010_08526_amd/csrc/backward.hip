@@ -716,9 +716,15 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
                       void *dB, const WsLayout &L, char *ws, hipStream_t st) {
   WsHeader *hdr = (WsHeader *)ws;
   int32_t *bins = (int32_t *)(ws + L.bins);
-  // float64 gradients are summed where they are wanted, float32 ones in the workspace
-  constexpr bool kInPlace = sizeof(VT) == sizeof(double);
-  double *acc = kInPlace ? (double *)dA : (double *)(ws + L.heavy_vals);
+  // float64 gradients are summed where they are wanted (unless that is over
+  // an input, which the terms still read), float32 ones in the workspace
+  const auto over = [&](const void *p, int64_t count) {
+    const uintptr_t a = (uintptr_t)dA, b = (uintptr_t)p;
+    return b < a + sizeof(VT) * (uintptr_t)A->nnz && a < b + sizeof(VT) * (uintptr_t)count;
+  };
+  const bool in_place = sizeof(VT) == sizeof(double) && !over(A->values, A->nnz) && !over(B->values, B->nnz) &&
+                        !over(dC, C->nnz);
+  double *acc = in_place ? (double *)dA : (double *)(ws + L.heavy_vals);
   const int64_t n = C->ncols;
   int rc = launch_init_header(hdr, (uint64_t)0, st);
   if (rc) return rc;
@@ -754,7 +760,7 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   }
   hipLaunchKernelGGL(k_mx_flag_if_nonzero, dim3(1), dim3(64), 0, st, &hdr->bin_count[kNumBins - 1], status, 7);
   LAUNCHCHK();
-  if (!kInPlace) {
+  if (!in_place) {
     hipLaunchKernelGGL(k_round<VT>, dim3(gz), dim3(256), 0, st, acc, A->nnz, (VT *)dA);
     LAUNCHCHK();
   }

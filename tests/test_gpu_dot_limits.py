@@ -108,3 +108,24 @@ def test_backward_forms_agree(dtype, monkeypatch):
     for bw in (fused, trans):
         with pytest.raises(S.SpgemmError):
             bw(dC.to(other))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_gradient_over_an_input(dtype):
+    """dA written over A's own values: the terms have read them by then."""
+    print(f"case: gradient over an input {dtype}", flush=True)
+    import ctypes
+    rng = np.random.default_rng(2)
+    A = _csc(400, [rng.choice(400, n, replace=False) for n in rng.integers(0, 80, 200)], rng, dtype).to("cuda")
+    B = _csc(200, [rng.choice(200, n, replace=False) for n in rng.integers(0, 60, 150)], rng, dtype).to("cuda")
+    C = S.spgemm(A, B)
+    dC = torch.from_numpy(rng.integers(1, 5, C.nnz)).to(dtype).cuda()
+    wA, wB = S.Backward(A, B, C)(dC)
+    ws = S.alloc_workspace(S.workspace_size(S.OP_BATCHED_BACKWARD, A, B, 0, C.ncols))
+    dB = torch.empty_like(B.values)
+    cd = S.desc(S.CSC(C.nrows, C.ncols, C.colptr, C.rowidx, None), S.F32)
+    S._check(S._lib.spgemm_batched_backward(ctypes.byref(S.desc(A)), ctypes.byref(S.desc(B)), ctypes.byref(cd),
+                                            S._ptr(dC), S._ptr(A.values), S._ptr(dB), S._ptr(ws), ws.numel(),
+                                            S._stream(None)), "spgemm_batched_backward")
+    S.check_ws(ws)
+    assert torch.equal(A.values, wA) and torch.equal(dB, wB)
