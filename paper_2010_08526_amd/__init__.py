@@ -735,11 +735,16 @@ def _fused_backward(A, B, b_values, C, dC_values, ws, stream=None):
 
 
 def _on_stream(stream):
-    """Context in which torch's own work goes to ``stream`` (None: the current one)."""
+    """Context in which torch's own work goes to ``stream``: a torch stream or
+    a handle (0: the default stream), or None for the current one."""
     if stream is None:
         return contextlib.nullcontext()
     if not isinstance(stream, torch.cuda.Stream):
-        stream = torch.cuda.ExternalStream(_stream(stream))
+        handle = _stream(stream)
+        if handle == int(torch.cuda.current_stream().cuda_stream):
+            return contextlib.nullcontext()
+        # (an ExternalStream of handle 0 is not the default stream but another one)
+        stream = torch.cuda.ExternalStream(handle) if handle else torch.cuda.default_stream()
     return torch.cuda.stream(stream)
 
 
