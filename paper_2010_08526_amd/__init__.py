@@ -310,12 +310,14 @@ class Plan:
     input_bytes: int
     reserve_bytes: int
     longest: int  # entries of C's longest column
+    ready: object = None  # event after which counts, if a tensor, may be read
 
     @property
     def nnz_host(self) -> np.ndarray:
         """int64 [rows, n] on the host."""
-        if isinstance(self.counts, torch.Tensor):
-            self.counts = self.counts.cpu().numpy()
+        if self.ready is not None:  # the stream read on may be another than the plan's
+            self.ready.synchronize()
+            self.counts, self.ready = self.counts.cpu().numpy(), None
         return self.counts
 
     @property
@@ -385,7 +387,8 @@ class Engine:
         whole = self._plan_whole(stream)
         if whole is not None:
             return whole
-        nnz_host = self.nnz.cpu().numpy()
+        with _on_stream(stream):  # where the symbolic pass is still at work
+            nnz_host = self.nnz.cpu().numpy()
         counts = nnz_host
         if self.sorted_output:  # the merged batch is held twice: as formed and sorted
             counts = nnz_host.copy()
@@ -416,8 +419,10 @@ class Engine:
             return None
         with _on_stream(stream):
             counts = self.nnz.clone()  # self.nnz is written again by the next product
+            ready = torch.cuda.Event()
+            ready.record()
         return Plan(self.flops, self.nnz, counts, [0, n], sums.reshape(1, rows), L, self.budget_bytes,
-                    self.input_bytes, self.reserve_bytes, int(longest.value))
+                    self.input_bytes, self.reserve_bytes, int(longest.value), ready)
 
     def _buffers(self, plan: Plan):
         widths = [b - a for a, b in zip(plan.bounds[:-1], plan.bounds[1:])]

@@ -60,3 +60,23 @@ def test_refresh_on_the_default_stream_by_handle():
     dA2, _ = bw(dC)
     bw.check()
     assert torch.allclose(dA2, 2 * dA, rtol=1e-12)
+
+
+@pytest.mark.parametrize("n", [8000, 40000])
+def test_counts_read_on_another_stream(n):
+    """A plan made on a busy side stream, its counts read on the default one
+    at once."""
+    print(f"case: counts on another stream {n}", flush=True)
+    A = synth.erdos_renyi(n, n, 3, 5, torch.float32)
+    B = synth.erdos_renyi(n, n, 5, 6, torch.float32)
+    eng = S.Engine(A.to("cuda"), B.to("cuda"))
+    side = torch.cuda.Stream()
+    want = oracle.count(A, B)
+    torch.cuda.synchronize()
+    for stream in (side, int(side.cuda_stream)):
+        eng.nnz.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(10_000_000)
+        plan = eng.plan(stream)
+        assert np.array_equal(plan.nnz_host[0], want) and plan.total_flops == 15 * n

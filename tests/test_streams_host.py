@@ -2,8 +2,10 @@
 torch's stream calls are replaced by stand-ins that record what is asked for."""
 from __future__ import annotations
 
+import contextlib
 import types
 
+import numpy as np
 import pytest
 import torch
 
@@ -16,15 +18,22 @@ class FakeCuda:
 
     def __init__(self, monkeypatch, current):
         self.entered = []
+        self.current = current
         stream = lambda h: types.SimpleNamespace(cuda_stream=h)  # noqa: E731
-        monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: stream(current))
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: stream(self.current))
         monkeypatch.setattr(torch.cuda, "default_stream", lambda *a: stream(0))
         monkeypatch.setattr(torch.cuda, "ExternalStream", lambda h: stream(h if h else "another stream"))
         monkeypatch.setattr(torch.cuda, "stream", self.enter)
 
+    @contextlib.contextmanager
+    def context(self, s):
+        before, self.current = self.current, s.cuda_stream
+        yield s
+        self.current = before
+
     def enter(self, s):
         self.entered.append(s.cuda_stream)
-        return types.SimpleNamespace(__enter__=lambda: s, __exit__=lambda *a: None)
+        return self.context(s)
 
 
 @pytest.mark.parametrize("current", [0, 4096])
@@ -35,3 +44,56 @@ def test_context_of_a_handle(monkeypatch, current, handle):
     S._on_stream(handle)
     used = fake.entered[0] if fake.entered else current
     assert used == (current if handle is None else handle)
+
+
+class Counts:
+    """Stand-in for the counts on the device: notes what is done on which stream."""
+
+    def __init__(self, fake, rows, n):
+        self.fake, self.rows, self.n, self.log = fake, rows, n, []
+
+    def data_ptr(self):
+        return 0
+
+    def clone(self):
+        self.log.append(("clone", self.fake.current))
+        return self
+
+    def cpu(self):
+        self.log.append(("read", self.fake.current))
+        return torch.ones((self.rows, self.n), dtype=torch.int64)
+
+
+@pytest.mark.parametrize("n", [100, 40000])
+@pytest.mark.parametrize("handle", [None, 0, 4096])
+def test_counts_are_read_after_the_symbolic_pass(monkeypatch, n, handle):
+    """The counts of a plan made on one stream and read on another: read (or
+    copied, and read once that is done) where the symbolic pass ran."""
+    fake = FakeCuda(monkeypatch, 0)
+    counts = Counts(fake, 1, n)
+
+    class Event:
+        def record(self, stream=None):
+            counts.log.append(("record", fake.current))
+
+        def synchronize(self):
+            counts.log.append(("wait", None))
+
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(S, "symbolic", lambda *a, **k: None)
+    monkeypatch.setattr(S._lib, "spgemm_count_sums", lambda *a: 0)
+    eng = object.__new__(S.Engine)
+    eng.A = eng.B = S.CSC(100, n, None, torch.zeros(0), None)
+    eng.L, eng.vbytes, eng.max_batches, eng.sorted_output = 1, 4, 1 << 16, False
+    eng.input_bytes, eng.reserve_bytes, eng.budget_bytes = 0, 0, 1 << 30
+    eng.flops = eng.ws_sym = None
+    eng.ws_scan = torch.zeros(16)
+    eng.nnz = counts
+    plan = eng.plan(handle)
+    assert np.array_equal(plan.nnz_host, np.ones((1, n)))
+    s = handle or 0
+    if n < 32768:
+        assert counts.log == [("read", s)]
+    else:
+        assert counts.log == [("clone", s), ("record", s), ("wait", None), ("read", 0)]
+    assert plan.nnz_host is plan.nnz_host
