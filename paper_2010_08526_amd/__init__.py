@@ -532,7 +532,6 @@ class Engine:
         cp = torch.empty(n + 1, dtype=torch.int64, device=dev)
         ri = torch.empty(max(1, total), dtype=torch.int32, device=dev)
         v = torch.empty(max(1, total), dtype=self.vdtype, device=dev)
-        colptr(self.nnz[L if L > 1 else 0], cp, self.ws_scan, stream)
         vb = self.vbytes
         part_max = plan.batch_nnz[:, :L].sum(1).max() if L > 1 else 0
         key = (int(sizes.max()) if self.sorted_output else 0, int(part_max))
@@ -548,6 +547,11 @@ class Engine:
                 st["dcp"] = torch.empty(L * n + 1, dtype=torch.int64, device=dev)
                 st["ws"] = alloc_workspace(workspace_size(OP_COLPTR, None, None, 0, L * n), dev)
             self._stage = st
+        # the memory comes from the current stream's pool, where what held it
+        # before may still be at work (run() waits for ``stream`` before it
+        # hands the output on)
+        _wait_for_current(stream)
+        colptr(self.nnz[L if L > 1 else 0], cp, self.ws_scan, stream)
         if L > 1:  # the layers' counts one after another: layer l's pointers start at l * n
             dcp = st["dcp"]
             colptr(self.nnz[:L].reshape(-1), dcp, st["ws"], stream)
@@ -751,6 +755,14 @@ def _on_stream(stream):
         # (an ExternalStream of handle 0 is not the default stream but another one)
         stream = torch.cuda.ExternalStream(handle) if handle else torch.cuda.default_stream()
     return torch.cuda.stream(stream)
+
+
+def _wait_for_current(stream):
+    """Work queued on ``stream`` from here on waits for the current stream's."""
+    current = torch.cuda.current_stream()
+    if stream is not None and _stream(stream) != int(current.cuda_stream):
+        with _on_stream(stream):
+            torch.cuda.current_stream().wait_stream(current)
 
 
 class Backward:

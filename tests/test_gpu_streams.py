@@ -8,6 +8,7 @@ import torch
 
 import oracle
 import synth
+from tests.gpu_util import assert_matches
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +81,24 @@ def test_counts_read_on_another_stream(n):
             torch.cuda._sleep(10_000_000)
         plan = eng.plan(stream)
         assert np.array_equal(plan.nnz_host[0], want) and plan.total_flops == 15 * n
+
+
+def test_output_memory_in_use_on_another_stream():
+    """A product on a side stream whose output takes memory that the default
+    stream, behind a long kernel, has yet to write to."""
+    print("case: output memory in use", flush=True)
+    A = synth.erdos_renyi(20000, 20000, 6, 5, torch.float64)
+    eng = S.Engine(A.to("cuda"), A.to("cuda"))
+    side = torch.cuda.Stream()
+    want, _ = eng.run(stream=side)
+    torch.cuda.synchronize()
+    n = want.nnz
+    x = [torch.empty(n, dtype=torch.float64, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")]
+    torch.cuda._sleep(10_000_000)
+    for t in x:
+        t.fill_(7)
+    del x, t
+    C, _ = eng.run(stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(C.colptr, want.colptr)
+    assert_matches(C, oracle.spgemm(A, A), torch.float64, "side stream")

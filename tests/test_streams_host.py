@@ -19,7 +19,9 @@ class FakeCuda:
     def __init__(self, monkeypatch, current):
         self.entered = []
         self.current = current
-        stream = lambda h: types.SimpleNamespace(cuda_stream=h)  # noqa: E731
+        self.waits = []  # (stream, the stream it waits for)
+        stream = lambda h: types.SimpleNamespace(  # noqa: E731
+            cuda_stream=h, wait_stream=lambda o: self.waits.append((h, o.cuda_stream)))
         monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: stream(self.current))
         monkeypatch.setattr(torch.cuda, "default_stream", lambda *a: stream(0))
         monkeypatch.setattr(torch.cuda, "ExternalStream", lambda h: stream(h if h else "another stream"))
@@ -97,3 +99,27 @@ def test_counts_are_read_after_the_symbolic_pass(monkeypatch, n, handle):
     else:
         assert counts.log == [("clone", s), ("record", s), ("wait", None), ("read", 0)]
     assert plan.nnz_host is plan.nnz_host
+
+
+@pytest.mark.parametrize("handle", [None, 0, 4096])
+@pytest.mark.parametrize("layers", [1, 2])
+def test_new_output_waits_for_the_memory(monkeypatch, handle, layers):
+    """The first kernel that writes a whole product's output, whose memory is
+    the current stream's, comes after that stream's work."""
+    fake = FakeCuda(monkeypatch, 0)
+    order = []
+    monkeypatch.setattr(S, "colptr", lambda *a: order.append(len(fake.waits)))
+    monkeypatch.setattr(S, "numeric", lambda *a: order.append(len(fake.waits)))
+    monkeypatch.setattr(S, "merge", lambda *a: order.append(len(fake.waits)))
+    monkeypatch.setattr(S, "alloc_workspace", lambda *a: torch.zeros(256, dtype=torch.uint8))
+    eng = object.__new__(S.Engine)
+    eng.A = eng.B = S.CSC(4, 4, None, torch.zeros(0), None)
+    eng.L, eng.vbytes, eng.vdtype, eng.sorted_output, eng.semiring = layers, 4, torch.float32, False, 0
+    eng.device, eng._stage = "cpu", None
+    eng.ws_scan = eng.ws_num = eng.ws_mrg = eng.flops = torch.zeros(16)
+    rows = layers + 1 if layers > 1 else 1
+    eng.nnz = torch.ones((rows, 4), dtype=torch.int64)
+    plan = types.SimpleNamespace(batch_nnz=np.full((1, rows), 4), nbatches=1, bounds=[0, 4], longest=1)
+    eng._whole(plan, handle)
+    assert fake.waits == ([(4096, 0)] if handle == 4096 else [])
+    assert order and set(order) == {len(fake.waits)}
