@@ -759,8 +759,10 @@ def _on_stream(stream):
 
 def _wait_for_current(stream):
     """Work queued on ``stream`` from here on waits for the current stream's."""
+    if stream is None:
+        return
     current = torch.cuda.current_stream()
-    if stream is not None and _stream(stream) != int(current.cuda_stream):
+    if _stream(stream) != int(current.cuda_stream):
         with _on_stream(stream):
             torch.cuda.current_stream().wait_stream(current)
 
@@ -784,9 +786,14 @@ class Backward:
         self.ws_f = None
         with _on_stream(stream):
             longest = int((C.colptr[1:] - C.colptr[:-1]).max()) if C.ncols > 0 else 0
-            if longest <= FUSED_COL_MAX and A.values is not None and B.values is not None:
-                self._b = B.values.clone()
-                self.ws_f = alloc_workspace(workspace_size(OP_BATCHED_BACKWARD, A, B, 0, C.ncols), C.rowidx.device)
+        if longest <= FUSED_COL_MAX and A.values is not None and B.values is not None:
+            # both from the current stream's pool, as all memory here: gradients
+            # may be asked for on another stream than this one
+            self._b = torch.empty_like(B.values)
+            self.ws_f = alloc_workspace(workspace_size(OP_BATCHED_BACKWARD, A, B, 0, C.ncols), C.rowidx.device)
+            _wait_for_current(stream)
+            with _on_stream(stream):
+                self._b.copy_(B.values)
         if self.ws_f is None:
             self._transposes(B, stream)
 

@@ -123,3 +123,33 @@ def test_new_output_waits_for_the_memory(monkeypatch, handle, layers):
     eng._whole(plan, handle)
     assert fake.waits == ([(4096, 0)] if handle == 4096 else [])
     assert order and set(order) == {len(fake.waits)}
+
+
+@pytest.mark.parametrize("handle", [None, 0, 4096])
+def test_gradient_memory_is_the_current_streams(monkeypatch, handle):
+    """What a Backward keeps is used, and given back, on any stream: it is not
+    taken from the pool of the stream that fills it; the fill waits for it."""
+    fake = FakeCuda(monkeypatch, 0)
+    pools, fills = [], []
+
+    class Values(torch.Tensor):
+        @classmethod
+        def __torch_function__(cls, func, types, args=(), kwargs=None):
+            name = func.__name__
+            if name in ("clone", "empty_like"):
+                pools.append(fake.current)
+            if name in ("clone", "copy_"):
+                fills.append((fake.current, len(fake.waits)))
+            return super().__torch_function__(func, types, args, kwargs or {})
+
+    def workspace(nbytes, device=None):
+        pools.append(fake.current)
+        return torch.zeros(256, dtype=torch.uint8)
+
+    monkeypatch.setattr(S, "alloc_workspace", workspace)
+    cp, ri = torch.arange(5), torch.arange(4, dtype=torch.int32)
+    M = S.CSC(4, 4, cp, ri, torch.ones(4).as_subclass(Values))
+    bw = S.Backward(M, M, M, stream=handle)
+    assert bw.ws_f is not None and torch.equal(torch.Tensor(bw._b), torch.ones(4))
+    assert pools == [0, 0]
+    assert fills == [(handle or 0, 1 if handle else 0)]
