@@ -793,7 +793,7 @@ class Backward:
             self.ws_f = alloc_workspace(workspace_size(OP_BATCHED_BACKWARD, A, B, 0, C.ncols), C.rowidx.device)
             _wait_for_current(stream)
             with _on_stream(stream):
-                self._b.copy_(B.values)
+                self._b.copy_(B.values.detach())
         if self.ws_f is None:
             self._transposes(B, stream)
 
@@ -820,7 +820,7 @@ class Backward:
         self.B = B
         if self.ws_f is not None:
             with _on_stream(stream):
-                self._b.copy_(B.values)
+                self._b.copy_(B.values.detach())  # not a step of any graph
         if "BT" in self.__dict__:  # B^T's values are re-gathered
             permute(B.values, self.permB, False, self.BT.values, stream)
 

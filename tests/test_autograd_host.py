@@ -1,0 +1,21 @@
+"""What autograd sees of the binding, checked without a GPU."""
+from __future__ import annotations
+
+import torch
+
+import paper_2010_08526_amd as S
+
+
+def test_kept_values_are_no_part_of_a_graph(monkeypatch):
+    """A Backward made, and refreshed, with values that require gradients
+    records nothing: its copy of them has no history that could grow."""
+    monkeypatch.setattr(S, "alloc_workspace", lambda *a: torch.zeros(256, dtype=torch.uint8))
+    v = torch.ones(4, requires_grad=True)
+    M = S.CSC(4, 4, torch.arange(5), torch.arange(4, dtype=torch.int32), v)
+    bw = S.Backward(M, M, M)
+    assert bw.ws_f is not None
+    for k in range(3):
+        assert not bw._b.requires_grad and bw._b.grad_fn is None
+        assert torch.equal(bw._b, M.values)
+        M.values = v * (k + 2)
+        bw.refresh_values(M)
