@@ -864,9 +864,9 @@ class SpGEMMFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, d_vals, _d_cp, _d_ri):
-        if d_vals is None:
-            return None, None, None, None, None, None
         a_vals, b_vals = ctx.saved_tensors
+        if d_vals is None:  # a gradient of zeros
+            return torch.zeros_like(a_vals), torch.zeros_like(b_vals), None, None, None, None
         A = CSC(ctx.A.nrows, ctx.A.ncols, ctx.A.colptr, ctx.A.rowidx, a_vals)
         B = CSC(ctx.B.nrows, ctx.B.ncols, ctx.B.colptr, ctx.B.rowidx, b_vals)
         if ctx.longest <= FUSED_COL_MAX:  # no transposes: see Backward

@@ -1,6 +1,8 @@
 """What autograd sees of the binding, checked without a GPU."""
 from __future__ import annotations
 
+import types
+
 import torch
 
 import paper_2010_08526_amd as S
@@ -19,3 +21,11 @@ def test_kept_values_are_no_part_of_a_graph(monkeypatch):
         assert torch.equal(bw._b, M.values)
         M.values = v * (k + 2)
         bw.refresh_values(M)
+
+
+def test_undefined_gradient_counts_as_zero():
+    """A consumer of C's values that has no gradient for them: dA and dB are
+    zeros (not missing)."""
+    a, b = torch.ones(5), torch.ones(7)
+    dA, dB, *rest = S.SpGEMMFn.backward(types.SimpleNamespace(saved_tensors=(a, b)), None, None, None)
+    assert torch.equal(dA, torch.zeros(5)) and torch.equal(dB, torch.zeros(7)) and rest == [None] * 4
