@@ -167,9 +167,9 @@ def plan_batches(nnz_host, ncols: int, n_layers: int, value_bytes: int, input_by
     """Returns (bounds: list[int], batch_nnz: np.ndarray[b, rows])."""
     nnz_host = np.ascontiguousarray(np.asarray(nnz_host, dtype=np.int64))
     rows = n_layers + 1 if n_layers > 1 else 1
-    max_batches = max(1, min(max_batches, ncols))  # a batch holds at least one column
-    bounds = np.zeros(max_batches + 1, np.int64)
-    tot = np.zeros(max_batches * rows, np.int64)
+    max_batches = min(max_batches, max(1, ncols))  # a batch holds at least one column
+    bounds = np.zeros(max(1, max_batches) + 1, np.int64)
+    tot = np.zeros(max(1, max_batches) * rows, np.int64)
     nb = _i32(0)
     _check(_lib.spgemm_plan_batches(nnz_host.ctypes.data, ncols, n_layers, value_bytes, int(input_bytes),
                                     int(budget_bytes), int(reserve_bytes), max_batches, bounds.ctypes.data,

@@ -67,6 +67,15 @@ def test_planner_matches_oracle_rule(seed):
         assert np.array_equal(tot[i], nnz[:, bounds[i]:bounds[i + 1]].sum(1))
 
 
+@pytest.mark.parametrize("max_batches", [0, -1, -5])
+@pytest.mark.parametrize("n", [0, 3])
+def test_planner_refuses_no_batches(max_batches, n):
+    """Fewer than one batch is an error, also where one would do."""
+    with pytest.raises(S.SpgemmError) as e:
+        S.plan_batches(np.ones(n, np.int64), n, 1, 4, 0, 1000, 0, max_batches=max_batches)
+    assert e.value.status == S.E_INVAL
+
+
 def test_planner_errors():
     nnz = np.array([10, 20, 30], np.int64)
     with pytest.raises(S.SpgemmError) as e:
