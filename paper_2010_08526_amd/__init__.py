@@ -296,29 +296,40 @@ def layer_bounds(kdim: int, n_layers: int) -> list[tuple[int, int]]:
     return [(min(kdim, l * w), min(kdim, l * w + w)) for l in range(n_layers)]
 
 
+class _Unread:
+    """Counts on the device, and the event after which they may be read (on
+    any stream)."""
+
+    def __init__(self, counts: torch.Tensor):
+        self.counts = counts
+        self.ready = torch.cuda.Event()
+        self.ready.record()
+
+    def read(self) -> np.ndarray:
+        self.ready.synchronize()
+        return self.counts.cpu().numpy()
+
+
 @dataclass
 class Plan:
     """Result of the symbolic pass and the planner for one product."""
 
     flops: torch.Tensor  # int64 [n] per output column (device)
     nnz: torch.Tensor  # int64 [rows, n] (device)
-    counts: object  # nnz as it was: numpy, or a tensor that is read back on first use
+    nnz_host: np.ndarray  # int64 [rows, n]; read back on first use where the plan did not need it
     bounds: list
     batch_nnz: np.ndarray  # [b, rows]
     n_layers: int
     budget_bytes: int
     input_bytes: int
     reserve_bytes: int
-    longest: int  # entries of C's longest column
-    ready: object = None  # event after which counts, if a tensor, may be read
+    longest: int | None = None  # entries of C's longest column, if known
 
     @property
-    def nnz_host(self) -> np.ndarray:
-        """int64 [rows, n] on the host."""
-        if self.ready is not None:  # the stream read on may be another than the plan's
-            self.ready.synchronize()
-            self.counts, self.ready = self.counts.cpu().numpy(), None
-        return self.counts
+    def counts(self):
+        """nnz_host, or where it has not been read back the tensor it comes from."""
+        c = self.__dict__["nnz_host"]
+        return c.counts if isinstance(c, _Unread) else c
 
     @property
     def nbatches(self) -> int:
@@ -327,6 +338,23 @@ class Plan:
     @property
     def total_flops(self) -> int:
         return int(self.flops.sum())
+
+    def _read_counts(self) -> np.ndarray:
+        c = self.__dict__["nnz_host"]
+        if isinstance(c, _Unread):
+            c = self.__dict__["nnz_host"] = c.read()
+        return c
+
+    def _set_counts(self, c):
+        self.__dict__["nnz_host"] = c
+
+    def __getstate__(self):  # saved or copied: with the counts themselves
+        self._read_counts()
+        return dict(self.__dict__)
+
+
+# a field to the constructor, to dataclasses and to saved plans, read when asked for
+Plan.nnz_host = property(Plan._read_counts, Plan._set_counts)
 
 
 class Engine:
@@ -418,11 +446,9 @@ class Engine:
         if (4 + self.vbytes) * held + 8 * (L + 1 if L > 1 else 1) * n > avail or self.max_batches < 1:
             return None
         with _on_stream(stream):
-            counts = self.nnz.clone()  # self.nnz is written again by the next product
-            ready = torch.cuda.Event()
-            ready.record()
+            counts = _Unread(self.nnz.clone())  # self.nnz is written again by the next product
         return Plan(self.flops, self.nnz, counts, [0, n], sums.reshape(1, rows), L, self.budget_bytes,
-                    self.input_bytes, self.reserve_bytes, int(longest.value), ready)
+                    self.input_bytes, self.reserve_bytes, int(longest.value))
 
     def _buffers(self, plan: Plan):
         widths = [b - a for a, b in zip(plan.bounds[:-1], plan.bounds[1:])]
@@ -494,7 +520,7 @@ class Engine:
         (tensors, or addresses that the pointers count from)."""
         A, B, L = self.A, self.B, self.L
         c0, c1 = plan.bounds[i], plan.bounds[i + 1]
-        top = plan.longest
+        top = NO_BOUND if plan.longest is None else plan.longest
         if L == 1:
             if self.sorted_output:  # formed in row order (hashed columns staged)
                 numeric_sorted(A, B, c0, c1, self.flops[c0:c1], ccp, *out, *hashed, self.ws_num, stream,
