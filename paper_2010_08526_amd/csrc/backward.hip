@@ -733,13 +733,15 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   LAUNCHCHK();
   BinCaps caps = bin_caps(1);
   caps.cap[kNumBins - 2] = kNumTableCap[kNumBins - 2];  // whatever fits the largest table is formed
-  hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n,
-                     std::min(g_min_bin_value(), kNumBins - 2), caps, bins, hdr);
-  LAUNCHCHK();
+  if (n > 0) {
+    hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n,
+                       std::min(g_min_bin_value(), kNumBins - 2), caps, bins, hdr);
+    LAUNCHCHK();
+  }
   DotArgs<VT> a{A->colptr, A->rowidx, (const VT *)A->values, C->colptr, C->rowidx, (const VT *)dC,
                 B->colptr, B->rowidx, (const VT *)B->values, (VT *)dB, acc, C->nrows, A->ncols, A->nnz};
   int32_t *status = &hdr->status;
-  for (int b = 0; b < kNumBins + 1; b++) {
+  for (int b = 0; n > 0 && b < kNumBins + 1; b++) {  // (no columns: dA is zero)
     const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
     static const char *kNames[kNumBins + 1] = {"fbwd_wave64", "fbwd_wave256", "fbwd_wave1024", "fbwd_block4096",
                                                "fbwd_block10240", "fbwd_wave512", "fbwd_block2048"};

@@ -129,3 +129,22 @@ def test_gradient_over_an_input(dtype):
                                             S._stream(None)), "spgemm_batched_backward")
     S.check_ws(ws)
     assert torch.equal(A.values, wA) and torch.equal(dB, wB)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("shape", [(6, 3, 0), (5, 0, 7), (0, 4, 3)])
+def test_gradients_of_empty_products(shape, dtype):
+    """No columns, no inner dimension, no rows: gradients of zeros."""
+    print(f"case: empty gradients {shape} {dtype}", flush=True)
+    m, k, n = shape
+    A = synth.erdos_renyi(m, k, min(m, 2), 3, dtype).to("cuda")
+    B = synth.erdos_renyi(k, n, min(k, 2), 4, dtype).to("cuda")
+    C = S.spgemm(A, B)
+    assert C.nnz == 0
+    bw = S.Backward(A, B, C)
+    dA, dB = bw(C.values)
+    bw.check()
+    assert torch.equal(dA, torch.zeros_like(A.values)) and torch.equal(dB, torch.zeros_like(B.values))
+    a, b = A.values.clone().requires_grad_(True), B.values.clone().requires_grad_(True)
+    S.SpGEMMFn.apply(a, b, A, B)[0].sum().backward()
+    assert torch.equal(a.grad, torch.zeros_like(a)) and torch.equal(b.grad, torch.zeros_like(b))
