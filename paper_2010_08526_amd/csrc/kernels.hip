@@ -1297,7 +1297,7 @@ __global__ __launch_bounds__(256) void k_esc_wave_n(ProductArgs<VT> a, int64_t c
     }
     wave_sync();  // the ranking reuses the arrays
     int rank[E];
-    rank_rows<kWave, E, true>(row, n, l, L, (uint32_t *)nullptr, rank);
+    rank_rows<kWave, E, Ties::kUsual>(row, n, l, L, (uint32_t *)nullptr, rank);
 #pragma unroll
     for (int e = 0; e < E; e++)
       if (l + e * kWave < n) {
@@ -1391,7 +1391,7 @@ __global__ __launch_bounds__(kEscThreads) void k_esc_block(ProductArgs<VT> a, in
     }
     __syncthreads();  // the ranking reuses the arrays
     int rank[E];
-    rank_rows<T, E, true>(row, n, tid, L, s_red, rank);
+    rank_rows<T, E, Ties::kUsual>(row, n, tid, L, s_red, rank);
 #pragma unroll
     for (int e = 0; e < E; e++)
       if (tid + e * T < n) {
@@ -3849,7 +3849,7 @@ int spgemm_numeric_sorted_upto(const spgemm_csc *A, const spgemm_csc *B, int64_t
   T.rowidx = tmp_rowidx;
   T.values = tmp_values;
   return sort_column_lists(&T, c_rowidx, c_values, (int32_t *)((char *)ws + L.bins), (WsHeader *)ws,
-                           use_esc ? flops : nullptr, esc_cf_max, s, max_len);
+                           use_esc ? flops : nullptr, esc_cf_max, s, std::min(max_len, A->nrows));
 }
 
 int spgemm_merge(const spgemm_csc *parts, int32_t n_parts, const int64_t *c_colptr, int32_t *c_rowidx,

@@ -829,7 +829,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
 #pragma unroll
       for (int i = 0; i < KE; i++) row[i] = t + i * kPrThreads < kept ? s.list.pos[t + i * kPrThreads] : 0;
       __syncthreads();
-      rank_rows<kPrThreads, KE, false>(row, kept, t, s.rank, s_red, rank);
+      rank_rows<kPrThreads, KE, Ties::kNone>(row, kept, t, s.rank, s_red, rank);
       int32_t *dst = stage + j * (int64_t)k;
 #pragma unroll
       for (int i = 0; i < KE; i++)

@@ -8,8 +8,10 @@
 // few buckets (more than kRankCrowd entries in one) are ranked by a bitonic
 // sort of (row, entry number) instead, so no input costs more than that.
 //
-// With DUP, equal rows are ordered by entry number (a stable sort); without,
-// rows are distinct (equal rows get the same rank: callers check the result).
+// Equal rows are ordered by entry number (a stable sort).  Where none are
+// expected (Ties::kRare) an entry is ranked without its number, and columns
+// found to hold a row twice are ranked by the bitonic sort: keeping the numbers
+// costs 2.4 of 196 us of a captured product of 64 instances and its sort.
 #pragma once
 
 #include "device.hpp"
@@ -17,6 +19,9 @@
 namespace spg {
 
 constexpr int kRankCrowd = 64;
+
+// Equal rows in a column: usual, rare, or none (equal rows would get one rank).
+enum class Ties { kUsual, kRare, kNone };
 
 // Largest value over the wave (unsigned).
 __device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
@@ -79,7 +84,7 @@ __device__ __forceinline__ void bitonic_u64(uint64_t *comp, int n2, int t) {
 // THREADS / 64 words of LDS (unused by a single wave).  All threads call it
 // (a wave: THREADS = 64); LDS contents written before must be past a barrier.
 // On return every thread has its ranks and the LDS may be rewritten.
-template <int THREADS, int E, bool DUP, int N, class VT>
+template <int THREADS, int E, Ties TIES, int N, class VT>
 __device__ __forceinline__ void rank_rows(const int32_t (&row)[E], int n, int t, RankLds<N, VT> &L, uint32_t *s_red,
                                           int (&rank)[E]) {
   static_assert(N == THREADS * E, "one register per entry");
@@ -157,17 +162,19 @@ __device__ __forceinline__ void rank_rows(const int32_t (&row)[E], int n, int t,
     if (t == 0) L.cnt[nb] = n;
   }
   sync();
-  if (big <= kRankCrowd) {  // uniform
+  bool by_number = big > kRankCrowd;  // uniform
+  if (!by_number) {
 #pragma unroll
     for (int e = 0; e < E; e++) {
       const int i = t + e * THREADS;
       if (i < n) {
         const int p = L.cnt[((uint32_t)row[e] - lo) >> sh] + old[e];
         L.u.s.key[p] = row[e];
-        if (DUP) L.ord[p] = (uint16_t)i;
+        if (TIES == Ties::kUsual) L.ord[p] = (uint16_t)i;
       }
     }
     sync();
+    bool twice = false;
 #pragma unroll
     for (int e = 0; e < E; e++) {
       const int i = t + e * THREADS;
@@ -177,15 +184,26 @@ __device__ __forceinline__ void rank_rows(const int32_t (&row)[E], int n, int t,
         const int c0 = L.cnt[b], c1 = L.cnt[b + 1];
         int r = c0;
         if (c1 - c0 > 1) {
+          int same = 0;
           for (int q = c0; q < c1; q++) {
             const uint32_t k = (uint32_t)L.u.s.key[q];
-            r += k < (uint32_t)row[e] || (DUP && k == (uint32_t)row[e] && L.ord[q] < i) ? 1 : 0;
+            r += k < (uint32_t)row[e] || (TIES == Ties::kUsual && k == (uint32_t)row[e] && L.ord[q] < i) ? 1 : 0;
+            if (TIES == Ties::kRare) same += k == (uint32_t)row[e] ? 1 : 0;
           }
+          twice |= same > 1;
         }
         rank[e] = r;
       }
     }
-  } else {
+    if constexpr (TIES == Ties::kRare) {
+      if constexpr (kOne)
+        by_number = __ballot(twice) != 0;
+      else
+        by_number = __syncthreads_or(twice ? 1 : 0) != 0;
+    }
+  }
+  if (by_number) {  // uniform
+    sync();  // the ranking above has read the keys
     const int n2 = 1 << log2_ceil64(n);
 #pragma unroll
     for (int e = 0; e < E; e++) {

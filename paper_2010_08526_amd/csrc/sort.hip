@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void k_sort_wave512(const int64_t *cp, const i
       }
     }
     int rank[E];
-    rank_rows<kWave, E, false>(row, len, l, L, (uint32_t *)nullptr, rank);
+    rank_rows<kWave, E, Ties::kRare>(row, len, l, L, (uint32_t *)nullptr, rank);
 #pragma unroll
     for (int e = 0; e < E; e++)
       if (l + e * kWave < len) {
@@ -159,9 +159,7 @@ __global__ __launch_bounds__(256) void k_sort_wave512(const int64_t *cp, const i
         ro[b + t] = k;
         vo[b + t] = L.u.s.val[t];
         bad |= k < 0 || (int64_t)k >= m;
-        // a repeated row: two entries took one place, which shows next to them
-        // or leaves a place that no entry took
-        bad |= L.u.s.key[rank[e]] != row[e] || (t + 1 < len && L.u.s.key[t + 1] <= k);
+        bad |= t + 1 < len && L.u.s.key[t + 1] <= k;  // a repeated row sits next to its twin
       }
     }
     if (__ballot(bad) && l == 0) flag_error(status, kSortDupCode);
@@ -198,7 +196,7 @@ __global__ __launch_bounds__(kSortBlockThreads) void k_sort_block(const int64_t 
       }
     }
     int rank[E];
-    rank_rows<kSortBlockThreads, E, false>(row, len, t, L, s_red, rank);
+    rank_rows<kSortBlockThreads, E, Ties::kRare>(row, len, t, L, s_red, rank);
 #pragma unroll
     for (int e = 0; e < E; e++)
       if (t + e * kSortBlockThreads < len) {
@@ -214,7 +212,7 @@ __global__ __launch_bounds__(kSortBlockThreads) void k_sort_block(const int64_t 
         const int32_t k = L.u.s.key[q];
         ro[b + q] = k;
         vo[b + q] = L.u.s.val[q];
-        bad |= k < 0 || (int64_t)k >= m || L.u.s.key[rank[e]] != row[e] || (q + 1 < len && L.u.s.key[q + 1] <= k);
+        bad |= k < 0 || (int64_t)k >= m || (q + 1 < len && L.u.s.key[q + 1] <= k);
       }
     }
     if (__ballot(bad) && lane() == 0) flag_error(status, kSortDupCode);
@@ -347,7 +345,6 @@ template <class VT>
 int sort_typed(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHeader *hdr,
                const int64_t *skip_flops, double skip_cf, hipStream_t st, int64_t max_len) {
   const int64_t n = C->ncols;
-  max_len = std::min(max_len, C->nrows);  // longer columns hold a row twice: listed, and flagged below
   ProfScope prof("sort_columns", st);
   hipLaunchKernelGGL(k_sort_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, n, lists, hdr, skip_flops,
                      skip_cf, max_len);
@@ -415,7 +412,7 @@ int spgemm_sort_columns(const spgemm_csc *C, int32_t *rowidx_out, void *values_o
   st = launch_init_header((WsHeader *)ws, (uint64_t)0, s);
   if (st) return st;
   return sort_column_lists(C, rowidx_out, values_out, (int32_t *)((char *)ws + L.bins), (WsHeader *)ws, nullptr, 0.0,
-                           s, INT64_MAX);
+                           s, C->nnz);
 }
 
 }  // extern "C"

@@ -69,6 +69,26 @@ def test_sort_columns_reports_a_repeated_row(n, shape):
         S.check_ws(ws)
 
 
+@pytest.mark.parametrize("n", [2, 64, 65, 100, 512, 513, 4096])
+@pytest.mark.parametrize("m", [5, 60, 3000, 100000])
+def test_sort_columns_keeps_repeated_rows(n, m):
+    """Columns with repeated rows, longer than the matrix has rows or not:
+    reported, and sorted with every entry kept (up to 4096 entries)."""
+    print(f"case: repeated rows kept n={n} m={m}", flush=True)
+    rng = np.random.default_rng(n + m)
+    r = rng.integers(0, m, n).astype(np.int32)
+    r[-1] = r[0]
+    v = rng.standard_normal(n)
+    C = S.CSC(m, 1, torch.tensor([0, n], device="cuda"), torch.from_numpy(r).cuda(), torch.from_numpy(v).cuda())
+    ws = S.alloc_workspace(S.workspace_size(S.OP_SORT, C))
+    T = S.sort_columns(C, ws=ws)
+    assert S.ws_status_code(ws) == (S.E_DEVICE, 11)
+    gr, gv = T.rowidx.cpu().numpy(), T.values.cpu().numpy()
+    assert np.array_equal(gr, np.sort(r))
+    order, want = np.lexsort((gv, gr)), np.lexsort((v, r))
+    assert np.array_equal(gv[order], v[want])
+
+
 @pytest.mark.parametrize("m", [3, 60, 700, 5000, 300000])
 @pytest.mark.parametrize("shape", ["even", "crowd"])
 def test_expand_sort_compress_classes(m, shape):
