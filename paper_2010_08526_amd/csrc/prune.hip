@@ -803,37 +803,37 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
 #pragma unroll
           for (int i = 0; i < E; i++)
             if (((tie >> i) & 1u) && rk[i] < rth) tie &= ~(1u << i);
-          if (above + ra + re != k) {  // a row twice: the column is cut to k entries below
-            if (t == 0) flag_error(status, kPrDupRows);
-          }
+          left = above + ra + re != k;  // a row twice: the kernels that follow report it and keep the first k
         }
         have = keep | tie;
         kept = k;
       }
-      // the kept positions, one list again, in input order
-      if (t == 0) s_n = 0;
-      __syncthreads();  // also: the list is in registers
+      if (!left) {  // uniform
+        // the kept positions, one list again, in input order
+        if (t == 0) s_n = 0;
+        __syncthreads();  // also: the list is in registers
 #pragma unroll
-      for (int i = 0; i < E; i++) {
-        const bool in = (have >> i) & 1u;
-        const uint64_t m = __ballot(in);
-        if (m == 0) continue;
-        int at = 0;
-        if (l == 0) at = atomicAdd(&s_n, __popcll(m));
-        at = readlane(at, 0) + mbcnt(m);
-        if (in) s.list.pos[at] = pos[i];
+        for (int i = 0; i < E; i++) {
+          const bool in = (have >> i) & 1u;
+          const uint64_t m = __ballot(in);
+          if (m == 0) continue;
+          int at = 0;
+          if (l == 0) at = atomicAdd(&s_n, __popcll(m));
+          at = readlane(at, 0) + mbcnt(m);
+          if (in) s.list.pos[at] = pos[i];
+        }
+        __syncthreads();
+        int32_t row[KE];
+        int rank[KE];
+#pragma unroll
+        for (int i = 0; i < KE; i++) row[i] = t + i * kPrThreads < kept ? s.list.pos[t + i * kPrThreads] : 0;
+        __syncthreads();
+        rank_rows<kPrThreads, KE, Ties::kNone>(row, kept, t, s.rank, s_red, rank);
+        int32_t *dst = stage + j * (int64_t)k;
+#pragma unroll
+        for (int i = 0; i < KE; i++)
+          if (t + i * kPrThreads < kept) dst[rank[i]] = row[i];
       }
-      __syncthreads();
-      int32_t row[KE];
-      int rank[KE];
-#pragma unroll
-      for (int i = 0; i < KE; i++) row[i] = t + i * kPrThreads < kept ? s.list.pos[t + i * kPrThreads] : 0;
-      __syncthreads();
-      rank_rows<kPrThreads, KE, Ties::kNone>(row, kept, t, s.rank, s_red, rank);
-      int32_t *dst = stage + j * (int64_t)k;
-#pragma unroll
-      for (int i = 0; i < KE; i++)
-        if (t + i * kPrThreads < kept) dst[rank[i]] = row[i];
     }
     if (t == 0) {
       cnt[j] = left ? 0 : kept;

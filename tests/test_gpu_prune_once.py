@@ -86,6 +86,30 @@ def test_prune_once_reports_a_repeated_row():
         S.prune_topk(C, 0.0, 10)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_prune_once_keeps_the_first_of_repeated_rows(dtype):
+    """Columns with one row 384 times at the cut and 64 larger entries after
+    them, in slots of another wave that has nothing before: reported, and of the
+    entries at or above the cut the first k are kept, in input order."""
+    import ctypes
+    print(f"case: prune once first k {dtype}", flush=True)
+    n, k, cols = 2048, 200, 50
+    slot, thread = torch.arange(n) // 256, torch.arange(n) % 256
+    again = (thread < 64) & (slot < 6)
+    larger = (thread >= 192) & (slot == 7)
+    r = torch.where(again, 0, 1 + torch.arange(n)).to(torch.int32).repeat(cols).cuda()
+    v = torch.where(again, 1.0, torch.where(larger, 2.0, -1.0)).to(dtype).repeat(cols).cuda()
+    C = S.CSC(n + 1, cols, torch.arange(0, n * cols + 1, n, device="cuda"), r, v)
+    out = (torch.empty(cols + 1, dtype=torch.int64, device="cuda"),
+           torch.empty(k * cols, dtype=torch.int32, device="cuda"), torch.empty(k * cols, dtype=dtype, device="cuda"))
+    ws = S.alloc_workspace(S.workspace_size(S.OP_PRUNE, C))
+    S._check(S._lib.spgemm_prune_topk(ctypes.byref(S.desc(C)), 0.0, k, *[S._ptr(x) for x in out], k * cols, S._ptr(ws),
+                                      ws.numel(), S._stream(None)), "prune")
+    assert S.ws_status_code(ws) == (S.E_DEVICE, 10)
+    assert torch.equal(out[0].cpu(), torch.arange(0, k * cols + 1, k))
+    assert torch.all(out[1] == 0) and torch.all(out[2] == 1.0)
+
+
 def test_prune_once_in_a_graph():
     print("case: prune once graph", flush=True)
     rng = np.random.default_rng(3)
