@@ -751,6 +751,29 @@ def permute(src: torch.Tensor, perm: torch.Tensor, scatter: bool = False, out: t
 # Largest column of C whose gradient terms the fused backward forms (the
 # largest LDS table is at most half full).
 FUSED_COL_MAX = 5120
+# Longest row of B, and terms of C's pattern per entry of it, from which the
+# adds to one address bound the fused backward: each takes about 12 ns (22 where
+# A's column is long), whatever else there is to do.  Called again and again, by
+# float32 (float64 likewise), n = 262,144, a row of B in every column: 3.20 ms
+# against 1.77 by transposed patterns at 1 entry of C's pattern per entry of the
+# row, 3.22 against 2.85 at 64, 5.81 against 3.89 at 128 (columns of A of 32), but
+# 6.5 against 20.2 at 509; a row in a quarter of 1e6 columns: 3.56 against 3.80
+# at 64.  Rows of 4096: 77 against 88 us; of 8192: 126 against 122-130.
+HUB_ROW_MIN = 4096
+HUB_ROW_TERMS = 128
+
+
+def _hub_row(longest_row: int, nnz_c: int) -> bool:
+    """Whether adds to the same entries of dA would bound the fused backward."""
+    return longest_row > HUB_ROW_MIN and nnz_c < HUB_ROW_TERMS * longest_row
+
+
+def _longest_row(M, stream=None) -> int:
+    """Entries of M's longest row."""
+    T, _ = transpose(M, values=False, perm=False, stream=stream)
+    with _on_stream(stream):
+        return int((T.colptr[1:] - T.colptr[:-1]).max()) if M.nrows > 0 else 0
+
 
 
 def _fused_backward(A, B, b_values, C, dC_values, ws, stream=None):
@@ -802,8 +825,10 @@ class Backward:
     against 0.92 ms by two masked products and two permutations over patterns
     already transposed (0.33 against 0.57 ms on a scale 12 R-MAT graph, whose
     hubs many columns add to at once).  Longer columns have no LDS table to
-    hold them: then the transposes of A's and B's patterns and
-    of C's pattern are formed once (per structure) and reused."""
+    hold them, and a row of B with most of the entries (see HUB_ROW_MIN) makes
+    the traversal wait for the adds to a few entries of dA: then the transposes
+    of A's and B's patterns and of C's pattern are formed once (per structure)
+    and reused."""
 
     _LAZY = ("ws_tr", "AT", "permA", "CT", "permC", "BT", "permB", "ws_b", "ws_a")
 
@@ -812,7 +837,10 @@ class Backward:
         self.ws_f = None
         with _on_stream(stream):
             longest = int((C.colptr[1:] - C.colptr[:-1]).max()) if C.ncols > 0 else 0
-        if longest <= FUSED_COL_MAX and A.values is not None and B.values is not None:
+        fused = longest <= FUSED_COL_MAX and A.values is not None and B.values is not None
+        if fused and _hub_row(B.ncols, C.nnz):  # (a row holds at most one entry per column)
+            fused = not _hub_row(_longest_row(B, stream), C.nnz)
+        if fused:
             # both from the current stream's pool, as all memory here: gradients
             # may be asked for on another stream than this one
             self._b = torch.empty_like(B.values)
@@ -895,7 +923,9 @@ class SpGEMMFn(torch.autograd.Function):
             return torch.zeros_like(a_vals), torch.zeros_like(b_vals), None, None, None, None
         A = CSC(ctx.A.nrows, ctx.A.ncols, ctx.A.colptr, ctx.A.rowidx, a_vals)
         B = CSC(ctx.B.nrows, ctx.B.ncols, ctx.B.colptr, ctx.B.rowidx, b_vals)
-        if ctx.longest <= FUSED_COL_MAX:  # no transposes: see Backward
+        # no transposes: see Backward (formed here, on every call, they cost more
+        # than any row's adds: 8.6 ms against 3.3 in the worst case above)
+        if ctx.longest <= FUSED_COL_MAX:
             ws = alloc_workspace(workspace_size(OP_BATCHED_BACKWARD, A, B, 0, B.ncols), ctx.C.rowidx.device)
             dA, dB = _fused_backward(A, B, b_vals, ctx.C, d_vals.contiguous(), ws)
             check_ws(ws, "device-side check (backward)")

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import types
 
+import pytest
 import torch
 
 import paper_2010_08526_amd as S
@@ -29,3 +30,9 @@ def test_undefined_gradient_counts_as_zero():
     a, b = torch.ones(5), torch.ones(7)
     dA, dB, *rest = S.SpGEMMFn.backward(types.SimpleNamespace(saved_tensors=(a, b)), None, None, None)
     assert torch.equal(dA, torch.zeros(5)) and torch.equal(dB, torch.zeros(7)) and rest == [None] * 4
+
+
+@pytest.mark.parametrize("row, nnz_c, hub", [(4096, 4096, False), (4097, 4097, True), (4097, 128 * 4097 - 1, True),
+                                             (4097, 128 * 4097, False), (10**7, 10**9, True), (0, 0, False)])
+def test_rule_of_the_fused_gradients(row, nnz_c, hub):
+    assert S._hub_row(row, nnz_c) == hub

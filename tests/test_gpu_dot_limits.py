@@ -148,3 +148,28 @@ def test_gradients_of_empty_products(shape, dtype):
     a, b = A.values.clone().requires_grad_(True), B.values.clone().requires_grad_(True)
     S.SpGEMMFn.apply(a, b, A, B)[0].sum().backward()
     assert torch.equal(a.grad, torch.zeros_like(a)) and torch.equal(b.grad, torch.zeros_like(b))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("row", [4096, 4097])
+def test_gradients_with_a_long_row(row, dtype):
+    """A row of B in 4096 columns (one traversal) and in one more (transposed
+    patterns), of few other entries; exact."""
+    print(f"case: gradients with a long row {row} {dtype}", flush=True)
+    rng = np.random.default_rng(row)
+    n = 6000
+    A = _csc(300, [rng.choice(300, 8, replace=False) for _ in range(50)], rng, dtype)
+    B = _csc(50, [np.array([7, 20]) if j < row else np.array([j % 7]) for j in rng.permutation(n)], rng, dtype)
+    Ad, Bd = A.to("cuda"), B.to("cuda")
+    C = S.spgemm(Ad, Bd)
+    dC = torch.from_numpy(rng.integers(1, 5, C.nnz)).to(dtype).cuda()
+    bw = S.Backward(Ad, Bd, C)
+    assert S._longest_row(Bd) == row and (bw.ws_f is None) == (row > 4096)
+    G = oracle.Mat(C.nrows, C.ncols, C.colptr.cpu().numpy(), C.rowidx.cpu().numpy(), dC.double().cpu().numpy())
+    gA, gB = oracle.grad_a(A, B, G), oracle.grad_b(A, B, G)
+    for k in (1, 3):
+        dA, dB = bw(dC)
+        bw.check()
+        assert np.array_equal(dA.double().cpu().numpy(), k * gA)
+        assert np.array_equal(dB.double().cpu().numpy(), gB)
+        bw.refresh_values(S.CSC(Bd.nrows, n, Bd.colptr, Bd.rowidx, Bd.values * 3))
