@@ -62,12 +62,32 @@ __global__ __launch_bounds__(256) void k_tr_count(const int32_t *ri, int64_t nnz
   }
 }
 
+// The last column in [lo, hi) that starts at or before p (cp[lo] <= p < cp[hi]),
+// found by a whole wave, 64 probes a step.
+__device__ __forceinline__ int64_t column_of(const int64_t *cp, int64_t lo, int64_t hi, int64_t p) {
+  while (hi - lo > 1) {
+    const int64_t d = (hi - lo + kWave - 1) / kWave;
+    const int64_t j = min(lo + (int64_t)lane() * d, hi);
+    const uint64_t le = __ballot(j < hi && cp[j] <= p);  // lane 0 always
+    const int c = 63 - __clzll((long long)le);
+    const int64_t nlo = lo + (int64_t)c * d;
+    hi = min(hi, nlo + d);
+    lo = nlo;
+  }
+  return lo;
+}
+
 // Entries in tiles of kTrTile consecutive ones, whatever the columns' lengths:
 // the tile's columns mark where they start in LDS, a prefix maximum gives
 // every entry its column, and an entry goes to its row's column pointer plus
 // its rank.  Random atomics (23e9 a second) and random writes bound a
 // transpose, so each entry pays for one of each: 1.0e7 entries, two per
 // column: 1.87 ms with a wave per column and a second atomic, 0.81 now.
+// A tile that spans more than kTrSpan columns, nearly all of them empty, has its
+// entries look their columns up instead (a binary search each, kTrPer in
+// flight): 4000 entries in 5,000,000 columns 12.1 ms -> 0.10, 1,000,000 entries in
+// as many 149 -> 140 us; at 8000 columns a tile both take 48 us.
+constexpr int64_t kTrSpan = 8192;
 constexpr int kTrPer = 16;
 constexpr int kTrTile = 256 * kTrPer;
 template <class VT>
@@ -80,43 +100,59 @@ __global__ __launch_bounds__(256) void k_tr_scatter(const int64_t *cp, const int
   const int64_t first = max(cp[0], (int64_t)0), end = min(cp[ncols], nnz);
   for (int64_t p0 = first + (int64_t)blockIdx.x * kTrTile; p0 < end; p0 += (int64_t)gridDim.x * kTrTile) {
     const int64_t p1 = min(end, p0 + kTrTile);
-    // the last column that starts at or before p0 (64 probes a step)
-    int64_t lo = 0, hi = ncols;  // cp[lo] <= p0 < cp[hi]
-    while (hi - lo > 1) {
-      const int64_t d = (hi - lo + kWave - 1) / kWave;
-      const int64_t j = min(lo + (int64_t)l * d, hi);
-      const uint64_t le = __ballot(j < hi && cp[j] <= p0);  // lane 0 always
-      const int c = 63 - __clzll((long long)le);
-      const int64_t nlo = lo + (int64_t)c * d;
-      hi = min(hi, nlo + d);
-      lo = nlo;
+    const int64_t lo = column_of(cp, 0, ncols, p0);
+    if (ncols - lo > kTrSpan && cp[lo + kTrSpan] < p1) {  // uniform
+      // the entries' columns, each from lo up: cp[a] <= p < cp[b]
+      const int64_t hi = column_of(cp, lo + kTrSpan, ncols, p1 - 1) + 1;
+      int64_t a[kTrPer], b[kTrPer];
+#pragma unroll
+      for (int i = 0; i < kTrPer; i++) {
+        a[i] = lo;
+        b[i] = hi;
+      }
+      for (int64_t left = hi - lo; left > 1; left = (left + 1) / 2) {
+        int64_t c[kTrPer];
+#pragma unroll
+        for (int i = 0; i < kTrPer; i++) c[i] = cp[(a[i] + b[i]) / 2];
+#pragma unroll
+        for (int i = 0; i < kTrPer; i++) {
+          const int64_t mid = (a[i] + b[i]) / 2;
+          if (c[i] <= p0 + t + i * 256)
+            a[i] = mid;
+          else
+            b[i] = mid;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kTrPer; i++) s_own[t + i * 256] = (int)(a[i] - lo);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kTrPer; i++) s_own[t + i * 256] = 0;
+      __syncthreads();
+      for (int64_t j0 = lo + 1;; j0 += 256) {
+        const int64_t j = j0 + t;
+        const int64_t c = j < ncols ? cp[j] : p1;
+        if (c > p0 && c < p1) atomicMax(&s_own[c - p0], (int)(j - lo));
+        if (!__syncthreads_or(t == 255 && c < p1)) break;
+      }
+      // prefix maximum, kTrPer consecutive entries per thread
+      int x[kTrPer], top = 0;
+#pragma unroll
+      for (int i = 0; i < kTrPer; i++) {
+        top = max(top, s_own[t * kTrPer + i]);
+        x[i] = top;
+      }
+      const int incl = wave_incl_max(top);
+      if (l == kWave - 1) s_w[w] = incl;
+      __syncthreads();
+      int before = wave_prev(incl);
+#pragma unroll
+      for (int z = 0; z < 4; z++)
+        if (z < w) before = max(before, s_w[z]);
+#pragma unroll
+      for (int i = 0; i < kTrPer; i++) s_own[t * kTrPer + i] = max(x[i], before);
+      __syncthreads();
     }
-#pragma unroll
-    for (int i = 0; i < kTrPer; i++) s_own[t + i * 256] = 0;
-    __syncthreads();
-    for (int64_t j0 = lo + 1;; j0 += 256) {
-      const int64_t j = j0 + t;
-      const int64_t c = j < ncols ? cp[j] : p1;
-      if (c > p0 && c < p1) atomicMax(&s_own[c - p0], (int)(j - lo));
-      if (!__syncthreads_or(t == 255 && c < p1)) break;
-    }
-    // prefix maximum, kTrPer consecutive entries per thread
-    int x[kTrPer], top = 0;
-#pragma unroll
-    for (int i = 0; i < kTrPer; i++) {
-      top = max(top, s_own[t * kTrPer + i]);
-      x[i] = top;
-    }
-    const int incl = wave_incl_max(top);
-    if (l == kWave - 1) s_w[w] = incl;
-    __syncthreads();
-    int before = wave_prev(incl);
-#pragma unroll
-    for (int z = 0; z < 4; z++)
-      if (z < w) before = max(before, s_w[z]);
-#pragma unroll
-    for (int i = 0; i < kTrPer; i++) s_own[t * kTrPer + i] = max(x[i], before);
-    __syncthreads();
 #pragma unroll 4
     for (int i = 0; i < kTrPer; i++) {
       const int64_t p = p0 + t + i * 256;
