@@ -54,6 +54,35 @@ def test_transpose_tiles(case, dtype):
             assert np.array_equal(pm.cpu().numpy()[order], want)
 
 
+@pytest.mark.parametrize("span", [8191, 8192, 8193, 8194, 16385, 300000])
+@pytest.mark.parametrize("nnz", [2, 5, 4096, 4097, 9000])
+def test_transpose_of_mostly_empty_columns(span, nnz):
+    """Entries spread over `span` columns between empty ones, the first and the
+    last of them not empty, some of several entries: tiles on both sides of the
+    span from which entries look their columns up."""
+    print(f"case: transpose span {span} nnz {nnz}", flush=True)
+    rng = np.random.default_rng(span + nnz)
+    m, before, after = 20000, 700, 9001
+    n = before + span + after
+    at = np.concatenate([[0, span - 1], rng.integers(0, span, nnz - 2)])
+    lens = np.bincount(before + at, minlength=n)
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, c, replace=False) for c in lens[lens > 0]]).astype(np.int32)
+    v = rng.standard_normal(nnz)
+    X = S.CSC(m, n, torch.from_numpy(cp).cuda(), torch.from_numpy(ri).cuda(), torch.from_numpy(v).cuda())
+    ws = S.alloc_workspace(S.workspace_size(S.OP_TRANSPOSE, X))
+    T, pm = S.transpose(X, ws)
+    S.check_ws(ws)
+    col = np.repeat(np.arange(n), lens)
+    want = np.lexsort((col, ri))
+    tcp, tri = T.colptr.cpu().numpy(), T.rowidx.cpu().numpy()
+    assert np.array_equal(tcp, np.concatenate([[0], np.cumsum(np.bincount(ri, minlength=m))]))
+    order = np.lexsort((tri, np.repeat(np.arange(m), np.diff(tcp))))
+    assert np.array_equal(tri[order], col[want])
+    assert np.array_equal(T.values.cpu().numpy()[order], v[want])
+    assert np.array_equal(pm.cpu().numpy()[order], want)
+
+
 def test_transpose_reports_a_bad_row():
     print("case: transpose bad row", flush=True)
     X = S.CSC(5, 2, torch.tensor([0, 2, 3], device="cuda"), torch.tensor([1, 7, 2], dtype=torch.int32, device="cuda"),
