@@ -191,6 +191,10 @@ int spgemm_numeric(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t
 int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
                       void *ws, size_t ws_bytes, void *stream);
 
+/* The same with the largest count of every row (longest_host: [rows]). */
+int spgemm_count_sums_rows(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
+                           void *ws, size_t ws_bytes, void *stream);
+
 /* spgemm_numeric for a caller that knows that no column of the call holds
  * more than max_len entries (from the symbolic counts it read back): kernels
  * for longer columns are not launched.  A longer column sets status 4. */

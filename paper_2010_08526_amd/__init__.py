@@ -205,7 +205,7 @@ def numeric(A, B, c0: int, c1: int, layer: int, n_layers: int, flops, c_colptr, 
 
 COUNT_SUMS_MAX_ROWS = 64
 SLAB_MIN_ROWS = 5120  # more rows than this: heavy columns are formed from a slabbed copy of A
-_lib.spgemm_count_sums.argtypes = [_vp, _i64, _i32, _vp, ctypes.POINTER(_i64), _vp, _sz, _vp]
+_lib.spgemm_count_sums_rows.argtypes = [_vp, _i64, _i32, _vp, _vp, _vp, _sz, _vp]
 _lib.spgemm_numeric_upto.argtypes = [_P, _P, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i32, _i64, _vp, _sz, _vp]
 _lib.spgemm_numeric_sorted.argtypes = [_P, _P, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, ctypes.c_double, _i32, _vp,
                                        _sz, _vp]
@@ -324,6 +324,7 @@ class Plan:
     input_bytes: int
     reserve_bytes: int
     longest: int | None = None  # entries of C's longest column, if known
+    row_longest: np.ndarray | None = None  # [rows] the same of every layer's product, and C's, if known
 
     @property
     def counts(self):
@@ -426,7 +427,7 @@ class Engine:
         if self.sorted_output:
             tot[:, -1] //= 2
         return Plan(self.flops, self.nnz, nnz_host, bounds, tot, self.L, self.budget_bytes, self.input_bytes,
-                    self.reserve_bytes, int(nnz_host[-1].max(initial=0)))
+                    self.reserve_bytes, int(nnz_host[-1].max(initial=0)), nnz_host.max(axis=1, initial=0))
 
     def _plan_whole(self, stream=None) -> Plan | None:
         """The plan of a product that fits as a whole, from sums formed on the
@@ -438,9 +439,10 @@ class Engine:
         if n * rows < 32768 or rows > COUNT_SUMS_MAX_ROWS:
             return None
         sums = np.zeros(rows, np.int64)
-        longest = _i64(0)
-        _check(_lib.spgemm_count_sums(_ptr(self.nnz), n, rows, sums.ctypes.data, ctypes.byref(longest),
-                                      _ptr(self.ws_scan), self.ws_scan.numel(), _stream(stream)), "spgemm_count_sums")
+        longest = np.zeros(rows, np.int64)
+        _check(_lib.spgemm_count_sums_rows(_ptr(self.nnz), n, rows, sums.ctypes.data, longest.ctypes.data,
+                                           _ptr(self.ws_scan), self.ws_scan.numel(), _stream(stream)),
+               "spgemm_count_sums_rows")
         avail = self.budget_bytes - self.input_bytes - self.reserve_bytes
         held = int(sums[-1]) * (2 if self.sorted_output else 1) + (int(sums[:-1].sum()) if L > 1 else 0)
         if (4 + self.vbytes) * held + 8 * (L + 1 if L > 1 else 1) * n > avail or self.max_batches < 1:
@@ -448,7 +450,7 @@ class Engine:
         with _on_stream(stream):
             counts = _Unread(self.nnz.clone())  # self.nnz is written again by the next product
         return Plan(self.flops, self.nnz, counts, [0, n], sums.reshape(1, rows), L, self.budget_bytes,
-                    self.input_bytes, self.reserve_bytes, int(longest.value))
+                    self.input_bytes, self.reserve_bytes, int(longest[-1]), longest)
 
     def _buffers(self, plan: Plan):
         widths = [b - a for a, b in zip(plan.bounds[:-1], plan.bounds[1:])]
@@ -531,8 +533,10 @@ class Engine:
                 marks.append(("numeric_sorted" if self.sorted_output else "numeric", e0, mark()))
             return
         for l, D in enumerate(parts):
+            # the layer's own bound: C may have columns that need the slabbed copy
+            # of A where none of the layer's does
             numeric(A, B, c0, c1, l, L, self.flops[c0:c1], D.colptr, D.rowidx, D.values, self.ws_num, stream,
-                    self.semiring, top)
+                    self.semiring, top if plan.row_longest is None else int(plan.row_longest[l]))
         e1 = mark()
         merge(parts, ccp, *hashed, self.ws_mrg, stream, self.semiring)
         e2 = mark()

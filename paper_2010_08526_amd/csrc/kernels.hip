@@ -2899,8 +2899,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(const int64_t *x, i
   }
 }
 
-// Sums of the rows of counts[rows][n] (res[0, rows)) and the largest count of
-// the last row (res[rows]); res all zero on entry.
+// Sums of the rows of counts[rows][n] (res[0, rows)) and the rows' largest
+// counts (res[rows, 2 rows)); res all zero on entry.
 __global__ __launch_bounds__(256) void k_count_sums(const int64_t *counts, int64_t n, int rows, uint64_t *res) {
   __shared__ int64_t s_sum[4], s_max[4];
   const int row = blockIdx.y;
@@ -2922,9 +2922,8 @@ __global__ __launch_bounds__(256) void k_count_sums(const int64_t *counts, int64
   __syncthreads();
   if (threadIdx.x == 0) {
     atomicAdd((unsigned long long *)&res[row], (unsigned long long)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]));
-    if (row == rows - 1)
-      atomicMax((unsigned long long *)&res[rows],
-                (unsigned long long)max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3])));
+    atomicMax((unsigned long long *)&res[rows + row],
+              (unsigned long long)max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3])));
   }
 }
 
@@ -3901,8 +3900,8 @@ int spgemm_colptr(const int64_t *counts, int64_t n, int64_t *colptr_out, void *w
   return launch_colptr_scan(counts, n, colptr_out, (int64_t *)(w + L.scan), s, (WsHeader *)w);
 }
 
-int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
-                      void *ws, size_t ws_bytes, void *stream) {
+int spgemm_count_sums_rows(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
+                           void *ws, size_t ws_bytes, void *stream) {
   if (n < 0 || rows < 1 || rows > SPGEMM_COUNT_SUMS_MAX_ROWS || (n > 0 && !counts) || !sums_host || !longest_host)
     return SPGEMM_E_INVAL;
   int st = check_ws(ws, ws_bytes, kHeaderBytes);
@@ -3910,21 +3909,29 @@ int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *s
   hipStream_t s = (hipStream_t)stream;
   // the second half of the header block is free
   uint64_t *res = (uint64_t *)((char *)ws + 2048);
-  static_assert(2048 + 8 * (SPGEMM_COUNT_SUMS_MAX_ROWS + 1) <= kHeaderBytes, "results fit the header block");
-  static_assert(8 * (SPGEMM_COUNT_SUMS_MAX_ROWS + 1) <= sizeof(WsHeader) * kStatusMany, "and the pinned buffer");
-  hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(256), 0, s, (int64_t *)res, (int64_t)rows + 1);
+  static_assert(2048 + 16 * SPGEMM_COUNT_SUMS_MAX_ROWS <= kHeaderBytes, "results fit the header block");
+  static_assert(16 * SPGEMM_COUNT_SUMS_MAX_ROWS <= sizeof(WsHeader) * kStatusMany, "and the pinned buffer");
+  hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(256), 0, s, (int64_t *)res, (int64_t)2 * rows);
   LAUNCHCHK();
   const unsigned gx = std::max(1u, std::min(grid_of(n, 2048), (unsigned)device_cus()));
   hipLaunchKernelGGL(k_count_sums, dim3(gx, (unsigned)rows), dim3(256), 0, s, counts, n, (int)rows, res);
   LAUNCHCHK();
   st = pin_buffer();
   if (st) return st;
-  const size_t bytes = 8 * ((size_t)rows + 1);
-  HIPCHK(hipMemcpyAsync(g_pin.hdr, res, bytes, hipMemcpyDeviceToHost, s));
+  const size_t bytes = 8 * (size_t)rows;
+  HIPCHK(hipMemcpyAsync(g_pin.hdr, res, 2 * bytes, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  memcpy(sums_host, g_pin.hdr, 8 * (size_t)rows);
-  memcpy(longest_host, (const char *)g_pin.hdr + 8 * (size_t)rows, 8);
+  memcpy(sums_host, g_pin.hdr, bytes);
+  memcpy(longest_host, (const char *)g_pin.hdr + bytes, bytes);
   return SPGEMM_OK;
+}
+
+int spgemm_count_sums(const int64_t *counts, int64_t n, int32_t rows, int64_t *sums_host, int64_t *longest_host,
+                      void *ws, size_t ws_bytes, void *stream) {
+  int64_t longest[SPGEMM_COUNT_SUMS_MAX_ROWS];
+  const int st = spgemm_count_sums_rows(counts, n, rows, sums_host, longest_host ? longest : nullptr, ws, ws_bytes, stream);
+  if (st == SPGEMM_OK) *longest_host = longest[rows - 1];
+  return st;
 }
 
 int spgemm_batched_forward(const spgemm_csc *A, const spgemm_csc *B, int64_t nnz_cap, int64_t *flops_out,

@@ -125,3 +125,24 @@ def test_plan_from_device_sums(layers, sorted_output):
     eng.budget_bytes = eng.input_bytes + eng.reserve_bytes
     with pytest.raises(S.SpgemmError):
         eng.plan()
+
+
+@pytest.mark.parametrize("n", [40, 9000])
+def test_layers_below_the_merged_length(n):
+    """Columns of more than 5120 rows of which no layer forms more: every
+    count's longest column is planned with (from the host and from sums on the
+    device), and the product is the oracle's."""
+    print(f"case: layers below the merged length {n}", flush=True)
+    m, k, L = 20000, 800, 4
+    A = synth.erdos_renyi(m, k, 40, 5, torch.float64)
+    few = synth.erdos_renyi(k, n - 8, 2, 6, torch.float64)
+    many = synth.erdos_renyi(k, 8, 300, 7, torch.float64)
+    B = synth.CSC(k, n, torch.cat([few.colptr, many.colptr[1:] + few.nnz]), torch.cat([few.rowidx, many.rowidx]),
+                  torch.cat([few.values, many.values]))
+    eng = S.Engine(A.to("cuda"), B.to("cuda"), L)
+    C, plan = eng.run()
+    P = oracle.spgemm(A, B)
+    assert (plan.nnz_host.size >= 32768) == (n == 9000)
+    assert np.array_equal(plan.row_longest, plan.nnz_host.max(axis=1))
+    assert plan.row_longest[:L].max() <= 5120 < plan.longest == np.diff(P.colptr).max()
+    assert_matches(C, P, torch.float64, "layers")

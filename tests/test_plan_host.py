@@ -55,3 +55,20 @@ def test_plan_without_a_bound(monkeypatch):
         plan = S.Plan(*_values(), longest=longest)
         eng._form(plan, 0, None, 10, [], (None, None), (None, None))
         assert bounds.pop() == want
+
+
+def test_layers_have_bounds_of_their_own(monkeypatch):
+    """A layer's product is bounded by its own longest column, not by C's."""
+    bounds = []
+    monkeypatch.setattr(S, "numeric", lambda *a: bounds.append(a[-1]))
+    monkeypatch.setattr(S, "merge", lambda *a: None)
+    eng = object.__new__(S.Engine)
+    eng.A = eng.B = S.CSC(4, 6, None, torch.zeros(0), None)
+    eng.L, eng.sorted_output, eng.semiring, eng.flops = 2, False, 0, torch.zeros(6)
+    eng.ws_num = eng.ws_mrg = None
+    parts = [S.CSC(4, 6, None, None, None)] * 2
+    for more, want in (({}, [S.NO_BOUND] * 2), ({"longest": 6}, [6, 6]),
+                       ({"longest": 6, "row_longest": np.array([2, 4, 6])}, [2, 4])):
+        eng._form(S.Plan(*_values(), **more), 0, None, 10, parts, (None, None), (None, None))
+        assert bounds == want
+        bounds.clear()

@@ -83,7 +83,7 @@ def test_counts_are_read_after_the_symbolic_pass(monkeypatch, n, handle):
 
     monkeypatch.setattr(torch.cuda, "Event", Event)
     monkeypatch.setattr(S, "symbolic", lambda *a, **k: None)
-    monkeypatch.setattr(S._lib, "spgemm_count_sums", lambda *a: 0)
+    monkeypatch.setattr(S._lib, "spgemm_count_sums_rows", lambda *a: 0)
     eng = object.__new__(S.Engine)
     eng.A = eng.B = S.CSC(100, n, None, torch.zeros(0), None)
     eng.L, eng.vbytes, eng.max_batches, eng.sorted_output = 1, 4, 1 << 16, False
@@ -119,7 +119,7 @@ def test_new_output_waits_for_the_memory(monkeypatch, handle, layers):
     eng.ws_scan = eng.ws_num = eng.ws_mrg = eng.flops = torch.zeros(16)
     rows = layers + 1 if layers > 1 else 1
     eng.nnz = torch.ones((rows, 4), dtype=torch.int64)
-    plan = types.SimpleNamespace(batch_nnz=np.full((1, rows), 4), nbatches=1, bounds=[0, 4], longest=1)
+    plan = types.SimpleNamespace(batch_nnz=np.full((1, rows), 4), nbatches=1, bounds=[0, 4], longest=1, row_longest=None)
     eng._whole(plan, handle)
     assert fake.waits == ([(4096, 0)] if handle == 4096 else [])
     assert order and set(order) == {len(fake.waits)}
