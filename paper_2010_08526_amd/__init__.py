@@ -402,8 +402,7 @@ class Engine:
             free, _ = torch.cuda.mem_get_info()
             budget_bytes = int(free * 0.9) + self.input_bytes + self.reserve_bytes
         self.budget_bytes = int(budget_bytes)
-        self._bufs = None  # output buffers of run_batch
-        self._stage = None  # staging of a whole product (run without a consumer)
+        self._bufs = {}  # output buffers of run_batch and staging of a whole product, by name
 
     # -- passes --------------------------------------------------------------
     def plan(self, stream=None) -> Plan:
@@ -452,34 +451,29 @@ class Engine:
         return Plan(self.flops, self.nnz, counts, [0, n], sums.reshape(1, rows), L, self.budget_bytes,
                     self.input_bytes, self.reserve_bytes, int(longest[-1]), longest)
 
-    def _buffers(self, plan: Plan):
-        widths = [b - a for a, b in zip(plan.bounds[:-1], plan.bounds[1:])]
-        wmax = max(widths) if widths else 0
-        L = self.L
-        if L == 1:
-            need = (wmax, int(plan.batch_nnz[:, 0].max()) if plan.nbatches else 0, 0)
-        else:
-            need = (wmax, int(plan.batch_nnz[:, L].max()), int(plan.batch_nnz[:, :L].sum(1).max()))
-        if self._bufs is None or any(x > y for x, y in zip(need, self._bufs["need"])):
-            dev = self.device
-            bufs = {"need": need,
-                    "ccp": torch.empty(need[0] + 1, dtype=torch.int64, device=dev),
-                    "cri": torch.empty(max(1, need[1]), dtype=torch.int32, device=dev),
-                    "cv": torch.empty(max(1, need[1]), dtype=self.vdtype, device=dev)}
-            if self.sorted_output:
-                bufs["sri"] = torch.empty(max(1, need[1]), dtype=torch.int32, device=dev)
-                bufs["sv"] = torch.empty(max(1, need[1]), dtype=self.vdtype, device=dev)
-            if L > 1:
-                bufs["dcp"] = torch.empty((L, need[0] + 1), dtype=torch.int64, device=dev)
-                bufs["dri"] = torch.empty(max(1, need[2]), dtype=torch.int32, device=dev)
-                bufs["dv"] = torch.empty(max(1, need[2]), dtype=self.vdtype, device=dev)
-            self._bufs = bufs
-        return self._bufs
+    def _hold(self, name: str, count: int, dtype) -> torch.Tensor:
+        """The engine's buffer of that name, of at least ``count`` elements
+        (the planner leaves room for one of each)."""
+        t = self._bufs.get(name)
+        if t is None or t.numel() < count:
+            t = None
+            self._bufs.pop(name, None)  # replaced, not joined
+            t = self._bufs[name] = torch.empty(max(1, int(count)), dtype=dtype, device=self.device)
+        return t
+
+    def _hashed(self, plan: Plan):
+        """(rows, values) of the largest batch, in hash-table order."""
+        size = plan.batch_nnz[:, -1].max(initial=0)
+        return self._hold("cri", size, torch.int32), self._hold("cv", size, self.vdtype)
+
+    def _partials(self, plan: Plan):
+        """(rows, values) of the partial products of the batch with most."""
+        part = plan.batch_nnz[:, :self.L].sum(1).max(initial=0)
+        return self._hold("dri", part, torch.int32), self._hold("dv", part, self.vdtype)
 
     def release_buffers(self):
         """Drops the output buffers (they are allocated again, at the size the next plan needs)."""
-        self._bufs = None
-        self._stage = None
+        self._bufs = {}
 
     def run_batch(self, plan: Plan, i: int, stream=None, marks=None) -> CSC:
         """Forms batch i; the returned CSC views buffers reused by the next call.
@@ -495,22 +489,27 @@ class Engine:
             return e
         c0, c1 = plan.bounds[i], plan.bounds[i + 1]
         w = c1 - c0
-        bufs = self._buffers(plan)
-        ccp = bufs["ccp"][:w + 1]
+        wmax = max(b - a for a, b in zip(plan.bounds[:-1], plan.bounds[1:]))
+        ccp = self._hold("ccp", wmax + 1, torch.int64)[:w + 1]
+        hashed = self._hashed(plan)
         nnzc = int(plan.batch_nnz[i, -1])
+        out = hashed
+        if self.sorted_output:
+            size = plan.batch_nnz[:, -1].max()
+            out = self._hold("sri", size, torch.int32), self._hold("sv", size, self.vdtype)
         parts = []
         e0 = mark()
         if L > 1:
+            held = self._hold("dcp", L * (wmax + 1), torch.int64)
+            dri, dv = self._partials(plan)
             off = 0
             for l in range(L):
-                dcp = bufs["dcp"][l, :w + 1]
+                dcp = held[l * (w + 1):(l + 1) * (w + 1)]
                 colptr(self.nnz[l, c0:c1], dcp, self.ws_scan, stream)
                 cnt = int(plan.batch_nnz[i, l])
-                parts.append(CSC(A.nrows, w, dcp, bufs["dri"][off:off + cnt], bufs["dv"][off:off + cnt]))
+                parts.append(CSC(A.nrows, w, dcp, dri[off:off + cnt], dv[off:off + cnt]))
                 off += cnt
         colptr(self.nnz[L if L > 1 else 0, c0:c1], ccp, self.ws_scan, stream)
-        hashed = (bufs["cri"], bufs["cv"])
-        out = (bufs["sri"], bufs["sv"]) if self.sorted_output else hashed
         self._form(plan, i, ccp, nnzc, parts, hashed, out, stream, mark, e0, marks)
         return CSC(A.nrows, w, ccp, out[0][:nnzc], out[1][:nnzc])
 
@@ -563,28 +562,18 @@ class Engine:
         ri = torch.empty(max(1, total), dtype=torch.int32, device=dev)
         v = torch.empty(max(1, total), dtype=self.vdtype, device=dev)
         vb = self.vbytes
-        part_max = plan.batch_nnz[:, :L].sum(1).max() if L > 1 else 0
-        key = (int(sizes.max()) if self.sorted_output else 0, int(part_max))
-        st = self._stage
-        if st is None or st["key"][0] < key[0] or st["key"][1] < key[1]:
-            self._stage = None
-            st = {"key": key,
-                  "ri": torch.empty(max(1, key[0]), dtype=torch.int32, device=dev),
-                  "v": torch.empty(max(1, key[0]), dtype=self.vdtype, device=dev),
-                  "dri": torch.empty(max(1, key[1]), dtype=torch.int32, device=dev),
-                  "dv": torch.empty(max(1, key[1]), dtype=self.vdtype, device=dev)}
-            if L > 1:
-                st["dcp"] = torch.empty(L * n + 1, dtype=torch.int64, device=dev)
-                st["ws"] = alloc_workspace(workspace_size(OP_COLPTR, None, None, 0, L * n), dev)
-            self._stage = st
+        staged = self._hashed(plan) if self.sorted_output else None
+        if L > 1:
+            dri, dv = self._partials(plan)
+            dcp = self._hold("dcp", L * n + 1, torch.int64)
+            ws = self._hold("wcp", workspace_size(OP_COLPTR, None, None, 0, L * n), torch.uint8)
         # the memory comes from the current stream's pool, where what held it
         # before may still be at work (run() waits for ``stream`` before it
         # hands the output on)
         _wait_for_current(stream)
         colptr(self.nnz[L if L > 1 else 0], cp, self.ws_scan, stream)
         if L > 1:  # the layers' counts one after another: layer l's pointers start at l * n
-            dcp = st["dcp"]
-            colptr(self.nnz[:L].reshape(-1), dcp, st["ws"], stream)
+            colptr(self.nnz[:L].reshape(-1), dcp, ws, stream)
             before = np.concatenate([[0], np.cumsum(plan.batch_nnz[:, :L].sum(0))])  # entries of earlier layers
         off = 0
         done = np.zeros(max(1, L), np.int64)
@@ -597,12 +586,12 @@ class Engine:
                     s = int(before[l] + done[l])  # the pointers' count at this batch's first column
                     cnt = int(plan.batch_nnz[i, l])
                     parts.append(spgemm_csc(int(A.nrows), c1 - c0, cnt, _ptr(dcp) + 8 * (l * n + c0),
-                                            _ptr(st["dri"]) + 4 * (at - s), _ptr(st["dv"]) + vb * (at - s),
+                                            _ptr(dri) + 4 * (at - s), _ptr(dv) + vb * (at - s),
                                             _DTYPE[self.vdtype]))
                     at += cnt
                 done += plan.batch_nnz[i, :L]
             out = (_ptr(ri), _ptr(v))
-            hashed = (_ptr(st["ri"]) - 4 * off, _ptr(st["v"]) - vb * off) if self.sorted_output else out
+            hashed = (_ptr(staged[0]) - 4 * off, _ptr(staged[1]) - vb * off) if self.sorted_output else out
             self._form(plan, i, cp[c0:c1 + 1], int(sizes[i]), parts, hashed, out, stream)
             off += int(sizes[i])
         return CSC(A.nrows, n, cp, ri[:total], v[:total])

@@ -115,7 +115,7 @@ def test_new_output_waits_for_the_memory(monkeypatch, handle, layers):
     eng = object.__new__(S.Engine)
     eng.A = eng.B = S.CSC(4, 4, None, torch.zeros(0), None)
     eng.L, eng.vbytes, eng.vdtype, eng.sorted_output, eng.semiring = layers, 4, torch.float32, False, 0
-    eng.device, eng._stage = "cpu", None
+    eng.device, eng._bufs = "cpu", {}
     eng.ws_scan = eng.ws_num = eng.ws_mrg = eng.flops = torch.zeros(16)
     rows = layers + 1 if layers > 1 else 1
     eng.nnz = torch.ones((rows, 4), dtype=torch.int64)
