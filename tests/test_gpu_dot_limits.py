@@ -173,3 +173,38 @@ def test_gradients_with_a_long_row(row, dtype):
         assert np.array_equal(dA.double().cpu().numpy(), k * gA)
         assert np.array_equal(dB.double().cpu().numpy(), gB)
         bw.refresh_values(S.CSC(Bd.nrows, n, Bd.colptr, Bd.rowidx, Bd.values * 3))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("longest", [5120, 5121])
+def test_form_of_the_gradients_at_the_limit(longest, dtype, monkeypatch):
+    """C's longest column has as many rows as the largest table takes, or one
+    more: one traversal, or transposed patterns, by Backward and by SpGEMMFn;
+    exact."""
+    print(f"case: form of the gradients {longest} {dtype}", flush=True)
+    rng = np.random.default_rng(longest)
+    m = 6000
+    rows = rng.permutation(m)[:longest]
+    A = _csc(m, [rows[i:i + 64] for i in range(0, longest, 64)] + [rng.choice(m, 3, replace=False)], rng, dtype)
+    B = _csc(A.ncols, [np.arange(A.ncols - 1), np.array([A.ncols - 1]), np.array([0, A.ncols - 2])], rng, dtype)
+    Ad, Bd = A.to("cuda"), B.to("cuda")
+    C = S.spgemm(Ad, Bd)
+    assert int((C.colptr[1:] - C.colptr[:-1]).max()) == longest
+    dC = torch.from_numpy(rng.integers(1, 5, C.nnz)).to(dtype).cuda()
+    bw = S.Backward(Ad, Bd, C)
+    assert (bw.ws_f is not None) == (longest == 5120)
+    dA, dB = bw(dC)
+    bw.check()
+    G = oracle.Mat(C.nrows, C.ncols, C.colptr.cpu().numpy(), C.rowidx.cpu().numpy(), dC.double().cpu().numpy())
+    gA, gB = oracle.grad_a(A, B, G), oracle.grad_b(A, B, G)
+    assert np.array_equal(dA.double().cpu().numpy(), gA) and np.array_equal(dB.double().cpu().numpy(), gB)
+
+    formed = []
+    monkeypatch.setattr(S, "_fused_backward", lambda *a, f=S._fused_backward: formed.append(1) or f(*a))
+    a, b = Ad.values.clone().requires_grad_(True), Bd.values.clone().requires_grad_(True)
+    c, cp, ri = S.SpGEMMFn.apply(a, b, Ad, Bd)
+    c.backward(torch.ones_like(c))
+    assert len(formed) == (longest == 5120)
+    G = oracle.Mat(C.nrows, C.ncols, cp.cpu().numpy(), ri.cpu().numpy(), np.ones(C.nnz))
+    assert np.array_equal(a.grad.double().cpu().numpy(), oracle.grad_a(A, B, G))
+    assert np.array_equal(b.grad.double().cpu().numpy(), oracle.grad_b(A, B, G))
