@@ -226,7 +226,6 @@ struct DotArgs {
 // with no entry need no work.  Columns that fill at most half of what bins 2
 // and 3 hold take tables of half the slots (two more lists): LDS, and with it
 // the waves in flight, is what bounds these kernels.
-constexpr int kMxColsPerWave = 16;
 __global__ __launch_bounds__(256) void k_mxty_bin(const int64_t *Ycp, const int64_t *Mcp, int64_t ncol, int min_bin,
                                                   BinCaps caps, int32_t *bins, WsHeader *hdr) {
   constexpr int NL = kNumBins + 2;

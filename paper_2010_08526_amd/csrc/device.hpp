@@ -85,11 +85,6 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
   return __longlong_as_double((long long)readlane64((int64_t)__double_as_longlong(v), l));
 }
 
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
-
 __device__ __forceinline__ int wave_sum_i32(int v) { return readlane(wave_incl_add(v), 63); }
 
 // Number of set lanes of `mask` below this lane.
