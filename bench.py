@@ -759,11 +759,14 @@ def main():
     res, A = headline(args, torch, np, S, synth)
     torch.cuda.empty_cache()
     if not args.no_extras:
+        import paper_2010_08526_amd.batched as Bt
         for name, fn in (("fwd_bwd", fwd_bwd), ("batched", batched), ("layered", layered), ("bsweep", bsweep),
                          ("prune", prune), ("aat", aat), ("sorted_output", sorted_output)):
             if name in args.extras.split(","):
                 res[name] = fn(args, torch, np, S, synth)
                 torch.cuda.empty_cache()
+                for which in (1, 2, 3):  # what a section tuned is its own: the library keeps it for the process
+                    Bt.set_bin_caps(which, None)
     res["cpu_baseline"] = None if args.no_cpu_baseline else cpu_baseline(A, args.cpu_seconds)
     print(json.dumps(res), flush=True)
 

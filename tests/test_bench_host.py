@@ -76,3 +76,26 @@ def test_default_run_covers_every_section():
     assert set(args.extras.split(",")) == {"fwd_bwd", "batched", "layered", "bsweep", "prune", "aat", "sorted_output"}
     for name in args.extras.split(","):
         assert callable(getattr(b, name))
+
+
+def test_sections_do_not_inherit_tuned_thresholds(monkeypatch, capsys):
+    """What one section's autotuner sets for the process is undone before the
+    next section runs."""
+    import torch
+
+    import paper_2010_08526_amd.batched as Bt
+    b = _bench()
+    log = []
+    monkeypatch.setattr(torch.cuda, "set_device", lambda *a: None)
+    monkeypatch.setattr(torch.cuda, "empty_cache", lambda *a: None)
+    monkeypatch.setattr(Bt, "set_bin_caps", lambda which, caps=None: log.append((which, caps)))
+    monkeypatch.setattr(b, "headline", lambda *a: ({}, None))
+    monkeypatch.setattr(b, "cpu_baseline", lambda *a: None)
+    names = ["fwd_bwd", "batched", "layered", "bsweep", "prune", "aat", "sorted_output"]
+    for name in names:
+        monkeypatch.setattr(b, name, lambda *a, name=name: log.append(name))
+    monkeypatch.setattr(sys, "argv", ["bench.py"])
+    b.main()
+    reset = [(1, None), (2, None), (3, None)]
+    assert log == [x for name in names for x in [name] + reset]
+    capsys.readouterr()
