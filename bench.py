@@ -631,8 +631,8 @@ def prune(args, torch, np, S, synth):
     entries of each column): the headline product at its default budget,
     every batch pruned to its 100 largest entries per column.  Kernel times
     come from the library's per-launch HIP events; bytes are the compulsory
-    ones (rows and values read once, column pointers, per-column selection
-    state written and read once, kept entries written)."""
+    ones (every value and the kept entries' rows read once, column pointers,
+    kept entries written)."""
     dev = torch.device("cuda:0")
     A = synth.rmat(args.scale, 16, synth.WORKLOADS["rmat20"].seed, dtype=torch.float32, device=dev)
     eng = S.Engine(A, A, 1, budget_bytes=1 << 62)
@@ -658,7 +658,7 @@ def prune(args, torch, np, S, synth):
     prof = S.profile_report()
     S.profile_enable(False)
     ms = sum(prof.get(n, (0.0, 0))[0] for n in ("prune_select", "prune_fill"))
-    nbytes = 8 * stats["entries"] + 2 * 8 * (stats["cols"] + pl.nbatches) + 2 * 20 * stats["cols"] + 8 * stats["kept"]
+    nbytes = 4 * stats["entries"] + 2 * 8 * (stats["cols"] + pl.nbatches) + (4 + 8) * stats["kept"]
     gbs = nbytes / (ms * 1e-3) / 1e9 if ms > 0 else None
     log(f"prune: {pl.nbatches} batches, {stats['entries']:.4e} entries -> {stats['kept']:.4e} kept (k={k}), "
         f"select {prof.get('prune_select', (0, 0))[0]:.1f} ms + fill {prof.get('prune_fill', (0, 0))[0]:.1f} ms, "
