@@ -28,6 +28,25 @@ BinCaps bin_caps(int which);  // 0: symbolic, 1: numeric / merge / masked produc
 int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *colptr_out, int64_t *bsum, hipStream_t st,
                        WsHeader *hdr = nullptr);
 
+// What launch_init_header does, for kernels that do it beside their own work.
+__device__ __forceinline__ void init_header(WsHeader *h, uint64_t keep_tag, int keep_status, int keep_left) {
+  if (!keep_status) h->status = 0;
+  if (!keep_left) h->left_tag = 0;  // every other operation may overwrite the slabbed copy
+  h->left_new = 0;
+  for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
+  for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
+  for (int b = 0; b < 4; b++) h->esc_count[b] = 0;
+  for (int b = 0; b < 4; b++) h->sort_count[b] = 0;
+  h->sort_cursor = 0;
+  h->half_count[0] = h->half_count[1] = 0;
+  h->split_cursor = 0;
+  h->items = 0;
+  h->item_cursor = 0;
+  h->nwide = 0;
+  h->wide_cursor = 0;
+  if (keep_tag != kKeepAnyTag && h->clean_tag != keep_tag) h->clean_tag = 0;
+}
+
 inline unsigned grid_of(int64_t n, int64_t per) { return (unsigned)((n + per - 1) / per); }
 
 #define HIPCHK(x)                              \

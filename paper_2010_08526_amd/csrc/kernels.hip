@@ -452,24 +452,6 @@ __device__ __forceinline__ void traverse_merge(const PartDesc *P, int nparts, in
 // ============================================================================
 // Small kernels: header init, fills.
 // ============================================================================
-__device__ __forceinline__ void init_header(WsHeader *h, uint64_t keep_tag, int keep_status, int keep_left) {
-  if (!keep_status) h->status = 0;
-  if (!keep_left) h->left_tag = 0;  // every other operation may overwrite the slabbed copy
-  h->left_new = 0;
-  for (int b = 0; b < kNumBins; b++) h->bin_count[b] = 0;
-  for (int b = 0; b < kNumBins; b++) h->cursor[b] = 0;
-  for (int b = 0; b < 4; b++) h->esc_count[b] = 0;
-  for (int b = 0; b < 4; b++) h->sort_count[b] = 0;
-  h->sort_cursor = 0;
-  h->half_count[0] = h->half_count[1] = 0;
-  h->split_cursor = 0;
-  h->items = 0;
-  h->item_cursor = 0;
-  h->nwide = 0;
-  h->wide_cursor = 0;
-  if (keep_tag != kKeepAnyTag && h->clean_tag != keep_tag) h->clean_tag = 0;
-}
-
 __global__ void k_init_header(WsHeader *h, uint64_t keep_tag, int keep_status = 0, int keep_left = 0) {
   if (threadIdx.x == 0) init_header(h, keep_tag, keep_status, keep_left);
 }
