@@ -232,6 +232,11 @@ int spgemm_merge(const spgemm_csc *parts, int32_t n_parts, const int64_t *c_colp
 int spgemm_transpose(const spgemm_csc *X, int64_t *t_colptr, int32_t *t_rowidx, void *t_values, int64_t *perm,
                      void *ws, size_t ws_bytes, void *stream);
 
+/* Entries of X's longest row, to host memory (rows out of range are not
+ * counted and set the workspace status).  Reads the pattern only.
+ * Synchronizes the stream.  Workspace: as for spgemm_transpose. */
+int spgemm_longest_row(const spgemm_csc *X, int64_t *longest_host, void *ws, size_t ws_bytes, void *stream);
+
 /* Masked product out(k,j) = sum over i of X(i,k) * Y(i,j) for every stored
  * entry (k,j) of the pattern M, written at M's storage position
  * (out_values[M.nnz], X's dtype; X and Y share a dtype; M's values are not

@@ -695,6 +695,7 @@ def spgemm_topk(A, B, threshold: float, k: int, *, layers: int = 1, budget_bytes
 
 # ------------------------------------------------------------ gradient support
 _lib.spgemm_transpose.argtypes = [_P, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
+_lib.spgemm_longest_row.argtypes = [_P, ctypes.POINTER(_i64), _vp, _sz, _vp]
 _lib.spgemm_masked_xty.argtypes = [_P, _P, _P, _vp, _vp, _sz, _vp]
 _lib.spgemm_permute.argtypes = [_vp, _vp, _i64, _i32, _i32, _vp, _vp]
 
@@ -744,29 +745,31 @@ def permute(src: torch.Tensor, perm: torch.Tensor, scatter: bool = False, out: t
 # Largest column of C whose gradient terms the fused backward forms (the
 # largest LDS table is at most half full).
 FUSED_COL_MAX = 5120
-# Longest row of B, and terms of C's pattern per entry of it, from which the
+# Longest row of B, and entries of C (or B) per entry of it, from which the
 # adds to one address bound the fused backward: each takes about 12 ns (22 where
 # A's column is long), whatever else there is to do.  Called again and again, by
 # float32 (float64 likewise), n = 262,144, a row of B in every column: 3.20 ms
-# against 1.77 by transposed patterns at 1 entry of C's pattern per entry of the
-# row, 3.22 against 2.85 at 64, 5.81 against 3.89 at 128 (columns of A of 32), but
+# against 1.77 by transposed patterns at 1 entry of C per entry of the row,
+# 3.22 against 2.85 at 64, 5.81 against 3.89 at 128 (columns of A of 32), but
 # 6.5 against 20.2 at 509; a row in a quarter of 1e6 columns: 3.56 against 3.80
 # at 64.  Rows of 4096: 77 against 88 us; of 8192: 126 against 122-130.
 HUB_ROW_MIN = 4096
 HUB_ROW_TERMS = 128
 
 
-def _hub_row(longest_row: int, nnz_c: int) -> bool:
-    """Whether adds to the same entries of dA would bound the fused backward."""
-    return longest_row > HUB_ROW_MIN and nnz_c < HUB_ROW_TERMS * longest_row
+def _hub_row(longest_row: int, nnz_b: int, nnz_c: int) -> bool:
+    """Whether adds to the same entries of dA would bound the fused backward
+    (it has about as many terms as B or C has entries, or more)."""
+    return longest_row > HUB_ROW_MIN and max(nnz_b, nnz_c) < HUB_ROW_TERMS * longest_row
 
 
 def _longest_row(M, stream=None) -> int:
     """Entries of M's longest row."""
-    T, _ = transpose(M, values=False, perm=False, stream=stream)
-    with _on_stream(stream):
-        return int((T.colptr[1:] - T.colptr[:-1]).max()) if M.nrows > 0 else 0
-
+    out = _i64(0)
+    ws = alloc_workspace(workspace_size(OP_TRANSPOSE, M), M.rowidx.device)
+    _check(_lib.spgemm_longest_row(ctypes.byref(desc(M)), ctypes.byref(out), _ptr(ws), ws.numel(), _stream(stream)),
+           "spgemm_longest_row")
+    return int(out.value)
 
 
 def _fused_backward(A, B, b_values, C, dC_values, ws, stream=None):
@@ -831,8 +834,8 @@ class Backward:
         with _on_stream(stream):
             longest = int((C.colptr[1:] - C.colptr[:-1]).max()) if C.ncols > 0 else 0
         fused = longest <= FUSED_COL_MAX and A.values is not None and B.values is not None
-        if fused and _hub_row(B.ncols, C.nnz):  # (a row holds at most one entry per column)
-            fused = not _hub_row(_longest_row(B, stream), C.nnz)
+        if fused and _hub_row(B.ncols, B.nnz, C.nnz):  # (a row holds at most one entry per column)
+            fused = not _hub_row(_longest_row(B, stream), B.nnz, C.nnz)
         if fused:
             # both from the current stream's pool, as all memory here: gradients
             # may be asked for on another stream than this one

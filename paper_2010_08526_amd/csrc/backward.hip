@@ -35,7 +35,9 @@ __global__ void k_tr_zero(unsigned long long *p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// Row counts, and each entry's place among its row's entries (as counted).
+// Row counts and, with RANK, each entry's place among its row's entries (as
+// counted).
+template <bool RANK>
 __global__ __launch_bounds__(256) void k_tr_count(const int32_t *ri, int64_t nnz, int64_t m, unsigned long long *cnt,
                                                   int32_t *rank, int32_t *status) {
   constexpr int U = 4;  // entries a thread has in flight
@@ -50,15 +52,21 @@ __global__ __launch_bounds__(256) void k_tr_count(const int32_t *ri, int64_t nnz
       c_[u] = 0;
       if (p0 + u * step < nnz) {
         const int32_t r = opaque(r_[u]);
-        if ((uint32_t)r < (uint32_t)m)
-          c_[u] = atomicAdd(&cnt[r], 1ull);
-        else
+        if ((uint32_t)r < (uint32_t)m) {
+          if constexpr (RANK)
+            c_[u] = atomicAdd(&cnt[r], 1ull);
+          else
+            atomicAdd(&cnt[r], 1ull);
+        } else {
           flag_error(status, 3);
+        }
       }
     }
+    if constexpr (RANK) {
 #pragma unroll
-    for (int u = 0; u < U; u++)
-      if (p0 + u * step < nnz) rank[p0 + u * step] = (int32_t)c_[u];
+      for (int u = 0; u < U; u++)
+        if (p0 + u * step < nnz) rank[p0 + u * step] = (int32_t)c_[u];
+    }
   }
 }
 
@@ -828,7 +836,7 @@ static int transpose_typed(const spgemm_csc *X, int64_t *t_colptr, int32_t *t_ro
   hipLaunchKernelGGL(k_tr_zero, dim3(g), dim3(256), 0, st, cnt, m);
   LAUNCHCHK();
   if (X->nnz > 0) {
-    hipLaunchKernelGGL(k_tr_count, dim3(g), dim3(256), 0, st, X->rowidx, X->nnz, m, cnt, rank, &hdr->status);
+    hipLaunchKernelGGL(k_tr_count<true>, dim3(g), dim3(256), 0, st, X->rowidx, X->nnz, m, cnt, rank, &hdr->status);
     LAUNCHCHK();
   }
   rc = launch_colptr_scan((const int64_t *)cnt, m, t_colptr, (int64_t *)(ws + L.scan), st);
@@ -864,6 +872,32 @@ int spgemm_transpose(const spgemm_csc *X, int64_t *t_colptr, int32_t *t_rowidx, 
   if (t_values && X->dtype == SPGEMM_F64)
     return transpose_typed<double>(X, t_colptr, t_rowidx, t_values, perm, L, (char *)ws, s);
   return transpose_typed<float>(X, t_colptr, t_rowidx, t_values, perm, L, (char *)ws, s);
+}
+
+int spgemm_longest_row(const spgemm_csc *X, int64_t *longest_host, void *ws, size_t ws_bytes, void *stream) {
+  int st = check_csc(X, false);
+  if (st) return st;
+  if (!longest_host) return SPGEMM_E_INVAL;
+  WsLayout L;
+  st = ws_layout(SPGEMM_OP_TRANSPOSE, X, nullptr, 0, 0, 1, &L);
+  if (st) return st;
+  st = check_ws(ws, ws_bytes, L.total);
+  if (st) return st;
+  hipStream_t s = (hipStream_t)stream;
+  WsHeader *hdr = (WsHeader *)ws;
+  st = launch_init_header(hdr, (uint64_t)0, s);
+  if (st) return st;
+  unsigned long long *cnt = (unsigned long long *)((char *)ws + L.bins);
+  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid_of(std::max(X->nrows, X->nnz), 256), 8 * device_cus()));
+  hipLaunchKernelGGL(k_tr_zero, dim3(g), dim3(256), 0, s, cnt, X->nrows);
+  LAUNCHCHK();
+  if (X->nnz > 0) {
+    hipLaunchKernelGGL(k_tr_count<false>, dim3(g), dim3(256), 0, s, X->rowidx, X->nnz, X->nrows, cnt,
+                       (int32_t *)nullptr, &hdr->status);
+    LAUNCHCHK();
+  }
+  int64_t sum;
+  return spgemm_count_sums((const int64_t *)cnt, X->nrows, 1, &sum, longest_host, ws, ws_bytes, stream);
 }
 
 int spgemm_masked_xty(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc *M, void *out_values, void *ws,

@@ -35,4 +35,4 @@ def test_undefined_gradient_counts_as_zero():
 @pytest.mark.parametrize("row, nnz_c, hub", [(4096, 4096, False), (4097, 4097, True), (4097, 128 * 4097 - 1, True),
                                              (4097, 128 * 4097, False), (10**7, 10**9, True), (0, 0, False)])
 def test_rule_of_the_fused_gradients(row, nnz_c, hub):
-    assert S._hub_row(row, nnz_c) == hub
+    assert S._hub_row(row, row, nnz_c) == hub and S._hub_row(row, nnz_c, 0) == hub

@@ -91,3 +91,15 @@ def test_transpose_reports_a_bad_row():
     S.transpose(X, ws)
     with pytest.raises(S.SpgemmError):
         S.check_ws(ws)
+
+
+@pytest.mark.parametrize("m, n, nnz", [(1, 1, 1), (5, 0, 0), (0, 3, 0), (7, 4000, 9000), (100000, 300, 20000)])
+def test_longest_row(m, n, nnz):
+    print(f"case: longest row {m} {n} {nnz}", flush=True)
+    rng = np.random.default_rng(nnz)
+    at = rng.choice(m * n, nnz, replace=False) if nnz else np.zeros(0, int)
+    at.sort()
+    lens = np.bincount(at // max(m, 1), minlength=n)
+    X = S.CSC(m, n, torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)).cuda(),
+              torch.from_numpy((at % max(m, 1)).astype(np.int32)).cuda(), None)
+    assert S._longest_row(X) == np.bincount(at % max(m, 1), minlength=1).max()
