@@ -137,16 +137,28 @@ __device__ __forceinline__ void stage_sort_desc(uint64_t *s_v, uint32_t *s_r, in
   }
 }
 
+// Which of the columns j0 ... j0 + per a workgroup has to work on (bit i: column
+// j0 + i): its one or, with LEFT, those that k_prune_top has not settled, found
+// one per lane (looked at one by one, 100,000 settled columns took 25 us).
+template <bool LEFT>
+__device__ __forceinline__ uint64_t prune_columns(int64_t j0, int64_t per, int64_t ncols, const uint64_t *cutv) {
+  if constexpr (!LEFT) return 1ull;
+  const int64_t j = j0 + lane();
+  const uint64_t m = __ballot(lane() < per && j < ncols && cutv[j] != kTopDone);
+  __syncthreads();  // cutv is written below
+  return m;
+}
+
 // cnt[j]: entries column j keeps; (cutv[j], cutr[j]): the smallest kept key
 // ((0, 0) keeps every candidate).  The histogram of the first digit also
 // counts the candidates, so a column that keeps all of them is read once.
-template <typename VT>
+template <bool LEFT, typename VT>
 __global__ __launch_bounds__(kPrThreads) void k_prune_select(const int64_t *__restrict__ colptr,
                                                              const int32_t *__restrict__ rowidx,
                                                              const VT *__restrict__ vals, int64_t ncols, double thr,
                                                              int64_t nnz, int64_t k, int64_t *__restrict__ cnt,
                                                              uint64_t *__restrict__ cutv, uint32_t *__restrict__ cutr,
-                                                             int left_only, int32_t *status) {
+                                                             int32_t *status) {
   constexpr int VD = (int)sizeof(VT), ND = VD + 4;
   constexpr int kShift = 8 * VD - kWideBits;  // value key bits below the wide digit
   __shared__ int s_hist[256];
@@ -158,8 +170,10 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_select(const int64_t *__re
   __shared__ int s_ncw[kPrWaves];  // candidates counted by each wave
   int *s_whist = reinterpret_cast<int *>(s_wide);
   const int t = threadIdx.x;
-  for (int64_t j = blockIdx.x; j < ncols; j += gridDim.x) {
-    if (left_only && cutv[j] != kTopLeft) continue;  // settled by k_prune_top
+  const int64_t per = LEFT ? min((int64_t)kWave, (ncols + gridDim.x - 1) / gridDim.x) : 1;
+  for (int64_t j0 = (int64_t)blockIdx.x * per; j0 < ncols; j0 += (int64_t)gridDim.x * per)
+  for (uint64_t todo = prune_columns<LEFT>(j0, per, ncols, cutv); todo; todo &= todo - 1) {
+    const int64_t j = LEFT ? j0 + __builtin_ctzll(todo) : j0;
     int64_t b = colptr[j], e = colptr[j + 1];
     if (b < 0 || e < b || e > nnz) {  // pointers outside the arrays: the column counts as empty
       if (t == 0) flag_error(status, 5);
@@ -432,22 +446,24 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_select(const int64_t *__re
 // Compacts the kept entries of every column, in input order, to
 // out_colptr[j] ... out_colptr[j + 1].  A column that holds more keys at the
 // cut than its count (a row twice) writes only its count and flags status.
-template <typename VT>
+template <bool LEFT, typename VT>
 __global__ __launch_bounds__(kPrThreads) void k_prune_fill(
     const int64_t *__restrict__ colptr, const int32_t *__restrict__ rowidx, const VT *__restrict__ vals,
     int64_t ncols, int64_t nnz, double thr, const uint64_t *__restrict__ cutv, const uint32_t *__restrict__ cutr,
     const int64_t *__restrict__ out_colptr, int32_t *__restrict__ out_rowidx, VT *__restrict__ out_vals,
-    int left_only, int32_t *status) {
+    int32_t *status) {
   __shared__ int s_cnt[kFillUnroll][kPrWaves];
   __shared__ int s_any[2][kPrWaves];
   const int t = threadIdx.x, w = t / kWave;
   int par = 0;
-  for (int64_t j = blockIdx.x; j < ncols; j += gridDim.x) {
+  const int64_t per = LEFT ? min((int64_t)kWave, (ncols + gridDim.x - 1) / gridDim.x) : 1;
+  for (int64_t j0 = (int64_t)blockIdx.x * per; j0 < ncols; j0 += (int64_t)gridDim.x * per)
+  for (uint64_t todo = prune_columns<LEFT>(j0, per, ncols, cutv); todo; todo &= todo - 1) {
+    const int64_t j = LEFT ? j0 + __builtin_ctzll(todo) : j0;
     int64_t b = colptr[j], e = colptr[j + 1];
     if (b < 0 || e < b || e > nnz) b = e = 0;  // flagged by the select kernel
     const int64_t o = out_colptr[j], lim = out_colptr[j + 1];
     const uint64_t cv = cutv[j];
-    if (left_only && cv == kTopDone) continue;  // written by k_prune_take
     const uint32_t cr = cutr[j];
     int64_t run = 0;
     // kFillUnroll coalesced slots per thread per step (entry c0 + q * 256 + t
@@ -914,8 +930,12 @@ int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr,
   }
   if (n > 0) {
     ProfScope prof("prune_select", st);
-    hipLaunchKernelGGL(k_prune_select<VT>, dim3(top ? std::min(grid, 4096u) : grid), dim3(kPrThreads), 0, st, C->colptr,
-                       C->rowidx, (const VT *)C->values, n, thr, C->nnz, k, cnt, cutv, cutr, top ? 1 : 0, &hdr->status);
+    if (top)
+      hipLaunchKernelGGL((k_prune_select<true, VT>), dim3(std::min(grid, 4096u)), dim3(kPrThreads), 0, st, C->colptr,
+                         C->rowidx, (const VT *)C->values, n, thr, C->nnz, k, cnt, cutv, cutr, &hdr->status);
+    else
+      hipLaunchKernelGGL((k_prune_select<false, VT>), dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
+                         (const VT *)C->values, n, thr, C->nnz, k, cnt, cutv, cutr, &hdr->status);
     LAUNCHCHK();
   }
   rc = launch_colptr_scan(cnt, n, out_colptr, (int64_t *)(ws + L.scan), st);
@@ -932,9 +952,14 @@ int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr,
     LAUNCHCHK();
   }
   ProfScope prof("prune_fill", st);
-  hipLaunchKernelGGL(k_prune_fill<VT>, dim3(top ? std::min(grid, 4096u) : grid), dim3(kPrThreads), 0, st, C->colptr,
-                     C->rowidx, (const VT *)C->values, n, C->nnz, thr, (const uint64_t *)cutv, (const uint32_t *)cutr,
-                     (const int64_t *)out_colptr, out_rowidx, (VT *)out_values, top ? 1 : 0, &hdr->status);
+  if (top)
+    hipLaunchKernelGGL((k_prune_fill<true, VT>), dim3(std::min(grid, 4096u)), dim3(kPrThreads), 0, st, C->colptr,
+                       C->rowidx, (const VT *)C->values, n, C->nnz, thr, (const uint64_t *)cutv, (const uint32_t *)cutr,
+                       (const int64_t *)out_colptr, out_rowidx, (VT *)out_values, &hdr->status);
+  else
+    hipLaunchKernelGGL((k_prune_fill<false, VT>), dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
+                       (const VT *)C->values, n, C->nnz, thr, (const uint64_t *)cutv, (const uint32_t *)cutr,
+                       (const int64_t *)out_colptr, out_rowidx, (VT *)out_values, &hdr->status);
   LAUNCHCHK();
   return SPGEMM_OK;
 }
