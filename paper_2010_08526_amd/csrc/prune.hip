@@ -9,7 +9,7 @@
 // their input order, so the hash-table order of the numeric pass carries
 // over unchanged.
 //
-// For k up to 1024 on columns of at least k entries on average, k_prune_top
+// For small k against the columns' lengths (see read_once), k_prune_top
 // reads every column once (see there).  Otherwise, and for columns with too
 // many equal values for it:
 //
@@ -577,22 +577,55 @@ __device__ __forceinline__ double key_value(uint64_t k) {
 // workgroup (1 <= need <= their number), by 8-bit digits, most significant
 // first.  Digits stop once no more than `stop` keys are at or above the chosen
 // bucket: returned is its lower edge (the key itself after the last digit).
-// above / equal: the keys above the bucket, and in it.  s_hist: 2 x 256 + 4
-// words; a digit uses one half while the other is cleared.  Contains barriers.
-template <int E, typename KT>
+// above / equal: the keys above the bucket, and in it.  With TIGHT (32-bit keys
+// whose high digits are alike: rows) the digits that all keys share are passed
+// over: 50,000 columns of 300 entries of 8 values, k = 10, 611 -> 569 us.  (The
+// same for the low digits of float64 values takes registers that cost more.)
+// s_hist: kKthWords words; a digit uses one of two histograms while the other is
+// cleared.  Contains barriers.
+constexpr int kKthWords = 2 * 256 + 4 + 2 * kPrWaves;
+template <bool TIGHT, int E, typename KT>
 __device__ __forceinline__ KT block_kth(const KT (&key)[E], uint32_t have, int need, int stop, int *s_hist, int &above,
                                         int &equal) {
   constexpr int ND = (int)sizeof(KT);
+  static_assert(!TIGHT || ND == 4, "32-bit keys");
   int *s_sel = s_hist + 512;
+  uint32_t *s_key = reinterpret_cast<uint32_t *>(s_hist + 516);  // each wave's largest key and largest complement
   const int t = threadIdx.x;
   KT prefix = 0;
   above = 0;
   equal = 0;
   s_hist[t] = 0;  // (256 threads)
   __syncthreads();
+  int top = ND - 1, par = 0;
+  if constexpr (TIGHT) {
+    // the highest digit in which the keys differ; those above it are the prefix
+    uint32_t hi = 0, nlo = 0;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      hi = max(hi, (have >> e) & 1u ? key[e] : 0u);
+      nlo = max(nlo, (have >> e) & 1u ? ~key[e] : 0u);
+    }
+    hi = wave_umax(hi);
+    nlo = wave_umax(nlo);
+    if (lane() == 0) {
+      s_key[t / kWave] = hi;
+      s_key[kPrWaves + t / kWave] = nlo;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int z = 0; z < kPrWaves; z++) {
+      hi = max(hi, s_key[z]);
+      nlo = max(nlo, s_key[kPrWaves + z]);
+    }
+    const uint32_t diff = hi ^ ~nlo;
+    top = diff == 0 ? 0 : (31 - __clz((int)diff)) / 8;  // (alike: the last digit counts them)
+    if (top < 3) prefix = hi & (~0u << (8 * (top + 1)));
+  }
 #pragma unroll 1
-  for (int d = ND - 1; d >= 0; d--) {
-    int *h_cur = s_hist + 256 * (d & 1 ? 0 : 1), *h_next = s_hist + 256 * (d & 1 ? 1 : 0);
+  for (int d = top; d >= 0; d--) {
+    int *h_cur = s_hist + 256 * par, *h_next = s_hist + 256 * (par ^ 1);
+    par ^= 1;
     const KT mask = d == ND - 1 ? KT(0) : (KT)(~KT(0) << (8 * (d + 1)));
 #pragma unroll
     for (int e = 0; e < E; e++)
@@ -668,7 +701,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
     RankLds<kTopMaxK, int32_t> rank;
   };
   __shared__ Lds s;
-  __shared__ int s_hist[2 * 256 + 4];
+  __shared__ int s_hist[kKthWords];
   __shared__ uint32_t s_red[4 * kPrWaves];
   __shared__ int s_add[3];  // entries appended by the steps t, t + 1, t + 2 (mod 3)
   __shared__ int s_n;
@@ -709,7 +742,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
         }
         if (__syncthreads_count(has ? 1 : 0) >= k) {  // uniform
           int above, equal;
-          const KT kth = block_kth<1>(mk, has ? 1u : 0u, k, (k + kPrThreads) / 2, s_hist, above, equal);
+          const KT kth = block_kth<false, 1>(mk, has ? 1u : 0u, k, (k + kPrThreads) / 2, s_hist, above, equal);
           const KT least = (KT)order_key(VT(-INFINITY));
           const VT edge = key_value(kth < least ? least : kth);
           lo = edge > lo ? edge : lo;
@@ -755,7 +788,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
         int above, equal;
         // (the lower edge of the k-th largest key's bucket will do, unless
         // the bucket is crowded; no value is below -infinity)
-        KT kth = block_kth<E>(key, have, k, (k + kLimit) / 2, s_hist, above, equal);
+        KT kth = block_kth<false, E>(key, have, k, (k + kLimit) / 2, s_hist, above, equal);
         const KT least = (KT)order_key(VT(-INFINITY));
         kth = kth < least ? least : kth;
         if (t == 0) s_n = 0;
@@ -799,7 +832,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
       }
       if (n > k) {
         int above, equal;
-        const KT kth = block_kth<E>(key, have, k, k, s_hist, above, equal);
+        const KT kth = block_kth<false, E>(key, have, k, k, s_hist, above, equal);
         uint32_t keep = 0, tie = 0;
 #pragma unroll
         for (int i = 0; i < E; i++) {
@@ -815,7 +848,7 @@ __global__ __launch_bounds__(kPrThreads) void k_prune_top(const int64_t *__restr
 #pragma unroll
           for (int i = 0; i < E; i++) rk[i] = (tie >> i) & 1u ? row_key(rowidx[b + pos[i]]) : 0u;
           int ra, re;
-          const uint32_t rth = block_kth<E>(rk, tie, k - above, k - above, s_hist, ra, re);
+          const uint32_t rth = block_kth<true, E>(rk, tie, k - above, k - above, s_hist, ra, re);
 #pragma unroll
           for (int i = 0; i < E; i++)
             if (((tie >> i) & 1u) && rk[i] < rth) tie &= ~(1u << i);
@@ -900,6 +933,30 @@ inline float threshold_of(double thr, float) {
   return (double)f < thr ? std::nextafterf(f, INFINITY) : f;
 }
 
+// Whether columns are read by k_prune_top.  It stages k positions per column in
+// out_values, which holds that many where columns hold k entries or more on
+// average; three more launches (25 us) have to be won back, and a large k against
+// the column means that the bound rises slowly and lists are sorted through.  Two
+// kernels against it, us, uniform values:
+//   float32, k = 10:  n x 100: 62 90 (n = 1000), 143 131 (10,000), 475 348 (50,000)
+//                     n x 1200: 105 109 (4000), 204 192 (12,000); n x 1000: 113 119
+//                     (5000), 289 264 (20,000)
+//                     n x 3000: 78 83 (400), 96 83 (1500); n x 8000: 103 83 (4)
+//   float64, k = 10:  n x 1200: 81 84 (400), 115 85 (1500); n x 2048: 100 83 (4)
+//   float32, k / length 1/16, 1/10, 1/8 at 4000 x 5000: 200 171, 200 191, 201 204;
+//                     k = 100, 256, 600 at 20,000 x 1000: 283 283, 287 298, 282 328
+// (Values of few kinds, whose ties have to be broken by row, can take up to 1.2
+// times as long as by the two kernels, in short float64 columns 1.4.)
+inline bool read_once(int vbytes, int64_t nnz, int64_t n, int64_t k) {
+  const int64_t mean = nnz / n;
+  if (k < 1 || k > mean || k > kTopMaxK - kTopMaxK / 16) return false;
+  if (k > (mean >= 2048 ? mean / 16 : 256)) return false;
+  if (vbytes == 8) return mean >= 2048 || n >= 8192 || nnz >= (1 << 20);
+  if (mean >= 8192) return true;
+  if (mean >= 2048) return nnz >= (1 << 22);
+  return mean < 512 ? n >= 8192 : nnz >= (1 << 24);
+}
+
 template <typename VT>
 int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr, int32_t *out_rowidx,
                 void *out_values, const WsLayout &L, char *ws, hipStream_t st) {
@@ -911,16 +968,12 @@ int prune_typed(const spgemm_csc *C, double thr, int64_t k, int64_t *out_colptr,
   uint64_t *cutv = (uint64_t *)(ws + L.pr_cutv);
   uint32_t *cutr = (uint32_t *)(ws + L.pr_cutr);
   const unsigned grid = (unsigned)(n < kPrMaxGrid ? n : kPrMaxGrid);
-  // The one-reading kernel stages k positions per column in out_values, which
-  // holds that many where k * n is within the output's bound, that is, where
-  // columns hold k entries or more on average; otherwise most columns keep
-  // everything and the two kernels below read them as often.
-  const bool top = n > 0 && k >= 1 && k <= kTopMaxK && k <= C->nnz / n;
+  const bool top = n > 0 && read_once((int)sizeof(VT), C->nnz, n, k);
   int32_t *stage = (int32_t *)out_values;
   if (top) {
     ProfScope prof("prune_select", st);
     const VT t = threshold_of(thr, VT(0));
-    if (k <= 512)
+    if (3 * k <= 2 * (2560 - kTopStep))  // the list can grow by half before the bound rises
       hipLaunchKernelGGL((k_prune_top<2560, VT>), dim3(grid), dim3(kPrThreads), 0, st, C->colptr, C->rowidx,
                          (const VT *)C->values, n, t, C->nnz, (int)k, cnt, cutv, stage, &hdr->status);
     else

@@ -72,6 +72,49 @@ def test_prune_once(kind, dtype):
             assert np.array_equal(G.values.double().cpu().numpy(), P.values.astype(np.float64)), what
 
 
+@pytest.mark.parametrize("kind", ["normal", "rising", "falling", "levels", "few_large", "equal", "special"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_prune_once_among_long_columns(kind, dtype):
+    """Columns long enough on average for the one reading up to its largest k,
+    lists of both sizes; short columns, and ones shorter than k, among them."""
+    print(f"case: prune once long {kind} {dtype}", flush=True)
+    rng = np.random.default_rng(len(kind) + 7)
+    lens = [0, 1, 300, 339, 341, 343, 511, 513, 959, 961, 1023, 1025, 2047, 2048, 2049, 3000, 9000, 60011, 300007]
+    m = 400000
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, n, replace=False) for n in lens]).astype(np.int32)
+    v = torch.from_numpy(np.concatenate([_values(kind, n, rng) for n in lens])).to(dtype)
+    M = synth.CSC(m, len(lens), torch.from_numpy(cp), torch.from_numpy(ri), v)
+    D = M.to("cuda")
+    assert 16 * 960 <= M.nnz // len(lens)
+    for k, thr in ((1, -np.inf), (340, 0.0), (341, -np.inf), (342, 0.1), (600, -np.inf), (960, 0.0), (961, 0.0)):
+        G = S.prune_topk(D, thr, k)
+        P = oracle.prune_topk(M, thr, k)
+        what = f"{kind} k={k} thr={thr}"
+        assert np.array_equal(G.colptr.cpu().numpy(), P.colptr), what
+        assert np.array_equal(G.rowidx.cpu().numpy(), P.rowidx), what  # input order
+        assert np.array_equal(G.values.double().cpu().numpy(), P.values.astype(np.float64)), what
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("lens, k", [(100, 100), (100, 10), (5, 5), (5, 1)])
+def test_prune_once_of_many_short_columns(dtype, lens, k):
+    """Enough short columns for the one reading; ties by the dozen."""
+    print(f"case: prune once short {lens} {k} {dtype}", flush=True)
+    rng = np.random.default_rng(lens + k)
+    n, m = 9000, 70001
+    ln = np.maximum(rng.integers(lens - 2, lens + 6, n), 0)
+    cp = np.concatenate([[0], np.cumsum(ln)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, c, replace=False) for c in ln]).astype(np.int32)
+    v = torch.from_numpy(rng.integers(0, 6, ri.size) / 4.0).to(dtype)
+    M = synth.CSC(m, n, torch.from_numpy(cp), torch.from_numpy(ri), v)
+    assert k <= M.nnz // n
+    G, P = S.prune_topk(M.to("cuda"), 0.25, k), oracle.prune_topk(M, 0.25, k)
+    assert np.array_equal(G.colptr.cpu().numpy(), P.colptr)
+    assert np.array_equal(G.rowidx.cpu().numpy(), P.rowidx)
+    assert np.array_equal(G.values.double().cpu().numpy(), P.values.astype(np.float64))
+
+
 def test_prune_once_reports_a_repeated_row():
     """Two equal entries of one row at the cut."""
     print("case: prune once repeated row", flush=True)
@@ -99,7 +142,13 @@ def test_prune_once_keeps_the_first_of_repeated_rows(dtype):
     larger = (thread >= 192) & (slot == 7)
     r = torch.where(again, 0, 1 + torch.arange(n)).to(torch.int32).repeat(cols).cuda()
     v = torch.where(again, 1.0, torch.where(larger, 2.0, -1.0)).to(dtype).repeat(cols).cuda()
-    C = S.CSC(n + 1, cols, torch.arange(0, n * cols + 1, n, device="cuda"), r, v)
+    # (and one long column, by which the columns are long enough on average)
+    long = 400000
+    r = torch.cat([r, torch.arange(long, dtype=torch.int32, device="cuda")])
+    v = torch.cat([v, torch.arange(long, device="cuda").to(dtype)])
+    cp = torch.cat([torch.arange(0, n * cols + 1, n), torch.tensor([n * cols + long])])
+    cols += 1
+    C = S.CSC(long, cols, cp.cuda(), r, v)
     out = (torch.empty(cols + 1, dtype=torch.int64, device="cuda"),
            torch.empty(k * cols, dtype=torch.int32, device="cuda"), torch.empty(k * cols, dtype=dtype, device="cuda"))
     ws = S.alloc_workspace(S.workspace_size(S.OP_PRUNE, C))
@@ -107,7 +156,8 @@ def test_prune_once_keeps_the_first_of_repeated_rows(dtype):
                                       ws.numel(), S._stream(None)), "prune")
     assert S.ws_status_code(ws) == (S.E_DEVICE, 10)
     assert torch.equal(out[0].cpu(), torch.arange(0, k * cols + 1, k))
-    assert torch.all(out[1] == 0) and torch.all(out[2] == 1.0)
+    assert torch.all(out[1][:-k] == 0) and torch.all(out[2][:-k] == 1.0)
+    assert torch.equal(out[1][-k:].cpu(), torch.arange(long - k, long, dtype=torch.int32))
 
 
 def test_prune_once_in_a_graph():
