@@ -237,7 +237,8 @@ struct DotArgs {
 // heavy_code: the status of a column above the largest table (0: none, the
 // caller forms those itself).
 __global__ __launch_bounds__(256) void k_mxty_bin(const int64_t *Ycp, const int64_t *Mcp, int64_t ncol, int min_bin,
-                                                  BinCaps caps, int32_t *bins, WsHeader *hdr, int heavy_code) {
+                                                  BinCaps caps, int32_t *bins, WsHeader *hdr, int heavy_code,
+                                                  int halves) {
   constexpr int NL = kNumBins + 2;
   __shared__ int s_cnt[NL];
   __shared__ int s_base[NL];
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(256) void k_mxty_bin(const int64_t *Ycp, const int6
     bin = max(bin, min_bin);
     if (bin == kNumBins - 1 && heavy_code) flag_error(&hdr->status, heavy_code);
     // half tables: listed from the end of their bin's array
-    if ((bin == 2 || bin == 3) && 2 * u <= kNumTableCap[bin]) bin += kNumBins - 2;
+    if ((bin == 2 || bin == 3) && (halves >> (bin - 2)) & 1 && 2 * u <= kNumTableCap[bin]) bin += kNumBins - 2;
   }
   s_bin[t] = bin;
   s_pos[t] = bin >= 0 ? atomicAdd(&s_cnt[bin], 1) : 0;
@@ -683,7 +684,7 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
   int rc = launch_init_header(hdr, zero_region_tag(kTagMasked, L), st);
   if (rc) return rc;
   hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, Y->colptr, M->colptr, n, g_min_bin_value(),
-                     bin_caps(1), bins, hdr, sync ? 0 : 7);
+                     bin_caps(1), bins, hdr, sync ? 0 : 7, half_tables(n));
   LAUNCHCHK();
   WsHeader h;
   int cnt[kNumBins];
@@ -700,7 +701,7 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
   int32_t *status = &hdr->status;
   for (int b = 0; b < kNumBins + 1; b++) {
     const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
-    const int c = half < 0 ? cnt[b] : (sync ? h.half_count[half] : -1);
+    const int c = half < 0 ? cnt[b] : (sync ? h.half_count[half] : ((half_tables(n) >> half) & 1 ? -1 : 0));
     if (c == 0) continue;
     ProfScope prof("masked_xty", st);
     const int32_t *list = half < 0 ? bins + (int64_t)b * n : bins + (int64_t)(half + 3) * n - 1;
@@ -790,7 +791,7 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   caps.cap[kNumBins - 2] = kNumTableCap[kNumBins - 2];  // whatever fits the largest table is formed
   if (n > 0) {
     hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n,
-                       std::min(g_min_bin_value(), kNumBins - 2), caps, bins, hdr, 7);
+                       std::min(g_min_bin_value(), kNumBins - 2), caps, bins, hdr, 7, half_tables(n));
     LAUNCHCHK();
   }
   DotArgs<VT> a{A->colptr, A->rowidx, (const VT *)A->values, C->colptr, C->rowidx, (const VT *)dC,
@@ -800,6 +801,7 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
     const int half = b - (kNumBins - 1);  // 0, 1: the half tables of bins 2 and 3
     static const char *kNames[kNumBins + 1] = {"fbwd_wave64", "fbwd_wave256", "fbwd_wave1024", "fbwd_block4096",
                                                "fbwd_block10240", "fbwd_wave512", "fbwd_block2048"};
+    if (half >= 0 && !((half_tables(n) >> half) & 1)) continue;
     ProfScope prof(kNames[b], st);
     const int32_t *list = half < 0 ? bins + (int64_t)b * n : bins + (int64_t)(half + 3) * n - 1;
     const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];

@@ -28,6 +28,18 @@ BinCaps bin_caps(int which);  // 0: symbolic, 1: numeric / merge / masked produc
 int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *colptr_out, int64_t *bsum, hipStream_t st,
                        WsHeader *hdr = nullptr);
 
+// Bins of whose columns those that fill at most half of what the bin holds take
+// tables of half the slots (bit 0: bin 2, bit 1: bin 3), for a call over ncol
+// columns.  Half tables let more columns run at once and are fuller, so searches
+// in them are longer: they pay once the columns do not all run at once in full
+// ones anyway.  Masked products, columns of 130-256 rows (bin 2), half against
+// full: 0.77 to 1.1 times as fast at 50 to 2000 columns, 1.25 to 1.75 at 4000;
+// of 520-1024 rows (bin 3), 0.73 to 1.1 at 50 to 500 columns, 1.0 to 2.4 at 1000
+// (numeric pass 0.88 to 1.0 and 1.9 to 2.2; 0.95 to 1.0 and 1.2 to 1.7).
+inline int half_tables(int64_t ncol) {
+  return (ncol > 12 * (int64_t)device_cus() ? 1 : 0) | (ncol > 3 * (int64_t)device_cus() ? 2 : 0);
+}
+
 // What launch_init_header does, for kernels that do it beside their own work.
 __device__ __forceinline__ void init_header(WsHeader *h, uint64_t keep_tag, int keep_status, int keep_left) {
   if (!keep_status) h->status = 0;

@@ -599,7 +599,7 @@ __global__ __launch_bounds__(256) void k_bin_flops(const int64_t *Acp, const int
 // pointers.
 __global__ __launch_bounds__(256) void k_bin_len(const int64_t *c_colptr, int64_t ncol, int32_t *bins, WsHeader *hdr,
                                                  int min_bin, BinCaps caps, const int64_t *esc_flops, double esc_cf,
-                                                 int64_t max_len) {
+                                                 int64_t max_len, int halves) {
   const int64_t jj = (int64_t)blockIdx.x * 256 + threadIdx.x;
   int bin = -1;
   if (jj < ncol) {
@@ -608,7 +608,7 @@ __global__ __launch_bounds__(256) void k_bin_len(const int64_t *c_colptr, int64_
     if (len > 0) bin = max(bin_of(len, caps), min_bin);
     // columns that fill at most half of what bins 2 and 3 hold take tables of
     // half the slots (see k_num_wave)
-    if ((bin == 2 || bin == 3) && 2 * len <= kNumTableCap[bin]) bin += kHalfList - 2;
+    if ((bin == 2 || bin == 3) && (halves >> (bin - 2)) & 1 && 2 * len <= kNumTableCap[bin]) bin += kHalfList - 2;
     if (esc_flops && len > 0) {
       const int e = esc_class(esc_flops[jj], len, esc_cf);
       if (e >= 0) bin = kNumBins + e;
@@ -3372,11 +3372,12 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   if (L.P > 0 && L.P <= kItemSlabs && max_len != INT64_MAX && std::min(max_len, A->nrows) > kNumTableCap[kNumBins - 2])
     caps.cap[kNumBins - 2] = caps.cap[kNumBins - 3];
   max_len = std::min(max_len, A->nrows);
+  const int halves = half_tables(ncol);
   hipLaunchKernelGGL(k_init_header, dim3(1), dim3(64), 0, st, hdr, zero_region_tag(kTagProduct, L),
                      keep_status ? 1 : 0, 1);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_bin_len, dim3(grid_of(ncol, 256)), dim3(256), 0, st, c_colptr, ncol, bins, hdr, g_min_bin,
-                     caps, esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0, max_len);
+                     caps, esc ? esc->flops : (const int64_t *)nullptr, esc ? esc->cf : 0.0, max_len, halves);
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;
@@ -3386,9 +3387,11 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   // about 4.6 us of the stream's time)
   for (int b = g_min_bin + 1; b < kNumBins; b++)
     if (cnt[b] < 0 && (max_len <= caps.cap[b - 1] || (b < kNumBins - 1 && caps.cap[b] == caps.cap[b - 1]))) cnt[b] = 0;
-  const int half_cnt[2] = {sync ? h.half_count[0] : cnt[2], sync ? h.half_count[1] : cnt[3]};
-  for (int b = 2; b <= 3; b++)
-    if (cnt[b] < 0 && 2 * max_len <= kNumTableCap[b]) cnt[b] = 0;  // its half tables hold every column
+  int half_cnt[2] = {sync ? h.half_count[0] : cnt[2], sync ? h.half_count[1] : cnt[3]};
+  for (int b = 2; b <= 3; b++) {
+    if (!((halves >> (b - 2)) & 1)) half_cnt[b - 2] = 0;
+    else if (cnt[b] < 0 && 2 * max_len <= kNumTableCap[b]) cnt[b] = 0;  // its half tables hold every column
+  }
   ProductSrc<VT, SR> src;
   src.a = product_args<VT>(A, B, klo, khi);
   src.c0 = c0;
@@ -3517,7 +3520,7 @@ static int merge_typed(const spgemm_csc *parts, int32_t n_parts, const int64_t *
     LAUNCHCHK();
   }
   hipLaunchKernelGGL(k_bin_len, dim3(grid_of(L.ncol, 256)), dim3(256), 0, st, c_colptr, L.ncol, bins, hdr, g_min_bin,
-                     g_caps[1], (const int64_t *)nullptr, 0.0, INT64_MAX);
+                     g_caps[1], (const int64_t *)nullptr, 0.0, INT64_MAX, half_tables(L.ncol));
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;

@@ -48,6 +48,38 @@ def test_masked_product_limits(dtype, mix):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n", [768, 769, 3072, 3073])
+def test_half_tables_by_columns(n, dtype):
+    """As many columns as take full tables only, and one more than that for
+    either of the bins with half tables: products, masked products and both
+    gradients of columns at the tables' limits; exact."""
+    print(f"case: half tables {n} {dtype}", flush=True)
+    rng = np.random.default_rng(n)
+    m = 2100
+    lens = [128, 129, 256, 257, 512, 513, 1024, 1025, 2048]
+    one = _csc(m, [np.array([i]) for i in range(m)], rng, dtype)  # columns of one entry
+    B = _csc(m, [rng.permutation(m)[:lens[j % len(lens)]] for j in range(n)], rng, dtype)
+    A, Bd = one.to("cuda"), B.to("cuda")
+    C = S.spgemm(A, Bd, sorted_output=True)
+    P = oracle.spgemm(one, B)
+    assert np.array_equal(C.colptr.cpu().numpy(), P.colptr) and np.array_equal(C.rowidx.cpu().numpy(), P.rowidx)
+    assert np.array_equal(C.values.double().cpu().numpy(), P.values)
+    H = S.spgemm(A, Bd, layers=3)  # merged
+    order = np.lexsort((H.rowidx.cpu().numpy(), np.repeat(np.arange(n), np.diff(P.colptr))))
+    assert np.array_equal(H.values.double().cpu().numpy()[order], P.values)
+    M = _csc(m, [rng.permutation(m)[:5 + j % 3] for j in range(n)], rng, dtype)
+    got = S.masked_xty(A, C, M.to("cuda"))
+    assert np.array_equal(got.double().cpu().numpy(), oracle.masked_xty(one, P, M))
+    bw = S.Backward(A, Bd, C)
+    dA, dB = bw(C.values)
+    bw.check()
+    assert bw.ws_f is not None
+    G = oracle.Mat(m, n, P.colptr, P.rowidx, P.values)
+    assert np.array_equal(dA.double().cpu().numpy(), oracle.grad_a(one, B, G).astype(np.float32 if dtype == torch.float32 else np.float64))
+    assert np.array_equal(dB.double().cpu().numpy(), oracle.grad_b(one, B, G))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
 def test_gradient_limits(dtype):
     """Both gradients of products whose columns hold 1 to 5120 rows, the
     entries of B ranging from one per column to several per wave; exact."""
