@@ -16,11 +16,12 @@ int launch_init_header(WsHeader *h, uint64_t keep_tag, hipStream_t st);
 int launch_set_tag(WsHeader *h, uint64_t tag, hipStream_t st);
 // Row sort of C's columns into (ro, vo) with column lists in `lists`
 // (3 * C->ncols int32) and counters in hdr's sort_count and sort_cursor (zero
-// on entry).  Columns that esc_class(skip_flops[j], nnz_j, skip_cf) places in
+// on entry unless init is given, which sets the header up).  Columns that esc_class(skip_flops[j], nnz_j, skip_cf) places in
 // an expand-sort-compress kernel are skipped (skip_flops NULL: none).
 // Kernels for columns longer than max_len are not launched.
 int sort_column_lists(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists, WsHeader *hdr,
-                      const int64_t *skip_flops, double skip_cf, hipStream_t st, int64_t max_len);
+                      const int64_t *skip_flops, double skip_cf, hipStream_t st, int64_t max_len,
+                      bool init = false);
 int g_min_bin_value();  // the spgemm_debug_min_bin setting
 BinCaps bin_caps(int which);  // 0: symbolic, 1: numeric / merge / masked product
 // colptr_out[0] = 0, colptr_out[i+1] = counts[0] + ... + counts[i]; bsum holds n / 8192 + 2 int64

@@ -89,6 +89,28 @@ def test_sort_columns_keeps_repeated_rows(n, m):
     assert np.array_equal(gv[order], v[want])
 
 
+@pytest.mark.parametrize("n", [1, 1023, 1025, 4096, 4097])
+def test_sort_columns_by_number_of_columns(n):
+    """Columns listed by one workgroup, and one column more; a workspace that
+    held a status before."""
+    print(f"case: sort {n} columns", flush=True)
+    rng = np.random.default_rng(n)
+    m = 70000
+    lens = np.array([5, 64, 65, 0, 512, 513, 1, 2, 30, 4097])[rng.integers(0, 10, n) if n < 2000 else np.where(
+        rng.random(n) < 0.02, 9, rng.integers(0, 9, n))]
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, c, replace=False) for c in lens]).astype(np.int32)
+    v = rng.standard_normal(ri.size)
+    C = S.CSC(m, n, torch.from_numpy(cp).cuda(), torch.from_numpy(ri).cuda(), torch.from_numpy(v).cuda())
+    ws = S.alloc_workspace(S.workspace_size(S.OP_SORT, C))
+    ws[:1024].fill_(7)
+    T = S.sort_columns(C, ws=ws)
+    S.check_ws(ws)
+    order = np.lexsort((ri, np.repeat(np.arange(n), lens)))
+    assert np.array_equal(T.rowidx.cpu().numpy(), ri[order])
+    assert np.array_equal(T.values.cpu().numpy(), v[order])
+
+
 @pytest.mark.parametrize("m", [3, 60, 700, 5000, 300000])
 @pytest.mark.parametrize("shape", ["even", "crowd"])
 def test_expand_sort_compress_classes(m, shape):
