@@ -691,8 +691,10 @@ __global__ __launch_bounds__(256) void k_sym_wave(ProductArgs<float> a, int64_t 
 // One workgroup per column, table (TBL slots) or bitmap (one bit per row of
 // C, sized by the launch) shared by its waves.
 template <int TBL, int THREADS, bool BITS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(!BITS && THREADS == 1024 ? 4 : 8))) void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list,
-                                                       const int32_t *count_p, int64_t *nnz_out, int32_t *status) {
+__global__ __launch_bounds__(THREADS)
+__attribute__((amdgpu_waves_per_eu(!BITS && THREADS == 1024 ? 4 : 8)))
+void k_sym_block(ProductArgs<float> a, int64_t c0, const int32_t *list, const int32_t *count_p, int64_t *nnz_out,
+                 int32_t *status) {
   constexpr int NW = THREADS / kWave;
   extern __shared__ int32_t s_keys[];  // TBL slots, or (m + 31) / 32 words (all zero between columns)
   __shared__ SymScratch s_sc[NW];
@@ -978,9 +980,10 @@ __global__ __launch_bounds__(256) void k_num_wave(Src src, const int32_t *list, 
 }
 
 template <int TBL, int THREADS, class VT, class Src>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TBL <= 2048 ? 5 : (THREADS == 1024 ? 4 : 2)))) void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p,
-                                                       const int64_t *c_colptr, int32_t *out_ri, VT *out_v,
-                                                       int32_t *status) {
+__global__ __launch_bounds__(THREADS)
+__attribute__((amdgpu_waves_per_eu(TBL <= 2048 ? 5 : (THREADS == 1024 ? 4 : 2))))
+void k_num_block(Src src, const int32_t *list, int dir, const int32_t *count_p, const int64_t *c_colptr,
+                 int32_t *out_ri, VT *out_v, int32_t *status) {
   constexpr int NW = THREADS / kWave;
   static_assert(TBL % 4 == 0, "tables cleared 16 bytes at a time");
   static_assert(TBL <= 65536, "slot numbers fit 16 bits");
@@ -2634,7 +2637,8 @@ __global__ __launch_bounds__(kHvWideThreads) void k_hv_wide(HvArgs<VT> a, int64_
     if (threadIdx.x < kWords) s_bits[threadIdx.x] = 0u;
     __syncthreads();
     int outside = 0;
-    int bad = hv_traverse<VT, SR, kHvWidePipe>(a, a.Bcp[col], a.Bcp[col + 1], sa, sb, w, NW, 1, s_sc[w], (const HvPre<VT> *)nullptr, [&](int32_t row, double v) {
+    int bad = hv_traverse<VT, SR, kHvWidePipe>(a, a.Bcp[col], a.Bcp[col + 1], sa, sb, w, NW, 1, s_sc[w],
+                                               (const HvPre<VT> *)nullptr, [&](int32_t row, double v) {
       const uint32_t r = (uint32_t)row - rb;
       if (r < (uint32_t)kHvWideRows) {
         SR::acc(&s_acc[r], v);
@@ -3233,36 +3237,49 @@ static int symbolic_pass(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
     switch (b) {
       case 0:
         if (bits(64))
-          hipLaunchKernelGGL((k_sym_wave<64, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][0], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<64, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][0], ncol)), dim3(256), 0,
+                             st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_wave<64, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][0], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<64, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][0], ncol)), dim3(256), 0,
+                             st, a, c0, list, cp, nnz_row, status);
         break;
       case 1:
         if (bits(256))
-          hipLaunchKernelGGL((k_sym_wave<256, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][1], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<256, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][1], ncol)), dim3(256), 0,
+                             st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_wave<256, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][1], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<256, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][1], ncol)), dim3(256), 0,
+                             st, a, c0, list, cp, nnz_row, status);
         break;
       case 2:
         if (bits(1024))
-          hipLaunchKernelGGL((k_sym_wave<1024, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][2], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<1024, true>), dim3(bin_grid(cnt[b], true, g_bpc[0][2], ncol)), dim3(256), 0,
+                             st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_wave<1024, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][2], ncol)), dim3(256), 0, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_wave<1024, false>), dim3(bin_grid(cnt[b], true, g_bpc[0][2], ncol)), dim3(256), 0,
+                             st, a, c0, list, cp, nnz_row, status);
         break;
       case 3:
         if (bits(4096))
-          hipLaunchKernelGGL((k_sym_block<4096, 256, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][3], fit(256, (int64_t)wb)), ncol)), dim3(256), wb, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<4096, 256, true>),
+                             dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][3], fit(256, (int64_t)wb)), ncol)),
+                             dim3(256), wb, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_block<4096, 256, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][3], ncol)), dim3(256), 4096 * 4, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<4096, 256, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][3], ncol)),
+                             dim3(256), 4096 * 4, st, a, c0, list, cp, nnz_row, status);
         break;
       case 4:
         if (bits(32768))
-          hipLaunchKernelGGL((k_sym_block<32768, 512, true>), dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][4], fit(512, (int64_t)wb)), ncol)), dim3(512), wb, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<32768, 512, true>),
+                             dim3(bin_grid(cnt[b], false, std::max(g_bpc[0][4], fit(512, (int64_t)wb)), ncol)),
+                             dim3(512), wb, st, a, c0, list, cp, nnz_row, status);
         else
-          hipLaunchKernelGGL((k_sym_block<32768, 1024, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][4], ncol)), dim3(1024), 32768 * 4, st, a, c0, list, cp, nnz_row, status);
+          hipLaunchKernelGGL((k_sym_block<32768, 1024, false>), dim3(bin_grid(cnt[b], false, g_bpc[0][4], ncol)),
+                             dim3(1024), 32768 * 4, st, a, c0, list, cp, nnz_row, status);
         break;
       default:
-        hipLaunchKernelGGL(k_sym_bitmap, dim3(bin_grid(cnt[b], false, fit(1024, (int64_t)bm), ncol)), dim3(1024), bm, st, a, c0, list, cp, &hdr->cursor[b], nnz_row, status);
+        hipLaunchKernelGGL(k_sym_bitmap, dim3(bin_grid(cnt[b], false, fit(1024, (int64_t)bm), ncol)), dim3(1024), bm,
+                           st, a, c0, list, cp, &hdr->cursor[b], nnz_row, status);
         break;
     }
     LAUNCHCHK();
@@ -3297,13 +3314,34 @@ static int accumulate_pass(const Src &src, const int *cnt, const int *half_cnt, 
     const int32_t *cp = half < 0 ? &hdr->bin_count[b] : &hdr->half_count[half];
     const int dir = half < 0 ? 1 : -1;
     switch (b) {
-      case 0: hipLaunchKernelGGL((k_num_wave<64, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][0], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 1: hipLaunchKernelGGL((k_num_wave<256, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][1], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 2: hipLaunchKernelGGL((k_num_wave<1024, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][2], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 3: hipLaunchKernelGGL((k_num_block<4096, 256, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][3], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 4: hipLaunchKernelGGL((k_num_block<10240, 1024, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][4], ncol)), dim3(1024), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      case 5: hipLaunchKernelGGL((k_num_wave<512, VT, Src>), dim3(bin_grid(c, true, 2 * g_bpc[1][2], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
-      default: hipLaunchKernelGGL((k_num_block<2048, 256, VT, Src>), dim3(bin_grid(c, false, 2 * g_bpc[1][3], ncol)), dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status); break;
+      case 0:
+        hipLaunchKernelGGL((k_num_wave<64, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][0], ncol)), dim3(256), 0, st,
+                           src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
+      case 1:
+        hipLaunchKernelGGL((k_num_wave<256, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][1], ncol)), dim3(256), 0, st,
+                           src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
+      case 2:
+        hipLaunchKernelGGL((k_num_wave<1024, VT, Src>), dim3(bin_grid(c, true, g_bpc[1][2], ncol)), dim3(256), 0, st,
+                           src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
+      case 3:
+        hipLaunchKernelGGL((k_num_block<4096, 256, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][3], ncol)), dim3(256),
+                           0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
+      case 4:
+        hipLaunchKernelGGL((k_num_block<10240, 1024, VT, Src>), dim3(bin_grid(c, false, g_bpc[1][4], ncol)),
+                           dim3(1024), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
+      case 5:
+        hipLaunchKernelGGL((k_num_wave<512, VT, Src>), dim3(bin_grid(c, true, 2 * g_bpc[1][2], ncol)), dim3(256), 0,
+                           st, src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
+      default:
+        hipLaunchKernelGGL((k_num_block<2048, 256, VT, Src>), dim3(bin_grid(c, false, 2 * g_bpc[1][3], ncol)),
+                           dim3(256), 0, st, src, list, dir, cp, c_colptr, out_ri, out_v, status);
+        break;
     }
     LAUNCHCHK();
   }
