@@ -125,11 +125,12 @@ int spgemm_workspace_size(int op, const spgemm_csc *A, const spgemm_csc *B, int6
  * ranges of width w = ceil(k/L) (layer l covers [l*w, min(k,(l+1)*w)), some
  * possibly empty; Sec. III-B, Alg. 2) and nnz_out holds (L+1) rows of
  * (c1-c0) int64 each: row l = nnz of column j of the layer product
- * A(:,K_l)*B(K_l,:), row L = nnz of C(:,j).  Counts come from hash tables,
- * not from bounds.  Synchronizes `stream` once per pass (per layer, and once
- * for row L) to read the per-bin column counts that size the launches; the
- * counts themselves stay on the device.  A row of B outside [0,k) sets the
- * workspace status (code 1) and the entry is skipped. */
+ * A(:,K_l)*B(K_l,:), row L = nnz of C(:,j).  Counts come from hash tables or
+ * bitmaps, not from bounds.  With more than 8192 columns, and with layers,
+ * synchronizes `stream` once per pass (per layer, and once for row L) to read
+ * the per-bin column counts that size the launches; the counts themselves stay
+ * on the device.  A row of B outside [0,k) sets the workspace status (code 1)
+ * and the entry is skipped. */
 int spgemm_symbolic(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, int64_t c1, int32_t n_layers,
                     int64_t *flops_out, int64_t *nnz_out, void *ws, size_t ws_bytes, void *stream);
 
@@ -321,8 +322,9 @@ int spgemm_batched_masked_xty(const spgemm_csc *X, const spgemm_csc *Y, const sp
  *   dB(k,j)  = sum over i in A(:,k) of A(i,k) * dC(i,j)       -> dB_out[nnz(B)]
  *   dA(i,k) += B(k,j) * dC(i,j) for every i in A(:,k)          -> dA_out[nnz(A)]
  * dA is accumulated with float64 atomics (float32: in the workspace, rounded
- * once; float64: in dA_out, which is overwritten; summation order is not fixed, so dA may differ in the last bits between
- * calls).  C gives only the pattern (values not read).  Columns of C above
+ * once; float64: in dA_out, which is overwritten, or in the workspace where
+ * dA_out lies over an input; summation order is not fixed, so dA may differ in
+ * the last bits between calls).  C gives only the pattern (values not read).  Columns of C above
  * the largest LDS table are reported through the workspace status; the
  * transpose-based path (spgemm_transpose + spgemm_masked_xty) handles them.
  * Workspace: SPGEMM_OP_BATCHED_BACKWARD with A, B. */
@@ -364,10 +366,10 @@ int spgemm_prune_topk(const spgemm_csc *C, double threshold, int64_t k, int64_t 
  * must be unique within each column, as in every output of this library; a
  * repeated row or a row outside [0, C.nrows) sets the workspace status
  * (code 11), and in columns of more than 4096 entries leaves some positions
- * of that column unwritten (nothing outside the column is written).  Columns of
- * up to 64 entries are sorted by one wavefront, up to 4096 by one workgroup
- * in LDS, longer ones by row windows of 2^19 rows ranked through an LDS
- * bitmap.  Asynchronous, no host synchronization (graph-capturable).
+ * of that column unwritten (nothing outside the column is written; shorter
+ * columns are sorted with every entry kept).  Columns of up to 512 entries are
+ * sorted by one wavefront, up to 4096 by one workgroup in LDS, longer ones by
+ * row windows of up to 2^19 rows ranked through an LDS bitmap.  Asynchronous, no host synchronization (graph-capturable).
  * Workspace: SPGEMM_OP_SORT with A = C. */
 int spgemm_sort_columns(const spgemm_csc *C, int32_t *rowidx_out, void *values_out, void *ws, size_t ws_bytes,
                         void *stream);
@@ -382,7 +384,7 @@ int spgemm_sort_columns(const spgemm_csc *C, int32_t *rowidx_out, void *values_o
  *   - a column with flops_j <= 4096 and flops_j <= esc_cf_max * nnz_j is
  *     formed by expand-sort-compress: every product term placed in LDS,
  *     sorted by row, runs of equal rows combined in row order (one
- *     wavefront per column up to 64 terms, one workgroup up to 4096), and
+ *     wavefront per column up to 512 terms, one workgroup up to 4096), and
  *     written straight to c_rowidx / c_values;
  *   - every other column is formed by the hash kernels of spgemm_numeric
  *     into tmp_rowidx / tmp_values (device arrays addressed by the same
@@ -435,7 +437,7 @@ int spgemm_profile_report(char *buf_host, size_t buf_bytes);
 /* Synchronizes `stream` and reports the device-side status word of a
  * workspace used by the calls above: SPGEMM_OK, or SPGEMM_E_DEVICE if a
  * kernel found counts that disagree with the product or an index out of
- * range.  Clears the word.  The only call here that blocks the host. */
+ * range.  Clears the word. */
 int spgemm_ws_status(void *ws, void *stream);
 
 /* As spgemm_ws_status; *code_host (may be NULL) receives the device-side
@@ -446,7 +448,7 @@ int spgemm_ws_status(void *ws, void *stream);
  * index, 7 a column above the largest LDS table in a call without a host
  * synchronization, 8 an output larger than the capacity given, 9 a
  * malformed internal work item, 10 a row twice in a pruned column that had
- * more than k candidates. */
+ * more than k candidates, 11 a row twice, or out of range, in a sorted column. */
 int spgemm_ws_status_code(void *ws, void *stream, int32_t *code_host);
 
 /* spgemm_ws_status_code for n workspaces with one synchronization per 8:
