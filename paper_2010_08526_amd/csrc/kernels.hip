@@ -3176,7 +3176,9 @@ constexpr int64_t kLdsPerCu = 160 * 1024;
 
 // Columns up to which the symbolic pass launches its few kernels without
 // reading the bins' counts back first: 4096 columns took 165 us with the
-// read-back (whole product), 148 without.
+// read-back (whole product), 148 without; at 8192 and 8193, 8 per column, the
+// pass itself takes 26.5 and 31.3 us.  Beyond, the launches over empty bins
+// count less and less either way.
 constexpr int64_t kBlindCols = 8192;
 constexpr int64_t kItemSlabs = 64;  // see numeric_typed
 
@@ -3405,7 +3407,8 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   // a scale 13 R-MAT square: 0.25 ms in tables, 0.08 as items).  Up to 64 slabs:
   // their items are looked for slab by slab, and over the 489 slabs of a
   // 2,000,000-row graph in 16 layers the numeric pass took 1.30 s that way, 1.06
-  // with the tables; at 64 slabs (scale 18) both are within 1%.
+  // with the tables; at 64 slabs (scale 18) both are within 1%, at 128 (a
+  // sixteenth of scale 19) 6.26 ms against 6.11, at 256 13.92 against 13.89.
   BinCaps caps = g_caps[1];
   if (L.P > 0 && L.P <= kItemSlabs && max_len != INT64_MAX && std::min(max_len, A->nrows) > kNumTableCap[kNumBins - 2])
     caps.cap[kNumBins - 2] = caps.cap[kNumBins - 3];
