@@ -198,3 +198,55 @@ def test_prune_once_in_a_graph():
         assert np.array_equal(out[0].cpu().numpy(), P.colptr)
         assert np.array_equal(out[1][:n].cpu().numpy(), P.rowidx)
         assert np.array_equal(out[2][:n].double().cpu().numpy(), P.values.astype(np.float64))
+
+
+def test_many_short_columns_in_a_graph():
+    """The one reading over many short columns, and a sort of few columns, both
+    captured and replayed over new values and rows."""
+    import ctypes
+    print("case: prune short and sort few in a graph", flush=True)
+    rng = np.random.default_rng(9)
+    n, m, k = 9000, 5000, 5
+    lens = rng.integers(10, 40, n)
+    cp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ri = np.concatenate([rng.choice(m, c, replace=False) for c in lens]).astype(np.int32)
+    M = synth.CSC(m, n, torch.from_numpy(cp), torch.from_numpy(ri), torch.from_numpy(rng.random(ri.size)).float())
+    D = M.to("cuda")
+    few = S.CSC(m, 300, D.colptr[:301], D.rowidx[:int(cp[300])], D.values[:int(cp[300])])
+    out = (torch.empty(n + 1, dtype=torch.int64, device="cuda"),
+           torch.empty(k * n, dtype=torch.int32, device="cuda"), torch.empty(k * n, device="cuda"))
+    srt = (torch.empty_like(few.rowidx), torch.empty_like(few.values))
+    ws = S.alloc_workspace(S.workspace_size(S.OP_PRUNE, D))
+    ws2 = S.alloc_workspace(S.workspace_size(S.OP_SORT, few))
+
+    def call():
+        S._check(S._lib.spgemm_prune_topk(ctypes.byref(S.desc(D)), 0.2, k, *[S._ptr(x) for x in out], k * n,
+                                          S._ptr(ws), ws.numel(), S._stream(None)), "prune")
+        S.sort_columns(few, *srt, ws=ws2)
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        call()
+    torch.cuda.current_stream().wait_stream(s)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    col = np.repeat(np.arange(300), lens[:300])
+    for i in range(4):
+        D.values.copy_(torch.rand_like(D.values))  # eager work between replays
+        D.rowidx.copy_(torch.remainder(D.rowidx + 1 + i, m))
+        for x in out + srt:
+            x.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        S.check_many([ws, ws2])
+        H = synth.CSC(m, n, M.colptr, D.rowidx.cpu(), D.values.cpu())
+        P = oracle.prune_topk(H, 0.2, k)
+        assert np.array_equal(out[0].cpu().numpy(), P.colptr)
+        kept = int(out[0][-1])
+        assert np.array_equal(out[1][:kept].cpu().numpy(), P.rowidx)
+        assert np.array_equal(out[2][:kept].double().cpu().numpy(), P.values.astype(np.float64))
+        r, v = H.rowidx.numpy()[:col.size], H.values.numpy()[:col.size]
+        order = np.lexsort((r, col))
+        assert np.array_equal(srt[0].cpu().numpy(), r[order]) and np.array_equal(srt[1].cpu().numpy(), v[order])
