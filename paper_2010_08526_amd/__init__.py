@@ -767,6 +767,7 @@ def _longest_row(M, stream=None) -> int:
     """Entries of M's longest row."""
     out = _i64(0)
     ws = alloc_workspace(workspace_size(OP_TRANSPOSE, M), M.rowidx.device)
+    _wait_for_current(stream)
     _check(_lib.spgemm_longest_row(ctypes.byref(desc(M)), ctypes.byref(out), _ptr(ws), ws.numel(), _stream(stream)),
            "spgemm_longest_row")
     return int(out.value)

@@ -153,3 +153,13 @@ def test_gradient_memory_is_the_current_streams(monkeypatch, handle):
     assert bw.ws_f is not None and torch.equal(torch.Tensor(bw._b), torch.ones(4))
     assert pools == [0, 0]
     assert fills == [(handle or 0, 1 if handle else 0)]
+
+
+@pytest.mark.parametrize("handle", [None, 0, 4096])
+def test_longest_row_waits_for_its_workspace(monkeypatch, handle):
+    fake = FakeCuda(monkeypatch, 0)
+    waited = []
+    monkeypatch.setattr(S, "alloc_workspace", lambda *a: torch.zeros(256, dtype=torch.uint8))
+    monkeypatch.setattr(S._lib, "spgemm_longest_row", lambda *a: waited.append(len(fake.waits)) or 0)
+    S._longest_row(S.CSC(4, 4, torch.arange(5), torch.arange(4, dtype=torch.int32), None), handle)
+    assert waited == [1 if handle else 0]
