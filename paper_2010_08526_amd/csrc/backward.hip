@@ -684,7 +684,7 @@ static int mxty_typed(const spgemm_csc *X, const spgemm_csc *Y, const spgemm_csc
   int rc = launch_init_header(hdr, zero_region_tag(kTagMasked, L), st);
   if (rc) return rc;
   hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, Y->colptr, M->colptr, n, g_min_bin_value(),
-                     bin_caps(1), bins, hdr, sync ? 0 : 7, half_tables(n));
+                     num_caps(Y->nrows), bins, hdr, sync ? 0 : 7, half_tables(n));
   LAUNCHCHK();
   WsHeader h;
   int cnt[kNumBins];
@@ -787,7 +787,7 @@ static int fbwd_typed(const spgemm_csc *A, const spgemm_csc *B, const spgemm_csc
   // products of 256: 50.7 -> 40.1 us)
   hipLaunchKernelGGL(k_fbwd_init, dim3(gz), dim3(256), 0, st, hdr, acc, A->nnz);
   LAUNCHCHK();
-  BinCaps caps = bin_caps(1);
+  BinCaps caps = num_caps(C->nrows);
   caps.cap[kNumBins - 2] = kNumTableCap[kNumBins - 2];  // whatever fits the largest table is formed
   if (n > 0) {
     hipLaunchKernelGGL(k_mxty_bin, dim3(grid_of(n, 256)), dim3(256), 0, st, C->colptr, B->colptr, n,

@@ -23,7 +23,10 @@ int sort_column_lists(const spgemm_csc *C, int32_t *ro, void *vo, int32_t *lists
                       const int64_t *skip_flops, double skip_cf, hipStream_t st, int64_t max_len,
                       bool init = false);
 int g_min_bin_value();  // the spgemm_debug_min_bin setting
-BinCaps bin_caps(int which);  // 0: symbolic, 1: numeric / merge / masked product
+// thresholds of numeric, merge and masked products over columns of up to m rows:
+// those in force, but where the largest table holds every column it takes those
+// above its threshold too (no workspace is set aside for heavier ones then)
+BinCaps num_caps(int64_t m);
 // colptr_out[0] = 0, colptr_out[i+1] = counts[0] + ... + counts[i]; bsum holds n / 8192 + 2 int64
 // (hdr, if given, is initialised as by launch_init_header(hdr, 0, st))
 int launch_colptr_scan(const int64_t *counts, int64_t n, int64_t *colptr_out, int64_t *bsum, hipStream_t st,

@@ -2969,7 +2969,11 @@ int device_cus() {
 }
 
 int g_min_bin_value() { return g_min_bin; }
-BinCaps bin_caps(int which) { return g_caps[which ? 1 : 0]; }
+BinCaps num_caps(int64_t m) {
+  BinCaps c = g_caps[1];
+  if (m <= kNumTableCap[kNumBins - 2]) c.cap[kNumBins - 2] = kNumTableCap[kNumBins - 2];
+  return c;
+}
 
 int launch_set_tag(WsHeader *h, uint64_t tag, hipStream_t st) {
   hipLaunchKernelGGL(k_set_tag, dim3(1), dim3(64), 0, st, h, tag);
@@ -3409,7 +3413,7 @@ static int numeric_typed(const spgemm_csc *A, const spgemm_csc *B, int64_t c0, i
   // 2,000,000-row graph in 16 layers the numeric pass took 1.30 s that way, 1.06
   // with the tables; at 64 slabs (scale 18) both are within 1%, at 128 (a
   // sixteenth of scale 19) 6.26 ms against 6.11, at 256 13.92 against 13.89.
-  BinCaps caps = g_caps[1];
+  BinCaps caps = num_caps(A->nrows);
   if (L.P > 0 && L.P <= kItemSlabs && max_len != INT64_MAX && std::min(max_len, A->nrows) > kNumTableCap[kNumBins - 2])
     caps.cap[kNumBins - 2] = caps.cap[kNumBins - 3];
   max_len = std::min(max_len, A->nrows);
@@ -3561,7 +3565,7 @@ static int merge_typed(const spgemm_csc *parts, int32_t n_parts, const int64_t *
     LAUNCHCHK();
   }
   hipLaunchKernelGGL(k_bin_len, dim3(grid_of(L.ncol, 256)), dim3(256), 0, st, c_colptr, L.ncol, bins, hdr, g_min_bin,
-                     g_caps[1], (const int64_t *)nullptr, 0.0, INT64_MAX, half_tables(L.ncol));
+                     num_caps(L.m), (const int64_t *)nullptr, 0.0, INT64_MAX, half_tables(L.ncol));
   LAUNCHCHK();
   int cnt[kNumBins];
   WsHeader h;

@@ -240,3 +240,34 @@ def test_form_of_the_gradients_at_the_limit(longest, dtype, monkeypatch):
     G = oracle.Mat(C.nrows, C.ncols, cp.cpu().numpy(), ri.cpu().numpy(), np.ones(C.nnz))
     assert np.array_equal(a.grad.double().cpu().numpy(), oracle.grad_a(A, B, G))
     assert np.array_equal(b.grad.double().cpu().numpy(), oracle.grad_b(A, B, G))
+
+
+@pytest.mark.parametrize("layers, sorted_output", [(1, False), (1, True), (3, False)])
+def test_lower_thresholds_with_few_rows(layers, sorted_output):
+    """Thresholds below the largest table's capacity, as the autotuner sets
+    them, and columns above them of matrices with no more rows than that table
+    takes: the thresholds change speed, never results."""
+    import paper_2010_08526_amd.batched as Bt
+    print(f"case: lower thresholds {layers} {sorted_output}", flush=True)
+    rng = np.random.default_rng(layers)
+    m = 5000
+    A = _csc(m, [rng.choice(m, 60, replace=False) for _ in range(300)], rng, torch.float64)
+    B = _csc(300, [rng.choice(300, n, replace=False) for n in (1, 30, 70, 150, 290) * 3], rng, torch.float64)
+    Ad, Bd = A.to("cuda"), B.to("cuda")
+    P = oracle.spgemm(A, B)
+    Bt.set_bin_caps(1, (24, 96, 384, 1536, 3840))
+    try:
+        C = S.spgemm(Ad, Bd, layers=layers, sorted_output=sorted_output)
+        order = np.lexsort((C.rowidx.cpu().numpy(), np.repeat(np.arange(C.ncols), np.diff(P.colptr))))
+        assert np.diff(P.colptr).max() > 3840
+        assert np.array_equal(C.rowidx.cpu().numpy()[order], P.rowidx)
+        assert np.array_equal(C.values.cpu().numpy()[order], P.values)
+        got = S.masked_xty(Ad, C, Bd)
+        D = oracle.Mat(m, C.ncols, P.colptr, C.rowidx.cpu().numpy(), C.values.cpu().numpy())
+        assert np.array_equal(got.cpu().numpy(), oracle.masked_xty(A, D, B))
+        eng = Bt.BatchedEngine(Ad, Bd)
+        eng.forward()
+        eng.check()
+        assert np.array_equal(eng.values.sort()[0].cpu().numpy(), np.sort(P.values))
+    finally:
+        Bt.set_bin_caps(1, None)
